@@ -28,6 +28,8 @@ struct dgc_handle {
   std::vector<TensorPlan> plans;     // T
   std::vector<int64_t> k;            // T
   std::vector<int64_t> draws;        // T
+  std::vector<int32_t> first_part;   // T: the tensor's first entry in emit_blocks
+  bool any_band = false;             // some tensor's threshold is found by way of a band (TensorPlan.exact == 2)
   std::vector<uint32_t> tile_info;   // ceil(n / kWaveTile)
   std::vector<float> tile_thr_init;  // ceil(n / kWaveTile): NaN where a tile is not wholly inside one tensor
   std::vector<EmitBlock> emit_blocks;  // work list of the emit pass
@@ -143,6 +145,7 @@ int64_t topk_count(double density, int64_t n) {
 void build_plan(dgc_handle* h) {
   const dgc_config& c = h->cfg;
   const int64_t B = c.sample_block;
+  h->any_band = false;
   for (int32_t j = 0; j < h->num_tensors; ++j) {
     const int64_t n = h->offsets[j + 1] - h->offsets[j];
     TensorPlan& p = h->plans[j];
@@ -165,6 +168,11 @@ void build_plan(dgc_handle* h) {
       p.rank = (int32_t)k;
       p.nblocks = 0;
       h->draws[j] = 0;
+      if (n > kBandSample && k < n) {  // more than a workgroup of select_kernel holds in registers
+        p.exact = 2;
+        p.nblocks = (uint32_t)h->first_part[j];
+        h->any_band = true;
+      }
     } else {
       const int64_t draws = (s + B - 1) / B;
       const int64_t count = draws * B;
@@ -412,6 +420,7 @@ dgc_status dgc_create(dgc_handle** out, const dgc_config* cfg, int32_t num_tenso
       const int32_t nb = (int32_t)((t1 - t0) / kEmitTiles + 1);
       for (int64_t f = t0; f <= t1; f += kEmitTiles)
         h->emit_blocks.push_back(EmitBlock{t, (int32_t)f, nb, 0, h->offsets[t], h->offsets[t + 1]});
+      h->first_part.push_back((int32_t)h->emit_blocks.size() - nb);
     }
     // element ranges of the receive side: kMergeEmitBlocks consecutive emit workgroups' parts of one tensor
     for (size_t b = 0; b < h->emit_blocks.size();) {
@@ -596,11 +605,18 @@ dgc_status dgc_compress(dgc_handle* h, const float* g, float* u, float* v, int32
   int shift = 0;
   while ((1 << shift) < c.sample_block) ++shift;
   sa.block_shift = shift;
+  sa.bands = h->any_band ? at<BandState>(workspace, h->lay.part_found) : nullptr;
+  sa.band_list = at<uint32_t>(workspace, h->lay.wire_sums);
   sa.seed_lo = (uint32_t)(c.seed & 0xFFFFFFFFu);
   sa.seed_hi = (uint32_t)(c.seed >> 32);
   sa.iter_lo = (uint32_t)(iteration & 0xFFFFFFFFu);
   sa.iter_hi = (uint32_t)(iteration >> 32);
   if (!hip_ok(launch_select(sa, h->num_tensors, stream), "launch select kernel")) return DGC_ERR_HIP;
+  if (h->any_band &&
+      !hip_ok(launch_band(sa, at<EmitBlock>(workspace, h->lay.emit_blocks), (int32_t)h->emit_blocks.size(),
+                          h->num_tensors, stream),
+              "launch band kernels"))
+    return DGC_ERR_HIP;
   if (ev && !hip_ok(hipEventRecord(ev[2], stream), "record event")) return DGC_ERR_HIP;
 
   StreamArgs ta{};

@@ -270,7 +270,150 @@ __device__ __forceinline__ uint32_t select_in_registers(SelectShared& sh, const 
   return prefix;
 }
 
-template <bool NESTEROV>
+// Key of descending rank `rank` among the `count` keys a workgroup holds in registers (kNoKey marks an
+// empty slot).  Every thread returns the same.
+__device__ __forceinline__ uint32_t rank_registers(SelectShared& sh, const uint32_t (&key)[kSelectRegKeys], int32_t count,
+                                                   uint32_t rank, int tid) {
+  // Gradients of one tensor share a few exponents, so a histogram over the leading key
+  // bits of all candidates piles tens of thousands of LDS atomics on a handful of bins,
+  // and every histogram pass costs half a dozen barriers of 1024 threads (ranking 32 Ki
+  // keys that way took 20 us, against 3 us this way).  At the paper's densities the
+  // rank r is a few dozen, and a floor below which no key matters is cheap to get: if
+  // every one of the 16 wavefronts names the t-th largest of its threads' largest
+  // keys, 16 t > r, then the smallest of the 16 answers has more than r keys at or
+  // above it.  What lies at or above that floor (a few times r keys) is listed in LDS
+  // and ranked by direct counting.  Anything that does not fit this pattern takes the
+  // histogram passes.
+  constexpr int kWaves = kSelectThreads / 64;
+  const uint32_t t_rounds = rank / kWaves + 1;  // kWaves * t_rounds > rank
+  if (count > 2 * kSelectThreads && t_rounds <= (uint32_t)kSelectFloorRounds) {
+    const int lane = tid & 63;
+    uint32_t top = 0;  // this thread's largest key (every thread has keys: count > 2048)
+#pragma unroll
+    for (int i = 0; i < kSelectRegKeys; ++i)
+      if (key[i] != kNoKey) top = key[i] > top ? key[i] : top;
+    uint32_t tth = 0;
+    for (uint32_t round = 0; round < t_rounds; ++round) {
+      uint32_t m = top;
+      for (int d = 32; d >= 1; d >>= 1) {
+        const uint32_t o = __shfl_xor(m, d);
+        m = o > m ? o : m;
+      }
+      tth = m;
+      const unsigned long long holders = __ballot(top == m);
+      if (lane == __ffsll((long long)holders) - 1) top = 0;  // one holder of the maximum steps down
+    }
+    if (lane == 0) sh.wave_tot[tid >> 6] = tth;
+    if (tid == 0) sh.surv_n = 0;
+    __syncthreads();
+    uint32_t floor_key = sh.wave_tot[0];
+#pragma unroll
+    for (int w = 1; w < kWaves; ++w) floor_key = sh.wave_tot[w] < floor_key ? sh.wave_tot[w] : floor_key;
+#pragma unroll
+    for (int i = 0; i < kSelectRegKeys; ++i)
+      if (key[i] != kNoKey && key[i] >= floor_key) {
+        const uint32_t pos = atomicAdd(&sh.surv_n, 1u);
+        if (pos < (uint32_t)kSelectThreads) sh.surv[pos] = key[i];
+      }
+    __syncthreads();
+    const uint32_t listed = sh.surv_n;
+    if (listed <= (uint32_t)kSelectThreads) {
+      const uint32_t found = rank_directly(sh, tid, listed, rank);
+      __syncthreads();
+      return found;
+    }
+    __syncthreads();
+  }
+  return select_in_registers<kSelectRegKeys>(sh, key, 0u, rank, tid);
+}
+
+// The same among `count` candidates that are evaluated from g, u, v anew in every pass.
+__device__ __forceinline__ uint32_t rank_reevaluated(SelectShared& sh, const Candidates& c, int32_t count, uint32_t rank,
+                                                     int tid) {
+  uint32_t prefix = 0;
+  int consumed = 0;
+#pragma unroll 1
+  for (int pass = 0; pass < 3; ++pass) {
+    const int bits = pass == 2 ? 9 : 11;
+    const int shift = 31 - consumed - bits;
+    const uint32_t digit_mask = (1u << bits) - 1u;
+    for (int i = tid; i < kSelectBins; i += kSelectThreads) sh.hist[i] = 0;
+    __syncthreads();
+    for (int32_t p0 = tid; p0 < count; p0 += kSelectInFlight * kSelectThreads) {
+      float gg[kSelectInFlight], uu[kSelectInFlight], vv[kSelectInFlight];
+#pragma unroll
+      for (int q = 0; q < kSelectInFlight; ++q) {
+        const int32_t p = p0 + q * kSelectThreads;
+        gg[q] = uu[q] = vv[q] = 0.0f;
+        if (p < count) {
+          const int64_t e = c.offset + c.position(p);
+          gg[q] = c.g[e];
+          uu[q] = c.u[e];
+          vv[q] = c.v[e];
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < kSelectInFlight; ++q) {
+        const int32_t p = p0 + q * kSelectThreads;
+        if (p < count) {
+          float u1, v1;
+          momentum_update(gg[q], uu[q], vv[q], c.m, c.scale, c.nesterov, u1, v1);
+          const uint32_t k = __float_as_uint(v1) & 0x7FFFFFFFu;
+          if (pass == 0 || (k >> (shift + bits)) == prefix)
+            atomicAdd(&sh.hist[(k >> shift) & digit_mask], 1u);
+        }
+      }
+    }
+    __syncthreads();
+    uint32_t bin, above, members;
+    find_bin<kSelectThreads>(sh.hist, sh.wave_tot, sh.sel, tid, rank, bin, above, members);
+    prefix = (prefix << bits) | bin;
+    rank -= above;
+    consumed += bits;
+  }
+  return prefix;
+}
+
+// The threshold of tensor j into the tables.  Tiles that lie wholly inside the tensor get it into the
+// per-tile table, which is all the streaming pass looks at on its fast path.
+__device__ __forceinline__ void write_threshold(const SelectArgs& a, int j, const TensorPlan& plan, float thr, int tid) {
+  const int64_t tile_first = (plan.offset + kWaveTile - 1) / kWaveTile;
+  const int64_t tile_end = (plan.offset + plan.n) / kWaveTile;
+  if (tid == 0) {
+    a.thr[j] = thr;
+    if (a.out_thr) a.out_thr[j] = thr;
+  }
+  for (int64_t t = tile_first + tid; t < tile_end; t += kSelectThreads) a.tile_thr[t] = thr;
+}
+
+__device__ __forceinline__ Candidates candidates_of(const SelectArgs& a, int j, const TensorPlan& plan, float scale,
+                                                    bool nesterov) {
+  Candidates c;
+  c.g = a.g;
+  c.u = a.u;
+  c.v = a.v;
+  c.offset = plan.offset;
+  c.nblocks = plan.nblocks;
+  c.block_shift = a.block_shift;
+  c.exact = plan.exact;
+  c.m = a.momentum;
+  c.scale = scale;
+  c.nesterov = nesterov;
+  uint32_t h = mix32(a.seed_lo ^ 0x9E3779B9u);
+  h = mix32(h ^ a.seed_hi);
+  h = mix32(h ^ a.iter_lo);
+  h = mix32(h ^ a.iter_hi);
+  c.key = mix32(h ^ (uint32_t)j);
+  return c;
+}
+
+__device__ __forceinline__ BandState* band_state(const SelectArgs& a, const TensorPlan& plan) {
+  return reinterpret_cast<BandState*>(reinterpret_cast<char*>(a.bands) + (size_t)plan.nblocks * kBandStride);
+}
+__device__ __forceinline__ int64_t band_list_begin(int64_t offset) { return 3 * (offset >> kBandListShift); }
+
+// BANDS: some tensors are ranked by way of a band (TensorPlan.exact == 2).
+template <bool NESTEROV, bool BANDS>
 __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectArgs a) {
   __shared__ SelectShared sh;
   const int tid = threadIdx.x;
@@ -312,41 +455,20 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectArgs a) {
     a.state->scale = a.scale_const;
     a.state->flags = 0;
   }
-  // Tiles that lie wholly inside this tensor get the threshold written into the per-tile
-  // table, which is all the streaming pass looks at on its fast path.
-  const int64_t tile_first = (plan.offset + kWaveTile - 1) / kWaveTile;
-  const int64_t tile_end = (plan.offset + plan.n) / kWaveTile;
   if (plan.rank >= plan.count) {  // the strict comparison then passes everything
-    if (tid == 0) {
-      a.thr[j] = -1.0f;
-      if (a.out_thr) a.out_thr[j] = -1.0f;
-    }
-    for (int64_t t = tile_first + tid; t < tile_end; t += kSelectThreads) a.tile_thr[t] = -1.0f;
+    write_threshold(a, j, plan, -1.0f, tid);
     return;
   }
 
-  Candidates c;
-  c.g = a.g;
-  c.u = a.u;
-  c.v = a.v;
-  c.offset = plan.offset;
-  c.nblocks = plan.nblocks;
-  c.block_shift = a.block_shift;
-  c.exact = plan.exact;
-  c.m = a.momentum;
-  c.scale = scale;
-  c.nesterov = NESTEROV;
-  {
-    uint32_t h = mix32(a.seed_lo ^ 0x9E3779B9u);
-    h = mix32(h ^ a.seed_hi);
-    h = mix32(h ^ a.iter_lo);
-    h = mix32(h ^ a.iter_hi);
-    c.key = mix32(h ^ (uint32_t)j);
+  Candidates c = candidates_of(a, j, plan, scale, NESTEROV);
+  if (BANDS && plan.exact == 2) {  // a sample for the band of an exact selection
+    c.exact = 0;
+    c.block_shift = kBandBlockShift;
+    c.nblocks = (uint32_t)(plan.n >> kBandBlockShift);
   }
 
-  const int32_t count = plan.count;
-  uint32_t prefix = 0;
-  uint32_t rank = (uint32_t)plan.rank;
+  const int32_t count = (BANDS && plan.exact == 2) ? kBandSample : plan.count;
+  const uint32_t rank = (uint32_t)plan.rank;
   uint32_t thr_bits = 0;
 
   if (count <= kSelectRegKeys * kSelectThreads) {
@@ -359,7 +481,7 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectArgs a) {
     // empty mark afterwards.  (With `if (p < count)` around them the compiler copied the whole
     // register array at every such branch: some 400 moves per thread in a kernel that spends as
     // much time issuing instructions as waiting for memory, 16 wavefronts sharing four SIMDs.)
-    if (!plan.exact && a.block_shift >= 2) {
+    if (!c.exact && c.block_shift >= 2) {
       // Sampled blocks of at least four elements: a thread takes four consecutive elements of a
       // drawn block at a time (one 16-byte load per array; a block starts at a multiple of its size
       // from the tensor's start, which need not be 16-byte aligned: dword-aligned vector loads), so
@@ -369,7 +491,7 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectArgs a) {
       constexpr int kQuads = kSelectRegKeys / 4;       // per thread
       constexpr int kQuadsInFlight = 4;
       const int32_t quads = count >> 2;                // blocks are whole multiples of four elements
-      const int qshift = a.block_shift - 2;            // log2(quads per block)
+      const int qshift = c.block_shift - 2;            // log2(quads per block)
 #pragma unroll
       for (int r = 0; r < kQuads / kQuadsInFlight; ++r) {
         if (r == 0 || r * kQuadsInFlight * kSelectThreads < quads) {  // uniform
@@ -378,7 +500,7 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectArgs a) {
           for (int q = 0; q < kQuadsInFlight; ++q) {
             const int32_t qd = tid + (r * kQuadsInFlight + q) * kSelectThreads;
             const int32_t qq = qd < quads ? qd : 0;
-            const int64_t e = c.offset + c.position((qq >> qshift) << a.block_shift) + ((qq & ((1 << qshift) - 1)) << 2);
+            const int64_t e = c.offset + c.position((qq >> qshift) << c.block_shift) + ((qq & ((1 << qshift) - 1)) << 2);
             gg[q] = *reinterpret_cast<const vec4u*>(c.g + e);
             uu[q] = *reinterpret_cast<const vec4u*>(c.u + e);
             vv[q] = *reinterpret_cast<const vec4u*>(c.v + e);
@@ -419,107 +541,208 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectArgs a) {
         }
       }
     }
-    // Gradients of one tensor share a few exponents, so a histogram over the leading key
-    // bits of all candidates piles tens of thousands of LDS atomics on a handful of bins,
-    // and every histogram pass costs half a dozen barriers of 1024 threads (ranking 32 Ki
-    // keys that way took 20 us, against 3 us this way).  At the paper's densities the
-    // rank r is a few dozen, and a floor below which no key matters is cheap to get: if
-    // every one of the 16 wavefronts names the t-th largest of its threads' largest
-    // keys, 16 t > r, then the smallest of the 16 answers has more than r keys at or
-    // above it.  What lies at or above that floor (a few times r keys) is listed in LDS
-    // and ranked by direct counting.  Anything that does not fit this pattern takes the
-    // histogram passes.
-    constexpr int kWaves = kSelectThreads / 64;
-    const uint32_t t_rounds = rank / kWaves + 1;  // kWaves * t_rounds > rank
-    bool done = false;
-    if (count > 2 * kSelectThreads && t_rounds <= (uint32_t)kSelectFloorRounds) {
-      const int lane = tid & 63;
-      uint32_t top = 0;  // this thread's largest key (every thread has keys: count > 2048)
+    if (BANDS && plan.exact == 2) {
+      // A band that holds the rank unless the number of sampled elements above the exact threshold is
+      // seven standard deviations off (and 32 more, for small ranks and for values that come in
+      // clusters).  Nothing depends on it but the time: a band that misses is noticed.
+      const double share = (double)plan.rank / (double)plan.n;
+      const double mid = share * (double)kBandSample;
+      const double reach = 32.0 + ceil(7.0 * sqrt(mid * (1.0 - share)));
+      const double low = ceil(mid) + reach, high = floor(mid) - reach;
+      const uint32_t floor_key = low < (double)count ? rank_registers(sh, key, count, (uint32_t)low, tid) : 0xFFFFFFFFu;
+      uint32_t ceil_key = high >= 0.0 ? rank_registers(sh, key, count, (uint32_t)high, tid) : 0x80000000u;
+      if (ceil_key == floor_key) ++ceil_key;
+      if (tid == 0) *band_state(a, plan) = BandState{floor_key, ceil_key, 0u, 0u, 0u};
+      return;
+    }
+    thr_bits = rank_registers(sh, key, count, rank, tid);
+  } else {
+    thr_bits = rank_reevaluated(sh, c, count, rank, tid);
+  }
+  write_threshold(a, j, plan, __uint_as_float(thr_bits), tid);
+}
+
+// ---------------------------------------------------------------------------
+// Exact threshold of a tensor too large for a workgroup's registers
+// (paper: Algorithm 3 "thr <- s% of |V[j]|" taken literally)
+// ---------------------------------------------------------------------------
+// Two kernels after select_kernel, which has named the band (see kBandSample).  A workgroup of the
+// collecting pass reads kBandElements elements of g, u, v (12 bytes each, once: HBM bounds it), counts
+// the keys above the band and those equal to its floor, and appends those inside it to the tensor's
+// list, one returning atomic per workgroup.  A wavefront collects its keys in a segment of LDS of its
+// own, placed by votes.
+template <bool NESTEROV>
+__global__ __launch_bounds__(kBandThreads) void collect_band_kernel(SelectArgs a, const EmitBlock* __restrict__ blocks) {
+  constexpr int kWaves = kBandThreads / 64;
+  constexpr int kRounds = kBandElements / (4 * kBandThreads);
+  constexpr int kRoundsInFlight = 4;
+  constexpr int kSegment = kBandElements / kWaves;
+  typedef float quad __attribute__((ext_vector_type(4)));
+  __shared__ uint32_t list[kBandElements];
+  __shared__ uint32_t counts[3][kWaves];
+  __shared__ uint32_t base_sh;
+  const EmitBlock blk = blocks[blockIdx.x / kBandsPerPart];
+  const TensorPlan plan = a.plans[blk.tensor];
+  if (plan.exact != 2) return;
+  const int64_t base = (int64_t)blk.first_tile * kWaveTile + (int64_t)(blockIdx.x % kBandsPerPart) * kBandElements;
+  if (base >= blk.hi || base + kBandElements <= blk.lo) return;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = tid >> 6;
+  const float scale = a.scale_from_state ? a.state->scale : a.scale_const;
+  BandState* st = band_state(a, plan);
+  const uint32_t floor_key = st->floor_key, ceil_key = st->ceil_key;
+  uint32_t above = 0, ties = 0, listed = 0;  // of the wavefront
+#pragma unroll 1
+  for (int r0 = 0; r0 < kRounds; r0 += kRoundsInFlight) {
+    quad x[kRoundsInFlight], y[kRoundsInFlight], z[kRoundsInFlight];
+    bool in[kRoundsInFlight];  // all four elements belong to the tensor
 #pragma unroll
-      for (int i = 0; i < kSelectRegKeys; ++i)
-        if (key[i] != kNoKey) top = key[i] > top ? key[i] : top;
-      uint32_t tth = 0;
-      for (uint32_t round = 0; round < t_rounds; ++round) {
-        uint32_t m = top;
-        for (int d = 32; d >= 1; d >>= 1) {
-          const uint32_t o = __shfl_xor(m, d);
-          m = o > m ? o : m;
+    for (int r = 0; r < kRoundsInFlight; ++r) {
+      const int64_t e = base + (r0 + r) * (4 * kBandThreads) + tid * 4;
+      in[r] = e >= blk.lo && e + 4 <= blk.hi;
+      if (in[r]) {
+        x[r] = __builtin_nontemporal_load(reinterpret_cast<const quad*>(a.g + e));
+        y[r] = __builtin_nontemporal_load(reinterpret_cast<const quad*>(a.u + e));
+        z[r] = __builtin_nontemporal_load(reinterpret_cast<const quad*>(a.v + e));
+      } else {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          const bool one = e + c >= blk.lo && e + c < blk.hi;
+          x[r][c] = one ? a.g[e + c] : 0.0f;
+          y[r][c] = one ? a.u[e + c] : 0.0f;
+          z[r][c] = one ? a.v[e + c] : 0.0f;
         }
-        tth = m;
-        const unsigned long long holders = __ballot(top == m);
-        if (lane == __ffsll((long long)holders) - 1) top = 0;  // one holder of the maximum steps down
       }
-      if (lane == 0) sh.wave_tot[tid >> 6] = tth;
+    }
+#pragma unroll
+    for (int r = 0; r < kRoundsInFlight; ++r) {
+      const int64_t e = base + (r0 + r) * (4 * kBandThreads) + tid * 4;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        float u1, v1;
+        momentum_update(x[r][c], y[r][c], z[r][c], a.momentum, scale, NESTEROV, u1, v1);
+        const uint32_t key = __float_as_uint(v1) & 0x7FFFFFFFu;
+        const bool mine = in[r] || (e + c >= blk.lo && e + c < blk.hi);
+        above += (uint32_t)__popcll(__ballot(mine && key >= ceil_key));
+        ties += (uint32_t)__popcll(__ballot(mine && key == floor_key));
+        // (a floor of all ones lies below every key)
+        const bool inside = mine && (int32_t)key > (int32_t)floor_key && key < ceil_key;
+        const unsigned long long votes = __ballot(inside);
+        if (inside)
+          list[wave * kSegment + listed +
+               __builtin_amdgcn_mbcnt_hi((uint32_t)(votes >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)votes, 0u))] = key;
+        listed += (uint32_t)__popcll(votes);
+      }
+    }
+  }
+  if (lane == 0) {
+    counts[0][wave] = above;
+    counts[1][wave] = ties;
+    counts[2][wave] = listed;
+  }
+  __syncthreads();
+  uint32_t before = 0, total = 0;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) {
+    if (w < wave) before += counts[2][w];
+    total += counts[2][w];
+  }
+  if (tid == 0) {
+    uint32_t all_above = 0, all_ties = 0;
+    for (int w = 0; w < kWaves; ++w) {
+      all_above += counts[0][w];
+      all_ties += counts[1][w];
+    }
+    if (all_above) atomicAdd(&st->above, all_above);
+    if (all_ties) atomicAdd(&st->ties, all_ties);
+    base_sh = total ? atomicAdd(&st->listed, total) : 0u;
+  }
+  __syncthreads();
+  const int64_t begin = band_list_begin(blk.lo);
+  const int64_t cap = band_list_begin(blk.hi) - begin;
+  const int64_t at = (int64_t)base_sh + before;
+  uint32_t* __restrict__ out = a.band_list + begin;
+  for (uint32_t i = lane; i < listed; i += 64)
+    if (at + i < cap) out[at + i] = list[wave * kSegment + i];  // (a list that does not fit is not used)
+}
+
+// One workgroup per tensor: the key of the wanted rank, from the band's list by histograms of 2048 bins
+// over the interval that holds it, the last few hundred ranked directly.
+template <bool NESTEROV>
+__global__ __launch_bounds__(kSelectThreads) void rank_band_kernel(SelectArgs a) {
+  typedef uint32_t vec4u __attribute__((ext_vector_type(4), aligned(4)));
+  constexpr int kLoads = 4;
+  __shared__ SelectShared sh;
+  const int tid = threadIdx.x;
+  const int j = blockIdx.x;
+  const TensorPlan plan = a.plans[j];
+  if (plan.exact != 2) return;
+  const BandState st = *band_state(a, plan);
+  const int64_t begin = band_list_begin(plan.offset);
+  const int64_t cap = band_list_begin(plan.offset + plan.n) - begin;
+  const uint32_t k = (uint32_t)plan.rank;
+  const uint32_t m = st.listed;
+  uint32_t thr_bits = 0;
+  if (k >= st.above && k - st.above < m && (int64_t)m <= cap) {
+    const uint32_t* __restrict__ list = a.band_list + begin;
+    uint32_t rank = k - st.above;
+    uint32_t lo = st.floor_key + 1u, width = st.ceil_key - lo;  // the keys lie in [lo, lo + width)
+    const uint32_t quads = m >> 2;
+    auto walk = [&](auto f) {  // f(key) for every key of the list
+      for (uint32_t q0 = tid; q0 < quads; q0 += kLoads * kSelectThreads) {
+        vec4u x[kLoads];
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i) {
+          const uint32_t q = q0 + i * kSelectThreads;
+          x[i] = *reinterpret_cast<const vec4u*>(list + 4 * (int64_t)(q < quads ? q : 0u));
+        }
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i) {
+          if (q0 + i * kSelectThreads < quads) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) f(x[i][c]);
+          }
+        }
+      }
+      if (tid < (int)(m & 3u)) f(list[4 * (int64_t)quads + tid]);
+    };
+#pragma unroll 1
+    for (;;) {
+      const int shift = width > (uint32_t)kSelectBins ? 21 - __clz((int)(width - 1u)) : 0;  // 11 bits stay
+      for (int i = tid; i < kSelectBins; i += kSelectThreads) sh.hist[i] = 0;
       if (tid == 0) sh.surv_n = 0;
       __syncthreads();
-      uint32_t floor_key = sh.wave_tot[0];
-#pragma unroll
-      for (int w = 1; w < kWaves; ++w) floor_key = sh.wave_tot[w] < floor_key ? sh.wave_tot[w] : floor_key;
-#pragma unroll
-      for (int i = 0; i < kSelectRegKeys; ++i)
-        if (key[i] != kNoKey && key[i] >= floor_key) {
-          const uint32_t pos = atomicAdd(&sh.surv_n, 1u);
-          if (pos < (uint32_t)kSelectThreads) sh.surv[pos] = key[i];
-        }
+      walk([&](uint32_t key) {
+        if (key - lo < width) atomicAdd(&sh.hist[(key - lo) >> shift], 1u);
+      });
       __syncthreads();
-      const uint32_t listed = sh.surv_n;
-      if (listed <= (uint32_t)kSelectThreads) {
-        thr_bits = rank_directly(sh, tid, listed, rank);
-        done = true;
+      uint32_t bin, over, members;
+      find_bin<kSelectThreads>(sh.hist, sh.wave_tot, sh.sel, tid, rank, bin, over, members);
+      rank -= over;
+      lo += bin << shift;
+      width = 1u << shift;
+      if (shift == 0) {
+        thr_bits = lo;
+        break;
       }
-      __syncthreads();
-    }
-    if (!done) thr_bits = select_in_registers<kSelectRegKeys>(sh, key, 0u, rank, tid);
-  } else {
-    // ---- candidates re-evaluated in every pass -----------------------------------
-    int consumed = 0;
-#pragma unroll 1
-    for (int pass = 0; pass < 3; ++pass) {
-      const int bits = pass == 2 ? 9 : 11;
-      const int shift = 31 - consumed - bits;
-      const uint32_t digit_mask = (1u << bits) - 1u;
-      for (int i = tid; i < kSelectBins; i += kSelectThreads) sh.hist[i] = 0;
-      __syncthreads();
-      for (int32_t p0 = tid; p0 < count; p0 += kSelectInFlight * kSelectThreads) {
-        float gg[kSelectInFlight], uu[kSelectInFlight], vv[kSelectInFlight];
-#pragma unroll
-        for (int q = 0; q < kSelectInFlight; ++q) {
-          const int32_t p = p0 + q * kSelectThreads;
-          gg[q] = uu[q] = vv[q] = 0.0f;
-          if (p < count) {
-            const int64_t e = c.offset + c.position(p);
-            gg[q] = c.g[e];
-            uu[q] = c.u[e];
-            vv[q] = c.v[e];
-          }
-        }
-#pragma unroll
-        for (int q = 0; q < kSelectInFlight; ++q) {
-          const int32_t p = p0 + q * kSelectThreads;
-          if (p < count) {
-            float u1, v1;
-            momentum_update(gg[q], uu[q], vv[q], c.m, c.scale, c.nesterov, u1, v1);
-            const uint32_t k = __float_as_uint(v1) & 0x7FFFFFFFu;
-            if (pass == 0 || (k >> (shift + bits)) == prefix)
-              atomicAdd(&sh.hist[(k >> shift) & digit_mask], 1u);
-          }
-        }
+      if (members <= (uint32_t)kSelectDirect) {
+        walk([&](uint32_t key) {
+          if (key - lo < width) sh.surv[atomicAdd(&sh.surv_n, 1u)] = key;
+        });
+        __syncthreads();
+        thr_bits = rank_directly(sh, tid, members, rank);
+        break;
       }
-      __syncthreads();
-      uint32_t bin, above, members;
-      find_bin<kSelectThreads>(sh.hist, sh.wave_tot, sh.sel, tid, rank, bin, above, members);
-      prefix = (prefix << bits) | bin;
-      rank -= above;
-      consumed += bits;
     }
-    thr_bits = prefix;
+  } else if (k >= st.above + m && k - (st.above + m) < st.ties) {
+    thr_bits = st.floor_key;
+  } else {  // the band missed, or its list did not fit
+    const float scale = a.scale_from_state ? a.state->scale : a.scale_const;
+    const Candidates c = candidates_of(a, j, plan, scale, NESTEROV);
+    thr_bits = rank_reevaluated(sh, c, plan.count, k, tid);
   }
-  const float thr = __uint_as_float(thr_bits);
-  if (tid == 0) {
-    a.thr[j] = thr;
-    if (a.out_thr) a.out_thr[j] = thr;
-  }
-  for (int64_t t = tile_first + tid; t < tile_end; t += kSelectThreads) a.tile_thr[t] = thr;
+  write_threshold(a, j, plan, __uint_as_float(thr_bits), tid);
 }
 
 // ---------------------------------------------------------------------------
@@ -1925,10 +2148,27 @@ hipError_t launch_norm(const float* g, int64_t n, double* partials, hipStream_t 
 }
 
 hipError_t launch_select(const SelectArgs& a, int32_t num_tensors, hipStream_t stream) {
-  if (a.nesterov)
-    hipLaunchKernelGGL(select_kernel<true>, dim3((unsigned)num_tensors), dim3(kSelectThreads), 0, stream, a);
-  else
-    hipLaunchKernelGGL(select_kernel<false>, dim3((unsigned)num_tensors), dim3(kSelectThreads), 0, stream, a);
+  const dim3 grid((unsigned)num_tensors), block(kSelectThreads);
+  if (a.bands) {
+    if (a.nesterov) hipLaunchKernelGGL((select_kernel<true, true>), grid, block, 0, stream, a);
+    else hipLaunchKernelGGL((select_kernel<false, true>), grid, block, 0, stream, a);
+  } else {
+    if (a.nesterov) hipLaunchKernelGGL((select_kernel<true, false>), grid, block, 0, stream, a);
+    else hipLaunchKernelGGL((select_kernel<false, false>), grid, block, 0, stream, a);
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_band(const SelectArgs& a, const EmitBlock* blocks, int32_t num_blocks, int32_t num_tensors,
+                       hipStream_t stream) {
+  const dim3 grid((unsigned)(num_blocks * kBandsPerPart));
+  if (a.nesterov) {
+    hipLaunchKernelGGL(collect_band_kernel<true>, grid, dim3(kBandThreads), 0, stream, a, blocks);
+    hipLaunchKernelGGL(rank_band_kernel<true>, dim3((unsigned)num_tensors), dim3(kSelectThreads), 0, stream, a);
+  } else {
+    hipLaunchKernelGGL(collect_band_kernel<false>, grid, dim3(kBandThreads), 0, stream, a, blocks);
+    hipLaunchKernelGGL(rank_band_kernel<false>, dim3((unsigned)num_tensors), dim3(kSelectThreads), 0, stream, a);
+  }
   return hipGetLastError();
 }
 

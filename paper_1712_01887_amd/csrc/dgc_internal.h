@@ -102,12 +102,33 @@ constexpr int kSelectDirect = 256;    // a bin with at most this many members is
 constexpr int kSelectBins = 2048;     // 11-bit digits
 constexpr int kSelectFloorRounds = 8; // ranks below 16 * this take the short cut over the threads' largest keys
 constexpr int kSelectInFlight = 8;    // candidates each thread gathers before using any
+// Exact selection (DGC_FLAG_EXACT_SELECT, or a sample as large as the tensor) from more candidates than
+// the workgroup's registers hold: select_kernel draws kBandSample elements (blocks of 1 << kBandBlockShift)
+// and names a band of keys that holds the wanted rank almost surely, collect_band_kernel reads the
+// tensor once, spread over the chip, and lists the keys inside the band, rank_band_kernel ranks them.
+// The list of a tensor takes three words per 64 elements of the block-sum and mask areas, which are
+// free until the streaming pass.  On the 161-tensor set of 25.6 M elements the three kernels take
+// 22 + 55 + 12 us at 0.1 % (the reads, 12 bytes per element, at 5.6 TB/s) and no more than 40 us more at
+// 25 %; three workgroup-wide passes over a whole tensor, which are still the way out when a band misses,
+// took 1385 us.
+constexpr int kBandSample = kSelectRegKeys * kSelectThreads;
+constexpr int kBandBlockShift = 5;
+constexpr int kBandListShift = 6;       // three list words per 64 elements
+constexpr int kBandThreads = 256;
+constexpr int kBandElements = 8192;     // elements per workgroup of the collecting pass
+constexpr int kBandsPerPart = kEmitElements / kBandElements;
+struct BandState {  // one per tensor, at the place of its first part in the part table: a line of its own,
+                    // because atomics on one line are carried out one after the other (9 ns each)
+  uint32_t floor_key, ceil_key;  // the band: floor_key < key < ceil_key
+  uint32_t above, ties, listed;  // keys at or above ceil_key, keys equal to floor_key, keys inside the band
+};
 
 // Clipping norm: a fixed number of partial sums keeps the result reproducible.
 constexpr int kNormThreads = 256;
 constexpr int kNormMaxBlocks = 512;
 
 constexpr int kMaxPayloads = 64;
+constexpr size_t kBandStride = 2 * sizeof(int32_t) * kMaxPayloads;  // a part's entries in the part table
 static_assert(kMaxPayloads <= 32768, "a payload's number is packed above a 16-bit index");
 
 // ---- device-resident state (start of the workspace) ------------------------
@@ -124,8 +145,8 @@ struct TensorPlan {
   int64_t n;        // elements
   int32_t count;    // candidates: n (whole tensor) or draws * block
   int32_t rank;     // 0-based descending rank that becomes the threshold
-  uint32_t nblocks; // aligned sample blocks in the tensor (sampled mode)
-  int32_t exact;    // 1: candidates are elements 0..n-1
+  uint32_t nblocks; // aligned sample blocks in the tensor (sampled mode); by way of a band: the tensor's first part
+  int32_t exact;    // 0: sampled; 1: candidates are elements 0..n-1; 2: the same, by way of a band
   int32_t k;             // clamp(ceil(d n), 1, n)
   int32_t refine_limit;  // floor(refine_alpha * k): more passes than this trigger the re-threshold
 };
@@ -155,6 +176,8 @@ struct SelectArgs {
   int32_t scale_from_state;  // 1: clipping is on; the scale comes from `partials` and is filed in `state`
   int32_t nesterov;
   int32_t block_shift;  // log2(sample_block)
+  BandState* bands;     // device, one slot of kBandStride bytes per part; null: no tensor has a band
+  uint32_t* band_list;  // device, see band_list_begin
   uint32_t seed_lo, seed_hi, iter_lo, iter_hi;
 };
 
@@ -290,6 +313,8 @@ hipError_t launch_clear_words(uint32_t* p, size_t words, hipStream_t stream);  /
 int32_t norm_blocks(int64_t n);  // partial sums launch_norm leaves
 hipError_t launch_norm(const float* g, int64_t n, double* partials, hipStream_t stream);
 hipError_t launch_select(const SelectArgs& a, int32_t num_tensors, hipStream_t stream);
+hipError_t launch_band(const SelectArgs& a, const EmitBlock* blocks, int32_t num_blocks, int32_t num_tensors,
+                       hipStream_t stream);
 hipError_t launch_stream(const StreamArgs& a, hipStream_t stream);
 hipError_t launch_ceiling(const float* a, float* b, float* c, int64_t n, int groups, hipStream_t stream);
 hipError_t launch_refine(const RefineArgs& a, int32_t num_tensors, hipStream_t stream);
