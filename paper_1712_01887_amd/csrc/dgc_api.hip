@@ -1013,9 +1013,6 @@ dgc_status dgc_encode(dgc_handle* h, const int32_t* idx, const float* val, const
   hipStream_t stream = static_cast<hipStream_t>(stream_);
   st = sync_workspace(h, workspace, workspace_bytes, out_offsets_host, false, stream);
   if (st != DGC_OK) return st;
-  int64_t widest = 0;
-  for (int32_t j = 0; j < h->num_tensors; ++j)
-    if (out_offsets_host[j + 1] - out_offsets_host[j] > widest) widest = out_offsets_host[j + 1] - out_offsets_host[j];
   const uint32_t total_blocks = h->wire_first_block[(size_t)h->num_tensors];
   if ((size_t)total_blocks > h->wire_slots) return DGC_ERR_CAPACITY;
   EncodeArgs ea{};
@@ -1031,7 +1028,8 @@ dgc_status dgc_encode(dgc_handle* h, const int32_t* idx, const float* val, const
   ea.state = at<DeviceState>(workspace, h->lay.state);
   ea.capacity = entry_capacity;
   ea.num_tensors = h->num_tensors;
-  if (!hip_ok(launch_encode(ea, widest, (int32_t)total_blocks, stream), "launch encode kernels")) return DGC_ERR_HIP;
+  ea.total_blocks = (int32_t)total_blocks;
+  if (!hip_ok(launch_encode(ea, stream), "launch encode kernels")) return DGC_ERR_HIP;
   return DGC_OK;
 }
 
@@ -1045,7 +1043,8 @@ dgc_status dgc_decode_accumulate(dgc_handle* h, float* dense, int64_t n, int32_t
   if (num_payloads > kMaxPayloads) return DGC_ERR_CAPACITY;
   if (!aligned(dense, 4)) return DGC_ERR_ALIGNMENT;
   DecodeArgs da{};
-  int64_t slots = 0;
+  int64_t most = 0;
+  int64_t slots[4] = {0, 0, 0, 0};  // blocks of all payloads, by block size
   for (int32_t w = 0; w < num_payloads; ++w) {
     const int64_t c = entry_counts_host[w];
     if (c < 0 || c >= (int64_t)1 << 31) return DGC_ERR_INVALID_ARG;
@@ -1054,25 +1053,23 @@ dgc_status dgc_decode_accumulate(dgc_handle* h, float* dense, int64_t n, int32_t
     da.runs[w] = runs_ptrs_host[w];
     da.vals[w] = vals_ptrs_host[w];
     da.count[w] = c;
-    da.seg.begin[w] = (int32_t)slots;
-    slots += (c + kWireChunk - 1) / kWireChunk;
-    if (slots > (int64_t)h->wire_slots) return DGC_ERR_CAPACITY;
+    if (c > most) most = c;
+    for (int s = 0; s < 4; ++s) slots[s] += ceil_div(c, (int64_t)kDecodeBlock << s);
+    if (slots[3] > (int64_t)h->wire_slots) return DGC_ERR_CAPACITY;
   }
-  da.seg.begin[num_payloads] = (int32_t)slots;
+  while (slots[da.block_shift] > (int64_t)h->wire_slots) ++da.block_shift;
+  for (int32_t w = 0; w < num_payloads; ++w)
+    da.seg.begin[w + 1] = da.seg.begin[w] + (int32_t)ceil_div(da.count[w], (int64_t)kDecodeBlock << da.block_shift);
   hipStream_t stream = static_cast<hipStream_t>(stream_);
   dgc_status st = sync_workspace(h, workspace, workspace_bytes, nullptr, false, stream);
   if (st != DGC_OK) return st;
+  if (most == 0) return DGC_OK;
   da.sums = at<uint32_t>(workspace, h->lay.wire_sums);
   da.dense = dense;
   da.n = n;
   da.diag_flags = diag_flags_dev;
-  if (h->cfg.flags & DGC_FLAG_DETERMINISTIC_ACCUMULATE) {
-    // one payload after the other: inside a payload every position is distinct
-    for (int32_t w = 0; w < num_payloads; ++w)
-      if (!hip_ok(launch_decode(da, w, 1, false, stream), "launch decode kernels")) return DGC_ERR_HIP;
-  } else {
-    if (!hip_ok(launch_decode(da, 0, num_payloads, true, stream), "launch decode kernels")) return DGC_ERR_HIP;
-  }
+  da.num = num_payloads;
+  if (!hip_ok(launch_decode(da, (h->cfg.flags & DGC_FLAG_DETERMINISTIC_ACCUMULATE) != 0, stream), "launch decode kernels")) return DGC_ERR_HIP;
   return DGC_OK;
 }
 

@@ -88,12 +88,25 @@ static_assert(kEmitElements <= 65536 && kEmitElements % kPartThreads == 0 &&
                   (kEmitElements / 32) % kPartClearThreads == 0,
               "dealt evenly");
 
-// Wire format (32-bit values + 16-bit zero-run lengths): pairs or entries handled by one
-// workgroup, kWirePerThread consecutive ones per thread.
+// Wire format (32-bit values + 16-bit zero-run lengths).  Encoder: pairs handled by one workgroup, the
+// lanes of a wavefront on neighbouring pairs.
 constexpr int kWireThreads = 256;
-constexpr int kWirePerThread = 16;
-constexpr int kWireChunk = kWireThreads * kWirePerThread;
+constexpr int kWireChunk = 4096;
+constexpr int kWireRounds = kWireChunk / kWireThreads;   // rounds of 64 pairs a wavefront takes
+constexpr int kWireSelfScan = 1024;  // block sums a workgroup of the second pass adds up for itself, without a scan launch
 constexpr int kScanThreads = 1024;
+constexpr int kScanPer = 8;          // block sums per thread and round of the scan
+// Decoder: entries a wavefront decodes at a time (eight per lane: one 16-byte load of runs), positions
+// recorded every kDecodeBlock << s entries, s the smallest for which the block sums fit the workspace.
+constexpr int kDecodePer = 8;
+constexpr int kDecodeBlock = 64 * kDecodePer;
+static_assert((kWireChunk >> 3) == kDecodeBlock, "s goes up to 3: the blocks the workspace is sized for");
+// Range form of the decoder: a workgroup owns a range of elements and adds the entries that fall into it
+// in LDS, payloads in order (32 KB: four workgroups per compute unit), then touches `dense` once per element.
+constexpr int kDecodeRange = 8192;
+constexpr int kDecodeThreads = 256;
+constexpr int kDecodeTasks = 4;       // blocks of entries a wavefront of the range form holds at a time
+constexpr int kDecodeSelfScan = 256;  // block sums a wavefront of the direct form adds up for itself, without a scan launch
 
 // Threshold selection: one workgroup per tensor.
 constexpr int kSelectThreads = 1024;
@@ -281,6 +294,8 @@ struct EncodeArgs {
   DeviceState* state;
   int64_t capacity;              // entries that fit in runs / vals
   int32_t num_tensors;
+  int32_t total_blocks;          // workgroup slots of all tensors
+  int32_t self_scan;             // the second pass adds the block sums up itself
 };
 
 // Segments of the block-sum array handed to the scan kernel: segment s is
@@ -293,11 +308,14 @@ struct DecodeArgs {
   const uint16_t* runs[kMaxPayloads];
   const float* vals[kMaxPayloads];
   int64_t count[kMaxPayloads];   // entries
-  ScanSegments seg;              // workgroup slots of every payload in `sums`
-  uint32_t* sums;
+  ScanSegments seg;              // blocks of every payload in `sums`
+  uint32_t* sums;                // positions a block covers; after the scan, the position it starts at
   float* dense;
   int64_t n;
   uint32_t* diag_flags;          // may be null
+  int32_t num;                   // payloads
+  int32_t block_shift;           // a block is kDecodeBlock << block_shift entries
+  int32_t scanned;               // `sums` holds positions (a scan has run); 0: sizes
 };
 
 enum ScatterMode : int32_t {
@@ -336,8 +354,8 @@ hipError_t launch_merge_parts(float* dense, const RegionPayloads& p, int32_t num
                               float scale, hipStream_t stream);
 hipError_t launch_clear_parts(float* dense, const RegionPayloads& p, int32_t num, const int64_t* out_offsets_dev,
                               const MergeBlock* parts, int32_t num_parts, void* found, hipStream_t stream);
-hipError_t launch_encode(const EncodeArgs& a, int64_t widest_region, int32_t total_blocks, hipStream_t stream);
-hipError_t launch_decode(const DecodeArgs& a, int32_t first, int32_t num, bool atomic, hipStream_t stream);
+hipError_t launch_encode(EncodeArgs a, hipStream_t stream);
+hipError_t launch_decode(DecodeArgs a, bool in_order, hipStream_t stream);
 
 }  // namespace dgc
 #endif  // DGC_INTERNAL_H_

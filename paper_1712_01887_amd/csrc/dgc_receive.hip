@@ -2,6 +2,7 @@
 // of N workers' sparse payloads into one dense vector, without float atomics on the paths
 // that take payloads as dgc_compress writes them.
 
+#include "dgc_device.h"
 #include "dgc_internal.h"
 
 namespace dgc {
@@ -157,38 +158,8 @@ __global__ __launch_bounds__(kFlatThreads) void scatter_regions_kernel(float* de
 // (inside one payload the indices are distinct), and the sums are stored.  Every index
 // belongs to one workgroup, so plain loads and stores do.  (Float atomics complete at
 // about 20 G/s on this part wherever they are executed, plain scattered stores at 80 G/s.)
-//
-// Positions [lo, hi) of the list L[0, m) whose values lie in [xa, xb), for a list in which
-// "value < xa" and "value < xb" are monotone; every lane of the wavefront takes part and
-// gets the same answer.
-__device__ __forceinline__ void wave_equal_range(const int32_t* __restrict__ L, int m, int32_t xa, int32_t xb,
-                                                 int lane, int& out_lo, int& out_hi) {
-  const int half = lane >> 5;  // 0: lower bound of xa, 1: lower bound of xb
-  const int sub = lane & 31;
-  const int32_t x = half ? xb : xa;
-  int lo = 0, hi = m;  // the answer of this lane's half lies in [lo, hi]
-  while (__ballot(hi > lo)) {
-    const int span = hi - lo;
-    const int step = (span + 31) >> 5;
-    const int pos = lo + sub * step;
-    const bool less = span > 0 && pos < hi && L[pos] < x;
-    const unsigned long long votes = __ballot(less);
-    const int c = __popc((uint32_t)(votes >> (32 * half)));  // probes below x form a prefix
-    if (span > 0) {
-      if (c == 0) {
-        hi = lo;
-      } else {
-        const int next = lo + c * step;
-        lo = lo + (c - 1) * step + 1;
-        hi = next < hi ? next : hi;
-      }
-    }
-  }
-  out_lo = __shfl(lo, 0);
-  out_hi = __shfl(lo, 32);
-}
 
-// The same for two lists at once, with the probes of both in flight together (`safe` is any
+// wave_equal_range for two lists at once, with the probes of both in flight together (`safe` is any
 // readable word: it is read in place of a probe that has nothing left to ask).
 __device__ __forceinline__ void wave_equal_range2(const int32_t* __restrict__ L0, int m0, const int32_t* __restrict__ L1,
                                                   int m1, const int32_t* __restrict__ safe, int32_t xa, int32_t xb,

@@ -1,6 +1,9 @@
 // HIP kernels of the wire format of the DGC payload for gfx950 (wave64, CDNA4): 32-bit
 // values with 16-bit run lengths of zeros, both directions.
 
+#include <cmath>
+
+#include "dgc_device.h"
 #include "dgc_internal.h"
 
 namespace dgc {
@@ -17,31 +20,7 @@ namespace {
 // 1 + (gap >> 16) entries, the last of them (gap & 0xFFFF, value).  Trailing zeros are
 // not encoded.  Encoding needs every tensor's region in ascending index order
 // (DGC_FLAG_SORTED_OUTPUT); regions follow each other in tensor order, which is index
-// order.  Both directions are a prefix sum: three launches each (block sums, scan of
-// the block sums, write).
-
-// Exclusive prefix sum of `x` over the workgroup (kWireThreads threads); `total` gets the sum.
-__device__ __forceinline__ uint32_t wire_block_scan(uint32_t x, uint32_t* wave_sums, uint32_t& total) {
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  uint32_t incl = x;
-  for (int d = 1; d < 64; d <<= 1) {
-    const uint32_t t = __shfl_up(incl, d);
-    if (lane >= d) incl += t;
-  }
-  if (lane == 63) wave_sums[wave] = incl;
-  __syncthreads();
-  uint32_t before = 0;
-  total = 0;
-#pragma unroll
-  for (int w = 0; w < kWireThreads / 64; ++w) {
-    const uint32_t t = wave_sums[w];
-    if (w < wave) before += t;
-    total += t;
-  }
-  __syncthreads();
-  return before + incl - x;
-}
+// order.  Both directions are a prefix sum: block sums, their scan, write.
 
 // Index of the last pair of the nearest non-empty region before tensor j, or -1.
 // Called by one whole wavefront; every lane returns the same value.
@@ -67,169 +46,475 @@ __device__ __forceinline__ int32_t last_index_before(const EncodeArgs& a, int j)
   return -1;
 }
 
-// PASS 0: entries needed by the workgroup's pairs.  PASS 1: write them.
-// grid = (chunks of the widest region, tensors)
+// Tensor whose region holds workgroup slot `slot`: the last j with first_block[j] <= slot (a tensor with an
+// empty region takes no slot and shares its number with the next one).  One whole wavefront.
+__device__ __forceinline__ int tensor_of_slot(const EncodeArgs& a, uint32_t slot) {
+  const int lane = threadIdx.x & 63;
+  int below = 0;
+  for (int base = 0; base < a.num_tensors; base += 64) {
+    const int j = base + lane;
+    below += __popcll(__ballot(j < a.num_tensors && a.first_block[j] <= slot));
+  }
+  return below - 1;
+}
+
+// PASS 0: entries needed by the workgroup's pairs.  PASS 1: write them.  One workgroup per kWireChunk
+// pairs a region can hold.  A wavefront takes 64 neighbouring pairs at a time, one per lane, so that
+// every load and store is a straight run; its predecessor's index comes from the lane below, and only a
+// round with a gap of 65536 or more needs a scan (a pair takes one entry otherwise).  With sixteen
+// consecutive pairs per thread instead, 4.1 M pairs took 17 us to count and 71 us to write.
 template <int PASS>
 __global__ __launch_bounds__(kWireThreads) void encode_kernel(EncodeArgs a) {
-  __shared__ uint32_t wave_sums[kWireThreads / 64];
-  __shared__ int32_t region_prev;
-  const int j = blockIdx.y;
-  const uint32_t slot0 = a.first_block[j];
-  const uint32_t slots = a.first_block[j + 1] - slot0;
-  if (blockIdx.x >= slots) return;  // beyond this tensor's region
+  constexpr int kWaves = kWireThreads / 64;
+  __shared__ uint32_t wave_need[kWaves];
+  __shared__ uint32_t wave_before[kWaves];
+  const int lane = threadIdx.x & 63;
+  const int wave = threadIdx.x >> 6;
+  const int j = tensor_of_slot(a, blockIdx.x);
   const int64_t region = a.out_offsets[j];
   const int64_t cap = a.out_offsets[j + 1] - region;
   int64_t count = a.counts[j];
   if (count > cap) count = cap;
-  const int64_t begin = (int64_t)blockIdx.x * kWireChunk;
+  const int64_t begin = (int64_t)(blockIdx.x - a.first_block[j]) * kWireChunk;
+  const bool last_slot = PASS == 1 && a.self_scan && (int)blockIdx.x == a.total_blocks - 1;  // knows how many entries there are
   if (begin >= count) {
-    if (PASS == 0 && threadIdx.x == 0) a.sums[slot0 + blockIdx.x] = 0;
-    return;
-  }
-  if (blockIdx.x == 0) {
-    if (threadIdx.x < 64) {
-      const int32_t prev = last_index_before(a, j);
-      if (threadIdx.x == 0) region_prev = prev;
-    }
-    __syncthreads();
+    if (PASS == 0 && threadIdx.x == 0) a.sums[blockIdx.x] = 0;
+    if (!last_slot) return;
   }
   const int32_t* __restrict__ idx = a.idx + region;
-  const int64_t p0 = begin + (int64_t)threadIdx.x * kWirePerThread;
-  int32_t mine[kWirePerThread];
-  int32_t prev = -1;
-  if (p0 < count) prev = p0 > 0 ? idx[p0 - 1] : region_prev;
+  const int64_t p0 = begin + wave * (64 * kWireRounds);  // the wavefront's first pair
+  int32_t prev = -1;                                     // index of the pair before the round
+  if (p0 > 0 && p0 <= count) prev = idx[p0 - 1];
+  else if (p0 == 0 && count > 0) prev = last_index_before(a, j);
+  int32_t mine[kWireRounds];
 #pragma unroll
-  for (int k = 0; k < kWirePerThread; ++k) mine[k] = p0 + k < count ? idx[p0 + k] : 0;
-  uint32_t need = 0;
-  bool unsorted = false;
-  {
-    int32_t q = prev;
+  for (int r = 0; r < kWireRounds; ++r) {
+    const int64_t p = p0 + r * 64 + lane;
+    mine[r] = p < count ? idx[p] : 0;
+  }
+  float x[PASS == 1 ? kWireRounds : 1];
+  if (PASS == 1) {
+    const float* __restrict__ val = a.val + region;
 #pragma unroll
-    for (int k = 0; k < kWirePerThread; ++k) {
-      if (p0 + k < count) {
-        int32_t gap = mine[k] - q - 1;
-        if (gap < 0) {  // not ascending: flagged, encoded as if adjacent
-          gap = 0;
-          unsorted = true;
-        }
-        need += 1u + ((uint32_t)gap >> 16);
-        q = mine[k];
-      }
+    for (int r = 0; r < kWireRounds; ++r) {
+      const int64_t p = p0 + r * 64 + lane;
+      x[r] = p < count ? val[p] : 0.0f;
     }
   }
-  uint32_t total;
-  const uint32_t excl = wire_block_scan(need, wave_sums, total);
+  int32_t gap[kWireRounds];  // zeros before the lane's pair; not ascending: flagged, and encoded as if adjacent
+  uint32_t fillers = 0;      // of the lane
+  bool unsorted = false;
+#pragma unroll
+  for (int r = 0; r < kWireRounds; ++r) {
+    const bool have = p0 + r * 64 + lane < count;
+    int32_t before = __shfl_up(mine[r], 1);
+    if (lane == 0) before = prev;
+    prev = __builtin_amdgcn_readlane(mine[r], 63);
+    gap[r] = have ? mine[r] - before - 1 : 0;
+    if (gap[r] < 0) {
+      gap[r] = 0;
+      unsorted = true;
+    }
+    fillers += (uint32_t)gap[r] >> 16;
+  }
+  const int64_t left = count - p0;
+  const uint32_t pairs = left <= 0 ? 0u : left < 64 * kWireRounds ? (uint32_t)left : (uint32_t)(64 * kWireRounds);
+  const uint32_t need = pairs + wave_sum(fillers);  // of the wavefront
+  if (lane == 0) wave_need[wave] = need;
   if (PASS == 0) {
-    if (threadIdx.x == 0) a.sums[slot0 + blockIdx.x] = total;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      uint32_t total = 0;
+      for (int w = 0; w < kWaves; ++w) total += wave_need[w];
+      a.sums[blockIdx.x] = total;
+    }
     if (unsorted) atomicOr(&a.state->flags, (uint32_t)DGC_DIAG_UNSORTED);
     return;
   }
-  const float* __restrict__ val = a.val + region;
-  int64_t pos = (int64_t)a.sums[slot0 + blockIdx.x] + excl;  // sums hold the exclusive scan by now
+  uint32_t before_block = 0;
+  if (a.self_scan) {  // few block sums: every workgroup adds up those before its own
+    uint32_t mine_before = 0;
+    for (uint32_t i = threadIdx.x; i < blockIdx.x; i += kWireThreads) mine_before += a.sums[i];
+    mine_before = wave_sum(mine_before);
+    if (lane == 0) wave_before[wave] = mine_before;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) before_block += wave_before[w];
+  } else {
+    __syncthreads();
+    before_block = a.sums[blockIdx.x];
+  }
+  int64_t pos = before_block;
+  uint32_t block_total = 0;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) {
+    if (w < wave) pos += wave_need[w];
+    block_total += wave_need[w];
+  }
+  if (last_slot && threadIdx.x == 0) *a.num_entries = (int32_t)(before_block + block_total);
   bool overflow = false;
-  int32_t q = prev;
-#pragma unroll 1
-  for (int k = 0; k < kWirePerThread; ++k) {
-    if (p0 + k >= count) break;
-    int32_t gap = mine[k] - q - 1;
-    if (gap < 0) gap = 0;
-    for (uint32_t f = (uint32_t)gap >> 16; f > 0; --f) {
-      if (pos < a.capacity) {
-        a.runs[pos] = 0xFFFFu;
-        a.vals[pos] = 0.0f;
+#pragma unroll
+  for (int r = 0; r < kWireRounds; ++r) {
+    const int64_t round_left = count - (p0 + r * 64);
+    if (round_left <= 0) break;
+    const bool have = lane < round_left;
+    const uint32_t fill = (uint32_t)gap[r] >> 16;
+    uint32_t incl = (uint32_t)lane + 1u;  // entries of the round up to and with this lane's
+    uint32_t total = round_left < 64 ? (uint32_t)round_left : 64u;
+    if (__ballot(fill != 0) != 0) {
+      incl = wave_inclusive_sum(have ? 1u + fill : 0u);
+      total = wave_last(incl);
+    }
+    if (have) {
+      int64_t at = pos + incl - 1u;  // of the pair's own entry
+      for (uint32_t f = fill; f > 0; --f) {
+        if (at - f < a.capacity) {
+          a.runs[at - f] = 0xFFFFu;
+          a.vals[at - f] = 0.0f;
+        } else {
+          overflow = true;
+        }
+      }
+      if (at < a.capacity) {
+        a.runs[at] = (uint16_t)((uint32_t)gap[r] & 0xFFFFu);
+        a.vals[at] = x[r];
       } else {
         overflow = true;
       }
-      ++pos;
     }
-    if (pos < a.capacity) {
-      a.runs[pos] = (uint16_t)((uint32_t)gap & 0xFFFFu);
-      a.vals[pos] = val[p0 + k];
-    } else {
-      overflow = true;
-    }
-    ++pos;
-    q = mine[k];
+    pos += total;
   }
   if (overflow) atomicOr(&a.state->flags, (uint32_t)DGC_DIAG_OVERFLOW);
 }
 
-// In-place exclusive prefix sum of every segment of `sums`; one workgroup per segment.
-// `total_out` (may be null) receives the sum of segment 0.
-__global__ __launch_bounds__(kScanThreads) void scan_kernel(uint32_t* sums, ScanSegments seg, int32_t* total_out) {
-  __shared__ uint32_t wave_sums[kScanThreads / 64];
+// In-place exclusive prefix sum of every segment of `sums`; one workgroup per segment.  Sums are formed in
+// 64 bits and held at 2^31 - 1, which lies behind every element (a stream that covers more than it may
+// cannot wrap round to a valid position).  `total_out` (may be null) receives the sum of segment 0;
+// `diag_flags` (may be null) DGC_DIAG_BAD_INDEX if a segment's sum exceeds `limit`.
+__global__ __launch_bounds__(kScanThreads) void scan_kernel(uint32_t* sums, ScanSegments seg, int32_t* total_out,
+                                                            int64_t limit, uint32_t* diag_flags) {
+  constexpr int kWaves = kScanThreads / 64;
+  __shared__ uint64_t wave_sums[kWaves];
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int32_t begin = seg.begin[blockIdx.x];
   const int32_t end = seg.begin[blockIdx.x + 1];
-  uint32_t carry = 0;
-  for (int32_t base = begin; base < end; base += kScanThreads) {
-    const int32_t i = base + threadIdx.x;
-    const uint32_t x = i < end ? sums[i] : 0u;
-    uint32_t incl = x;
+  uint64_t carry = 0;
+  for (int64_t base = begin; base < end; base += kScanThreads * kScanPer) {
+    const int64_t i0 = base + (int64_t)threadIdx.x * kScanPer;
+    uint32_t x[kScanPer];
+    uint64_t mine = 0;
+#pragma unroll
+    for (int k = 0; k < kScanPer; ++k) {
+      x[k] = i0 + k < end ? sums[i0 + k] : 0u;
+      mine += x[k];
+    }
+    uint64_t incl = mine;
     for (int d = 1; d < 64; d <<= 1) {
-      const uint32_t t = __shfl_up(incl, d);
+      const uint64_t t = __shfl_up(incl, d);
       if (lane >= d) incl += t;
     }
     if (lane == 63) wave_sums[wave] = incl;
     __syncthreads();
-    uint32_t before = 0, total = 0;
+    uint64_t before = carry, total = 0;
 #pragma unroll
-    for (int w = 0; w < kScanThreads / 64; ++w) {
-      const uint32_t t = wave_sums[w];
+    for (int w = 0; w < kWaves; ++w) {
+      const uint64_t t = wave_sums[w];
       if (w < wave) before += t;
       total += t;
     }
-    if (i < end) sums[i] = carry + before + incl - x;
+    uint64_t run = before + incl - mine;
+#pragma unroll
+    for (int k = 0; k < kScanPer; ++k) {
+      if (i0 + k < end) sums[i0 + k] = run < 0x7FFFFFFFull ? (uint32_t)run : 0x7FFFFFFFu;
+      run += x[k];
+    }
     carry += total;
     __syncthreads();
   }
-  if (total_out && blockIdx.x == 0 && threadIdx.x == 0) *total_out = (int32_t)carry;
+  if (threadIdx.x == 0) {
+    if (total_out && blockIdx.x == 0) *total_out = (int32_t)carry;
+    if (diag_flags && carry > (uint64_t)limit) atomicOr(diag_flags, (uint32_t)DGC_DIAG_BAD_INDEX);
+  }
 }
 
-// PASS 0: positions covered by the workgroup's entries (run + 1 each).
-// PASS 1: dense[position] += value.  grid = (chunks, payloads)
-template <int PASS, bool ATOMIC>
-__global__ __launch_bounds__(kWireThreads) void decode_kernel(DecodeArgs a, int32_t first) {
-  __shared__ uint32_t wave_sums[kWireThreads / 64];
-  const int w = first + blockIdx.y;
-  const int64_t count = a.count[w];
-  const int64_t begin = (int64_t)blockIdx.x * kWireChunk;
-  if (begin >= count) return;
-  const uint16_t* __restrict__ runs = a.runs[w];
-  const int64_t e0 = begin + (int64_t)threadIdx.x * kWirePerThread;
-  uint32_t run[kWirePerThread];
-  uint32_t span = 0;
+// ---- decoder ----------------------------------------------------------------
+// A wavefront takes kDecodeBlock consecutive entries, kDecodePer per lane.
+struct Entries {
+  uint32_t runs[kDecodePer / 2];  // two to a word
+  float val[kDecodePer];
+  int have;                       // entries of this lane that exist
+  __device__ __forceinline__ uint32_t run(int k) const { return (runs[k >> 1] >> (16 * (k & 1))) & 0xFFFFu; }
+};
+
+// Entries e0 .. e0 + kDecodePer - 1 of a payload of `count`; VALUES = false: the runs only.
+template <bool VALUES>
+__device__ __forceinline__ void load_entries(Entries& E, const uint16_t* __restrict__ runs, const float* __restrict__ vals,
+                                             int64_t count, int64_t e0) {
+  typedef float vec4u __attribute__((ext_vector_type(4), aligned(4)));
+  static_assert(kDecodePer == 8, "one 16-byte load of runs, two of values");
+  const int64_t left = count - e0;
+  E.have = left <= 0 ? 0 : left < kDecodePer ? (int)left : kDecodePer;
 #pragma unroll
-  for (int k = 0; k < kWirePerThread; ++k) {
-    run[k] = e0 + k < count ? (uint32_t)runs[e0 + k] : 0u;
-    if (e0 + k < count) span += run[k] + 1u;
-  }
-  uint32_t total;
-  const uint32_t excl = wire_block_scan(span, wave_sums, total);
-  const int32_t slot = a.seg.begin[w] + (int32_t)blockIdx.x;
-  if (PASS == 0) {
-    if (threadIdx.x == 0) a.sums[slot] = total;
-    return;
-  }
-  const float* __restrict__ vals = a.vals[w];
-  int64_t pos = (int64_t)a.sums[slot] + excl;
-  bool bad = false;
+  for (int k = 0; k < kDecodePer / 2; ++k) E.runs[k] = 0u;
 #pragma unroll
-  for (int k = 0; k < kWirePerThread; ++k) {
-    if (e0 + k < count) {
-      pos += run[k];
-      const float x = vals[e0 + k];
-      if (pos < a.n) {
-        if (ATOMIC) unsafeAtomicAdd(a.dense + pos, x);
-        else a.dense[pos] = a.dense[pos] + x;
-      } else {
-        bad = true;
-      }
-      ++pos;
+  for (int k = 0; k < kDecodePer; ++k) E.val[k] = 0.0f;
+  if (E.have == kDecodePer && (reinterpret_cast<uintptr_t>(runs) & 15) == 0) {  // e0 is a multiple of eight
+    const uint4 r = *reinterpret_cast<const uint4*>(runs + e0);
+    E.runs[0] = r.x;
+    E.runs[1] = r.y;
+    E.runs[2] = r.z;
+    E.runs[3] = r.w;
+  } else {
+#pragma unroll
+    for (int k = 0; k < kDecodePer; ++k)
+      if (k < E.have) E.runs[k >> 1] |= (uint32_t)runs[e0 + k] << (16 * (k & 1));
+  }
+  if (!VALUES) return;
+  if (E.have == kDecodePer) {
+    const vec4u a = *reinterpret_cast<const vec4u*>(vals + e0);
+    const vec4u b = *reinterpret_cast<const vec4u*>(vals + e0 + 4);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      E.val[k] = a[k];
+      E.val[4 + k] = b[k];
     }
+  } else {
+#pragma unroll
+    for (int k = 0; k < kDecodePer; ++k)
+      if (k < E.have) E.val[k] = vals[e0 + k];
+  }
+}
+
+// Positions the lane's entries cover.
+__device__ __forceinline__ uint32_t covered(const Entries& E) {
+  uint32_t span = (uint32_t)E.have;
+#pragma unroll
+  for (int k = 0; k < kDecodePer; ++k) span += E.run(k);
+  return span;
+}
+
+// Positions covered by every block of every payload.  grid = (blocks / wavefronts, payloads)
+__global__ __launch_bounds__(kWireThreads) void decode_sums_kernel(DecodeArgs a) {
+  const int lane = threadIdx.x & 63;
+  const int w = blockIdx.y;
+  const int block = (int)blockIdx.x * (kWireThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (block >= a.seg.begin[w + 1] - a.seg.begin[w]) return;
+  uint32_t sum = 0;
+  for (int sub = 0; sub < 1 << a.block_shift; ++sub) {
+    Entries E;
+    load_entries<false>(E, a.runs[w], nullptr, a.count[w],
+                        (((int64_t)block << a.block_shift) + sub) * kDecodeBlock + lane * kDecodePer);
+    sum += covered(E);
+  }
+  sum = wave_sum(sum);
+  if (lane == 0) a.sums[a.seg.begin[w] + block] = sum;
+}
+
+// Direct form: dense[position] += value, entry by entry.  grid = (blocks / wavefronts, payloads)
+// Bound by the rate of the scattered additions: about 20 G/s as atomics wherever they are carried out.
+template <bool ATOMIC>
+__global__ __launch_bounds__(kWireThreads) void decode_direct_kernel(DecodeArgs a, int32_t first) {
+  const int lane = threadIdx.x & 63;
+  const int w = first + blockIdx.y;
+  const int block = (int)blockIdx.x * (kWireThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int32_t slot0 = a.seg.begin[w];
+  if (block >= a.seg.begin[w + 1] - slot0) return;
+  Entries E;
+  int64_t e0 = ((int64_t)block << a.block_shift) * kDecodeBlock + lane * kDecodePer;
+  load_entries<true>(E, a.runs[w], a.vals[w], a.count[w], e0);
+  uint64_t pos;
+  if (a.scanned) {
+    pos = a.sums[slot0 + block];
+  } else {  // few blocks: the wavefront adds up those before its own
+    uint32_t before = 0;
+    for (int i = lane; i < block; i += 64) before += a.sums[slot0 + i];
+    // (a block covers up to 2^25 positions: the two halves are summed apart)
+    pos = (uint64_t)wave_sum(before & 0xFFFFu) + ((uint64_t)wave_sum(before >> 16) << 16);
+  }
+  bool bad = false;
+  for (int sub = 0;;) {
+    const uint32_t span = covered(E);
+    const uint32_t incl = wave_inclusive_sum(span);
+    uint64_t at = pos + (incl - span);
+#pragma unroll
+    for (int k = 0; k < kDecodePer; ++k) {
+      at += E.run(k);
+      if (k < E.have) {
+        if (at < (uint64_t)a.n) {
+          if (ATOMIC) unsafeAtomicAdd(a.dense + at, E.val[k]);
+          else a.dense[at] = a.dense[at] + E.val[k];
+        } else {
+          bad = true;
+        }
+        ++at;
+      }
+    }
+    if (++sub >= 1 << a.block_shift) break;
+    pos += wave_last(incl);
+    e0 += kDecodeBlock;
+    load_entries<true>(E, a.runs[w], a.vals[w], a.count[w], e0);
   }
   if (bad && a.diag_flags) atomicOr(a.diag_flags, (uint32_t)DGC_DIAG_BAD_INDEX);
+}
+
+// Range form: a workgroup owns kDecodeRange elements of `dense`.  One wavefront per payload finds, by
+// search among the positions the blocks start at, the blocks of entries that reach into the range; the
+// wavefronts take these blocks in turn, kDecodeTasks each at a time so that their loads are one wait, and
+// add the entries inside the range in LDS, payload after payload with a barrier between them (positions of
+// one payload are distinct).
+// PLAIN: the accumulator starts from `dense` and is written back: the ordered sum, bit for bit.  Otherwise
+// it starts from nothing (-0, which an element that no entry names still is at the end) and every
+// element that occurs is added to `dense` by one atomic: callers may add to one vector from several
+// streams at a time.  The atomics are what that form costs: 64 neighbouring elements go as four 64-byte
+// requests, 20 G of which complete per second, 195 us for 66 M elements whose every sector is
+// touched where plain stores take 75.
+// MULTI: a block is several kDecodeBlocks (streams so long that the block sums did not fit otherwise).
+template <bool PLAIN, bool MULTI>
+__global__ __launch_bounds__(kDecodeThreads) void decode_range_kernel(DecodeArgs a) {
+  typedef float vec4u __attribute__((ext_vector_type(4), aligned(4)));  // `dense` is aligned to 4 bytes
+  constexpr int kWaves = kDecodeThreads / 64;
+  constexpr int kQuads = kDecodeRange / 4 / kDecodeThreads;
+  constexpr int kBatch = kWaves * kDecodeTasks;
+  __shared__ alignas(16) float acc[kDecodeRange];
+  __shared__ int32_t first_block[kMaxPayloads];
+  __shared__ int32_t blocks[kMaxPayloads];
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t begin = (int64_t)blockIdx.x * kDecodeRange;
+  const int32_t length = a.n - begin < kDecodeRange ? (int32_t)(a.n - begin) : kDecodeRange;
+  float* __restrict__ range = a.dense + begin;
+
+  vec4u d[kQuads];
+#pragma unroll
+  for (int i = 0; i < kQuads; ++i) {
+    const int e = 4 * (tid + i * kDecodeThreads);
+    d[i] = vec4u{-0.0f, -0.0f, -0.0f, -0.0f};
+    if (PLAIN) {
+      if (e + 4 <= length) {
+        d[i] = *reinterpret_cast<const vec4u*>(range + e);
+      } else {
+        for (int c = 0; c < 4; ++c)
+          if (e + c < length) d[i][c] = range[e + c];
+      }
+    }
+  }
+  for (int w = wave; w < a.num; w += kWaves) {
+    const int32_t slot0 = a.seg.begin[w];
+    int lo = 0, hi = 0;
+    // the last block that starts at or before the range's first element, up to the last that starts inside
+    wave_equal_range(reinterpret_cast<const int32_t*>(a.sums) + slot0, a.seg.begin[w + 1] - slot0, (int32_t)begin + 1,
+                     (int32_t)(begin + length), lane, lo, hi);
+    if (lane == 0) {
+      first_block[w] = lo - 1;
+      blocks[w] = hi > lo - 1 && hi > 0 ? hi - (lo - 1) : 0;
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < kQuads; ++i) *reinterpret_cast<float4*>(&acc[4 * (tid + i * kDecodeThreads)]) = make_float4(d[i][0], d[i][1], d[i][2], d[i][3]);
+  __syncthreads();
+
+  // adds a block whose first entry's predecessors cover `pos` positions; returns what the block covers
+  auto add = [&](const Entries& E, uint32_t pos) {
+    uint32_t rel = pos - (uint32_t)begin;  // (positions stay below 2^32: see scan_kernel)
+    float sum[kDecodePer];
+    uint32_t at[kDecodePer];
+#pragma unroll
+    for (int k = 0; k < kDecodePer; ++k) {
+      rel += E.run(k);
+      at[k] = k < E.have && rel < (uint32_t)length ? rel : 0xFFFFFFFFu;
+      sum[k] = at[k] != 0xFFFFFFFFu ? acc[at[k]] + E.val[k] : 0.0f;
+      ++rel;
+    }
+#pragma unroll
+    for (int k = 0; k < kDecodePer; ++k)
+      if (at[k] != 0xFFFFFFFFu) acc[at[k]] = sum[k];
+  };
+
+  if (MULTI) {
+    for (int w = 0; w < a.num; ++w) {
+      for (int b = wave; b < blocks[w]; b += kWaves) {
+        const int32_t block = first_block[w] + b;
+        uint32_t pos = a.sums[a.seg.begin[w] + block];
+        for (int sub = 0; sub < 1 << a.block_shift; ++sub) {
+          Entries E;
+          load_entries<true>(E, a.runs[w], a.vals[w], a.count[w],
+                             (((int64_t)block << a.block_shift) + sub) * kDecodeBlock + lane * kDecodePer);
+          const uint32_t span = covered(E);
+          const uint32_t incl = wave_inclusive_sum(span);
+          add(E, pos + incl - span);
+          pos += wave_last(incl);
+        }
+      }
+      __syncthreads();
+    }
+  } else {
+    // tasks: the blocks of all payloads, one payload after the other
+    const uint32_t own = lane < a.num ? (uint32_t)blocks[lane] : 0u;
+    const uint32_t incl = wave_inclusive_sum(own);
+    const int total = (int)wave_last(incl);
+    if (total == 0) return;
+    const uint32_t task0 = lane < a.num ? incl - own : 0xFFFFFFFFu;  // lane w: first task of payload w
+    const int32_t block0 = lane < a.num ? first_block[lane] : 0;
+    auto payload_of_task = [&](int t) { return __popcll(__ballot(task0 <= (uint32_t)t)) - 1; };
+    for (int t0 = 0; t0 < total; t0 += kBatch) {
+      Entries E[kDecodeTasks];
+      uint32_t pos[kDecodeTasks];
+      int wk[kDecodeTasks];
+#pragma unroll
+      for (int k = 0; k < kDecodeTasks; ++k) {
+        const int t = t0 + k * kWaves + wave;
+        wk[k] = -1;
+        E[k].have = 0;
+        pos[k] = 0;
+        if (t < total) {  // uniform
+          const int w = payload_of_task(t);
+          const int32_t block = __builtin_amdgcn_readlane(block0, w) + t - __builtin_amdgcn_readlane((int)task0, w);
+          wk[k] = w;
+          pos[k] = a.sums[a.seg.begin[w] + block];
+          load_entries<true>(E[k], a.runs[w], a.vals[w], a.count[w], (int64_t)block * kDecodeBlock + lane * kDecodePer);
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < kDecodeTasks; ++k) {
+        if (wk[k] >= 0) {
+          const uint32_t span = covered(E[k]);
+          pos[k] += wave_inclusive_sum(span) - span;
+        }
+      }
+      const int w_first = payload_of_task(t0);
+      const int w_last = payload_of_task(t0 + kBatch < total ? t0 + kBatch - 1 : total - 1);
+      for (int w = w_first; w <= w_last; ++w) {
+#pragma unroll
+        for (int k = 0; k < kDecodeTasks; ++k)
+          if (wk[k] == w) add(E[k], pos[k]);
+        __syncthreads();
+      }
+    }
+  }
+
+#pragma unroll
+  for (int i = 0; i < kQuads; ++i) {
+    if (PLAIN) {
+      const int e = 4 * (tid + i * kDecodeThreads);
+      const float4 s = *reinterpret_cast<const float4*>(&acc[e]);
+      if (e + 4 <= length) {
+        *reinterpret_cast<vec4u*>(range + e) = vec4u{s.x, s.y, s.z, s.w};
+      } else {
+        const float sc[4] = {s.x, s.y, s.z, s.w};
+        for (int c = 0; c < 4; ++c)
+          if (e + c < length) range[e + c] = sc[c];
+      }
+    } else {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const int e = tid + (4 * i + c) * kDecodeThreads;
+        const float s = acc[e];
+        if (e < length && __float_as_uint(s) != 0x80000000u) unsafeAtomicAdd(range + e, s);
+      }
+    }
+  }
 }
 
 }  // namespace
@@ -237,38 +522,64 @@ __global__ __launch_bounds__(kWireThreads) void decode_kernel(DecodeArgs a, int3
 // ---------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------
-hipError_t launch_encode(const EncodeArgs& a, int64_t widest_region, int32_t total_blocks, hipStream_t stream) {
-  if (widest_region <= 0 || total_blocks <= 0) {  // nothing can have been emitted
-    hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(kScanThreads), 0, stream, a.sums, ScanSegments{}, a.num_entries);
+hipError_t launch_encode(EncodeArgs a, hipStream_t stream) {
+  ScanSegments seg{};
+  seg.begin[1] = a.total_blocks;
+  if (a.total_blocks <= 0) {  // nothing can have been emitted
+    hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(kScanThreads), 0, stream, a.sums, seg, a.num_entries, (int64_t)0,
+                       (uint32_t*)nullptr);
     return hipGetLastError();
   }
-  const int64_t chunks = ceil_div(widest_region, kWireChunk);
-  if (chunks > 0x7FFFFFFF || a.num_tensors > 65535) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)chunks, (unsigned)a.num_tensors);
+  a.self_scan = a.total_blocks <= kWireSelfScan ? 1 : 0;
+  const dim3 grid((unsigned)a.total_blocks);
   hipLaunchKernelGGL(encode_kernel<0>, grid, dim3(kWireThreads), 0, stream, a);
-  ScanSegments seg{};
-  seg.begin[0] = 0;
-  seg.begin[1] = total_blocks;
-  hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(kScanThreads), 0, stream, a.sums, seg, a.num_entries);
+  if (!a.self_scan)
+    hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(kScanThreads), 0, stream, a.sums, seg, a.num_entries, (int64_t)0,
+                       (uint32_t*)nullptr);
   hipLaunchKernelGGL(encode_kernel<1>, grid, dim3(kWireThreads), 0, stream, a);
   return hipGetLastError();
 }
 
-hipError_t launch_decode(const DecodeArgs& a, int32_t first, int32_t num, bool atomic, hipStream_t stream) {
-  int64_t most = 0;
-  for (int32_t w = first; w < first + num; ++w)
-    if (a.count[w] > most) most = a.count[w];
-  if (num <= 0 || most <= 0) return hipSuccess;
-  const dim3 grid((unsigned)ceil_div(most, kWireChunk), (unsigned)num);
-  ScanSegments seg{};
-  for (int32_t w = 0; w <= num; ++w) seg.begin[w] = a.seg.begin[first + w];
-  hipLaunchKernelGGL((decode_kernel<0, true>), grid, dim3(kWireThreads), 0, stream, a, first);
-  hipLaunchKernelGGL(scan_kernel, dim3((unsigned)num), dim3(kScanThreads), 0, stream, a.sums, seg,
-                     (int32_t*)nullptr);
-  if (atomic)
-    hipLaunchKernelGGL((decode_kernel<1, true>), grid, dim3(kWireThreads), 0, stream, a, first);
-  else
-    hipLaunchKernelGGL((decode_kernel<1, false>), grid, dim3(kWireThreads), 0, stream, a, first);
+// Which form (times in us).  The direct one costs its additions, 20 G/s as atomics; in order they are plain,
+// 40 G/s, and every payload has a launch of its own.  The range form costs an atomic request per 64-byte
+// sector of `dense` that occurs, or in order one pass over `dense` at 5 TB/s, and decodes every block once for
+// every range that it reaches into, about 1500 blocks per us.  Whole calls, encoder included, direct against
+// range as atomics: 66 M elements, 1 % of two workers 89 against 165, 6 % in all of four 229 against 157,
+// 25 % in all 950 against 267; 25.6 M elements, 0.4 % of sixteen workers 99 against 108.  In order, 25.6 M
+// elements, 0.1 % of sixteen workers: 384 with three launches per payload against 94.
+static bool use_range_form(const DecodeArgs& a, bool in_order) {
+  double entries = 0.0;
+  for (int32_t w = 0; w < a.num; ++w) entries += (double)a.count[w];
+  const double n = (double)a.n;
+  const double decode = (entries / kDecodeBlock + (double)a.num * n / kDecodeRange) / 1500.0;
+  if (in_order) return 10.0 + n * 8.0 / 5e6 + decode < 8.0 * a.num + entries / 40e3;
+  return n / 16.0 * (1.0 - std::exp(-16.0 * entries / n)) / 20e3 + decode < entries / 20e3;
+}
+
+hipError_t launch_decode(DecodeArgs a, bool in_order, hipStream_t stream) {
+  int32_t most = 0;  // blocks
+  for (int32_t w = 0; w < a.num; ++w) most = a.seg.begin[w + 1] - a.seg.begin[w] > most ? a.seg.begin[w + 1] - a.seg.begin[w] : most;
+  const unsigned groups = (unsigned)ceil_div(most, kWireThreads / 64);
+  hipLaunchKernelGGL(decode_sums_kernel, dim3(groups, (unsigned)a.num), dim3(kWireThreads), 0, stream, a);
+  const bool range = use_range_form(a, in_order);
+  a.scanned = range || most > kDecodeSelfScan || a.block_shift > 0 ? 1 : 0;
+  if (a.scanned)  // (the direct form sees for itself which entries lie behind the end)
+    hipLaunchKernelGGL(scan_kernel, dim3((unsigned)a.num), dim3(kScanThreads), 0, stream, a.sums, a.seg, (int32_t*)nullptr,
+                       a.n, range ? a.diag_flags : nullptr);
+  if (range) {
+    const dim3 grid((unsigned)ceil_div(a.n, kDecodeRange)), block(kDecodeThreads);
+    if (in_order && a.block_shift == 0) hipLaunchKernelGGL((decode_range_kernel<true, false>), grid, block, 0, stream, a);
+    else if (in_order) hipLaunchKernelGGL((decode_range_kernel<true, true>), grid, block, 0, stream, a);
+    else if (a.block_shift == 0) hipLaunchKernelGGL((decode_range_kernel<false, false>), grid, block, 0, stream, a);
+    else hipLaunchKernelGGL((decode_range_kernel<false, true>), grid, block, 0, stream, a);
+  } else if (in_order) {
+    for (int32_t w = 0; w < a.num; ++w) {  // inside a payload every position is distinct
+      const unsigned own = (unsigned)ceil_div(a.seg.begin[w + 1] - a.seg.begin[w], kWireThreads / 64);
+      if (own > 0) hipLaunchKernelGGL(decode_direct_kernel<false>, dim3(own), dim3(kWireThreads), 0, stream, a, w);
+    }
+  } else {
+    hipLaunchKernelGGL(decode_direct_kernel<true>, dim3(groups, (unsigned)a.num), dim3(kWireThreads), 0, stream, a, 0);
+  }
   return hipGetLastError();
 }
 

@@ -1,0 +1,123 @@
+"""The forms of the wire-format kernels at the sizes where they change over: encoder with and without a
+scan launch, decoder entry by entry and by range, blocks of 512 entries and more, streams that are not
+16-byte aligned, ends of blocks and ranges.  Run with `-m gpu` on an MI355X."""
+
+import numpy as np
+import pytest
+
+from oracle import dgc_oracle as O
+from paper_1712_01887_amd import binding as B
+from tests.parity import Pair
+
+pytestmark = pytest.mark.gpu
+
+DET = B.DGC_FLAG_DETERMINISTIC_ACCUMULATE
+
+
+def random_stream(rng, n, density, trailing=0):
+    """Entries of a random sparse vector of n - trailing elements: (runs, vals, positions)."""
+    idx = np.flatnonzero(rng.random(n - trailing) < density)
+    gap = np.diff(idx, prepend=-1) - 1
+    need = 1 + (gap >> 16)
+    end = np.cumsum(need)
+    runs = np.full(int(end[-1]) if idx.size else 0, 65535, np.int64)
+    runs[end - 1] = gap & 65535
+    vals = np.zeros(runs.size, np.float32)
+    vals[end - 1] = rng.standard_normal(idx.size).astype(np.float32)
+    return runs.astype(np.uint16), vals, np.cumsum(runs + 1) - 1
+
+
+def run_case(n, streams, flags, handle_n=None, shift=0, seed=0):
+    """Decodes onto a random vector; compares with the worker-ordered binary32 sum."""
+    import torch
+    rng = np.random.default_rng(seed)
+    dgc = B.Dgc(B.make_config(flags=flags), [0, handle_n or n])
+    start = rng.standard_normal(n).astype(np.float32)
+    start[:: 7] = -0.0
+    dense = torch.from_numpy(start).cuda()
+    dev_runs, dev_vals = [], []
+    for runs, vals, _ in streams:
+        r = torch.zeros(runs.size + 8, dtype=torch.int16, device="cuda")[shift:]
+        x = torch.zeros(vals.size + 8, device="cuda")[shift:]
+        r[: runs.size] = torch.from_numpy(runs.view(np.int16)).cuda()
+        x[: vals.size] = torch.from_numpy(vals).cuda()
+        dev_runs.append(r)
+        dev_vals.append(x)
+    bad = torch.zeros(1, dtype=torch.int32, device="cuda")
+    dgc.dgc_decode_accumulate(dense, dev_runs, dev_vals, [s[0].size for s in streams], bad)
+    expect = start.copy()
+    exact = start.astype(np.float64)
+    mags = np.abs(exact)
+    beyond = False
+    for runs, vals, pos in streams:
+        ok = pos < n
+        beyond |= not ok.all()
+        expect[pos[ok]] = expect[pos[ok]] + vals[ok]      # positions of one stream are distinct
+        exact[pos[ok]] += vals[ok]
+        mags[pos[ok]] += np.abs(vals[ok])
+    got = dense.cpu().numpy()
+    assert bool(bad.item() & B.DGC_DIAG_BAD_INDEX) == beyond
+    if flags & DET:
+        assert np.array_equal(got.view(np.uint32), expect.view(np.uint32))
+    else:
+        # a sum of N + 1 binary32 terms in any order: within N * 2**-24 of the exact one, relative to the terms
+        assert np.all(np.abs(got - exact) <= len(streams) * 2.0 ** -24 * mags)
+    dgc.close()
+
+
+@pytest.mark.parametrize("flags", [0, DET])
+@pytest.mark.parametrize("n,density,workers,shift", [
+    (1, 1.0, 1, 0), (7, 1.0, 3, 1), (511, 1.0, 2, 0), (513, 1.0, 2, 3), (8191, 0.5, 5, 0), (8193, 0.5, 5, 0),
+    (100001, 0.001, 2, 0), (100001, 0.9, 2, 1), (300000, 0.07, 1, 0), (300000, 0.03, 4, 0), (300000, 0.2, 16, 1),
+    (1000003, 0.0001, 3, 0), (1000003, 0.25, 4, 0), (3000001, 0.003, 64, 0),
+])
+def test_decode_forms(n, density, workers, shift, flags):
+    rng = np.random.default_rng([n, workers])
+    streams = [random_stream(rng, n, density, trailing=min(n - 1, 40 * (w % 2))) for w in range(workers)]
+    if workers > 2:
+        streams[1] = streams[1][0][:0], streams[1][1][:0], streams[1][2][:0]    # a worker that sends nothing
+    run_case(n, streams, flags, shift=shift)
+
+
+@pytest.mark.parametrize("flags", [0, DET])
+@pytest.mark.parametrize("n", [3000, 4000000])
+def test_decode_blocks_of_more_than_512_entries(n, flags):
+    """64 payloads with every element sent: the workspace holds one position per 2048 entries; summed into a
+    vector of the handle's size (range form) and into a long one (entry by entry, unless in order)."""
+    rng = np.random.default_rng(n)
+    run_case(n, [random_stream(rng, 3000, 1.0) for _ in range(64)], flags, handle_n=3000)
+
+
+@pytest.mark.parametrize("flags", [0, DET])
+@pytest.mark.parametrize("density", [0.002, 0.4])
+def test_decode_skips_and_flags_what_lies_behind_the_end(density, flags):
+    rng = np.random.default_rng(3)
+    streams = [random_stream(rng, 20000, density), random_stream(rng, 25000, density), random_stream(rng, 20000, density)]
+    run_case(20000, streams, flags, handle_n=25000)
+    # runs that add up to more than 2**32: nothing wraps round
+    runs = np.full(70000, 65535, np.uint16)
+    vals = np.ones(70000, np.float32)
+    run_case(70000, [(runs, vals, np.cumsum(runs.astype(np.int64) + 1) - 1)], flags)
+
+
+@pytest.mark.parametrize("sizes,density,layout_density", [
+    ([4097, 3, 66000, 8192], 0.5, 1.0),        # a few workgroups: block sums added up without a scan
+    ([5, 4600000, 77], 0.02, 1.0),             # more than 1024 of them: a scan launch
+    ([900001, 1], 0.00002, 0.0001),            # gaps of more than 65535 zeros in most rounds
+])
+def test_encode_forms(sizes, density, layout_density):
+    import torch
+    offsets = np.concatenate([[0], np.cumsum(sizes)])
+    n = int(offsets[-1])
+    p = Pair(offsets, layout_density=layout_density, momentum=0.0, density=density, seed=6, flags=B.DGC_FLAG_SORTED_OUTPUT)
+    g = np.random.default_rng(n).standard_normal(n).astype(np.float32)
+    res = p.step(g, 0, label=f"encode {sizes}")
+    want_runs, want_vals = O.encode(*O.flatten_payload(res))
+    runs = torch.zeros(want_runs.size + 4, dtype=torch.int16, device="cuda")
+    vals = torch.zeros(want_runs.size + 4, device="cuda")
+    num = torch.full((1,), -1, dtype=torch.int32, device="cuda")
+    p.dgc.dgc_encode(p.out_idx, p.out_val, p.out_counts, runs[:-4], vals[:-4], num)
+    assert int(num.item()) == want_runs.size
+    assert np.array_equal(runs.cpu().numpy()[:-4].view(np.uint16), want_runs) and not runs[-4:].any().item()
+    assert np.array_equal(vals.cpu().numpy()[:-4], want_vals) and not vals[-4:].any().item()
+    p.close()
