@@ -34,6 +34,7 @@ struct dgc_handle {
   std::vector<float> tile_thr_init;  // ceil(n / kWaveTile): NaN where a tile is not wholly inside one tensor
   std::vector<EmitBlock> emit_blocks;  // work list of the emit pass
   std::vector<MergeBlock> merge_blocks;  // work list of the receive side: ranges of several emit parts
+  int64_t longest_range = 0;             // elements of the longest of them
   std::vector<MergeBlock> part_blocks;   // the same with one emit part per range (warm-up densities)
   bool layout_may_overflow = true;       // some region of the registered layout is smaller than its tensor
   int64_t last_replace_expected = 0;     // pairs per range the payloads of the last dgc_decompress_replace_regions call let expect
@@ -103,6 +104,16 @@ std::mutex g_scratch_mutex;
 
 constexpr size_t kAlign = 256;
 constexpr double kMergeMaxDensity = 0.005;   // receive side: merge by element range in LDS up to here
+// ... and above it, unless the aggregate is replaced, where the set is small enough for all its ranges to be
+// merged at once, a compute unit each: what counts there is the number of launches (23 tensors of 0.27 M
+// elements, 1 %, four workers: 12.3 us in one launch against 3.6 + 10.1; 16 M elements, 0.8 %, three
+// workers: 113 against 128 for the whole pass).  Replacing, the part kernels write every range once and need
+// no previous indices: 37 against 39 us for the pass on the 23 tensors.
+constexpr size_t kMergeFewRanges = 256;
+// Sparse clear by scattered stores (80 G/s) up to this many pairs in all; the part kernels take 18 us however
+// few there are (23 tensors as above: 7.6 against 3.6 + 14.6 us), and as long as the stores at about this
+// number (122 M elements, 1.9 M pairs: 717 against 712 for the whole pass).
+constexpr double kScatterClearPairs = 2e6;
 constexpr double kStagedMinDensity = 0.005;  // compress: staged streaming pass above this density
 constexpr int kProfEvents = 5;
 inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
@@ -432,6 +443,7 @@ dgc_status dgc_create(dgc_handle** out, const dgc_config* cfg, int32_t num_tenso
       if (begin < h->offsets[t]) begin = h->offsets[t];
       if (end > h->offsets[t + 1]) end = h->offsets[t + 1];
       h->merge_blocks.push_back(MergeBlock{begin, end, t, 0});
+      if (end - begin > h->longest_range) h->longest_range = end - begin;
       b = e;
     }
     for (const EmitBlock& eb : h->emit_blocks) {
@@ -907,22 +919,23 @@ static dgc_status scatter_regions(dgc_handle* h, float* dense, int32_t num_paylo
   // workgroup merges the pairs of a range of up to 128 Ki elements in LDS and touches only
   // the elements that occur; at warm-up densities a workgroup keeps one emit part's whole
   // range of `dense` in LDS.
-  // Pairs a range of kMergeMaxRange elements can expect (the sampled threshold lets through up to a
+  // Pairs the longest range can expect (kMergeMaxRange elements, or the largest tensor if that is smaller; the sampled threshold lets through up to a
   // quarter more than the density on the inputs seen so far): the range kernel wants them, and the
   // previous payloads' indices when it replaces, in its registers and accumulator, and takes a much
   // slower way when they do not fit.  (Replacing an aggregate whose index lists are that long:
   // writing the whole of `dense` once, which needs none of them, is the cheaper way.)
-  const int64_t expected_new = (int64_t)std::ceil(1.25 * h->cfg.density * (double)kMergeMaxRange * (double)num_payloads);
+  const int64_t expected_new = (int64_t)std::ceil(1.25 * h->cfg.density * (double)h->longest_range * (double)num_payloads);
   const int64_t expected_old = (replace && num_old > 0) ? h->last_replace_expected : 0;
   const int64_t expected_pairs = expected_new > expected_old ? expected_new : expected_old;
-  const bool fits = h->cfg.density <= kMergeMaxDensity && expected_new <= kMergeCapLarge;
+  const bool fits = (h->cfg.density <= kMergeMaxDensity || (!replace && h->merge_blocks.size() <= kMergeFewRanges)) &&
+                    expected_new <= kMergeCapLarge;
   const bool few = fits && expected_old <= kMergeCapLarge;
   if (replace) h->last_replace_expected = fits ? expected_new : (int64_t)kMergeCapLarge + 1;
   const MergeBlock* parts = at<MergeBlock>(workspace, h->lay.part_blocks);
   const int32_t num_parts = (int32_t)h->part_blocks.size();
   void* found = at<char>(workspace, h->lay.part_found);
   if (clear) {
-    if (few) {
+    if (few || h->cfg.density * (double)h->n * (double)num_payloads <= kScatterClearPairs) {
       // the launch is sized for the pairs the density lets expect (the kernel strides over whatever
       // there is), not for regions that were laid out for a higher density
       int64_t expected = 0;
