@@ -13,6 +13,7 @@
 // inline function, which makes the sampled threshold an exact member of the
 // values the streaming pass later compares against it.
 
+#include "dgc_device.h"
 #include "dgc_internal.h"
 
 namespace dgc {
@@ -160,7 +161,7 @@ struct SelectShared {
   float scale;
   uint32_t hist[kSelectBins];
   uint32_t wave_tot[kSelectThreads / 64];
-  uint32_t surv[kSelectThreads];
+  alignas(16) uint32_t surv[kSelectThreads];
   uint32_t sel[3];
   uint32_t surv_n, result;
 };
@@ -206,17 +207,19 @@ __device__ __forceinline__ void find_bin(const uint32_t* hist, uint32_t* wave_to
   members = sel[2];
 }
 
-// The `m` <= kSelectThreads keys in sh.surv: the one of descending rank `rank`.  (Splitting the
+// The `m` <= kSelectThreads keys in sh.surv, which is zero behind them up to a multiple of four: the one of
+// descending rank `rank`.  Every thread compares one key with all, four to an LDS read.  (Splitting the
 // comparisons of one key over several threads, with the partial counts added in LDS, was measured:
 // no faster for the 100 to 200 keys that get here.)
 __device__ __forceinline__ uint32_t rank_directly(SelectShared& sh, int tid, uint32_t m, uint32_t rank) {
   if (tid < (int)m) {
     const uint32_t x = sh.surv[tid];
-    uint32_t greater = 0, equal = 0;
-    for (uint32_t i = 0; i < m; ++i) {
-      const uint32_t y = sh.surv[i];
-      greater += y > x;
-      equal += y == x;
+    uint32_t greater = 0, equal = 0;  // (a zero behind the keys can only add to the last rank's ties)
+    const uint4* __restrict__ four = reinterpret_cast<const uint4*>(sh.surv);
+    for (uint32_t i = 0; 4 * i < m; ++i) {
+      const uint4 y = four[i];
+      greater += (y.x > x) + (y.y > x) + (y.z > x) + (y.w > x);
+      equal += (y.x == x) + (y.y == x) + (y.z == x) + (y.w == x);
     }
     if (greater <= rank && rank < greater + equal) sh.result = x;  // ties write the same value
   }
@@ -256,6 +259,7 @@ __device__ __forceinline__ uint32_t select_in_registers(SelectShared& sh, const 
     if (consumed == 31) return prefix;
     if (members <= (uint32_t)kSelectDirect) {
       if (tid == 0) sh.surv_n = 0;
+      if (tid < 4) sh.surv[(members & ~3u) + tid] = 0;
       __syncthreads();
       const int low = 31 - consumed;  // key bits not yet fixed
 #pragma unroll
@@ -270,51 +274,53 @@ __device__ __forceinline__ uint32_t select_in_registers(SelectShared& sh, const 
   return prefix;
 }
 
-// Key of descending rank `rank` among the `count` keys a workgroup holds in registers (kNoKey marks an
-// empty slot).  Every thread returns the same.
-__device__ __forceinline__ uint32_t rank_registers(SelectShared& sh, const uint32_t (&key)[kSelectRegKeys], int32_t count,
+// Key of descending rank `rank` among the keys a workgroup holds in registers (kNoKey marks an empty
+// slot); threads 0 .. holders - 1 have at least one.  Every thread returns the same.
+__device__ __forceinline__ uint32_t rank_registers(SelectShared& sh, const uint32_t (&key)[kSelectRegKeys], int32_t holders,
                                                    uint32_t rank, int tid) {
   // Gradients of one tensor share a few exponents, so a histogram over the leading key
   // bits of all candidates piles tens of thousands of LDS atomics on a handful of bins,
   // and every histogram pass costs half a dozen barriers of 1024 threads (ranking 32 Ki
   // keys that way took 20 us, against 3 us this way).  At the paper's densities the
   // rank r is a few dozen, and a floor below which no key matters is cheap to get: if
-  // every one of the 16 wavefronts names the t-th largest of its threads' largest
-  // keys, 16 t > r, then the smallest of the 16 answers has more than r keys at or
-  // above it.  What lies at or above that floor (a few times r keys) is listed in LDS
+  // every one of the (up to 16) wavefronts whose threads all hold keys names the t-th largest of
+  // its threads' largest keys, with t times the wavefronts more than r, then the smallest of the
+  // answers has more than r keys at or above it.  What lies at or above that floor (a few times r
+  // keys; everything, if there are fewer than 64 holders) is listed in LDS
   // and ranked by direct counting.  Anything that does not fit this pattern takes the
   // histogram passes.
   constexpr int kWaves = kSelectThreads / 64;
-  const uint32_t t_rounds = rank / kWaves + 1;  // kWaves * t_rounds > rank
-  if (count > 2 * kSelectThreads && t_rounds <= (uint32_t)kSelectFloorRounds) {
-    const int lane = tid & 63;
-    uint32_t top = 0;  // this thread's largest key (every thread has keys: count > 2048)
+  const int lane = tid & 63;
+  const int wave = tid >> 6;
+  const uint32_t full_waves = (uint32_t)holders >= (uint32_t)kSelectThreads ? (uint32_t)kWaves : (uint32_t)holders >> 6;
+  const uint32_t t_rounds = full_waves > 0 ? rank / full_waves + 1 : 0;  // full_waves * t_rounds > rank
+  if (t_rounds <= (uint32_t)kSelectFloorRounds) {
+    int32_t top = -1;  // this thread's largest key (an empty slot counts as -1)
 #pragma unroll
-    for (int i = 0; i < kSelectRegKeys; ++i)
-      if (key[i] != kNoKey) top = key[i] > top ? key[i] : top;
+    for (int i = 0; i < kSelectRegKeys; ++i) top = (int32_t)key[i] > top ? (int32_t)key[i] : top;
+    uint32_t rest = top > 0 ? (uint32_t)top : 0u;
     uint32_t tth = 0;
     for (uint32_t round = 0; round < t_rounds; ++round) {
-      uint32_t m = top;
-      for (int d = 32; d >= 1; d >>= 1) {
-        const uint32_t o = __shfl_xor(m, d);
-        m = o > m ? o : m;
-      }
-      tth = m;
-      const unsigned long long holders = __ballot(top == m);
-      if (lane == __ffsll((long long)holders) - 1) top = 0;  // one holder of the maximum steps down
+      tth = wave_max(rest);
+      const unsigned long long holding = __ballot(rest == tth);
+      if (lane == __ffsll((long long)holding) - 1) rest = 0;  // one holder of the maximum steps down
     }
-    if (lane == 0) sh.wave_tot[tid >> 6] = tth;
+    if (lane == 0) sh.wave_tot[wave] = (uint32_t)wave < full_waves ? tth : 0x7FFFFFFFu;
     if (tid == 0) sh.surv_n = 0;
+    sh.surv[tid] = 0;
     __syncthreads();
     uint32_t floor_key = sh.wave_tot[0];
 #pragma unroll
     for (int w = 1; w < kWaves; ++w) floor_key = sh.wave_tot[w] < floor_key ? sh.wave_tot[w] : floor_key;
+    if (full_waves == 0) floor_key = 0;
+    if (top >= (int32_t)floor_key) {
 #pragma unroll
-    for (int i = 0; i < kSelectRegKeys; ++i)
-      if (key[i] != kNoKey && key[i] >= floor_key) {
-        const uint32_t pos = atomicAdd(&sh.surv_n, 1u);
-        if (pos < (uint32_t)kSelectThreads) sh.surv[pos] = key[i];
-      }
+      for (int i = 0; i < kSelectRegKeys; ++i)
+        if ((int32_t)key[i] >= (int32_t)floor_key) {
+          const uint32_t pos = atomicAdd(&sh.surv_n, 1u);
+          if (pos < (uint32_t)kSelectThreads) sh.surv[pos] = key[i];
+        }
+    }
     __syncthreads();
     const uint32_t listed = sh.surv_n;
     if (listed <= (uint32_t)kSelectThreads) {
@@ -476,12 +482,14 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectArgs a) {
     uint32_t key[kSelectRegKeys];
 #pragma unroll
     for (int i = 0; i < kSelectRegKeys; ++i) key[i] = kNoKey;
+    const bool quads_of_blocks = !c.exact && c.block_shift >= 2;
+    const int32_t holders = quads_of_blocks ? count >> 2 : count;  // threads with at least one candidate
     // The gather is written without branches around the loads and without conditional stores into
     // key[]: a candidate beyond the count reads candidate 0 instead and its key is replaced by the
     // empty mark afterwards.  (With `if (p < count)` around them the compiler copied the whole
     // register array at every such branch: some 400 moves per thread in a kernel that spends as
     // much time issuing instructions as waiting for memory, 16 wavefronts sharing four SIMDs.)
-    if (!c.exact && c.block_shift >= 2) {
+    if (quads_of_blocks) {
       // Sampled blocks of at least four elements: a thread takes four consecutive elements of a
       // drawn block at a time (one 16-byte load per array; a block starts at a multiple of its size
       // from the tensor's start, which need not be 16-byte aligned: dword-aligned vector loads), so
@@ -549,13 +557,13 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectArgs a) {
       const double mid = share * (double)kBandSample;
       const double reach = 32.0 + ceil(7.0 * sqrt(mid * (1.0 - share)));
       const double low = ceil(mid) + reach, high = floor(mid) - reach;
-      const uint32_t floor_key = low < (double)count ? rank_registers(sh, key, count, (uint32_t)low, tid) : 0xFFFFFFFFu;
-      uint32_t ceil_key = high >= 0.0 ? rank_registers(sh, key, count, (uint32_t)high, tid) : 0x80000000u;
+      const uint32_t floor_key = low < (double)count ? rank_registers(sh, key, holders, (uint32_t)low, tid) : 0xFFFFFFFFu;
+      uint32_t ceil_key = high >= 0.0 ? rank_registers(sh, key, holders, (uint32_t)high, tid) : 0x80000000u;
       if (ceil_key == floor_key) ++ceil_key;
       if (tid == 0) *band_state(a, plan) = BandState{floor_key, ceil_key, 0u, 0u, 0u};
       return;
     }
-    thr_bits = rank_registers(sh, key, count, rank, tid);
+    thr_bits = rank_registers(sh, key, holders, rank, tid);
   } else {
     thr_bits = rank_reevaluated(sh, c, count, rank, tid);
   }
@@ -727,6 +735,8 @@ __global__ __launch_bounds__(kSelectThreads) void rank_band_kernel(SelectArgs a)
         break;
       }
       if (members <= (uint32_t)kSelectDirect) {
+        if (tid < 4) sh.surv[(members & ~3u) + tid] = 0;
+        __syncthreads();
         walk([&](uint32_t key) {
           if (key - lo < width) sh.surv[atomicAdd(&sh.surv_n, 1u)] = key;
         });

@@ -26,6 +26,18 @@ __device__ __forceinline__ uint32_t wave_last(uint32_t x) { return (uint32_t)__b
 
 __device__ __forceinline__ uint32_t wave_sum(uint32_t x) { return wave_last(wave_inclusive_sum(x)); }
 
+// The largest of the wavefront's values, the same in every lane.
+__device__ __forceinline__ uint32_t wave_max(uint32_t x) {
+  auto larger = [](uint32_t a, int b) { return a > (uint32_t)b ? a : (uint32_t)b; };
+  x = larger(x, __builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false));
+  x = larger(x, __builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false));
+  x = larger(x, __builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false));
+  x = larger(x, __builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false));
+  x = larger(x, __builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false));
+  x = larger(x, __builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false));
+  return wave_last(x);
+}
+
 // Positions [lo, hi) of the list L[0, m) whose values lie in [xa, xb), for a list in which
 // "value < xa" and "value < xb" are monotone; every lane of the wavefront takes part and
 // gets the same answer.
