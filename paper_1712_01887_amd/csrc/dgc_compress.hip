@@ -1756,113 +1756,159 @@ __global__ __launch_bounds__(kEmitThreads) void emit_sorted_kernel(EmitArgs a) {
 // Emit pass after a STAGED streaming pass: the selected values of a tile that lies wholly
 // inside one tensor wait in the tile's slots of the staging array, in index order, and u
 // and v are masked already.  The part's payload is written in index order (as the sorted
-// variant does, with the same positions), values copied from the staging array; nothing
-// is listed in LDS and u, v are touched only where the region is full (the element is put
-// back: v' and, under factor masking, u') and in tiles shared between tensors, which the
-// streaming pass leaves alone.
+// variant does, with the same positions), values copied from the staging array; u, v are touched
+// only where the region is full (the element is put back: v' and, under factor masking, u') and in
+// tiles shared between tensors, which the streaming pass leaves alone.
+//
+// Bound by instructions at the lower densities of the warm-up and by the stores at the higher ones.  A
+// wavefront takes eight consecutive tiles; the counts of whole tiles come from the table that the
+// streaming pass has left, not from the mask words; values move four to a lane; the indices of a tile
+// with many selected elements are put in their places in LDS and leave from there four to a lane, too.
+// 122 M elements: 112 us at 25 %, 44 at 1.6 % (136 and 46 with the counts formed from the mask words and every
+// index stored where it belongs one by one); placing the indices of sparse tiles through LDS as well: 57 us
+// at 1.6 %.  Holding all eight tiles' values and words in registers took 220 of them and 224 us at 25 %.
+struct EmitStagedShared {
+  int cnt[kEmitTiles];                                // selected elements per tile, this tensor's
+  int base[kEmitThreads / 64];                        // slots taken before the part, by wavefront
+  uint16_t words[kEmitTiles * 64];                    // mask words, bits outside the tensor removed
+  alignas(16) int32_t list[kEmitThreads / 64][kWaveTile + 64];
+};
+
 __global__ __launch_bounds__(kEmitThreads) void emit_staged_kernel(EmitArgs a) {
+  typedef float fvec4u __attribute__((ext_vector_type(4), aligned(4)));
+  typedef int32_t ivec4u __attribute__((ext_vector_type(4), aligned(4)));
   constexpr int kWaves = kEmitThreads / 64;
   constexpr int kPerWave = kEmitTiles / kWaves;
   constexpr int kRows = kStreamUnroll;
-  __shared__ EmitTiles sh;
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
+  constexpr int kWalk = 128;  // tiles with fewer selected elements place their indices by a walk over each lane's bits
+  static_assert(kEmitTiles <= 64 && kWalk < 256, "one wavefront scans the counts; a row's positions fit a byte");
+  __shared__ EmitStagedShared sh;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const EmitBlock blk = a.blocks[blockIdx.x];
   const int j = blk.tensor;
-  const int64_t first = blk.first_tile;
-  emit_tiles(a, blk, sh);
-  if (sh.block_total == 0) return;
-  const int64_t lo = blk.lo;
-  const int64_t hi = blk.hi;
   const int64_t region = a.out_offsets[j];
   const int64_t cap = a.out_offsets[j + 1] - region;
-  int32_t* __restrict__ out_idx = a.out_idx + region;
-  float* __restrict__ out_val = a.out_val + region;
-  float* __restrict__ u = a.u;
-  float* __restrict__ v = a.v;
-  bool overflow = false;
-  // What a tile of the wavefront is, as far as the copy of its values goes.
-  auto tile_of = [&](int i, const float*& stage, float*& vals, int& room) {
-    const int tl = wave + i * kWaves;
-    const int64_t t = first + tl;
-    const int tile_total = sh.tile_tot[tl];
-    const bool staged = t * kWaveTile >= lo && (t + 1) * kWaveTile <= hi;
-    const int64_t slot0 = (int64_t)sh.block_base + sh.tile_base[tl];
-    stage = a.stage_v + t * kWaveTile;
-    vals = out_val + slot0;
-    // slots of the tile that exist (the rest of the tile overflows); none to copy for a shared tile
-    room = cap - slot0 >= tile_total ? tile_total : (cap > slot0 ? (int)(cap - slot0) : 0);
-    return staged;
-  };
-  // The values are a straight copy: the staging array holds a tile's in slot order.  The first
-  // 256 of every tile of the wavefront are loaded before any is stored (one wait for all).
+  const int64_t lo = blk.lo;
+  const int64_t hi = blk.hi;
+  const int64_t t0 = lo / kWaveTile;
+  const int64_t t1 = (hi - 1) / kWaveTile;
+  const int64_t first = blk.first_tile;
+  auto whole = [&](int64_t t) { return t * kWaveTile >= lo && (t + 1) * kWaveTile <= hi; };
+
+  // this wavefront's mask words, the counts of the part's tiles, and the counts of the tensor's tiles before it
+  uint16_t* words = sh.words + wave * (kPerWave * 64) + lane;  // of this lane: written and read by itself only
   {
-    float x[kPerWave][4];
+    uint32_t word[kPerWave];
 #pragma unroll
     for (int i = 0; i < kPerWave; ++i) {
-      const float* stage;
-      float* vals;
-      int room;
-      const bool staged = tile_of(i, stage, vals, room);
-#pragma unroll
-      for (int k = 0; k < 4; ++k) x[i][k] = (staged && k * 64 + lane < room) ? stage[k * 64 + lane] : 0.0f;
+      const int64_t t = first + wave * kPerWave + i;
+      word[i] = t <= t1 ? tensor_tile_word(a.mask, t, lane, lo, hi) : 0u;
     }
+    const int64_t t = first + tid;
+    if (tid < kEmitTiles && (t > t1 || whole(t))) sh.cnt[tid] = t <= t1 ? (int)a.tile_count[t] : 0;
 #pragma unroll
-    for (int i = 0; i < kPerWave; ++i) {
-      const float* stage;
-      float* vals;
-      int room;
-      const bool staged = tile_of(i, stage, vals, room);
-#pragma unroll
-      for (int k = 0; k < 4; ++k)
-        if (staged && k * 64 + lane < room) vals[k * 64 + lane] = x[i][k];
-    }
+    for (int i = 0; i < kPerWave; ++i) words[i * 64] = (uint16_t)word[i];
   }
+  int pre = tile_counts_partial<kEmitThreads>(a.tile_count, t0 + 1, first, tid);
+  if (first > t0 && wave == 0) pre += __popc(tensor_tile_word(a.mask, t0, lane, lo, hi));
+  pre = (int)wave_sum((uint32_t)pre);
+  if (lane == 0) sh.base[wave] = pre;
 #pragma unroll 1
   for (int i = 0; i < kPerWave; ++i) {
-    const int tl = wave + i * kWaves;
-    const int tile_total = sh.tile_tot[tl];
-    if (tile_total == 0) continue;
-    const uint32_t w = sh.words[tl * 64 + lane];
-    const int64_t t = first + tl;
-    const float* __restrict__ stage_v;
-    float* __restrict__ tile_val;
-    int room;
-    {
-      const float* stage;
-      float* vals;
-      const bool st = tile_of(i, stage, vals, room);
-      stage_v = stage;
-      tile_val = vals;
-      if (st) {
-        for (int s = 256 + lane; s < room; s += 64) vals[s] = stage[s];  // beyond a quarter of the tile
-      }
+    const int64_t t = first + wave * kPerWave + i;
+    if (t <= t1 && !whole(t)) {  // shared with a neighbour, or the ragged end: the tensor's own bits count
+      const int c = (int)wave_sum((uint32_t)__popc((uint32_t)words[i * 64]));
+      if (lane == 0) sh.cnt[wave * kPerWave + i] = c;
     }
-    const bool staged = t * kWaveTile >= lo && (t + 1) * kWaveTile <= hi;
-    const float* __restrict__ stage_u = a.stage_u ? a.stage_u + t * kWaveTile : nullptr;
-    int32_t* __restrict__ tile_idx = out_idx + ((int64_t)sh.block_base + sh.tile_base[tl]);
-    // the indices: an element's slot is rows before it + bits of its row in lower lanes + lower bits of its nibble
-    if (staged && tile_total < 256 && room == tile_total) {
-      // Fewer than 256 elements, all with a slot (at 1.6 % a tile selects 16): the counts of the
-      // lane's four rows ride in the bytes of one word (no byte can overflow), one scan over the
-      // lanes gives every row's "bits in lower lanes", the rows' totals shifted up by one, two and
-      // three bytes the "rows before it", and a lane walks its own bits, lowest first: two or
-      // three rounds instead of sixteen votes.
-      uint32_t x = w - ((w >> 1) & 0x5555u);
-      x = (x & 0x3333u) + ((x >> 2) & 0x3333u);  // a count per nibble
-      const uint32_t cnt = (x & 0xFu) | ((x & 0xF0u) << 4) | ((x & 0xF00u) << 8) | ((x & 0xF000u) << 12);
-      uint32_t incl = cnt;
-      for (int d = 1; d < 64; d <<= 1) {
-        const uint32_t up = __shfl_up(incl, d);
-        if (lane >= d) incl += up;
-      }
-      const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
-      uint32_t at = (incl - cnt) + ((tot << 8) + (tot << 16) + (tot << 24));  // next slot of each of the lane's rows
-      const int32_t e_lane = (int32_t)tile_element(t, lane, 0);
+  }
+  __syncthreads();
+  int base = 0;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) base += sh.base[w];
+  const int own = lane < kEmitTiles ? sh.cnt[lane] : 0;
+  const int incl = (int)wave_inclusive_sum((uint32_t)own);  // every wavefront scans the counts for itself
+  const int part_total = (int)wave_last((uint32_t)incl);
+  if (tid == 0 && (int)((first - t0) / kEmitTiles) == blk.tensor_blocks - 1) a.out_counts[j] = base + part_total;
+  if (part_total == 0) return;
+
+  float* __restrict__ u = a.u;
+  float* __restrict__ v = a.v;
+  int32_t* list = sh.list[wave];
+  bool overflow = false;
+  // what a tile of the wavefront is; the slots are counted from the part's first one
+  const int64_t part_room = cap - base;
+  auto tile_of = [&](int i, int& total, int& slot, int& room) {
+    const int tl = wave * kPerWave + i;
+    total = __builtin_amdgcn_readlane(own, tl);
+    slot = __builtin_amdgcn_readlane(incl, tl) - total;
+    // slots of the tile that exist (the rest of the tile overflows)
+    room = part_room - slot >= total ? total : (part_room > slot ? (int)(part_room - slot) : 0);
+    return whole(first + tl);
+  };
+  // The first 256 values of a tile are asked for before the tile before it is taken (up to three slots
+  // behind the last value are read with it: they belong to the tile).
+  auto first_values = [&](int i) {
+    int total, slot, room;
+    fvec4u x = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (tile_of(i, total, slot, room) && 4 * lane < room)
+      x = *reinterpret_cast<const fvec4u*>(a.stage_v + (first + wave * kPerWave + i) * kWaveTile + 4 * lane);
+    return x;
+  };
+  float* __restrict__ part_val = a.out_val + region + base;
+  int32_t* __restrict__ part_idx = a.out_idx + region + base;
+  // four consecutive values, or indices, of which the last `n - s` exist
+  auto put_values = [&](float* to, int s, int n, const fvec4u& y) {
+    if (s + 4 <= n) {
+      *reinterpret_cast<fvec4u*>(to + s) = y;
+    } else {
+#pragma unroll
+      for (int c = 0; c < 3; ++c)
+        if (s + c < n) to[s + c] = y[c];
+    }
+  };
+  auto put_indices = [&](int32_t* to, int s, int n, const int4& y) {
+    if (s + 4 <= n) {
+      *reinterpret_cast<ivec4u*>(to + s) = ivec4u{y.x, y.y, y.z, y.w};
+    } else {
+      if (s < n) to[s] = y.x;
+      if (s + 1 < n) to[s + 1] = y.y;
+      if (s + 2 < n) to[s + 2] = y.z;
+    }
+  };
+  fvec4u next = first_values(0);
+#pragma unroll 1
+  for (int i = 0; i < kPerWave; ++i) {
+    const fvec4u x = next;
+    if (i + 1 < kPerWave) next = first_values(i + 1);
+    int total, slot, room;
+    const bool staged = tile_of(i, total, slot, room);
+    if (total == 0) continue;  // uniform, as everything about the tile
+    const int64_t t = first + wave * kPerWave + i;
+    const uint32_t w = words[i * 64];
+    const int32_t e_lane = (int32_t)tile_element(t, lane, 0);
+    float* __restrict__ tile_val = part_val + slot;
+    int32_t* __restrict__ tile_idx = part_idx + slot;
+    if (staged) {
+      put_values(tile_val, 4 * lane, room, x);
+      for (int s = 256 + 4 * lane; s < room; s += 256)  // beyond a quarter of the tile
+        put_values(tile_val, s, room, *reinterpret_cast<const fvec4u*>(a.stage_v + t * kWaveTile + s));
+    }
+    if (staged && room == total && total < kWalk) {
+      // The counts of the lane's four rows ride in the bytes of one word (no byte can overflow), one scan
+      // over the lanes gives every row's "bits in lower lanes", the rows' totals shifted up by one, two
+      // and three bytes the "rows before it", and a lane walks its own bits, lowest first.
+      uint32_t y = w - ((w >> 1) & 0x5555u);
+      y = (y & 0x3333u) + ((y >> 2) & 0x3333u);  // a count per nibble
+      const uint32_t cnt = (y & 0xFu) | ((y & 0xF0u) << 4) | ((y & 0xF00u) << 8) | ((y & 0xF000u) << 12);
+      const uint32_t upto = wave_inclusive_sum(cnt);
+      const uint32_t tot = wave_last(upto);
+      uint32_t at = (upto - cnt) + ((tot << 8) + (tot << 16) + (tot << 24));  // next slot of each of the lane's rows
       uint32_t rem = w;
       while (__ballot(rem != 0u)) {
         if (rem != 0u) {
-          const int b = __ffs((int)rem) - 1;  // bit 4 r + c
+          const int b = __builtin_ctz(rem);  // bit 4 r + c
           const int r8 = (b >> 2) * 8;
           tile_idx[(at >> r8) & 0xFFu] = e_lane + (b >> 2) * 256 + (b & 3);
           at += 1u << r8;
@@ -1871,40 +1917,64 @@ __global__ __launch_bounds__(kEmitThreads) void emit_staged_kernel(EmitArgs a) {
       }
       continue;
     }
-    int row_base = 0;
+    const float* __restrict__ stage_v = a.stage_v + t * kWaveTile;
+    if (staged && room == total) {
+      // The same for more elements: the counts of two rows to a word, 16 bits each, two scans.  Every one
+      // of the sixteen elements is written to LDS, those not selected to a word of the lane's own behind the
+      // list (no branches).
+      const uint32_t n0 = __popc(w & 0xFu), n1 = __popc(w & 0xF0u), n2 = __popc(w & 0xF00u), n3 = __popc(w & 0xF000u);
+      const uint32_t cnt01 = n0 | (n1 << 16), cnt23 = n2 | (n3 << 16);
+      const uint32_t upto01 = wave_inclusive_sum(cnt01), upto23 = wave_inclusive_sum(cnt23);
+      const uint32_t tot01 = wave_last(upto01), tot23 = wave_last(upto23);
+      const uint32_t at01 = upto01 - cnt01, at23 = upto23 - cnt23;
+      const uint32_t row1 = tot01 & 0xFFFFu, row2 = row1 + (tot01 >> 16), row3 = row2 + (tot23 & 0xFFFFu);
+      const uint32_t row_at[4] = {at01 & 0xFFFFu, row1 + (at01 >> 16), row2 + (at23 & 0xFFFFu), row3 + (at23 >> 16)};
+      const uint32_t spare = (uint32_t)(kWaveTile + lane);
 #pragma unroll
+      for (int r = 0; r < kRows; ++r) {
+        uint32_t pos = row_at[r];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          const uint32_t bit = (w >> (4 * r + c)) & 1u;
+          list[bit ? pos : spare] = e_lane + r * 256 + c;
+          pos += bit;
+        }
+      }
+      __builtin_amdgcn_wave_barrier();  // (LDS operations of one wavefront are carried out in order)
+      for (int s = 4 * lane; s < total; s += 256) put_indices(tile_idx, s, total, *reinterpret_cast<const int4*>(&list[s]));
+      __builtin_amdgcn_wave_barrier();
+      continue;
+    }
+    // A tile shared between tensors, or one that the region has no room for: element by element.  An
+    // element's slot is rows before it + bits of its row in lower lanes + lower bits of its nibble.
+    const float* __restrict__ stage_u = a.stage_u ? a.stage_u + t * kWaveTile : nullptr;
+    int row_base = 0;
+#pragma unroll 1
     for (int r = 0; r < kRows; ++r) {
       const uint32_t nib = (w >> (4 * r)) & 0xFu;
-      int lower = 0, row = 0;
-#pragma unroll
+      const uint32_t upto = wave_inclusive_sum((uint32_t)__popc(nib));
+      int pos = row_base + (int)upto - __popc(nib);
+      row_base += (int)wave_last(upto);
+#pragma unroll 1
       for (int c = 0; c < 4; ++c) {
-        const unsigned long long vote = __ballot((nib >> c) & 1u);
-        lower += (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(vote >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)vote, 0u));
-        row += __popcll(vote);
-      }
-      int pos = row_base + lower;
-      const int32_t e0 = (int32_t)tile_element(t, lane, 4 * r);
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        if ((nib >> c) & 1u) {
-          if (pos < room) {
-            tile_idx[pos] = e0 + c;
-            if (!staged) {  // a tile shared between tensors: value taken and u, v masked here
-              tile_val[pos] = v[e0 + c];
-              v[e0 + c] = 0.0f;
-              if (a.factor_masking) u[e0 + c] = 0.0f;
-            }
-          } else {
-            overflow = true;
-            if (staged) {  // region full: the element goes back to where the streaming pass took it from
-              v[e0 + c] = stage_v[pos];
-              if (a.factor_masking && stage_u) u[e0 + c] = stage_u[pos];
-            }
+        if (!((nib >> c) & 1u)) continue;
+        const int32_t e = e_lane + r * 256 + c;
+        if (pos < room) {
+          tile_idx[pos] = e;
+          if (!staged) {  // value taken and u, v masked here
+            tile_val[pos] = v[e];
+            v[e] = 0.0f;
+            if (a.factor_masking) u[e] = 0.0f;
+          }
+        } else {
+          overflow = true;
+          if (staged) {  // region full: the element goes back to where the streaming pass took it from
+            v[e] = stage_v[pos];
+            if (a.factor_masking && stage_u) u[e] = stage_u[pos];
           }
         }
-        pos += (int)((nib >> c) & 1u);
+        ++pos;
       }
-      row_base += row;
     }
   }
   if (overflow) atomicOr(&a.state->flags, (uint32_t)DGC_DIAG_OVERFLOW);
