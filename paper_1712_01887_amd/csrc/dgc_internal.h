@@ -84,6 +84,7 @@ constexpr int kPartThreads = 1024;
 constexpr int kPartPer = 4;  // pairs a thread holds per round (8: 5 to 15 % slower at every warm-up density; 2: slower at 25 %)
 constexpr int kPartRound = kPartThreads * kPartPer;
 constexpr int kPartClearThreads = 256;
+constexpr int kPartClearLoads = 4;  // loads of four indices a lane has on their way
 static_assert(kEmitElements <= 65536 && kEmitElements % kPartThreads == 0 &&
                   (kEmitElements / 32) % kPartClearThreads == 0,
               "dealt evenly");

@@ -895,21 +895,35 @@ __global__ __launch_bounds__(kPartClearThreads) void clear_parts_kernel(float* _
   for (int k = 0; k < kWords; ++k) sh.bitmap[tid + k * kPartClearThreads] = 0;
   const int total = located_pairs(sh, p, num_payloads, region, found, (int)blockIdx.x, tid);
   if (total == 0) return;
-  for (int w = 0; w < num_payloads; ++w) {
-    const int n = sh.begin[w + 1] - sh.begin[w];
-    const int32_t* __restrict__ ip = sh.idx_at[w];
-    for (int first = 0; first < n; first += kPartClearThreads * kPartPer) {
-      int32_t r[kPartPer];
+  // A wavefront takes payloads w, w + waves, ...: the order does not matter here, and no barrier separates
+  // them.  Sixteen indices per lane are on their way at a time.
+  {
+    const int lane = tid & 63;
+    typedef int32_t vec4u __attribute__((ext_vector_type(4), aligned(4)));
+    auto mark = [&](int32_t i) {
+      const int64_t rr = (int64_t)i - blk.begin;  // outside the range: a foreign region
+      if (rr >= 0 && rr < length) atomicOr(&sh.bitmap[rr >> 5], 1u << (rr & 31));
+    };
+    for (int w = tid >> 6; w < num_payloads; w += kPartClearThreads / 64) {
+      const int n = sh.begin[w + 1] - sh.begin[w];
+      const int32_t* __restrict__ ip = sh.idx_at[w];
+      const int quads = n >> 2;
+      for (int first = lane; first < quads; first += 64 * kPartClearLoads) {
+        vec4u r[kPartClearLoads];
 #pragma unroll
-      for (int k = 0; k < kPartPer; ++k) {
-        const int q = first + tid + k * kPartClearThreads;
-        r[k] = q < n ? __builtin_nontemporal_load(ip + q) : -1;
-      }
+        for (int k = 0; k < kPartClearLoads; ++k) {
+          const int q = first + 64 * k;
+          r[k] = __builtin_nontemporal_load(reinterpret_cast<const vec4u*>(ip + 4 * (q < quads ? q : 0)));
+        }
 #pragma unroll
-      for (int k = 0; k < kPartPer; ++k) {
-        const int64_t rr = (int64_t)r[k] - blk.begin;  // outside the range: a foreign region, or no pair
-        if (r[k] >= 0 && rr >= 0 && rr < length) atomicOr(&sh.bitmap[rr >> 5], 1u << (rr & 31));
+        for (int k = 0; k < kPartClearLoads; ++k) {
+          if (first + 64 * k < quads) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) mark(r[k][c]);
+          }
+        }
       }
+      if (lane < (n & 3)) mark(ip[4 * quads + lane]);
     }
   }
   __syncthreads();
