@@ -690,7 +690,7 @@ __device__ __forceinline__ int located_pairs(Shared& sh, const RegionPayloads& p
 }
 
 struct PartShared {
-  float acc[kEmitElements];
+  alignas(16) float acc[kEmitElements];
   int32_t begin[kMaxPayloads + 1];  // number of pairs of the payloads before w inside the range
   const int32_t* idx_at[kMaxPayloads];  // payload w's first pair inside the range
   const float* val_at[kMaxPayloads];
@@ -706,9 +706,33 @@ __global__ __launch_bounds__(kPartThreads) void merge_parts_kernel(float* __rest
                                                                    int32_t num_blocks,
                                                                    const int2* __restrict__ found, float scale,
                                                                    int32_t scaled) {
-  constexpr int kElems = kEmitElements / kPartThreads;
+  typedef float fvec4u __attribute__((ext_vector_type(4), aligned(4)));  // a range starts anywhere
+  constexpr int kQuads = kEmitElements / 4 / kPartThreads;
   __shared__ PartShared sh;
   const int tid = threadIdx.x;
+  // four consecutive elements of a range of `len`, from element 4 * (tid + i * kPartThreads) on
+  auto load_quad = [&](const float* src, int32_t len, int i) {
+    const int e = 4 * (tid + i * kPartThreads);
+    fvec4u y = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (e + 4 <= len) {
+      y = __builtin_nontemporal_load(reinterpret_cast<const fvec4u*>(src + e));
+    } else {
+#pragma unroll
+      for (int c = 0; c < 3; ++c)
+        if (e + c < len) y[c] = src[e + c];
+    }
+    return y;
+  };
+  auto store_quad = [&](float* to, int32_t len, int i, const fvec4u& y) {
+    const int e = 4 * (tid + i * kPartThreads);
+    if (e + 4 <= len) {
+      __builtin_nontemporal_store(y, reinterpret_cast<fvec4u*>(to + e));
+    } else {
+#pragma unroll
+      for (int c = 0; c < 3; ++c)
+        if (e + c < len) to[e + c] = y[c];
+    }
+  };
   // The accumulator fills LDS, so a workgroup is alone on its compute unit: the grid is one
   // workgroup per compute unit and every workgroup takes parts b, b + grid, ...; the range of
   // the next part is requested before the finished one is written back, so that neither
@@ -716,16 +740,9 @@ __global__ __launch_bounds__(kPartThreads) void merge_parts_kernel(float* __rest
   int b = blockIdx.x;
   if (b >= num_blocks) return;
   MergeBlock blk = blocks[b];
-  float d[kElems];
-  {
-    const int32_t len = REPLACE ? 0 : (int32_t)(blk.end - blk.begin);
-    const float* __restrict__ src = dense + blk.begin;
+  fvec4u d[kQuads];
 #pragma unroll
-    for (int i = 0; i < kElems; ++i) {
-      const int e = tid + i * kPartThreads;
-      d[i] = e < len ? __builtin_nontemporal_load(src + e) : 0.0f;
-    }
-  }
+  for (int i = 0; i < kQuads; ++i) d[i] = load_quad(dense + blk.begin, REPLACE ? 0 : (int32_t)(blk.end - blk.begin), i);
   for (;;) {
     const int next_b = b + (int)gridDim.x;
     const bool more = next_b < num_blocks;
@@ -735,7 +752,7 @@ __global__ __launch_bounds__(kPartThreads) void merge_parts_kernel(float* __rest
     const int total = located_pairs(sh, p, num_payloads, out_offsets[blk.tensor], found, b, tid);
     if (total > 0) {
 #pragma unroll
-      for (int k = 0; k < kElems; ++k) sh.acc[tid + k * kPartThreads] = d[k];
+      for (int k = 0; k < kQuads; ++k) *reinterpret_cast<float4*>(&sh.acc[4 * (tid + k * kPartThreads)]) = make_float4(d[k][0], d[k][1], d[k][2], d[k][3]);
 
       if (total <= kPartRound) {
         // Few pairs (many payloads of a low density): all of them at once, whatever payload they
@@ -841,27 +858,18 @@ __global__ __launch_bounds__(kPartThreads) void merge_parts_kernel(float* __rest
       __syncthreads();
       }
     }
-    {  // (every d[i] is assigned anew: the old values must not stay alive through the rounds above)
-      const int32_t len = (more && !REPLACE) ? (int32_t)(next.end - next.begin) : 0;
-      const float* __restrict__ src = dense + next.begin;
+    // (every d[i] is assigned anew: the old values must not stay alive through the rounds above)
 #pragma unroll
-      for (int i = 0; i < kElems; ++i) {
-        const int e = tid + i * kPartThreads;
-        d[i] = e < len ? __builtin_nontemporal_load(src + e) : 0.0f;
-      }
-    }
+    for (int i = 0; i < kQuads; ++i) d[i] = load_quad(dense + next.begin, (more && !REPLACE) ? (int32_t)(next.end - next.begin) : 0, i);
     if (total > 0) {
 #pragma unroll
-      for (int k = 0; k < kElems; ++k) {
-        const int e = tid + k * kPartThreads;
-        if (e < length) __builtin_nontemporal_store(sh.acc[e], range + e);
+      for (int k = 0; k < kQuads; ++k) {
+        const float4 y = *reinterpret_cast<const float4*>(&sh.acc[4 * (tid + k * kPartThreads)]);
+        store_quad(range, length, k, fvec4u{y.x, y.y, y.z, y.w});
       }
     } else if (REPLACE) {
 #pragma unroll
-      for (int k = 0; k < kElems; ++k) {
-        const int e = tid + k * kPartThreads;
-        if (e < length) __builtin_nontemporal_store(0.0f, range + e);
-      }
+      for (int k = 0; k < kQuads; ++k) store_quad(range, length, k, fvec4u{0.0f, 0.0f, 0.0f, 0.0f});
     }
     if (!more) break;
     b = next_b;
