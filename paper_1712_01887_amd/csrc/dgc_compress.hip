@@ -1156,15 +1156,20 @@ __device__ __forceinline__ int tile_counts_partial(const uint32_t* __restrict__ 
 // tensor.  (A first version ran over the emit work list: every workgroup recounted its part's
 // mask words and took a ticket on the tensor's counter, the last to arrive went on; 17 us on the
 // 161-tensor set and 34 us on the 122 M-element set for what the per-tile counts already say.)
+// A workgroup lists up to kRefineList selected elements in LDS (index and key); the over-selection of a big
+// tensor goes to the payload region, which is free until the emit pass.
+constexpr int kRefinePer = 12;
+constexpr int kRefineList = kRefinePer * kRefineThreads;
 struct RefineShared {
-  uint32_t hist[kSelectBins];
-  uint32_t wave_tot[kRefineThreads / 64];
-  uint32_t sel[3];
+  SelectShared s;
+  uint32_t list[kRefineList];
+  uint32_t keys[kRefineList];
   int red[kRefineThreads / 64];
   int go;
   uint32_t passed;
   uint32_t listed;
 };
+static_assert(kRefineThreads == kSelectThreads, "the ranking is shared with select_kernel");
 
 // This thread's filtered mask word `wi` (0-based within the tensor's tiles) of tensor [lo, hi).
 __device__ __forceinline__ uint32_t tensor_mask_word(const uint16_t* mask, int64_t t0, int64_t wi, int64_t lo,
@@ -1241,7 +1246,171 @@ __global__ __launch_bounds__(kRefineThreads) void refine_kernel(RefineArgs a) {
   };
   constexpr uint32_t kFromRecord = 0x80000000u;  // list entry: the element sits in a record (indices are below 2^31)
 
-  if (passed <= cap) {
+  if (passed <= kRefineList) {
+    // From the records: one thread per tile, the counts of four tiles and then their records in flight
+    // together; from the mask words of the other tiles: by the wavefront whose lanes met them.
+    if (tid == 0) sh.listed = 0;
+    const float floor = a.thr[j];  // every selected element exceeds it
+    __syncthreads();
+    auto list_words = [&](int64_t tile, int l, uint32_t w) {  // a lane's mask word, this tensor's bits only
+      int pos = (int)atomicAdd(&sh.listed, (uint32_t)__popc(w));
+      while (w) {
+        const int q = __ffs(w) - 1;
+        w &= w - 1;
+        sh.list[pos++] = (uint32_t)tile_element(tile, l, q);
+      }
+    };
+    if (a.slotted) {
+      constexpr int kTilesInFlight = 4;
+#pragma unroll 1
+      for (int64_t first = t0; first <= t1; first += kTilesInFlight * kRefineThreads) {
+        uint32_t c[kTilesInFlight];
+        bool words_here[kTilesInFlight];
+#pragma unroll
+        for (int k = 0; k < kTilesInFlight; ++k) {
+          const int64_t tile = first + k * kRefineThreads + tid;
+          c[k] = tile <= t1 ? a.tile_count[tile] : 0u;
+        }
+        int4 e[kTilesInFlight][2], x[kTilesInFlight][2];
+#pragma unroll
+        for (int k = 0; k < kTilesInFlight; ++k) {
+          const int64_t tile = first + k * kRefineThreads + tid;
+          const bool whole = tile * kWaveTile >= lo && (tile + 1) * kWaveTile <= hi;
+          words_here[k] = tile <= t1 && (!whole || c[k] > (uint32_t)kSlotsPerTile);
+          if (words_here[k]) c[k] = 0u;
+          const int4* __restrict__ r = reinterpret_cast<const int4*>(records + tile * kSlotRecord);
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            e[k][h] = x[k][h] = make_int4(0, 0, 0, 0);
+            if (c[k] > 4u * h) {
+              e[k][h] = r[h];
+              x[k][h] = r[kSlotsPerTile / 4 + h];
+            }
+          }
+        }
+#pragma unroll
+        for (int k = 0; k < kTilesInFlight; ++k) {
+          if (c[k] == 0u) continue;
+          const uint32_t pos = atomicAdd(&sh.listed, c[k]);
+          const int32_t ee[8] = {e[k][0].x, e[k][0].y, e[k][0].z, e[k][0].w, e[k][1].x, e[k][1].y, e[k][1].z, e[k][1].w};
+          const int32_t xx[8] = {x[k][0].x, x[k][0].y, x[k][0].z, x[k][0].w, x[k][1].x, x[k][1].y, x[k][1].z, x[k][1].w};
+#pragma unroll
+          for (uint32_t q = 0; q < (uint32_t)kSlotsPerTile; ++q) {
+            if (q < c[k]) {
+              sh.list[pos + q] = (uint32_t)ee[q] | kFromRecord;
+              sh.keys[pos + q] = (uint32_t)xx[q] & 0x7FFFFFFFu;
+            }
+          }
+        }
+#pragma unroll
+        for (int k = 0; k < kTilesInFlight; ++k) {
+          for (unsigned long long m = __ballot(words_here[k]); m; m &= m - 1) {
+            const int64_t wi = (first - t0 + k * kRefineThreads + wave * 64 + (__ffsll((long long)m) - 1)) * 64 + lane;
+            int64_t tile;
+            int l;
+            const uint32_t w = tensor_mask_word(a.mask, t0, wi, lo, hi, tile, l);
+            if (w) list_words(tile, l, w);
+          }
+        }
+      }
+    } else {
+      // eight words (16 bytes) per load, four loads in flight per thread
+      const uint4* mask128 = reinterpret_cast<const uint4*>(a.mask + t0 * 64);
+      const int64_t chunks = words >> 3;
+      for (int64_t c0 = tid; c0 < chunks; c0 += 4 * kRefineThreads) {
+        uint4 m[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const int64_t c = c0 + k * kRefineThreads;
+          m[k] = c < chunks ? mask128[c] : make_uint4(0, 0, 0, 0);
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const int64_t c = c0 + k * kRefineThreads;
+          if ((m[k].x | m[k].y | m[k].z | m[k].w) == 0) continue;
+          const uint32_t pair[4] = {m[k].x, m[k].y, m[k].z, m[k].w};
+#pragma unroll
+          for (int h = 0; h < 8; ++h) {
+            uint32_t w = (pair[h >> 1] >> (16 * (h & 1))) & 0xFFFFu;
+            if (!w) continue;
+            const int64_t wi = c * 8 + h;
+            const int64_t tile = t0 + (wi >> 6);
+            const int l = (int)(wi & 63);
+            if (tile * kWaveTile < lo || (tile + 1) * kWaveTile > hi) {  // tile shared with a neighbour
+              uint32_t keep = 0;
+              for (int q = 0; q < kStreamUnroll * 4; ++q) {
+                const int64_t e = tile_element(tile, l, q);
+                if (e >= lo && e < hi) keep |= 1u << q;
+              }
+              w &= keep;
+              if (!w) continue;
+            }
+            list_words(tile, l, w);
+          }
+        }
+      }
+    }
+    for (int b = tid; b < kSelectBins; b += kRefineThreads) sh.s.hist[b] = 0;
+    if (tid == 0) sh.s.surv_n = 0;
+    __syncthreads();
+    const int count = (int)passed;
+    uint32_t key[kRefinePer];
+#pragma unroll
+    for (int q = 0; q < kRefinePer; ++q) {
+      const int p = tid + q * kRefineThreads;
+      key[q] = kNoKey;
+      if (p < count) {
+        const uint32_t e = sh.list[p];
+        key[q] = (e & kFromRecord) ? sh.keys[p] : (__float_as_uint(a.v[e]) & 0x7FFFFFFFu);
+      }
+    }
+    {
+      // One histogram over the four octaves above the sampled threshold, where the wanted rank nearly always
+      // is (the last bin takes everything beyond), and direct ranking of its bin; if that does not fit, the
+      // passes over the key's bits.
+      constexpr int kShift = 14;
+      const uint32_t low = floor >= 0.0f ? __float_as_uint(floor) : 0u;  // -1: everything was let through
+      auto bin_of = [&](uint32_t k) {
+        const uint32_t b = (k - low) >> kShift;
+        return b < (uint32_t)kSelectBins ? b : (uint32_t)kSelectBins - 1u;
+      };
+#pragma unroll
+      for (int q = 0; q < kRefinePer; ++q)
+        if (key[q] != kNoKey) atomicAdd(&sh.s.hist[bin_of(key[q])], 1u);
+      __syncthreads();
+      uint32_t bin, above, members;
+      find_bin<kRefineThreads>(sh.s.hist, sh.s.wave_tot, sh.s.sel, tid, rank, bin, above, members);
+      if (members <= (uint32_t)kSelectDirect) {
+        if (tid < 4) sh.s.surv[(members & ~3u) + tid] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < kRefinePer; ++q)
+          if (key[q] != kNoKey && bin_of(key[q]) == bin) sh.s.surv[atomicAdd(&sh.s.surv_n, 1u)] = key[q];
+        __syncthreads();
+        prefix = rank_directly(sh.s, tid, members, rank - above);
+      } else {
+        __syncthreads();
+        prefix = select_in_registers<kRefinePer>(sh.s, key, 0u, rank, tid);
+      }
+    }
+    // Clear the mask bit of every selected element that does not exceed the new threshold.
+    // A 16-bit mask word of a tile shared with a neighbour tensor also holds that tensor's
+    // bits, and its re-threshold may run at the same time: atomic AND on the 32-bit word.
+    // (Elements in records are dropped tile by tile below.)
+#pragma unroll
+    for (int q = 0; q < kRefinePer; ++q) {
+      const int p = tid + q * kRefineThreads;
+      if (p < count && !(key[q] > prefix) && !(sh.list[p] & kFromRecord)) {
+        const int64_t e = sh.list[p];
+        const int64_t tile = e / kWaveTile;
+        const int r = (int)(e % kWaveTile);
+        const int64_t h = tile * 64 + ((r & 255) >> 2);        // the lane's 16-bit word
+        const int b = (r >> 8) * 4 + (r & 3);
+        atomicAnd(&mask32[h >> 1], ~((1u << b) << (16 * (int)(h & 1))));
+        atomicSub(&a.tile_count[tile], 1u);
+      }
+    }
+  } else if (passed <= cap) {
     // The tensor's payload region is free until the emit pass: list the selected elements
     // there, then their keys, so that everything after one walk over the tiles is coalesced.
     uint32_t* list = reinterpret_cast<uint32_t*>(a.out_idx + region);
@@ -1325,23 +1494,20 @@ __global__ __launch_bounds__(kRefineThreads) void refine_kernel(RefineArgs a) {
       const int bits = pass == 2 ? 9 : 11;
       const int shift = 31 - consumed - bits;
       const uint32_t digit_mask = (1u << bits) - 1u;
-      for (int i = tid; i < kSelectBins; i += kRefineThreads) sh.hist[i] = 0;
+      for (int i = tid; i < kSelectBins; i += kRefineThreads) sh.s.hist[i] = 0;
       __syncthreads();
       for (int p = tid; p < count; p += kRefineThreads) {
         const uint32_t key = keys[p];
-        if (pass == 0 || (key >> (shift + bits)) == prefix) atomicAdd(&sh.hist[(key >> shift) & digit_mask], 1u);
+        if (pass == 0 || (key >> (shift + bits)) == prefix) atomicAdd(&sh.s.hist[(key >> shift) & digit_mask], 1u);
       }
       __syncthreads();
       uint32_t bin, above, members;
-      find_bin<kRefineThreads>(sh.hist, sh.wave_tot, sh.sel, tid, rank, bin, above, members);
+      find_bin<kRefineThreads>(sh.s.hist, sh.s.wave_tot, sh.s.sel, tid, rank, bin, above, members);
       prefix = (prefix << bits) | bin;
       rank -= above;
       consumed += bits;
     }
-    // Clear the mask bit of every selected element that does not exceed the new threshold.
-    // A 16-bit mask word of a tile shared with a neighbour tensor also holds that tensor's
-    // bits, and its re-threshold may run at the same time: atomic AND on the 32-bit word.
-    // (Elements in records are dropped tile by tile below.)
+    // mask bits as above
     for (int p = tid; p < count; p += kRefineThreads) {
       if (!(keys[p] > prefix) && !(list[p] & kFromRecord)) {
         const int64_t e = list[p];
@@ -1361,7 +1527,7 @@ __global__ __launch_bounds__(kRefineThreads) void refine_kernel(RefineArgs a) {
       const int bits = pass == 2 ? 9 : 11;
       const int shift = 31 - consumed - bits;
       const uint32_t digit_mask = (1u << bits) - 1u;
-      for (int i = tid; i < kSelectBins; i += kRefineThreads) sh.hist[i] = 0;
+      for (int i = tid; i < kSelectBins; i += kRefineThreads) sh.s.hist[i] = 0;
       __syncthreads();
       if (a.slotted) {
         for (int64_t tile = t0 + tid; tile <= t1; tile += kRefineThreads) {
@@ -1369,7 +1535,7 @@ __global__ __launch_bounds__(kRefineThreads) void refine_kernel(RefineArgs a) {
           const int c = (int)a.tile_count[tile];
           for (int q = 0; q < c; ++q) {
             const uint32_t key = (uint32_t)records[tile * kSlotRecord + kSlotsPerTile + q] & 0x7FFFFFFFu;
-            if (pass == 0 || (key >> (shift + bits)) == prefix) atomicAdd(&sh.hist[(key >> shift) & digit_mask], 1u);
+            if (pass == 0 || (key >> (shift + bits)) == prefix) atomicAdd(&sh.s.hist[(key >> shift) & digit_mask], 1u);
           }
         }
       }
@@ -1383,12 +1549,12 @@ __global__ __launch_bounds__(kRefineThreads) void refine_kernel(RefineArgs a) {
           w &= w - 1;
           const uint32_t key = __float_as_uint(a.v[tile_element(tile, l, q)]) & 0x7FFFFFFFu;
           if (pass == 0 || (key >> (shift + bits)) == prefix)
-            atomicAdd(&sh.hist[(key >> shift) & digit_mask], 1u);
+            atomicAdd(&sh.s.hist[(key >> shift) & digit_mask], 1u);
         }
       }
       __syncthreads();
       uint32_t bin, above, members;
-      find_bin<kRefineThreads>(sh.hist, sh.wave_tot, sh.sel, tid, rank, bin, above, members);
+      find_bin<kRefineThreads>(sh.s.hist, sh.s.wave_tot, sh.s.sel, tid, rank, bin, above, members);
       prefix = (prefix << bits) | bin;
       rank -= above;
       consumed += bits;
@@ -1420,26 +1586,51 @@ __global__ __launch_bounds__(kRefineThreads) void refine_kernel(RefineArgs a) {
   if (a.slotted) {
     __syncthreads();  // every walk over records and counts above is over
     int32_t* rec = reinterpret_cast<int32_t*>(a.mask);
-    for (int64_t tile = t0 + tid; tile <= t1; tile += kRefineThreads) {
-      if (!is_record(tile)) continue;
-      const int c = (int)a.tile_count[tile];
-      int32_t* r = rec + tile * kSlotRecord;
-      int kept = 0;
-      for (int q = 0; q < c; ++q) {
-        const int32_t e = r[q];
-        const int32_t xv = r[kSlotsPerTile + q];
-        const int32_t xu = r[2 * kSlotsPerTile + q];
-        if (((uint32_t)xv & 0x7FFFFFFFu) > prefix) {
-          r[kept] = e;
-          r[kSlotsPerTile + kept] = xv;
-          r[2 * kSlotsPerTile + kept] = xu;
-          ++kept;
-        } else {
-          a.v_out[e] = __int_as_float(xv);
-          if (a.factor_masking) a.u_out[e] = __int_as_float(xu);
+    constexpr int kTilesInFlight = 2;
+#pragma unroll 1
+    for (int64_t first = t0; first <= t1; first += kTilesInFlight * kRefineThreads) {
+      uint32_t c[kTilesInFlight];
+      int4 e[kTilesInFlight][2], x[kTilesInFlight][2], y[kTilesInFlight][2];
+#pragma unroll
+      for (int k = 0; k < kTilesInFlight; ++k) {
+        // the counts of the tiles and their lines (a record only if the count says so) are asked for together
+        const int64_t tile = first + k * kRefineThreads + tid;
+        const bool whole = tile <= t1 && tile * kWaveTile >= lo && (tile + 1) * kWaveTile <= hi;
+        const int4* line = reinterpret_cast<const int4*>(rec + tile * kSlotRecord);
+        c[k] = whole ? a.tile_count[tile] : 0u;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          e[k][h] = whole ? line[h] : make_int4(0, 0, 0, 0);
+          x[k][h] = whole ? line[kSlotsPerTile / 4 + h] : make_int4(0, 0, 0, 0);
+          y[k][h] = whole ? line[2 * kSlotsPerTile / 4 + h] : make_int4(0, 0, 0, 0);
         }
       }
-      if (kept != c) a.tile_count[tile] = (uint32_t)kept;
+#pragma unroll
+      for (int k = 0; k < kTilesInFlight; ++k) {
+        if (c[k] < 1u || c[k] > (uint32_t)kSlotsPerTile) continue;
+        const int64_t tile = first + k * kRefineThreads + tid;
+        int32_t* r = rec + tile * kSlotRecord;
+        const int32_t ee[8] = {e[k][0].x, e[k][0].y, e[k][0].z, e[k][0].w, e[k][1].x, e[k][1].y, e[k][1].z, e[k][1].w};
+        const int32_t xx[8] = {x[k][0].x, x[k][0].y, x[k][0].z, x[k][0].w, x[k][1].x, x[k][1].y, x[k][1].z, x[k][1].w};
+        const int32_t yy[8] = {y[k][0].x, y[k][0].y, y[k][0].z, y[k][0].w, y[k][1].x, y[k][1].y, y[k][1].z, y[k][1].w};
+        uint32_t kept = 0;
+#pragma unroll
+        for (int q = 0; q < kSlotsPerTile; ++q) {
+          if ((uint32_t)q >= c[k]) continue;
+          if (((uint32_t)xx[q] & 0x7FFFFFFFu) > prefix) {
+            if (kept != (uint32_t)q) {
+              r[kept] = ee[q];
+              r[kSlotsPerTile + kept] = xx[q];
+              r[2 * kSlotsPerTile + kept] = yy[q];
+            }
+            ++kept;
+          } else {
+            a.v_out[ee[q]] = __int_as_float(xx[q]);
+            if (a.factor_masking) a.u_out[ee[q]] = __int_as_float(yy[q]);
+          }
+        }
+        if (kept != c[k]) a.tile_count[tile] = kept;
+      }
     }
   }
   if (tid == 0) {
