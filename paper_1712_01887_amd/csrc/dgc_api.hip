@@ -442,7 +442,7 @@ dgc_status dgc_create(dgc_handle** out, const dgc_config* cfg, int32_t num_tenso
       int64_t end = (int64_t)(h->emit_blocks[e - 1].first_tile + kEmitTiles) * kWaveTile;
       if (begin < h->offsets[t]) begin = h->offsets[t];
       if (end > h->offsets[t + 1]) end = h->offsets[t + 1];
-      h->merge_blocks.push_back(MergeBlock{begin, end, t, 0});
+      h->merge_blocks.push_back(MergeBlock{(int32_t)begin, (int32_t)end, t, (int32_t)h->offsets[t], (int32_t)h->offsets[t + 1], 0});
       if (end - begin > h->longest_range) h->longest_range = end - begin;
       b = e;
     }
@@ -451,7 +451,8 @@ dgc_status dgc_create(dgc_handle** out, const dgc_config* cfg, int32_t num_tenso
       int64_t end = (int64_t)(eb.first_tile + kEmitTiles) * kWaveTile;
       if (begin < h->offsets[eb.tensor]) begin = h->offsets[eb.tensor];
       if (end > h->offsets[eb.tensor + 1]) end = h->offsets[eb.tensor + 1];
-      h->part_blocks.push_back(MergeBlock{begin, end, eb.tensor, 0});
+      h->part_blocks.push_back(MergeBlock{(int32_t)begin, (int32_t)end, eb.tensor, (int32_t)h->offsets[eb.tensor],
+                                          (int32_t)h->offsets[eb.tensor + 1], 0});
     }
     h->ws_out_offsets.resize(num_tensors + 1);
     h->wire_first_block.resize(num_tensors + 1);

@@ -263,9 +263,10 @@ struct EmitArgs {
 };
 
 struct MergeBlock {
-  int64_t begin;   // first element (flat index) of the range
-  int64_t end;     // one past its last element; the range lies inside one tensor
+  int32_t begin;    // first element (flat index) of the range
+  int32_t end;      // one past its last element; the range lies inside one tensor
   int32_t tensor;
+  int32_t lo, hi;   // the tensor's elements [lo, hi): where in a region a search starts
   int32_t pad;
 };
 

@@ -162,14 +162,23 @@ __global__ __launch_bounds__(kFlatThreads) void scatter_regions_kernel(float* de
 // wave_equal_range for two lists at once, with the probes of both in flight together (`safe` is any
 // readable word: it is read in place of a probe that has nothing left to ask).
 __device__ __forceinline__ void wave_equal_range2(const int32_t* __restrict__ L0, int m0, const int32_t* __restrict__ L1,
-                                                  int m1, const int32_t* __restrict__ safe, int32_t xa, int32_t xb,
+                                                  int m1, const int32_t* __restrict__ safe, const MergeBlock& blk,
                                                   int lane, int& lo_0, int& hi_0, int& lo_1, int& hi_1) {
   const int half = lane >> 5;
   const int sub = lane & 31;
-  const int32_t x = half ? xb : xa;
+  const int32_t x = half ? blk.end : blk.begin;
   const int32_t* __restrict__ A = m0 > 0 ? L0 : safe;
   const int32_t* __restrict__ B = m1 > 0 ? L1 : safe;
   int lo0 = 0, hi0 = m0, lo1 = 0, hi1 = m1;
+  if (m0 > kGuessFrom || m1 > kGuessFrom) {
+    const GuessRound<32> r0(Guess(m0, x, blk.lo, blk.hi), m0), r1(Guess(m1, x, blk.lo, blk.hi), m1);
+    const int32_t v0 = A[m0 > 0 ? r0.at(sub) : 0];
+    const int32_t v1 = B[m1 > 0 ? r1.at(sub) : 0];
+    const unsigned long long votes0 = __ballot(v0 < x);
+    const unsigned long long votes1 = __ballot(v1 < x);
+    if (m0 > 0) r0.narrow(__popc((uint32_t)(votes0 >> (32 * half))), lo0, hi0);
+    if (m1 > 0) r1.narrow(__popc((uint32_t)(votes1 >> (32 * half))), lo1, hi1);
+  }
   while (__ballot(hi0 > lo0 || hi1 > lo1)) {
     const int span0 = hi0 - lo0, span1 = hi1 - lo1;
     const int step0 = (span0 + 31) >> 5, step1 = (span1 + 31) >> 5;
@@ -219,7 +228,7 @@ __device__ __forceinline__ int locate_pairs(Shared& sh, const RegionPayloads& p,
     if (cnt > cap) cnt = cap;
     if (cnt < 0) cnt = 0;
     int lo, hi;
-    wave_equal_range(p.idx[w] + region, (int)cnt, (int32_t)blk.begin, (int32_t)blk.end, lane, lo, hi);
+    wave_equal_range<true>(p.idx[w] + region, (int)cnt, blk.begin, blk.end, blk.lo, blk.hi, lane, lo, hi);
     if (lane == 0) {
       sh.idx_at[w] = p.idx[w] + region + lo;
       sh.val_at[w] = p.val[w] ? p.val[w] + region + lo : nullptr;
@@ -261,8 +270,7 @@ __device__ __forceinline__ int locate_pairs2(Shared& sh, const RegionPayloads& p
     const int32_t* __restrict__ list = w < num_payloads ? p.idx[w] + region : safe;
     const int32_t* __restrict__ list2 = w < num_payloads2 ? p2.idx[w] + region : safe;
     int lo, hi, lo2, hi2;
-    wave_equal_range2(list, (int)cnt, list2, (int)cnt2, safe, (int32_t)blk.begin, (int32_t)blk.end, lane, lo, hi, lo2,
-                      hi2);
+    wave_equal_range2(list, (int)cnt, list2, (int)cnt2, safe, blk, lane, lo, hi, lo2, hi2);
     if (lane == 0) {
       if (w < num_payloads) {
         sh.idx_at[w] = list + lo;
@@ -622,13 +630,14 @@ __global__ __launch_bounds__(kFlatThreads) void locate_parts_kernel(RegionPayloa
   const int w = (int)(wave_id / waves_per_payload);
   const int b = (int)(wave_id % waves_per_payload) * 7 + group;
   const bool valid = w < num_payloads && b < num_blocks;
+  MergeBlock blk{};
   const int32_t* __restrict__ list = nullptr;
   int32_t x = 0;
   int lo = 0, hi = 0;  // the answer lies in [lo, hi]
   int cnt = 0;
   bool last = true;    // the tensor's last part: it ends where the region's pairs end
   if (valid) {
-    const MergeBlock blk = blocks[b];
+    blk = blocks[b];
     const int64_t region = out_offsets[blk.tensor];
     const int64_t cap = out_offsets[blk.tensor + 1] - region;
     int64_t c = p.counts[w][blk.tensor];
@@ -637,8 +646,14 @@ __global__ __launch_bounds__(kFlatThreads) void locate_parts_kernel(RegionPayloa
     cnt = (int)c;
     last = b + 1 >= num_blocks || blocks[b + 1].tensor != blk.tensor;
     list = p.idx[w] + region;
-    x = (int32_t)blk.begin;
+    x = blk.begin;
     hi = cnt;
+  }
+  // the first round around the place the part starts at if the pairs are spread evenly over the tensor
+  if (__ballot(cnt > 64)) {
+    const GuessRound<8> r(Guess(cnt, x, blk.lo, blk.hi > blk.lo ? blk.hi : blk.lo + 1), cnt);
+    const unsigned long long votes = __ballot(cnt > 0 && list[r.at(sub)] < x);
+    if (cnt > 0) r.narrow(__popc((uint32_t)(votes >> (8 * group)) & 0xFFu), lo, hi);
   }
   // first position whose index is not below x ("index < x" is monotone along a region)
   while (__ballot(hi > lo)) {
