@@ -418,6 +418,44 @@ __device__ __forceinline__ BandState* band_state(const SelectArgs& a, const Tens
 }
 __device__ __forceinline__ int64_t band_list_begin(int64_t offset) { return 3 * (offset >> kBandListShift); }
 
+// Clipping scale (paper: Appendix C equation 12).  With clipping on, the norm kernel has left its partial
+// sums, of which `part` is this thread's (thread t has partial t, or zero); every workgroup adds them in the
+// same fixed order (lanes, then wavefronts, in order), so all of them get the same bits, and the first one
+// also files the result for the streaming pass and for the diagnostics.
+static_assert(kNormMaxBlocks <= kSelectThreads, "a partial sum per thread");
+__device__ __forceinline__ float settle_scale(const SelectArgs& a, SelectShared& sh, double part, int j, int tid) {
+  if (!a.scale_from_state) {
+    if (tid == 0 && j == 0) {  // no clipping: start a clean record
+      a.state->norm = __longlong_as_double(0x7FF8000000000000ll);
+      a.state->scale = a.scale_const;
+      a.state->flags = 0;
+    }
+    return a.scale_const;
+  }
+  double s = part;
+  for (int d = 32; d >= 1; d >>= 1) s += __shfl_down(s, d);
+  if ((tid & 63) == 0) sh.red[tid >> 6] = s;
+  __syncthreads();
+  if (tid == 0) {
+    double total = 0.0;
+    for (int w = 0; w < kSelectThreads / 64; ++w) total += sh.red[w];
+    const double norm = sqrt(total);
+    float sc = 1.0f;
+    if (norm > a.thr_local) sc = (float)(a.thr_local / norm);
+    if (a.scale_override == a.scale_override) sc = a.scale_override;
+    sh.scale = sc;
+    if (j == 0) {
+      uint32_t flags = 0;
+      if (!(norm <= 1.79769313486231570e308)) flags |= DGC_DIAG_NONFINITE;  // NaN or infinity
+      a.state->norm = norm;
+      a.state->scale = sc;
+      a.state->flags = flags;
+    }
+  }
+  __syncthreads();
+  return sh.scale;
+}
+
 // BANDS: some tensors are ranked by way of a band (TensorPlan.exact == 2).
 template <bool NESTEROV, bool BANDS>
 __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectArgs a) {
@@ -425,48 +463,17 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectArgs a) {
   const int tid = threadIdx.x;
   const int j = blockIdx.x;
   const TensorPlan plan = a.plans[j];
+  // Asked for before the candidates and used after their first loads are on their way, so that the scale's
+  // chain of steps (sum over the lanes, over the wavefronts, square root) runs while those are outstanding.
+  const double part = a.scale_from_state && tid < a.num_partials ? a.partials[tid] : 0.0;
 
-  // Clipping scale (paper: Appendix C equation 12).  With clipping on, the norm kernel
-  // has left its partial sums; every workgroup adds them in the same fixed order (thread
-  // t takes partials t, t + 1024, ...; lanes, then wavefronts, in order), so all of them
-  // get the same bits, and the first one also files the result for the streaming pass
-  // and for the diagnostics.
-  float scale = a.scale_const;
-  if (a.scale_from_state) {
-    double s = 0.0;
-    for (int i = tid; i < a.num_partials; i += kSelectThreads) s += a.partials[i];
-    for (int d = 32; d >= 1; d >>= 1) s += __shfl_down(s, d);
-    if ((tid & 63) == 0) sh.red[tid >> 6] = s;
-    __syncthreads();
-    if (tid == 0) {
-      double total = 0.0;
-      for (int w = 0; w < kSelectThreads / 64; ++w) total += sh.red[w];
-      const double norm = sqrt(total);
-      float sc = 1.0f;
-      if (norm > a.thr_local) sc = (float)(a.thr_local / norm);
-      if (a.scale_override == a.scale_override) sc = a.scale_override;
-      sh.scale = sc;
-      if (j == 0) {
-        uint32_t flags = 0;
-        if (!(norm <= 1.79769313486231570e308)) flags |= DGC_DIAG_NONFINITE;  // NaN or infinity
-        a.state->norm = norm;
-        a.state->scale = sc;
-        a.state->flags = flags;
-      }
-    }
-    __syncthreads();
-    scale = sh.scale;
-  } else if (tid == 0 && j == 0) {  // no clipping: start a clean record
-    a.state->norm = __longlong_as_double(0x7FF8000000000000ll);
-    a.state->scale = a.scale_const;
-    a.state->flags = 0;
-  }
   if (plan.rank >= plan.count) {  // the strict comparison then passes everything
+    settle_scale(a, sh, part, j, tid);
     write_threshold(a, j, plan, -1.0f, tid);
     return;
   }
 
-  Candidates c = candidates_of(a, j, plan, scale, NESTEROV);
+  Candidates c = candidates_of(a, j, plan, a.scale_const, NESTEROV);
   if (BANDS && plan.exact == 2) {  // a sample for the band of an exact selection
     c.exact = 0;
     c.block_shift = kBandBlockShift;
@@ -513,6 +520,7 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectArgs a) {
             uu[q] = *reinterpret_cast<const vec4u*>(c.u + e);
             vv[q] = *reinterpret_cast<const vec4u*>(c.v + e);
           }
+          if (r == 0) c.scale = settle_scale(a, sh, part, j, tid);
 #pragma unroll
           for (int q = 0; q < kQuadsInFlight; ++q) {
             const bool ok = tid + (r * kQuadsInFlight + q) * kSelectThreads < quads;
@@ -539,6 +547,7 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectArgs a) {
             uu[q] = c.u[e];
             vv[q] = c.v[e];
           }
+          if (r == 0) c.scale = settle_scale(a, sh, part, j, tid);
 #pragma unroll
           for (int q = 0; q < kSelectInFlight; ++q) {
             const bool ok = tid + (r * kSelectInFlight + q) * kSelectThreads < count;
@@ -565,6 +574,7 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectArgs a) {
     }
     thr_bits = rank_registers(sh, key, holders, rank, tid);
   } else {
+    c.scale = settle_scale(a, sh, part, j, tid);
     thr_bits = rank_reevaluated(sh, c, count, rank, tid);
   }
   write_threshold(a, j, plan, __uint_as_float(thr_bits), tid);
@@ -1752,12 +1762,8 @@ __global__ __launch_bounds__(kEmitThreads) void emit_kernel(EmitArgs a) {
   int cnt = 0;
 #pragma unroll
   for (int i = 0; i < kPerWave; ++i) cnt += __popc(word[i]);
-  int incl = cnt;
-  for (int d = 1; d < 64; d <<= 1) {
-    const int t = __shfl_up(incl, d);
-    if (lane >= d) incl += t;
-  }
-  for (int d = 32; d >= 1; d >>= 1) pre += __shfl_xor(pre, d);
+  const int incl = (int)wave_inclusive_sum((uint32_t)cnt);
+  pre = (int)wave_sum((uint32_t)pre);
   if (lane == 63) wave_tot[wave] = incl;
   if (lane == 0) pre_tot[wave] = pre;
   __syncthreads();
@@ -2231,7 +2237,7 @@ __global__ __launch_bounds__(kEmitSlotThreads) void emit_slots_kernel(EmitArgs a
   const bool first_shared = t0 * kWaveTile < lo;
   int pre = tile_counts_partial<kEmitSlotThreads>(a.tile_count, first_shared ? t0 + 1 : t0, first, tid);
   if (first > t0 && first_shared && wave == 0) pre += __popc(tensor_tile_word(a.mask, t0, lane, lo, hi));
-  for (int d = 32; d >= 1; d >>= 1) pre += __shfl_xor(pre, d);
+  pre = (int)wave_sum((uint32_t)pre);
   if (lane == 0) sh.pre_tot[wave] = pre;
 
   const bool from_slots = inside && c_raw <= (uint32_t)kSlotsPerTile;  // (a flagged count is a large number)
@@ -2243,8 +2249,7 @@ __global__ __launch_bounds__(kEmitSlotThreads) void emit_slots_kernel(EmitArgs a
     const int k = wave * kTilesPerWave + (__ffsll((long long)m) - 1) / kLanesPerTile;
     const uint32_t w = tensor_tile_word(a.mask, first + k, lane, lo, hi);
     sh.words[k * 64 + lane] = (uint16_t)w;
-    int c = __popc(w);
-    for (int d = 32; d >= 1; d >>= 1) c += __shfl_xor(c, d);
+    const int c = (int)wave_sum((uint32_t)__popc(w));
     if (lane == 0) sh.cnt[k] = c;
   }
   __syncthreads();
@@ -2253,12 +2258,8 @@ __global__ __launch_bounds__(kEmitSlotThreads) void emit_slots_kernel(EmitArgs a
   for (int w = 0; w < kWaves; ++w) base += sh.pre_tot[w];
   // where every tile starts in the part: each wavefront scans the 32 counts for itself
   const int own = lane < kEmitTiles ? sh.cnt[lane] : 0;
-  int incl = own;
-  for (int d = 1; d < 32; d <<= 1) {
-    const int up = __shfl_up(incl, d);
-    if (lane >= d) incl += up;
-  }
-  const int total = __shfl(incl, kEmitTiles - 1);
+  const int incl = (int)wave_inclusive_sum((uint32_t)own);
+  const int total = __builtin_amdgcn_readlane(incl, kEmitTiles - 1);
   if (tid == 0 && (int)((first - t0) / kEmitTiles) == blk.tensor_blocks - 1) a.out_counts[j] = base + total;
   if (total == 0) return;
   const int excl = incl - own;
@@ -2294,12 +2295,7 @@ __global__ __launch_bounds__(kEmitSlotThreads) void emit_slots_kernel(EmitArgs a
     // Index order inside the tile is row (one 16-byte vector per lane), lane, component: an element's
     // position is the rows before it, plus the bits of its row in lower lanes, plus the lower bits of
     // its nibble.
-    int most = __popc(w);  // bits of the lane that has most
-    for (int d = 32; d >= 1; d >>= 1) {
-      const int o = __shfl_xor(most, d);
-      most = o > most ? o : most;
-    }
-    most = __builtin_amdgcn_readfirstlane(most);  // the same in every lane: branches on it are scalar
+    const int most = (int)wave_max((uint32_t)__popc(w));  // bits of the lane that has most (uniform)
     const int tile_count = __shfl(own, k);
     if (tile_count < 256 && most <= kEmitWalk) {
       // The usual case (a tile shared between tensors, or a dozen elements in one tile): positions
@@ -2309,12 +2305,8 @@ __global__ __launch_bounds__(kEmitSlotThreads) void emit_slots_kernel(EmitArgs a
       uint32_t xw = w - ((w >> 1) & 0x5555u);
       xw = (xw & 0x3333u) + ((xw >> 2) & 0x3333u);  // a count per nibble
       const uint32_t cnt = (xw & 0xFu) | ((xw & 0xF0u) << 4) | ((xw & 0xF00u) << 8) | ((xw & 0xF000u) << 12);
-      uint32_t inc = cnt;
-      for (int d = 1; d < 64; d <<= 1) {
-        const uint32_t up = __shfl_up(inc, d);
-        if (lane >= d) inc += up;
-      }
-      const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+      const uint32_t inc = wave_inclusive_sum(cnt);
+      const uint32_t tot = wave_last(inc);
       uint32_t next = (inc - cnt) + ((tot << 8) + (tot << 16) + (tot << 24));  // next position of each of the lane's rows
       const int32_t e_lane = (int32_t)tile_element(tk, lane, 0);
       uint32_t rem = w;

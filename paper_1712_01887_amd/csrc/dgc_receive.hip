@@ -215,6 +215,14 @@ __device__ __forceinline__ void wave_equal_range2(const int32_t* __restrict__ L0
   hi_1 = __shfl(lo1, 32);
 }
 
+// begin[1 .. num] holds lengths; afterwards begin[w] is the sum of the lengths before w.  One wavefront.
+static_assert(kMaxPayloads <= 64, "a payload per lane");
+__device__ __forceinline__ void begins_from_lengths(int32_t* begin, int num, int lane) {
+  const uint32_t sum = wave_inclusive_sum(lane < num ? (uint32_t)begin[lane + 1] : 0u);
+  if (lane < num) begin[lane + 1] = (int32_t)sum;
+  if (lane == 0) begin[0] = 0;
+}
+
 // Finds every payload's pairs inside [blk.begin, blk.end) and fills begin[], idx_at[] and
 // val_at[] (in LDS: a payload's pointers looked up per pair in the kernel's argument block
 // would put a load from memory in front of every pair load).
@@ -236,15 +244,7 @@ __device__ __forceinline__ int locate_pairs(Shared& sh, const RegionPayloads& p,
     }
   }
   __syncthreads();
-  if (tid == 0) {
-    int run = 0;
-    sh.begin[0] = 0;
-    for (int w = 0; w < num_payloads; ++w) {
-      const int len = sh.begin[w + 1];
-      sh.begin[w + 1] = run + len;
-      run += len;
-    }
-  }
+  if (tid < 64) begins_from_lengths(sh.begin, num_payloads, tid);
   __syncthreads();
   return sh.begin[num_payloads];
 }
@@ -285,24 +285,8 @@ __device__ __forceinline__ int locate_pairs2(Shared& sh, const RegionPayloads& p
     }
   }
   __syncthreads();
-  if (tid == 0) {
-    int run = 0;
-    sh.begin[0] = 0;
-    for (int w = 0; w < num_payloads; ++w) {
-      const int len = sh.begin[w + 1];
-      sh.begin[w + 1] = run + len;
-      run += len;
-    }
-  }
-  if (tid == 64) {
-    int run = 0;
-    sh2.begin[0] = 0;
-    for (int w = 0; w < num_payloads2; ++w) {
-      const int len = sh2.begin[w + 1];
-      sh2.begin[w + 1] = run + len;
-      run += len;
-    }
-  }
+  if (tid < 64) begins_from_lengths(sh.begin, num_payloads, tid);
+  if (tid >= 64 && tid < 128) begins_from_lengths(sh2.begin, num_payloads2, tid - 64);
   __syncthreads();
   total2 = sh2.begin[num_payloads2];
   return sh.begin[num_payloads];
@@ -466,11 +450,7 @@ __global__ __launch_bounds__(THREADS) void merge_regions_kernel(float* __restric
         c[k] = (uint32_t)__popc(sh.bitmap[tid * kWordsPerThread + k]);
         mine += c[k];
       }
-      uint32_t incl = mine;
-      for (int d = 1; d < 64; d <<= 1) {
-        const uint32_t t = __shfl_up(incl, d);
-        if (lane >= d) incl += t;
-      }
+      const uint32_t incl = wave_inclusive_sum(mine);
       if (lane == 63) sh.wave_sums[wave] = incl;
       __syncthreads();
       uint32_t run = incl - mine;
@@ -533,11 +513,7 @@ __global__ __launch_bounds__(THREADS) void merge_regions_kernel(float* __restric
         c[k] = (uint32_t)__popc(sh.bitmap[tid * kWordsPerThread + k]);
         mine += c[k];
       }
-      uint32_t incl = mine;
-      for (int d = 1; d < 64; d <<= 1) {
-        const uint32_t t = __shfl_up(incl, d);
-        if (lane >= d) incl += t;
-      }
+      const uint32_t incl = wave_inclusive_sum(mine);
       if (lane == 63) sh.wave_sums[wave] = incl;
       __syncthreads();
       uint32_t run = incl - mine, all = 0;
@@ -691,15 +667,7 @@ __device__ __forceinline__ int located_pairs(Shared& sh, const RegionPayloads& p
     sh.begin[tid + 1] = f.y;  // length for now
   }
   __syncthreads();
-  if (tid == 0) {
-    int run = 0;
-    sh.begin[0] = 0;
-    for (int w = 0; w < num_payloads; ++w) {
-      const int len = sh.begin[w + 1];
-      sh.begin[w + 1] = run + len;
-      run += len;
-    }
-  }
+  if (tid < 64) begins_from_lengths(sh.begin, num_payloads, tid);
   __syncthreads();
   return sh.begin[num_payloads];
 }
