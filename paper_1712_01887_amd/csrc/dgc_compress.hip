@@ -991,8 +991,7 @@ __global__ __launch_bounds__(kStreamThreads) void stream_kernel(StreamArgs a) {
         __builtin_nontemporal_store(z[r], v4 + r * 64);
       }
     }
-    int total = __popc(cand);
-    for (int d = 32; d >= 1; d >>= 1) total += __shfl_xor(total, d);
+    const int total = (int)wave_sum((uint32_t)__popc(cand));
     if (total > 0 && total <= kSlotsPerTile) {  // uniform
       // The few selected elements are taken row by row, one at a time, everything about them in
       // scalar registers (which lane, which of its four elements): the values are read from that
@@ -1086,8 +1085,7 @@ __global__ __launch_bounds__(kStreamThreads) void stream_kernel(StreamArgs a) {
   }
   a.mask[tile * 64 + lane] = (uint16_t)cand;
   // bits set in the tile, for the index-ordered emit pass (measured: no cost here)
-  int bits = __popc(cand);
-  for (int d = 32; d >= 1; d >>= 1) bits += __shfl_xor(bits, d);
+  const int bits = (int)wave_sum((uint32_t)__popc(cand));
   if (lane == 0) a.tile_count[tile] = (uint32_t)bits;
 }
 
@@ -1847,7 +1845,7 @@ __device__ __forceinline__ void emit_tiles(const EmitArgs& a, const EmitBlock& b
       word[i] = t <= t1 ? tensor_tile_word(a.mask, t, lane, lo, hi) : 0u;
     }
     // elements per tile: the lanes' bit counts of two tiles share a register (16 bits each,
-    // a tile holds at most 1024) and are summed over the wavefront by a butterfly
+    // a tile holds at most 1024) and are summed over the wavefront together
     uint32_t pair[kPerWave / 2];
 #pragma unroll
     for (int i = 0; i < kPerWave; ++i) {
@@ -1855,11 +1853,9 @@ __device__ __forceinline__ void emit_tiles(const EmitArgs& a, const EmitBlock& b
       if (i & 1) pair[i / 2] |= (uint32_t)__popc(word[i]) << 16;
       else pair[i / 2] = (uint32_t)__popc(word[i]);
     }
-    for (int d = 32; d >= 1; d >>= 1) {
 #pragma unroll
-      for (int i = 0; i < kPerWave / 2; ++i) pair[i] += __shfl_xor(pair[i], d);
-      before += __shfl_xor(before, d);
-    }
+    for (int i = 0; i < kPerWave / 2; ++i) pair[i] = wave_sum(pair[i]);
+    before = (int)wave_sum((uint32_t)before);
     if (lane == 0) {
       sh.wave_tot[wave] = before;
 #pragma unroll
@@ -1870,11 +1866,7 @@ __device__ __forceinline__ void emit_tiles(const EmitArgs& a, const EmitBlock& b
   __syncthreads();
   if (wave == 0) {
     const int own = lane < kEmitTiles ? sh.tile_tot[lane] : 0;
-    int incl = own;
-    for (int d = 1; d < 64; d <<= 1) {
-      const int t = __shfl_up(incl, d);
-      if (lane >= d) incl += t;
-    }
+    const int incl = (int)wave_inclusive_sum((uint32_t)own);
     if (lane < kEmitTiles) sh.tile_base[lane] = incl - own;
     if (lane == 63) {
       int base = 0;

@@ -22,14 +22,16 @@ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 #endif
 constexpr int kStreamUnroll = DGC_STREAM_UNROLL;
 constexpr int kWaveTile = 64 * 4 * kStreamUnroll;  // elements per wavefront
-constexpr int kStreamThreads = 128;                 // 2 wavefronts per workgroup
+constexpr int kStreamThreads = 64;                  // one wavefront per workgroup
 constexpr int kStreamWaves = kStreamThreads / 64;
 // Workgroups of the streaming pass a compute unit holds at a time.  The pass is faster with few
-// wavefronts in flight than with the 32 a compute unit could hold (six per compute unit move 5 %
-// more bytes per second than 32: fewer streams for the memory side to interleave), so every
-// launch asks for as much LDS as leaves room for this many workgroups in a compute unit's 160 KB.
-constexpr int kStreamResidentGroups = 3;
-constexpr int kStreamGroupsAfterNorm = 6;  // with clipping on: see launch_stream
+// wavefronts in flight than with the 32 a compute unit could hold (fewer streams for the memory side
+// to interleave), so every launch asks for as much LDS as leaves room for this many workgroups in a
+// compute unit's 160 KB.  122 M elements, 0.1 %, average over operand sets (they differ by where they
+// lie): four 387 us, five 378, six 387; workgroups of two wavefronts, two, three, four of them 387, 381
+// to 395, 409; all that fit 404.  25.6 M elements: five 81.6, three of two 82.5.
+constexpr int kStreamResidentGroups = 5;
+constexpr int kStreamGroupsAfterNorm = 12;  // with clipping on: see launch_stream
 constexpr size_t kLdsPerComputeUnit = (size_t)160 * 1024;
 // Tile table: one int32 per wave tile = index of the tensor that holds the tile's
 // first element, with the top bit set when the tile is not wholly inside one
