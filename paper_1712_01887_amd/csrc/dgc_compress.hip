@@ -792,23 +792,22 @@ __device__ __forceinline__ int64_t tile_element(int64_t tile, int lane, int q) {
   return tile * kWaveTile + (q >> 2) * 256 + lane * 4 + (q & 3);
 }
 
-// Mask bits of a lane's sixteen elements in a tile that is not wholly inside one tensor.  `zq`
-// points at the lane's column of the wavefront's v' in LDS (element q of the lane at zq[q * 64]).
+// Mask bits of a lane's sixteen elements (its v' in z) in a tile that is not wholly inside one tensor.
 // `j0` is the tensor of the tile's first element.  The starts of the tensors after it are
 // fetched 64 at a time, one per lane (those inside the tile form a prefix of the lanes because
-// the offsets ascend) and handed round with readlane, so that the tile is walked segment by
-// segment, each with its tensor's threshold: one round of loads per 64 tensors, however many
-// tensors share the tile.  A few hundred tiles of a launch come here; the loops are kept rolled
-// and the values in LDS so that this path does not set the register allocation of the whole
-// kernel (unrolled over register-held values it cost the streaming pass a wavefront per SIMD).
+// the offsets ascend) and handed round with readlane: one round of loads per 64 tensors, however many
+// tensors share the tile.  The tile's thresholds are laid out in LDS, one per element (`thr_at`, one word
+// per element of the tile), segment by segment, and every lane reads those of its elements: a tile of a
+// handful of tiny tensors took 16 dependent reads per segment when the lanes' values lay there instead.
 __device__ __forceinline__ uint32_t mixed_tile_mask(const StreamArgs& a, int64_t base, int lane, int32_t j0,
-                                                    const float* zq) {
-  constexpr int kElems = 4 * kStreamUnroll;
+                                                    const vec4 (&z)[kStreamUnroll], float* thr_at) {
   const int32_t tile_end = base + kWaveTile <= a.n ? kWaveTile : (int32_t)(a.n - base);
-  const int32_t lane4 = lane * 4;
-  uint32_t cand = 0;
   int32_t seg_lo = 0;            // the segment being closed starts here (relative to the tile)
   float seg_thr = a.thr[j0];     // ... and belongs to a tensor with this threshold
+  auto fill = [&](int32_t from, int32_t to, float t) {
+#pragma unroll 1
+    for (int32_t p = from + lane; p < to; p += 64) thr_at[p] = t;
+  };
   for (int32_t jb = j0 + 1; jb < a.num_tensors; jb += 64) {
     const int32_t jj = jb + lane;
     int32_t rel = kWaveTile;  // start of tensor jj relative to the tile, kWaveTile = not inside it
@@ -823,20 +822,23 @@ __device__ __forceinline__ uint32_t mixed_tile_mask(const StreamArgs& a, int64_t
     const int cnt = __popcll(__ballot(rel < kWaveTile));
     for (int i = 0; i < cnt; ++i) {
       const int32_t seg_hi = __builtin_amdgcn_readlane(rel, i);
-#pragma unroll 1
-      for (int q = 0; q < kElems; ++q) {
-        const int32_t p = (q >> 2) * 256 + lane4 + (q & 3);
-        if (p >= seg_lo && p < seg_hi && fabsf(zq[q * 64]) > seg_thr) cand |= 1u << q;
-      }
+      fill(seg_lo, seg_hi, seg_thr);
       seg_lo = seg_hi;
       seg_thr = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int32_t)__float_as_uint(t), i));
     }
     if (cnt < 64) break;
   }
-#pragma unroll 1
-  for (int q = 0; q < kElems; ++q) {
-    const int32_t p = (q >> 2) * 256 + lane4 + (q & 3);
-    if (p >= seg_lo && p < tile_end && fabsf(zq[q * 64]) > seg_thr) cand |= 1u << q;
+  fill(seg_lo, tile_end, seg_thr);
+  fill(tile_end, kWaveTile, __builtin_inff());  // beyond the set: nothing passes
+  __builtin_amdgcn_wave_barrier();              // (LDS operations of one wavefront are carried out in order)
+  uint32_t cand = 0;
+#pragma unroll
+  for (int r = 0; r < kStreamUnroll; ++r) {
+    const float4 t = *reinterpret_cast<const float4*>(thr_at + r * 256 + lane * 4);
+    const float tc[4] = {t.x, t.y, t.z, t.w};
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+      if (fabsf(z[r][c]) > tc[c]) cand |= 1u << (4 * r + c);
   }
   return cand;
 }
@@ -876,7 +878,7 @@ enum StreamMode : int { kStreamPlain = 0, kStreamStaged = 1, kStreamSlotted = 2 
 template <bool NESTEROV, bool SCALED, int MODE>
 __global__ __launch_bounds__(kStreamThreads) void stream_kernel(StreamArgs a) {
   constexpr bool STAGED = MODE == kStreamStaged;
-  __shared__ float mixed_z[kStreamWaves][4 * kStreamUnroll][64];  // for tiles shared between tensors only
+  __shared__ alignas(16) float mixed_thr[kStreamWaves][kWaveTile];  // for tiles shared between tensors only
   constexpr int U = kStreamUnroll;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform: table reads go scalar
@@ -1078,10 +1080,7 @@ __global__ __launch_bounds__(kStreamThreads) void stream_kernel(StreamArgs a) {
     for (int q = 0; q < 4 * U; ++q)
       if (fabsf(z[q >> 2][q & 3]) > thr) cand |= 1u << q;
   } else {
-    float* zq = &mixed_z[wave][0][lane];  // this lane's column: written and read by this lane only
-#pragma unroll
-    for (int q = 0; q < 4 * U; ++q) zq[q * 64] = z[q >> 2][q & 3];
-    cand = mixed_tile_mask(a, base, lane, j0, zq);
+    cand = mixed_tile_mask(a, base, lane, j0, z, mixed_thr[wave]);
   }
   a.mask[tile * 64 + lane] = (uint16_t)cand;
   // bits set in the tile, for the index-ordered emit pass (measured: no cost here)
@@ -2428,7 +2427,7 @@ hipError_t launch_band(const SelectArgs& a, const EmitBlock* blocks, int32_t num
 }
 
 // Dynamic LDS that nothing uses: it caps the workgroups a compute unit holds at `groups`.
-constexpr size_t kStreamStaticLds = sizeof(float) * kStreamWaves * 4 * kStreamUnroll * 64;  // mixed_z of stream_kernel
+constexpr size_t kStreamStaticLds = sizeof(float) * kStreamWaves * kWaveTile;  // mixed_thr of stream_kernel
 static size_t stream_lds_pad(int groups, size_t static_lds) {
   const size_t per = kLdsPerComputeUnit / (size_t)groups - 2048;  // (2 KB of slack for the allocation granule)
   const size_t limit = 64 * 1024;                                  // a workgroup's LDS without a function attribute

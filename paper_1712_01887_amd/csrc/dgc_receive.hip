@@ -235,8 +235,9 @@ __device__ __forceinline__ int locate_pairs(Shared& sh, const RegionPayloads& p,
     int64_t cnt = p.counts[w][blk.tensor];
     if (cnt > cap) cnt = cap;
     if (cnt < 0) cnt = 0;
-    int lo, hi;
-    wave_equal_range<true>(p.idx[w] + region, (int)cnt, blk.begin, blk.end, blk.lo, blk.hi, lane, lo, hi);
+    int lo = 0, hi = (int)cnt;
+    if (blk.begin != blk.lo || blk.end != blk.hi)  // (a range that is a whole tensor has all its pairs)
+      wave_equal_range<true>(p.idx[w] + region, (int)cnt, blk.begin, blk.end, blk.lo, blk.hi, lane, lo, hi);
     if (lane == 0) {
       sh.idx_at[w] = p.idx[w] + region + lo;
       sh.val_at[w] = p.val[w] ? p.val[w] + region + lo : nullptr;
@@ -269,8 +270,9 @@ __device__ __forceinline__ int locate_pairs2(Shared& sh, const RegionPayloads& p
     if (cnt2 < 0) cnt2 = 0;
     const int32_t* __restrict__ list = w < num_payloads ? p.idx[w] + region : safe;
     const int32_t* __restrict__ list2 = w < num_payloads2 ? p2.idx[w] + region : safe;
-    int lo, hi, lo2, hi2;
-    wave_equal_range2(list, (int)cnt, list2, (int)cnt2, safe, blk, lane, lo, hi, lo2, hi2);
+    int lo = 0, hi = (int)cnt, lo2 = 0, hi2 = (int)cnt2;
+    if (blk.begin != blk.lo || blk.end != blk.hi)  // (a range that is a whole tensor has all its pairs)
+      wave_equal_range2(list, (int)cnt, list2, (int)cnt2, safe, blk, lane, lo, hi, lo2, hi2);
     if (lane == 0) {
       if (w < num_payloads) {
         sh.idx_at[w] = list + lo;
@@ -623,13 +625,13 @@ __global__ __launch_bounds__(kFlatThreads) void locate_parts_kernel(RegionPayloa
     last = b + 1 >= num_blocks || blocks[b + 1].tensor != blk.tensor;
     list = p.idx[w] + region;
     x = blk.begin;
-    hi = cnt;
+    hi = x > blk.lo ? cnt : 0;  // (a tensor's first part starts at the region's start)
   }
   // the first round around the place the part starts at if the pairs are spread evenly over the tensor
-  if (__ballot(cnt > 64)) {
+  if (__ballot(hi > 64)) {
     const GuessRound<8> r(Guess(cnt, x, blk.lo, blk.hi > blk.lo ? blk.hi : blk.lo + 1), cnt);
-    const unsigned long long votes = __ballot(cnt > 0 && list[r.at(sub)] < x);
-    if (cnt > 0) r.narrow(__popc((uint32_t)(votes >> (8 * group)) & 0xFFu), lo, hi);
+    const unsigned long long votes = __ballot(hi > 0 && list[r.at(sub)] < x);
+    if (hi > 0) r.narrow(__popc((uint32_t)(votes >> (8 * group)) & 0xFFu), lo, hi);
   }
   // first position whose index is not below x ("index < x" is monotone along a region)
   while (__ballot(hi > lo)) {
