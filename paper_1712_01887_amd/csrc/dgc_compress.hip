@@ -1122,19 +1122,20 @@ __global__ __launch_bounds__(64) void ceiling_kernel(const float* __restrict__ a
 // (the last workgroup of a 4.7 M-element tensor adds up 4600 of them: with one count per load
 // that was three rounds of loads in a row, 6 us of the emit pass on a 122 M-element set).
 template <int THREADS>
-__device__ __forceinline__ int tile_counts_partial(const uint32_t* __restrict__ tc, int64_t b, int64_t e, int tid) {
+__device__ __forceinline__ int tile_counts_partial(const uint32_t* __restrict__ tc, int64_t b64, int64_t e64, int tid) {
+  const int32_t b = (int32_t)b64, e = (int32_t)e64;  // tiles: below 2^21
   int sum = 0;
   if (b >= e) return 0;
-  int64_t b4 = (b + 3) & ~(int64_t)3;  // first multiple of four at or above b
+  int32_t b4 = (b + 3) & ~3;  // first multiple of four at or above b
   if (b4 > e) b4 = e;
-  int64_t e4 = e & ~(int64_t)3;
+  int32_t e4 = e & ~3;
   if (e4 < b4) e4 = b4;
   // at most three counts before the aligned body and three behind it
-  if (tid < (int)(b4 - b)) sum += (int)(tc[b + tid] & kTileCountMask);
-  if (tid < (int)(e - e4)) sum += (int)(tc[e4 + tid] & kTileCountMask);
+  if (tid < b4 - b) sum += (int)(tc[b + tid] & kTileCountMask);
+  if (tid < e - e4) sum += (int)(tc[e4 + tid] & kTileCountMask);
   const uint4* __restrict__ tc4 = reinterpret_cast<const uint4*>(tc);  // the table starts on a 256-byte boundary
-  const int64_t q0 = b4 >> 2, q1 = e4 >> 2;
-  int64_t q = q0 + tid;
+  const int32_t q0 = b4 >> 2, q1 = e4 >> 2;
+  int32_t q = q0 + tid;
   for (; q + 3 * THREADS < q1; q += 4 * THREADS) {  // four loads in flight per thread
     uint4 c[4];
 #pragma unroll

@@ -134,7 +134,16 @@ __global__ __launch_bounds__(kWireThreads) void encode_kernel(EncodeArgs a) {
   uint32_t before_block = 0;
   if (a.self_scan) {  // few block sums: every workgroup adds up those before its own
     uint32_t mine_before = 0;
-    for (uint32_t i = threadIdx.x; i < blockIdx.x; i += kWireThreads) mine_before += a.sums[i];
+    const uint4* __restrict__ four = reinterpret_cast<const uint4*>(a.sums);  // starts on a 256-byte boundary
+    const uint32_t quads = blockIdx.x >> 2;
+    for (uint32_t i = threadIdx.x; i < quads; i += 4 * kWireThreads) {
+      uint4 c[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) c[k] = i + k * kWireThreads < quads ? four[i + k * kWireThreads] : make_uint4(0, 0, 0, 0);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) mine_before += (c[k].x + c[k].y) + (c[k].z + c[k].w);
+    }
+    if (threadIdx.x < (blockIdx.x & 3u)) mine_before += a.sums[4 * quads + threadIdx.x];
     mine_before = wave_sum(mine_before);
     if (lane == 0) wave_before[wave] = mine_before;
     __syncthreads();
@@ -209,11 +218,9 @@ __global__ __launch_bounds__(kScanThreads) void scan_kernel(uint32_t* sums, Scan
       x[k] = i0 + k < end ? sums[i0 + k] : 0u;
       mine += x[k];
     }
-    uint64_t incl = mine;
-    for (int d = 1; d < 64; d <<= 1) {
-      const uint64_t t = __shfl_up(incl, d);
-      if (lane >= d) incl += t;
-    }
+    // (below 2^32 per thread: the two halves are scanned apart, which cannot overflow 32 bits)
+    const uint64_t incl = (uint64_t)wave_inclusive_sum((uint32_t)mine & 0xFFFFu) +
+                          ((uint64_t)wave_inclusive_sum((uint32_t)(mine >> 16)) << 16);
     if (lane == 63) wave_sums[wave] = incl;
     __syncthreads();
     uint64_t before = carry, total = 0;

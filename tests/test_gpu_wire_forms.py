@@ -102,7 +102,7 @@ def test_decode_skips_and_flags_what_lies_behind_the_end(density, flags):
 
 @pytest.mark.parametrize("sizes,density,layout_density", [
     ([4097, 3, 66000, 8192], 0.5, 1.0),        # a few workgroups: block sums added up without a scan
-    ([5, 4600000, 77], 0.02, 1.0),             # more than 1024 of them: a scan launch
+    ([5, 4600000, 77], 0.02, 1.0),             # some thousand of them, most without a pair
     ([900001, 1], 0.00002, 0.0001),            # gaps of more than 65535 zeros in most rounds
 ])
 def test_encode_forms(sizes, density, layout_density):
@@ -121,3 +121,30 @@ def test_encode_forms(sizes, density, layout_density):
     assert np.array_equal(runs.cpu().numpy()[:-4].view(np.uint16), want_runs) and not runs[-4:].any().item()
     assert np.array_equal(vals.cpu().numpy()[:-4], want_vals) and not vals[-4:].any().item()
     p.close()
+
+
+def test_encode_with_more_block_sums_than_a_workgroup_adds_up():
+    """Regions of 70 M pairs between them, nearly empty: 17090 workgroup slots, so a scan launch."""
+    import torch
+    sizes = [69000001, 1000003]
+    offsets = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    dgc = B.Dgc(B.make_config(), offsets)
+    dgc.set_layout(offsets.tolist())
+    rng = np.random.default_rng(1)
+    per = [np.sort(rng.choice(s, k, replace=False)).astype(np.int64) + o for s, k, o in zip(sizes, (9000, 300), offsets)]
+    idx = torch.zeros(int(offsets[-1]), dtype=torch.int32, device="cuda")
+    val = torch.zeros(int(offsets[-1]), device="cuda")
+    x = [rng.standard_normal(p.size).astype(np.float32) for p in per]
+    for o, p, v in zip(offsets, per, x):
+        idx[o:o + p.size] = torch.from_numpy(p.astype(np.int32)).cuda()
+        val[o:o + p.size] = torch.from_numpy(v).cuda()
+    counts = torch.tensor([p.size for p in per], dtype=torch.int32, device="cuda")
+    want_runs, want_vals = O.encode(np.concatenate(per).astype(np.int32), np.concatenate(x))
+    runs = torch.zeros(want_runs.size, dtype=torch.int16, device="cuda")
+    vals = torch.zeros(want_runs.size, device="cuda")
+    num = torch.full((1,), -1, dtype=torch.int32, device="cuda")
+    dgc.dgc_encode(idx, val, counts, runs, vals, num)
+    assert int(num.item()) == want_runs.size
+    assert np.array_equal(runs.cpu().numpy().view(np.uint16), want_runs)
+    assert np.array_equal(vals.cpu().numpy(), want_vals)
+    dgc.close()
