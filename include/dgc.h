@@ -294,8 +294,9 @@ dgc_status dgc_decompress_accumulate(dgc_handle* h, float* dense, int64_t n, int
  * order inside a part is free, the indices of one payload are distinct).  The payloads are
  * merged by element range in on-chip memory, workers added in the order given, without
  * float atomics, which gives the result of the plain definition bit for bit at every
- * density: up to 0.5 %, as long as the payloads together let expect no more than 6144 pairs
- * in 131072 elements (density x payloads x 131072 x 1.25), a workgroup touches only the
+ * density: up to 0.5 % (and above it in sets of up to 256 ranges, unless an aggregate is
+ * replaced), as long as the payloads together let expect no more than 6144 pairs
+ * in the longest range (density x payloads x its elements x 1.25), a workgroup touches only the
  * elements that occur in a range of up to 131072; otherwise (the warm-up densities of
  * Section 4, or many payloads) it keeps one part's whole range of
  * `dense` on chip, after a launch that finds every payload's pairs of every part.  A
@@ -338,7 +339,7 @@ dgc_status dgc_decompress_replace_regions(dgc_handle* h, float* dense, int32_t n
  * dense[idx] = 0 for every pair of the given region-layout payloads: returns a
  * dense aggregate to all-zero after it has been consumed at the cost of the
  * payload size instead of a full fill.  Arguments as above.  Above a density of 0.5 % (or with
- * many payloads, see above) the regions must be as dgc_compress writes them: the indices of a part are
+ * many payloads, see above), if more than 2 M pairs are expected in all, the regions must be as dgc_compress writes them: the indices of a part are
  * marked in a bitmap on chip and every 64-byte sector with a marked element is written
  * once, whole (its other elements are read and written back unchanged).
  */
@@ -403,7 +404,9 @@ dgc_status dgc_encode(dgc_handle* h, const int32_t* idx, const float* val, const
  *   entry_counts_host                host, entries in each payload (the receiver knows
  *                                    the message sizes)
  * Entries that land outside [0, n) are skipped and flagged in *diag_flags_dev (may be
- * NULL).  Ordering and DGC_FLAG_DETERMINISTIC_ACCUMULATE as for dgc_decompress_accumulate.
+ * NULL).  Ordering and DGC_FLAG_DETERMINISTIC_ACCUMULATE as for dgc_decompress_accumulate; where
+ * many entries share a 64-byte sector, the payloads are summed on chip first, in order, and every
+ * element that occurs is added to `dense` once.
  * Errors: INVALID_ARG, ALIGNMENT, CAPACITY (more entries than a set of n elements can
  * need, or too many payloads), HIP.
  */

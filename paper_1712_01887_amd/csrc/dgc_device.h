@@ -46,7 +46,8 @@ struct Guess {
   __device__ __forceinline__ Guess(int m, int32_t x, int32_t from, int32_t to) {
     float f = (float)(x - from) / (float)(to - from);
     f = f < 0.0f ? 0.0f : f > 1.0f ? 1.0f : f;
-    place = (int)(f * (float)m);
+    const float at = f * (float)m;
+    place = at < (float)m ? (int)at : m;
     sigma = (int)sqrtf((float)m * f * (1.0f - f));
   }
 };
@@ -63,8 +64,8 @@ struct GuessRound {
     last = m - 1;
   }
   __device__ __forceinline__ int at(int i) const {
-    const int p = start + i * step;
-    return p < 0 ? 0 : p > last ? last : p;
+    const int64_t p = (int64_t)start + (int64_t)i * step;
+    return p < 0 ? 0 : p > last ? last : (int)p;
   }
   __device__ __forceinline__ void narrow(int below, int& lo, int& hi) const {  // `below` probes are less than x: a prefix
     if (below < PROBES) hi = at(below);

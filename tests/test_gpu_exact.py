@@ -101,3 +101,20 @@ def test_exact_ranks_nans_above_everything_and_sends_none(nans, density):
         assert np.array_equal(per_idx[j], res.indices[j]) and np.array_equal(per_val[j], res.values[j])
     assert np.array_equal(u.cpu().numpy(), ou, equal_nan=True) and np.array_equal(v.cpu().numpy(), ov, equal_nan=True)
     dgc.close()
+
+
+@pytest.mark.parametrize("density", [0.02, 0.3])
+def test_exact_where_the_band_is_crowded(density):
+    """Three tenths of the tensor lie inside the band, where its sample did not look: the list does not fit."""
+    sizes = [64, 200001]
+    offsets = np.concatenate([[0], np.cumsum(sizes)])
+    p = Pair(offsets, momentum=0.0, density=density, seed=12, flags=EXACT)
+    rng = np.random.default_rng(8)
+    g = rng.standard_normal(p.n).astype(np.float32)
+    pos = np.unique(band_sample(sizes[1], 12, 0, 1))
+    unseen = np.setdiff1d(np.arange(sizes[1]), pos)
+    crowd = rng.choice(unseen, 60000, replace=False)
+    mid = np.quantile(np.abs(g[offsets[1] + pos]), 1.0 - density)
+    g[offsets[1] + crowd] = (mid * (1.0 + 1e-6 * rng.integers(-50, 50, crowd.size))).astype(np.float32)
+    p.step(g, 0, label=f"exact, crowded band d={density}")
+    p.close()
