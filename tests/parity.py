@@ -23,6 +23,8 @@ the oracle.
 
 from __future__ import annotations
 
+import contextlib
+import gc
 import sys
 
 import numpy as np
@@ -34,6 +36,25 @@ from paper_1712_01887_amd import binding as B
 def say(msg: str) -> None:
     print(msg, flush=True)
     sys.stdout.flush()
+
+
+@contextlib.contextmanager
+def capture(graph):
+    """`with torch.cuda.graph(graph)`, with nothing collected inside.  An object that nobody uses any more but
+    that hangs in a reference cycle is finalized whenever Python's collector runs next.  If that is an earlier
+    CUDAGraph and a capture is under way, its destructor waits for the device, which a capture forbids; the
+    error leaves the destructor as a C++ exception, and the process is aborted.  (`pytest.raises(...) as err`
+    makes such a cycle: err holds the traceback, that the test's frame, and that err and all the other locals.)"""
+    import torch
+    gc.collect()
+    enabled = gc.isenabled()
+    gc.disable()
+    try:
+        with torch.cuda.graph(graph):
+            yield
+    finally:
+        if enabled:
+            gc.enable()
 
 
 def oracle_config(**kw) -> O.OracleConfig:

@@ -10,7 +10,7 @@ import pytest
 from oracle import dgc_oracle as O
 from paper_1712_01887_amd import binding as B
 from paper_1712_01887_amd import synthetic as S
-from tests.parity import gather_payload, oracle_config, say
+from tests.parity import capture, gather_payload, oracle_config, say
 
 pytestmark = pytest.mark.gpu
 
@@ -40,7 +40,7 @@ def test_captured_step_replays_match_the_oracle(flags, extra, warm):
 
     # a first call inside a capture would have to upload the tables: refused, nothing enqueued
     refused = torch.cuda.CUDAGraph()
-    with torch.cuda.graph(refused):
+    with capture(refused):
         with pytest.raises(B.DgcError) as err:
             dgc.dgc_compress(g_static, u, v, out_idx, out_val, out_counts, out_thr, iteration)
         assert err.value.status == B.DGC_ERR_STATE
@@ -55,7 +55,7 @@ def test_captured_step_replays_match_the_oracle(flags, extra, warm):
     u.zero_(); v.zero_(); dense.zero_()
 
     graph = torch.cuda.CUDAGraph()
-    with torch.cuda.graph(graph):
+    with capture(graph):
         dgc.dgc_compress(g_static, u, v, out_idx, out_val, out_counts, out_thr, iteration)
         dgc.dgc_decompress_accumulate_regions(dense, [out_idx], [out_val], [out_counts])
     u.zero_(); v.zero_(); dense.zero_()                     # capture does not run the kernels; be explicit anyway
