@@ -122,6 +122,9 @@ dgc_status dgc_destroy(dgc_handle* h);
  *     handle to another between calls (never between calls that overlap in time): the library
  *     notices and uploads the new owner's tables again, which costs several host-to-device
  *     copies per change of owner;
+ *   - calls that use one workspace, those of one handle too, must be ordered (one stream, or
+ *     events between streams): compress calls share scratch with each other, and so do the calls
+ *     of the receive side and of the wire format;
  *   - a workspace that was freed, overwritten by the caller, or allocated again at the same
  *     address must be announced with dgc_invalidate_workspace before its next use: the
  *     library cannot see that its tables are gone;
@@ -239,8 +242,10 @@ dgc_status dgc_compress(dgc_handle* h, const float* g, float* u, float* v, int32
  * process uses holds its own copy until the process ends), which serves gradient sets of up
  * to about 30 M elements (the ResNet-50-shaped set needs 6 MiB).  Same arguments, results and
  * errors as dgc_compress otherwise, and
- *   CAPACITY   dgc_workspace_bytes of the handle exceeds the array (dgc_last_error_string says
- *              by how much): use dgc_compress with a workspace of the caller's;
+ *   CAPACITY   the handle's tables and scratch exceed the array (dgc_last_error_string says
+ *              by how much): use dgc_compress with a workspace of the caller's.  The bound is
+ *              dgc_workspace_bytes less the list of exact selection (tensors of more than 32768
+ *              elements): the array serves no receive side, whose scratch the list takes;
  *   HIP        the array's address could not be obtained.
  * The call allocates nothing and frees nothing: it asks the runtime for the array's address the
  * first time it runs on a device and launches the kernels of dgc_compress.  Like dgc_compress, it

@@ -28,8 +28,8 @@ struct dgc_handle {
   std::vector<TensorPlan> plans;     // T
   std::vector<int64_t> k;            // T
   std::vector<int64_t> draws;        // T
-  std::vector<int32_t> first_part;   // T: the tensor's first entry in emit_blocks
   bool any_band = false;             // some tensor's threshold is found by way of a band (TensorPlan.exact == 2)
+  uint32_t most_bands = 0;           // tensors that take a band at some density
   std::vector<uint32_t> tile_info;   // ceil(n / kWaveTile)
   std::vector<float> tile_thr_init;  // ceil(n / kWaveTile): NaN where a tile is not wholly inside one tensor
   std::vector<EmitBlock> emit_blocks;  // work list of the emit pass
@@ -156,6 +156,7 @@ int64_t topk_count(double density, int64_t n) {
 void build_plan(dgc_handle* h) {
   const dgc_config& c = h->cfg;
   const int64_t B = c.sample_block;
+  uint32_t bands = 0;
   h->any_band = false;
   for (int32_t j = 0; j < h->num_tensors; ++j) {
     const int64_t n = h->offsets[j + 1] - h->offsets[j];
@@ -179,10 +180,13 @@ void build_plan(dgc_handle* h) {
       p.rank = (int32_t)k;
       p.nblocks = 0;
       h->draws[j] = 0;
-      if (n > kBandSample && k < n) {  // more than a workgroup of select_kernel holds in registers
-        p.exact = 2;
-        p.nblocks = (uint32_t)h->first_part[j];
-        h->any_band = true;
+      if (n > kBandSample) {  // more than a workgroup of select_kernel holds in registers
+        if (k < n) {
+          p.exact = 2;
+          p.nblocks = bands;
+          h->any_band = true;
+        }
+        ++bands;
       }
     } else {
       const int64_t draws = (s + B - 1) / B;
@@ -196,6 +200,7 @@ void build_plan(dgc_handle* h) {
       h->draws[j] = draws;
     }
   }
+  h->most_bands = bands;
   h->ws_plan_valid = false;
 }
 
@@ -217,7 +222,7 @@ void build_layout(dgc_handle* h) {
   l.merge_blocks = off; off = align_up(off + sizeof(MergeBlock) * h->merge_blocks.size());
   l.part_blocks = off;  off = align_up(off + sizeof(MergeBlock) * h->part_blocks.size());
   // (first pair, pairs) of every payload inside every part, left by the search that precedes the part kernels
-  l.part_found = off;   off = align_up(off + 2 * sizeof(int32_t) * kMaxPayloads * h->part_blocks.size());
+  l.part_found = off;   off = align_up(off + kPartEntries * h->part_blocks.size());
   // wire format: one block sum per kWireChunk pairs of every region (encoder, at most
   // n / kWireChunk + T) or per kWireChunk entries of every payload (decoder, an entry
   // stream of a set of n elements has at most n + (n >> 16) entries)
@@ -229,6 +234,16 @@ void build_layout(dgc_handle* h) {
   l.wire_first_block = off; off = align_up(off + sizeof(uint32_t) * (T + 1));
   l.wire_sums = off;    off = align_up(off + sizeof(uint32_t) * h->wire_slots);
   l.mask = off;         off = align_up(off + sizeof(uint16_t) * 64 * tiles);
+  l.total_without_bands = off;
+  // Exact selection of large tensors: areas of their own, so that a compress call writes no scratch of the
+  // receive side or of the wire format.  In a workspace without them (the static array, which serves
+  // compress calls only) the bands lie in the part table and the lists from the block sums on into the mask words.
+  l.bands = l.part_found;
+  l.band_list = l.wire_sums;
+  if (h->most_bands > 0) {
+    l.bands = off;      off = align_up(off + kBandStride * h->most_bands);
+    l.band_list = off;  off = align_up(off + 3 * sizeof(uint32_t) * (size_t)(h->n >> kBandListShift));
+  }
   l.total = off;
   // optional: staging arrays of the streaming pass at warm-up densities
   l.stage_v = off;      off = align_up(off + sizeof(float) * (size_t)h->n);
@@ -262,7 +277,7 @@ dgc_status sync_workspace(dgc_handle* h, void* ws, size_t ws_bytes, const int64_
                           bool need_plan, hipStream_t stream) {
   if (!ws) return DGC_ERR_INVALID_ARG;
   if (!aligned(ws, kAlign)) return DGC_ERR_ALIGNMENT;
-  if (ws_bytes < h->lay.total) return DGC_ERR_CAPACITY;
+  if (ws_bytes < h->lay.total_without_bands) return DGC_ERR_CAPACITY;
   const size_t T = (size_t)h->num_tensors;
   if (ws != h->ws || !workspace_owned_by(ws, h->id)) {
     h->ws = ws;
@@ -431,7 +446,6 @@ dgc_status dgc_create(dgc_handle** out, const dgc_config* cfg, int32_t num_tenso
       const int32_t nb = (int32_t)((t1 - t0) / kEmitTiles + 1);
       for (int64_t f = t0; f <= t1; f += kEmitTiles)
         h->emit_blocks.push_back(EmitBlock{t, (int32_t)f, nb, 0, h->offsets[t], h->offsets[t + 1]});
-      h->first_part.push_back((int32_t)h->emit_blocks.size() - nb);
     }
     // element ranges of the receive side: kMergeEmitBlocks consecutive emit workgroups' parts of one tensor
     for (size_t b = 0; b < h->emit_blocks.size();) {
@@ -618,8 +632,9 @@ dgc_status dgc_compress(dgc_handle* h, const float* g, float* u, float* v, int32
   int shift = 0;
   while ((1 << shift) < c.sample_block) ++shift;
   sa.block_shift = shift;
-  sa.bands = h->any_band ? at<BandState>(workspace, h->lay.part_found) : nullptr;
-  sa.band_list = at<uint32_t>(workspace, h->lay.wire_sums);
+  const bool band_areas = workspace_bytes >= h->lay.total;
+  sa.bands = h->any_band ? at<BandState>(workspace, band_areas ? h->lay.bands : h->lay.part_found) : nullptr;
+  sa.band_list = at<uint32_t>(workspace, band_areas ? h->lay.band_list : h->lay.wire_sums);
   sa.seed_lo = (uint32_t)(c.seed & 0xFFFFFFFFu);
   sa.seed_hi = (uint32_t)(c.seed >> 32);
   sa.iter_lo = (uint32_t)(iteration & 0xFFFFFFFFu);
@@ -717,10 +732,10 @@ dgc_status dgc_compress_static(dgc_handle* h, const float* g, float* u, float* v
                                float* out_val, const int64_t* out_offsets_host, int32_t* out_counts,
                                float* out_thr, uint64_t iteration, void* stream) {
   if (!h) return DGC_ERR_INVALID_ARG;
-  if (h->lay.total > kStaticScratchBytes) {
+  if (h->lay.total_without_bands > kStaticScratchBytes) {
     std::snprintf(g_last_error, sizeof(g_last_error),
                   "dgc_compress_static: this gradient set needs a workspace of %zu bytes, the static array has %zu",
-                  h->lay.total, kStaticScratchBytes);
+                  h->lay.total_without_bands, kStaticScratchBytes);
     return DGC_ERR_CAPACITY;
   }
   void* ws = nullptr;

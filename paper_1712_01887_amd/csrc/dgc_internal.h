@@ -124,8 +124,7 @@ constexpr int kSelectInFlight = 8;    // candidates each thread gathers before u
 // the workgroup's registers hold: select_kernel draws kBandSample elements (blocks of 1 << kBandBlockShift)
 // and names a band of keys that holds the wanted rank almost surely, collect_band_kernel reads the
 // tensor once, spread over the chip, and lists the keys inside the band, rank_band_kernel ranks them.
-// The list of a tensor takes three words per 64 elements of the block-sum and mask areas, which are
-// free until the streaming pass.  On the 161-tensor set of 25.6 M elements the three kernels take
+// The list of a tensor takes three words per 64 elements of an area of its own.  On the 161-tensor set of 25.6 M elements the three kernels take
 // 22 + 55 + 12 us at 0.1 % (the reads, 12 bytes per element, at 5.6 TB/s) and no more than 40 us more at
 // 25 %; three workgroup-wide passes over a whole tensor, which are still the way out when a band misses,
 // took 1385 us.
@@ -135,8 +134,8 @@ constexpr int kBandListShift = 6;       // three list words per 64 elements
 constexpr int kBandThreads = 256;
 constexpr int kBandElements = 8192;     // elements per workgroup of the collecting pass
 constexpr int kBandsPerPart = kEmitElements / kBandElements;
-struct BandState {  // one per tensor, at the place of its first part in the part table: a line of its own,
-                    // because atomics on one line are carried out one after the other (9 ns each)
+struct BandState {  // one per tensor, in a line of its own, because atomics on one line are carried out one
+                    // after the other (9 ns each)
   uint32_t floor_key, ceil_key;  // the band: floor_key < key < ceil_key
   uint32_t above, ties, listed;  // keys at or above ceil_key, keys equal to floor_key, keys inside the band
 };
@@ -146,7 +145,9 @@ constexpr int kNormThreads = 256;
 constexpr int kNormMaxBlocks = 512;
 
 constexpr int kMaxPayloads = 64;
-constexpr size_t kBandStride = 2 * sizeof(int32_t) * kMaxPayloads;  // a part's entries in the part table
+constexpr size_t kBandStride = 128;
+constexpr size_t kPartEntries = 2 * sizeof(int32_t) * kMaxPayloads;  // bytes of a part's entries in the part table
+static_assert(sizeof(BandState) <= kBandStride && kBandStride <= kPartEntries, "a tensor with a band has a part at least");
 static_assert(kMaxPayloads <= 32768, "a payload's number is packed above a 16-bit index");
 
 // ---- device-resident state (start of the workspace) ------------------------
@@ -163,7 +164,7 @@ struct TensorPlan {
   int64_t n;        // elements
   int32_t count;    // candidates: n (whole tensor) or draws * block
   int32_t rank;     // 0-based descending rank that becomes the threshold
-  uint32_t nblocks; // aligned sample blocks in the tensor (sampled mode); by way of a band: the tensor's first part
+  uint32_t nblocks; // aligned sample blocks in the tensor (sampled mode); by way of a band: its number among such tensors
   int32_t exact;    // 0: sampled; 1: candidates are elements 0..n-1; 2: the same, by way of a band
   int32_t k;             // clamp(ceil(d n), 1, n)
   int32_t refine_limit;  // floor(refine_alpha * k): more passes than this trigger the re-threshold
@@ -171,7 +172,9 @@ struct TensorPlan {
 
 struct WorkspaceLayout {
   size_t state, partials, offsets, out_offsets, plans, thr, tile_info, tile_thr, emit_blocks,
-      tile_count, merge_blocks, part_blocks, part_found, wire_first_block, wire_sums, mask, total,
+      tile_count, merge_blocks, part_blocks, part_found, wire_first_block, wire_sums, mask,
+      total_without_bands,             // what a workspace holds at least
+      bands, band_list, total,
       stage_v, stage_u, total_staged;  // staging arrays lie behind `total`: a workspace may end before them
 };
 
@@ -194,7 +197,7 @@ struct SelectArgs {
   int32_t scale_from_state;  // 1: clipping is on; the scale comes from `partials` and is filed in `state`
   int32_t nesterov;
   int32_t block_shift;  // log2(sample_block)
-  BandState* bands;     // device, one slot of kBandStride bytes per part; null: no tensor has a band
+  BandState* bands;     // device, a slot of kBandStride bytes per tensor that has a band; null: none has
   uint32_t* band_list;  // device, see band_list_begin
   uint32_t seed_lo, seed_hi, iter_lo, iter_hi;
 };

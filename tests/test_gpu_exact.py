@@ -118,3 +118,64 @@ def test_exact_where_the_band_is_crowded(density):
     g[offsets[1] + crowd] = (mid * (1.0 + 1e-6 * rng.integers(-50, 50, crowd.size))).astype(np.float32)
     p.step(g, 0, label=f"exact, crowded band d={density}")
     p.close()
+
+
+def test_exact_compress_leaves_the_scratch_of_the_receive_side_alone():
+    """Which bytes of the workspace the part kernels, the encoder and the decoder use is seen from what they
+    change; a compress call afterwards must not change them."""
+    import torch
+    offsets = np.concatenate([[0], np.cumsum([64, 200001, 40000, 70000])])
+    n = int(offsets[-1])
+    dgc = B.Dgc(B.make_config(momentum=0.9, density=0.02, seed=3, flags=EXACT | B.DGC_FLAG_SORTED_OUTPUT), offsets)
+    layout = dgc.dgc_recommended_payload_layout(0.02)
+    dgc.set_layout(layout)
+    dgc.ensure_workspace("cuda").fill_(0x5A)
+    u, v, dense = (torch.zeros(n, device="cuda") for _ in range(3))
+    out = dgc.alloc_payload("cuda")
+    grads = [torch.from_numpy((1e-2 * np.random.default_rng(it).standard_t(3, n)).astype(np.float32)).cuda() for it in range(2)]
+    dgc.dgc_compress(grads[0], u, v, *out, 0)
+    capacity = dgc.dgc_encode_max_entries(layout[-1])
+    runs, vals = torch.zeros(capacity, dtype=torch.int16, device="cuda"), torch.zeros(capacity, device="cuda")
+    entries = torch.zeros(1, dtype=torch.int32, device="cuda")
+
+    def changes(call):
+        before = dgc.workspace.clone()
+        call()
+        return before != dgc.workspace
+
+    payload = ([out[0]] * 3, [out[1]] * 3, [out[2]] * 3)
+    parts = changes(lambda: dgc.dgc_decompress_replace_regions(dense, *payload))
+    wire = changes(lambda: dgc.dgc_encode(out[0], out[1], out[2], runs, vals, entries))
+    wire |= changes(lambda: dgc.dgc_decode_accumulate(dense, [runs] * 3, [vals] * 3, [int(entries)] * 3))
+    assert int(parts.sum()) > 0 and int(wire.sum()) > 0
+    changed = changes(lambda: dgc.dgc_compress(grads[1], u, v, *out, 1))
+    assert int(changed.sum()) > 0
+    assert int((changed & parts).sum()) == 0 and int((changed & wire).sum()) == 0
+    dgc.close()
+
+
+def test_exact_selection_in_a_workspace_without_the_list():
+    """The static array holds the band lists in the place of the receive side's scratch."""
+    import torch
+    offsets = np.concatenate([[0], np.cumsum(SIZES)])
+    n = int(offsets[-1])
+    kw = dict(momentum=0.9, density=0.02, seed=3)
+    rng = np.random.default_rng(23)
+    sides = []
+    for _ in range(2):
+        dgc = B.Dgc(B.make_config(flags=EXACT, **kw), offsets)
+        dgc.set_layout(dgc.dgc_recommended_payload_layout(0.02))
+        sides.append((dgc, torch.zeros(n, device="cuda"), torch.zeros(n, device="cuda"), dgc.alloc_payload("cuda")))
+    sampled = B.Dgc(B.make_config(**kw), offsets)
+    # what a set without exact selection needs, a slot per tensor above 32768 elements, three words per 64 elements
+    extra = sides[0][0].dgc_workspace_bytes() - sampled.dgc_workspace_bytes()
+    assert 4 * 128 + 12 * (n // 64) <= extra <= 4 * 128 + 12 * (n // 64) + 512
+    for it in range(3):
+        g = torch.from_numpy((1e-2 * rng.standard_t(3, n)).astype(np.float32)).cuda()
+        sides[0][0].dgc_compress(g, *sides[0][1:3], *sides[0][3], it)
+        sides[1][0].dgc_compress_static(g, *sides[1][1:3], *sides[1][3], it)
+        for a, b in zip(sides[0][1:3], sides[1][1:3]):
+            assert torch.equal(a, b), it
+        assert torch.equal(sides[0][3][2], sides[1][3][2]) and torch.equal(sides[0][3][3], sides[1][3][3]), it
+    for dgc in (sides[0][0], sides[1][0], sampled):
+        dgc.close()
