@@ -411,7 +411,7 @@ dgc_status dgc_encode(dgc_handle* h, const int32_t* idx, const float* val, const
  * Entries that land outside [0, n) are skipped and flagged in *diag_flags_dev (may be
  * NULL).  Ordering and DGC_FLAG_DETERMINISTIC_ACCUMULATE as for dgc_decompress_accumulate; where
  * many entries share a 64-byte sector, the payloads are summed on chip first, in order, and every
- * element that occurs is added to `dense` once.
+ * element that occurs is added to `dense` once.  Elements that no entry names are never written, in any form.
  * Errors: INVALID_ARG, ALIGNMENT, CAPACITY (more entries than a set of n elements can
  * need, or too many payloads), HIP.
  */

@@ -370,18 +370,20 @@ __global__ __launch_bounds__(kWireThreads) void decode_direct_kernel(DecodeArgs 
 // wavefronts take these blocks in turn, kDecodeTasks each at a time so that their loads are one wait, and
 // add the entries inside the range in LDS, payload after payload with a barrier between them (positions of
 // one payload are distinct).
-// PLAIN: the accumulator starts from `dense` and is written back: the ordered sum, bit for bit.  Otherwise
-// it starts from nothing (-0, which an element that no entry names still is at the end) and every
-// element that occurs is added to `dense` by one atomic: callers may add to one vector from several
-// streams at a time.  The atomics are what that form costs: 64 neighbouring elements go as four 64-byte
+// PLAIN: the accumulator starts from `dense`, and the elements that have changed are stored: the ordered
+// sum, bit for bit.  Otherwise it starts from nothing (-0, which an element that no entry names still is at
+// the end) and every element that occurs is added to `dense` by one atomic: callers may add to one vector
+// from several streams at a time.  In neither form is an element stored that no entry names: it may be
+// another stream's to update.  (Whole ranges, stored as whole sectors: 132 instead of 152 us for 66 M
+// elements, 6.25 % of four workers, 182 instead of 192 at 25 % of two; 25.6 M, 0.1 % of sixteen: 78 and 77.)
+// The atomics are what that form costs: 64 neighbouring elements go as four 64-byte
 // requests, 20 G of which complete per second, 195 us for 66 M elements whose every sector is
 // touched where plain stores take 75.
 // MULTI: a block is several kDecodeBlocks (streams so long that the block sums did not fit otherwise).
 template <bool PLAIN, bool MULTI>
 __global__ __launch_bounds__(kDecodeThreads) void decode_range_kernel(DecodeArgs a) {
-  typedef float vec4u __attribute__((ext_vector_type(4), aligned(4)));  // `dense` is aligned to 4 bytes
   constexpr int kWaves = kDecodeThreads / 64;
-  constexpr int kQuads = kDecodeRange / 4 / kDecodeThreads;
+  constexpr int kEach = kDecodeRange / kDecodeThreads;
   constexpr int kBatch = kWaves * kDecodeTasks;
   __shared__ alignas(16) float acc[kDecodeRange];
   __shared__ int32_t first_block[kMaxPayloads];
@@ -393,19 +395,11 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_range_kernel(DecodeArgs
   const int32_t length = a.n - begin < kDecodeRange ? (int32_t)(a.n - begin) : kDecodeRange;
   float* __restrict__ range = a.dense + begin;
 
-  vec4u d[kQuads];
+  float d[kEach];  // what the accumulator starts from
 #pragma unroll
-  for (int i = 0; i < kQuads; ++i) {
-    const int e = 4 * (tid + i * kDecodeThreads);
-    d[i] = vec4u{-0.0f, -0.0f, -0.0f, -0.0f};
-    if (PLAIN) {
-      if (e + 4 <= length) {
-        d[i] = *reinterpret_cast<const vec4u*>(range + e);
-      } else {
-        for (int c = 0; c < 4; ++c)
-          if (e + c < length) d[i][c] = range[e + c];
-      }
-    }
+  for (int i = 0; i < kEach; ++i) {
+    const int e = tid + i * kDecodeThreads;
+    d[i] = PLAIN && e < length ? range[e] : -0.0f;
   }
   for (int w = wave; w < a.num; w += kWaves) {
     const int32_t slot0 = a.seg.begin[w];
@@ -419,7 +413,7 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_range_kernel(DecodeArgs
     }
   }
 #pragma unroll
-  for (int i = 0; i < kQuads; ++i) *reinterpret_cast<float4*>(&acc[4 * (tid + i * kDecodeThreads)]) = make_float4(d[i][0], d[i][1], d[i][2], d[i][3]);
+  for (int i = 0; i < kEach; ++i) acc[tid + i * kDecodeThreads] = d[i];
   __syncthreads();
 
   // adds a block whose first entry's predecessors cover `pos` positions; returns what the block covers
@@ -501,25 +495,15 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_range_kernel(DecodeArgs
     }
   }
 
+  int own = tid;
+  asm volatile("" : "+v"(own));  // (addresses and bounds formed anew: kept from the loads on, they cost a workgroup per compute unit)
 #pragma unroll
-  for (int i = 0; i < kQuads; ++i) {
-    if (PLAIN) {
-      const int e = 4 * (tid + i * kDecodeThreads);
-      const float4 s = *reinterpret_cast<const float4*>(&acc[e]);
-      if (e + 4 <= length) {
-        *reinterpret_cast<vec4u*>(range + e) = vec4u{s.x, s.y, s.z, s.w};
-      } else {
-        const float sc[4] = {s.x, s.y, s.z, s.w};
-        for (int c = 0; c < 4; ++c)
-          if (e + c < length) range[e + c] = sc[c];
-      }
-    } else {
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const int e = tid + (4 * i + c) * kDecodeThreads;
-        const float s = acc[e];
-        if (e < length && __float_as_uint(s) != 0x80000000u) unsafeAtomicAdd(range + e, s);
-      }
+  for (int i = 0; i < kEach; ++i) {
+    const int e = own + i * kDecodeThreads;
+    const float s = acc[e];
+    if (e < length && __float_as_uint(s) != __float_as_uint(d[i])) {
+      if (PLAIN) range[e] = s;
+      else unsafeAtomicAdd(range + e, s);
     }
   }
 }

@@ -148,3 +148,38 @@ def test_encode_with_more_block_sums_than_a_workgroup_adds_up():
     assert np.array_equal(runs.cpu().numpy().view(np.uint16), want_runs)
     assert np.array_equal(vals.cpu().numpy(), want_vals)
     dgc.close()
+
+
+@pytest.mark.parametrize("flags", [0, DET])
+@pytest.mark.parametrize("n,payloads", [(1 << 21, 6), ((1 << 22) + 77, 3)])   # by range in both orders
+def test_decoding_leaves_unnamed_elements_to_others(n, payloads, flags):
+    """Entries name elements of every other block of 64 only; those of the blocks between are counted up on
+    another stream meanwhile.  All values are small whole numbers: no order of additions changes a sum."""
+    import torch
+    rng = np.random.default_rng(n)
+    mine = (np.arange(n) // 64) % 2 == 0
+    dgc = B.Dgc(B.make_config(flags=flags), [0, n])
+    runs, vals, counts = [], [], []
+    expect = np.zeros(n, np.float32)
+    for w in range(payloads):
+        idx = np.flatnonzero(mine & (rng.random(n) < 0.3))
+        runs.append(torch.from_numpy((np.diff(idx, prepend=-1) - 1).astype(np.int16)).cuda())
+        vals.append(torch.full((idx.size,), float(w + 1), device="cuda"))
+        counts.append(idx.size)
+        expect[idx] += w + 1
+    dense = torch.zeros(n, device="cuda")
+    others = dense[: n // 128 * 128].view(-1, 2, 64)[:, 1]
+    rounds = 60
+    dgc.dgc_decode_accumulate(torch.zeros(n, device="cuda"), runs, vals, counts)   # uploads the tables
+    torch.cuda.synchronize()
+    here, there = torch.cuda.Stream(), torch.cuda.Stream()
+    for _ in range(rounds):
+        with torch.cuda.stream(here):
+            dgc.dgc_decode_accumulate(dense, runs, vals, counts)
+        with torch.cuda.stream(there):
+            others.add_(1.0)
+    torch.cuda.synchronize()
+    expect *= rounds
+    expect[: n // 128 * 128].reshape(-1, 2, 64)[:, 1] += rounds
+    assert np.array_equal(dense.cpu().numpy(), expect)
+    dgc.close()
