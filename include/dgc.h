@@ -299,10 +299,10 @@ dgc_status dgc_decompress_accumulate(dgc_handle* h, float* dense, int64_t n, int
  * order inside a part is free, the indices of one payload are distinct).  The payloads are
  * merged by element range in on-chip memory, workers added in the order given, without
  * float atomics, which gives the result of the plain definition bit for bit at every
- * density: up to 0.5 % (and above it in sets of up to 256 ranges, unless an aggregate is
- * replaced), as long as the payloads together let expect no more than 6144 pairs
- * in the longest range (density x payloads x its elements x 1.25), a workgroup touches only the
- * elements that occur in a range of up to 131072; otherwise (the warm-up densities of
+ * density: up to 0.5 %, as long as the payloads together let expect no more than 6144 pairs
+ * in the longest range (density x payloads x its elements x 1.25), and above it, unless an aggregate
+ * is replaced, in sets of up to 256 ranges that let expect no more than 6144 in the longest
+ * tensor, a workgroup touches only the elements that occur in a range of up to 131072; otherwise (the warm-up densities of
  * Section 4, or many payloads) it keeps one part's whole range of
  * `dense` on chip, after a launch that finds every payload's pairs of every part.  A
  * region laid out otherwise gives wrong sums (never an access out of bounds); for

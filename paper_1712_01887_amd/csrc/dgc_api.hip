@@ -35,6 +35,7 @@ struct dgc_handle {
   std::vector<EmitBlock> emit_blocks;  // work list of the emit pass
   std::vector<MergeBlock> merge_blocks;  // work list of the receive side: ranges of several emit parts
   int64_t longest_range = 0;             // elements of the longest of them
+  int64_t longest_tensor = 0;
   std::vector<MergeBlock> part_blocks;   // the same with one emit part per range (warm-up densities)
   bool layout_may_overflow = true;       // some region of the registered layout is smaller than its tensor
   int64_t last_replace_expected = 0;     // pairs per range the payloads of the last dgc_decompress_replace_regions call let expect
@@ -104,11 +105,14 @@ std::mutex g_scratch_mutex;
 
 constexpr size_t kAlign = 256;
 constexpr double kMergeMaxDensity = 0.005;   // receive side: merge by element range in LDS up to here
-// ... and above it, unless the aggregate is replaced, where the set is small enough for all its ranges to be
-// merged at once, a compute unit each: what counts there is the number of launches (23 tensors of 0.27 M
-// elements, 1 %, four workers: 12.3 us in one launch against 3.6 + 10.1; 16 M elements, 0.8 %, three
-// workers: 113 against 128 for the whole pass).  Replacing, the part kernels write every range once and need
-// no previous indices: 37 against 39 us for the pass on the 23 tensors.
+// ... and above it, unless the aggregate is replaced, where all ranges of the set are merged at once, a
+// compute unit each, and no tensor lets expect more pairs than the range kernel's accumulator holds: what
+// counts there is the number of launches (23 tensors of 0.27 M elements, 1 %, four workers: 12.3 us in one
+// launch against 3.6 + 10.1; replacing, the part kernels write every range once and need no previous
+// indices: 37 against 39 us for the pass).  The whole tensor is what counts, not the range: what a tensor
+// sends may all lie in one range (a few rows of an embedding), and a range that does not fit the accumulator
+// is two orders of magnitude slower (30 M elements, 0.8 %, four workers, pairs in a fiftieth of the tensor:
+// 5700 us by ranges, 45 by parts; 1 M elements, pairs in an eighth: 146 and 14).
 constexpr size_t kMergeFewRanges = 256;
 // Sparse clear by scattered stores (80 G/s) up to this many pairs in all; the part kernels take 18 us however
 // few there are (23 tensors as above: 7.6 against 3.6 + 14.6 us), and as long as the stores at about this
@@ -444,6 +448,7 @@ dgc_status dgc_create(dgc_handle** out, const dgc_config* cfg, int32_t num_tenso
       const int64_t t0 = h->offsets[t] / kWaveTile;
       const int64_t t1 = (h->offsets[t + 1] - 1) / kWaveTile;
       const int32_t nb = (int32_t)((t1 - t0) / kEmitTiles + 1);
+      if (h->offsets[t + 1] - h->offsets[t] > h->longest_tensor) h->longest_tensor = h->offsets[t + 1] - h->offsets[t];
       for (int64_t f = t0; f <= t1; f += kEmitTiles)
         h->emit_blocks.push_back(EmitBlock{t, (int32_t)f, nb, 0, h->offsets[t], h->offsets[t + 1]});
     }
@@ -935,16 +940,19 @@ static dgc_status scatter_regions(dgc_handle* h, float* dense, int32_t num_paylo
   // workgroup merges the pairs of a range of up to 128 Ki elements in LDS and touches only
   // the elements that occur; at warm-up densities a workgroup keeps one emit part's whole
   // range of `dense` in LDS.
-  // Pairs the longest range can expect (kMergeMaxRange elements, or the largest tensor if that is smaller; the sampled threshold lets through up to a
-  // quarter more than the density on the inputs seen so far): the range kernel wants them, and the
-  // previous payloads' indices when it replaces, in its registers and accumulator, and takes a much
-  // slower way when they do not fit.  (Replacing an aggregate whose index lists are that long:
-  // writing the whole of `dense` once, which needs none of them, is the cheaper way.)
-  const int64_t expected_new = (int64_t)std::ceil(1.25 * h->cfg.density * (double)h->longest_range * (double)num_payloads);
+  // Pairs the longest range can expect (kMergeMaxRange elements, or the largest tensor if that is smaller;
+  // the sampled threshold lets through up to a quarter more than the density on the inputs seen so far): the
+  // range kernel wants them, and the previous payloads' indices when it replaces, in its registers and
+  // accumulator, and takes a much slower way when they do not fit.  (Replacing an aggregate whose index
+  // lists are that long: writing the whole of `dense` once, which needs none of them, is the cheaper way.)
+  const auto expected_in = [&](int64_t elements) {
+    return (int64_t)std::ceil(1.25 * h->cfg.density * (double)elements * (double)num_payloads);
+  };
+  const bool sparse = h->cfg.density <= kMergeMaxDensity;
+  const int64_t expected_new = expected_in(sparse ? h->longest_range : h->longest_tensor);
   const int64_t expected_old = (replace && num_old > 0) ? h->last_replace_expected : 0;
   const int64_t expected_pairs = expected_new > expected_old ? expected_new : expected_old;
-  const bool fits = (h->cfg.density <= kMergeMaxDensity || (!replace && h->merge_blocks.size() <= kMergeFewRanges)) &&
-                    expected_new <= kMergeCapLarge;
+  const bool fits = (sparse || (!replace && h->merge_blocks.size() <= kMergeFewRanges)) && expected_new <= kMergeCapLarge;
   const bool few = fits && expected_old <= kMergeCapLarge;
   if (replace) h->last_replace_expected = fits ? expected_new : (int64_t)kMergeCapLarge + 1;
   const MergeBlock* parts = at<MergeBlock>(workspace, h->lay.part_blocks);

@@ -1,0 +1,87 @@
+"""Receive side with payloads whose pairs crowd a small part of a tensor (a few rows of an embedding), on both
+sides of the rule that picks a kernel above 0.5 %: the worker-ordered sum bit for bit, and no call an order of
+magnitude slower for the crowding.  Run with `-m gpu` on an MI355X."""
+
+import numpy as np
+import pytest
+
+from paper_1712_01887_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+
+def payloads_in(dgc, layout, sizes, density, workers, part, rng):
+    """Pairs of every worker: the share `density` of each tensor, all of them inside the share `part` of it."""
+    import torch
+    offsets = np.concatenate([[0], np.cumsum(sizes)])
+    host, dev = [], []
+    for _ in range(workers):
+        idx, val = np.zeros(layout[-1], np.int32), np.zeros(layout[-1], np.float32)
+        counts = np.zeros(len(sizes), np.int32)
+        lists = []
+        for j, size in enumerate(sizes):
+            k = int(np.ceil(density * size))
+            width = min(size, max(k, int(part * size)))
+            pos = np.sort(rng.choice(width, k, replace=False)) + (size - width) // 3 + offsets[j]
+            x = rng.standard_normal(k).astype(np.float32)
+            idx[layout[j]:layout[j] + k], val[layout[j]:layout[j] + k], counts[j] = pos, x, k
+            lists.append((pos, x))
+        host.append((np.concatenate([p for p, _ in lists]), np.concatenate([x for _, x in lists])))
+        dev.append(tuple(torch.from_numpy(t).cuda() for t in (idx, val, counts)))
+    return host, tuple([d[i] for d in dev] for i in range(3))
+
+
+def time_of(call):
+    """Median milliseconds of a call among others."""
+    import torch
+    call()
+    times = []
+    for _ in range(5):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(10):
+            call()
+        b.record()
+        b.synchronize()
+        times.append(a.elapsed_time(b) / 10)
+    return float(np.median(times))
+
+
+@pytest.mark.parametrize("sizes,density,workers,part", [
+    ([1 << 20], 0.008, 4, 0.125),                  # eight ranges that let expect 5243 pairs each
+    ([1 << 21, 65536, 300000], 0.0156, 2, 0.07),
+    ([12000000], 0.008, 4, 0.02),
+    ([60000, 300, 9000, 60000], 0.02, 4, 0.1),     # no tensor sends more than the accumulator holds
+    ([130000, 40000], 0.0094, 4, 0.03),            # ... at its limit
+])
+def test_crowded_pairs_above_half_a_percent(sizes, density, workers, part):
+    import torch
+    offsets = np.concatenate([[0], np.cumsum(sizes)])
+    n = int(offsets[-1])
+    dgc = B.Dgc(B.make_config(density=density), offsets)
+    layout = dgc.dgc_recommended_payload_layout(density)
+    dgc.set_layout(layout)
+    rng = np.random.default_rng(n)
+    start = rng.standard_normal(n).astype(np.float32)
+    times = {}
+    for share in (1.0, part):
+        host, dev = payloads_in(dgc, layout, sizes, density, workers, share, rng)
+        dense, theta = torch.from_numpy(start).cuda(), torch.from_numpy(start).cuda()
+        dgc.dgc_decompress_accumulate_regions(dense, *dev)
+        dgc.dgc_sparse_sgd_apply_regions(theta, 0.25, *dev)
+        expect, stepped = start.copy(), start.copy()
+        for idx, x in host:
+            expect[idx] = expect[idx] + x
+            stepped[idx] = stepped[idx] + np.float32(-0.25) * x
+        assert np.array_equal(dense.cpu().numpy().view(np.uint32), expect.view(np.uint32)), share
+        assert np.array_equal(theta.cpu().numpy().view(np.uint32), stepped.view(np.uint32)), share
+        dgc.dgc_dense_clear_regions(dense, dev[0], dev[2])
+        expect[np.concatenate([i for i, _ in host])] = 0.0
+        assert np.array_equal(dense.cpu().numpy().view(np.uint32), expect.view(np.uint32)), share
+        times[share] = (time_of(lambda: dgc.dgc_decompress_accumulate_regions(dense, *dev)),
+                        time_of(lambda: dgc.dgc_sparse_sgd_apply_regions(theta, 0.25, *dev)))
+    print("[crowded] ms, spread and crowded:", times, flush=True)
+    # spread 12 to 50 us on an idle card; a range that outgrows the accumulator takes 130 us to 5.7 ms
+    for spread, crowded in zip(times[1.0], times[part]):
+        assert crowded < 5.0 * spread + 0.02, times
+    dgc.close()
