@@ -38,58 +38,15 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t x) {
   return wave_last(x);
 }
 
-// Where to look first for x in an ascending list of m values that lie in [from, to): the place it has if they
-// are spread evenly, and the standard deviation of that place if they are spread at random.  Only the number
-// of probes depends on it.
-struct Guess {
-  int place, sigma;
-  __device__ __forceinline__ Guess(int m, int32_t x, int32_t from, int32_t to) {
-    float f = (float)(x - from) / (float)(to - from);
-    f = f < 0.0f ? 0.0f : f > 1.0f ? 1.0f : f;
-    const float at = f * (float)m;
-    place = at < (float)m ? (int)at : m;
-    sigma = (int)sqrtf((float)m * f * (1.0f - f));
-  }
-};
-
-// One round of PROBES probes around a guess, by as many neighbouring lanes (this one is number `sub`, the
-// group's votes start at bit `shift` of a ballot): the probe of this lane, and after the vote the bracket
-// [lo, hi] that the answer lies in.  The probes cover four standard deviations to either side.
-template <int PROBES>
-struct GuessRound {
-  int start, step, last;  // probe i is at clamp(start + i * step, 0, last)
-  __device__ __forceinline__ GuessRound(const Guess& g, int m) {
-    step = g.sigma / (PROBES / 8) + 1;
-    start = g.place - PROBES / 2 * step;
-    last = m - 1;
-  }
-  __device__ __forceinline__ int at(int i) const {
-    const int64_t p = (int64_t)start + (int64_t)i * step;
-    return p < 0 ? 0 : p > last ? last : (int)p;
-  }
-  __device__ __forceinline__ void narrow(int below, int& lo, int& hi) const {  // `below` probes are less than x: a prefix
-    if (below < PROBES) hi = at(below);
-    if (below > 0) lo = at(below - 1) + 1;
-    if (lo > hi) lo = hi;
-  }
-};
-constexpr int kGuessFrom = 1024;  // shorter lists take two rounds of 32 probes anyhow
-
 // Positions [lo, hi) of the list L[0, m) whose values lie in [xa, xb), for a list in which
 // "value < xa" and "value < xb" are monotone; every lane of the wavefront takes part and
-// gets the same answer.  GUESS: the values lie in [from, to), about evenly.
-template <bool GUESS>
+// gets the same answer.
 __device__ __forceinline__ void wave_equal_range(const int32_t* __restrict__ L, int m, int32_t xa, int32_t xb,
-                                                 int32_t from, int32_t to, int lane, int& out_lo, int& out_hi) {
+                                                 int lane, int& out_lo, int& out_hi) {
   const int half = lane >> 5;  // 0: lower bound of xa, 1: lower bound of xb
   const int sub = lane & 31;
   const int32_t x = half ? xb : xa;
   int lo = 0, hi = m;  // the answer of this lane's half lies in [lo, hi]
-  if (GUESS && m > kGuessFrom) {
-    const GuessRound<32> r(Guess(m, x, from, to), m);
-    const unsigned long long votes = __ballot(L[r.at(sub)] < x);
-    r.narrow(__popc((uint32_t)(votes >> (32 * half))), lo, hi);
-  }
   while (__ballot(hi > lo)) {
     const int span = hi - lo;
     const int step = (span + 31) >> 5;

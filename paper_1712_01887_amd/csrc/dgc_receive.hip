@@ -162,23 +162,14 @@ __global__ __launch_bounds__(kFlatThreads) void scatter_regions_kernel(float* de
 // wave_equal_range for two lists at once, with the probes of both in flight together (`safe` is any
 // readable word: it is read in place of a probe that has nothing left to ask).
 __device__ __forceinline__ void wave_equal_range2(const int32_t* __restrict__ L0, int m0, const int32_t* __restrict__ L1,
-                                                  int m1, const int32_t* __restrict__ safe, const MergeBlock& blk,
+                                                  int m1, const int32_t* __restrict__ safe, int32_t xa, int32_t xb,
                                                   int lane, int& lo_0, int& hi_0, int& lo_1, int& hi_1) {
   const int half = lane >> 5;
   const int sub = lane & 31;
-  const int32_t x = half ? blk.end : blk.begin;
+  const int32_t x = half ? xb : xa;
   const int32_t* __restrict__ A = m0 > 0 ? L0 : safe;
   const int32_t* __restrict__ B = m1 > 0 ? L1 : safe;
   int lo0 = 0, hi0 = m0, lo1 = 0, hi1 = m1;
-  if (m0 > kGuessFrom || m1 > kGuessFrom) {
-    const GuessRound<32> r0(Guess(m0, x, blk.lo, blk.hi), m0), r1(Guess(m1, x, blk.lo, blk.hi), m1);
-    const int32_t v0 = A[m0 > 0 ? r0.at(sub) : 0];
-    const int32_t v1 = B[m1 > 0 ? r1.at(sub) : 0];
-    const unsigned long long votes0 = __ballot(v0 < x);
-    const unsigned long long votes1 = __ballot(v1 < x);
-    if (m0 > 0) r0.narrow(__popc((uint32_t)(votes0 >> (32 * half))), lo0, hi0);
-    if (m1 > 0) r1.narrow(__popc((uint32_t)(votes1 >> (32 * half))), lo1, hi1);
-  }
   while (__ballot(hi0 > lo0 || hi1 > lo1)) {
     const int span0 = hi0 - lo0, span1 = hi1 - lo1;
     const int step0 = (span0 + 31) >> 5, step1 = (span1 + 31) >> 5;
@@ -237,7 +228,7 @@ __device__ __forceinline__ int locate_pairs(Shared& sh, const RegionPayloads& p,
     if (cnt < 0) cnt = 0;
     int lo = 0, hi = (int)cnt;
     if (blk.begin != blk.lo || blk.end != blk.hi)  // (a range that is a whole tensor has all its pairs)
-      wave_equal_range<true>(p.idx[w] + region, (int)cnt, blk.begin, blk.end, blk.lo, blk.hi, lane, lo, hi);
+      wave_equal_range(p.idx[w] + region, (int)cnt, blk.begin, blk.end, lane, lo, hi);
     if (lane == 0) {
       sh.idx_at[w] = p.idx[w] + region + lo;
       sh.val_at[w] = p.val[w] ? p.val[w] + region + lo : nullptr;
@@ -272,7 +263,7 @@ __device__ __forceinline__ int locate_pairs2(Shared& sh, const RegionPayloads& p
     const int32_t* __restrict__ list2 = w < num_payloads2 ? p2.idx[w] + region : safe;
     int lo = 0, hi = (int)cnt, lo2 = 0, hi2 = (int)cnt2;
     if (blk.begin != blk.lo || blk.end != blk.hi)  // (a range that is a whole tensor has all its pairs)
-      wave_equal_range2(list, (int)cnt, list2, (int)cnt2, safe, blk, lane, lo, hi, lo2, hi2);
+      wave_equal_range2(list, (int)cnt, list2, (int)cnt2, safe, blk.begin, blk.end, lane, lo, hi, lo2, hi2);
     if (lane == 0) {
       if (w < num_payloads) {
         sh.idx_at[w] = list + lo;
@@ -347,8 +338,11 @@ __device__ __forceinline__ int merge_slot(const MergeShared<CAP>& sh, int32_t r)
 // THREADS: 512 when there are at most eight payloads (one wavefront searches one payload's region,
 // and four workgroups of eight wavefronts fit a compute unit, LDS included: the 970 ranges of a
 // 122 M-element set then run all at once instead of in two rounds), 1024 otherwise.  Bound by latency, the
-// searches before all: replacing calls at 0.1 % 36.5 us on that set and 24.1 on 25.6 M elements with sixteen
-// payloads (38.0 and 25.7 with searches over the whole region).  kMergeCap:
+// searches before all: replacing calls at 0.1 % 35.2 us on that set and 24.5 on 25.6 M elements with sixteen
+// payloads.  (A first round of probes around the place that a range has if pairs are spread evenly took 34.9
+// and 23.7, but 49.1 instead of 39.1 where the pairs crowd three tenths of one large tensor: every workgroup
+// goes on from a bracket of its own, where the first rounds over the whole region read the same few sectors.
+// Both sets of probes in one round: no gain where pairs are spread evenly.)  kMergeCap:
 // pairs a workgroup takes into registers, slots of its LDS accumulator (a range with more takes
 // the slow way at the end of the kernel).
 template <bool REPLACE, int THREADS>
@@ -572,6 +566,41 @@ __global__ __launch_bounds__(THREADS) void merge_regions_kernel(float* __restric
   }
 }
 
+// Where to look first for x in an ascending list of m values that lie in [from, to): the place it has if they
+// are spread evenly, and the standard deviation of that place if they are spread at random.  Only the number
+// of probes depends on it.
+struct Guess {
+  int place, sigma;
+  __device__ __forceinline__ Guess(int m, int32_t x, int32_t from, int32_t to) {
+    float f = (float)(x - from) / (float)(to - from);
+    f = f < 0.0f ? 0.0f : f > 1.0f ? 1.0f : f;
+    const float at = f * (float)m;
+    place = at < (float)m ? (int)at : m;
+    sigma = (int)sqrtf((float)m * f * (1.0f - f));
+  }
+};
+
+// One round of eight probes of a list of m values by as many neighbouring lanes: the probe of lane i, and
+// after the vote the bracket [lo, hi] that the answer lies in.
+struct ProbeRound {
+  static constexpr int kProbes = 8;
+  int start, step, last;  // probe i is at clamp(start + i * step, 0, last)
+  // around a guess, four standard deviations to either side
+  __device__ __forceinline__ ProbeRound(const Guess& g, int m)
+      : start(g.place - kProbes / 2 * (g.sigma + 1)), step(g.sigma + 1), last(m - 1) {}
+  // over the whole list
+  __device__ __forceinline__ explicit ProbeRound(int m) : start(0), step((m + kProbes - 1) / kProbes), last(m - 1) {}
+  __device__ __forceinline__ int at(int i) const {
+    const int64_t p = (int64_t)start + (int64_t)i * step;
+    return p < 0 ? 0 : p > last ? last : (int)p;
+  }
+  __device__ __forceinline__ void narrow(int below, int& lo, int& hi) const {  // `below` probes are less than x: a prefix
+    if (below < kProbes && at(below) < hi) hi = at(below);
+    if (below > 0 && at(below - 1) >= lo) lo = at(below - 1) + 1;
+    if (lo > hi) lo = hi;
+  }
+};
+
 // Receive side at warm-up densities (paper: Section 4, warm-up training -- 25 % down to
 // 0.4 % of the elements are sent during the first epochs): with millions of pairs per
 // payload, adding them one by one to `dense` costs a scattered read-modify-write each.
@@ -596,8 +625,9 @@ __global__ __launch_bounds__(THREADS) void merge_regions_kernel(float* __restric
 // its tensor starts, so one bound per part is searched for).  The probes are what this
 // launch costs (each one a 64-byte sector from HBM: 350 MB with 32 probes per round and
 // two bounds per part), so eight lanes share a search: 8 probes per round, about seven
-// rounds for a region of a million pairs, fewer where the first guess is close: 26.7 us on 122 M elements
-// at 25 %, 30 with searches over the whole region.
+// rounds for a region of a million pairs, fewer where a first guess is close: 26.7 us on 122 M elements
+// at 25 %, 30 with searches over the whole region.  The first round probes around the guess and over the
+// whole region at once, so that a wrong guess (pairs that crowd a part of the tensor) costs no round.
 __global__ __launch_bounds__(kFlatThreads) void locate_parts_kernel(RegionPayloads p, int32_t num_payloads,
                                                                     const int64_t* __restrict__ out_offsets,
                                                                     const MergeBlock* __restrict__ blocks,
@@ -631,11 +661,16 @@ __global__ __launch_bounds__(kFlatThreads) void locate_parts_kernel(RegionPayloa
     x = blk.begin;
     hi = x > blk.lo ? cnt : 0;  // (a tensor's first part starts at the region's start)
   }
-  // the first round around the place the part starts at if the pairs are spread evenly over the tensor
+  // the first round around the place the part starts at if the pairs are spread evenly over the tensor, and
+  // over the whole region
   if (__ballot(hi > 64)) {
-    const GuessRound<8> r(Guess(cnt, x, blk.lo, blk.hi > blk.lo ? blk.hi : blk.lo + 1), cnt);
-    const unsigned long long votes = __ballot(hi > 0 && list[r.at(sub)] < x);
-    if (hi > 0) r.narrow(__popc((uint32_t)(votes >> (8 * group)) & 0xFFu), lo, hi);
+    const ProbeRound near(Guess(cnt, x, blk.lo, blk.hi > blk.lo ? blk.hi : blk.lo + 1), cnt), all(cnt);
+    const int32_t at_near = hi > 0 ? list[near.at(sub)] : 0, at_all = hi > 0 ? list[all.at(sub)] : 0;
+    const unsigned long long votes = __ballot(hi > 0 && at_near < x), votes_all = __ballot(hi > 0 && at_all < x);
+    if (hi > 0) {
+      near.narrow(__popc((uint32_t)(votes >> (8 * group)) & 0xFFu), lo, hi);
+      all.narrow(__popc((uint32_t)(votes_all >> (8 * group)) & 0xFFu), lo, hi);
+    }
   }
   // first position whose index is not below x ("index < x" is monotone along a region)
   while (__ballot(hi > lo)) {

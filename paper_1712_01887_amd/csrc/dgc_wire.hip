@@ -405,8 +405,8 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_range_kernel(DecodeArgs
     const int32_t slot0 = a.seg.begin[w];
     int lo = 0, hi = 0;
     // the last block that starts at or before the range's first element, up to the last that starts inside
-    wave_equal_range<false>(reinterpret_cast<const int32_t*>(a.sums) + slot0, a.seg.begin[w + 1] - slot0, (int32_t)begin + 1,
-                            (int32_t)(begin + length), 0, 0, lane, lo, hi);
+    wave_equal_range(reinterpret_cast<const int32_t*>(a.sums) + slot0, a.seg.begin[w + 1] - slot0, (int32_t)begin + 1,
+                            (int32_t)(begin + length), lane, lo, hi);
     if (lane == 0) {
       first_block[w] = lo - 1;
       blocks[w] = hi > lo - 1 && hi > 0 ? hi - (lo - 1) : 0;
