@@ -47,6 +47,7 @@ struct dgc_handle {
   bool ws_layout_valid = false;
   std::vector<int64_t> ws_out_offsets;
   std::vector<uint32_t> wire_first_block;  // T + 1: encoder workgroup slots per region of the bound layout
+  int32_t wire_widest = 0;                   // slots of one region at most
   size_t wire_slots = 0;                   // words reserved for block sums of the wire-format passes
   // optional kernel timing: five events per dgc_compress call
   // (start, after norm, after select, after stream, after emit)
@@ -347,11 +348,14 @@ dgc_status sync_workspace(dgc_handle* h, void* ws, size_t ws_bytes, const int64_
       h->layout_may_overflow = false;
       for (size_t j = 0; j < T; ++j)
         if (out_offsets[j + 1] - out_offsets[j] < h->offsets[j + 1] - h->offsets[j]) h->layout_may_overflow = true;
-      uint64_t slots = 0;
+      uint64_t slots = 0, widest = 0;
       for (size_t j = 0; j < T; ++j) {
         h->wire_first_block[j] = (uint32_t)slots;
-        slots += (uint64_t)((out_offsets[j + 1] - out_offsets[j] + kWireChunk - 1) / kWireChunk);
+        const uint64_t own = (uint64_t)((out_offsets[j + 1] - out_offsets[j] + kWireChunk - 1) / kWireChunk);
+        slots += own;
+        if (own > widest) widest = own;
       }
+      h->wire_widest = (int32_t)widest;
       h->wire_first_block[T] = (uint32_t)slots;
       if (!hip_ok(hipMemcpyAsync(at<char>(ws, h->lay.wire_first_block), h->wire_first_block.data(),
                                  sizeof(uint32_t) * (T + 1), hipMemcpyHostToDevice, stream),
@@ -1066,6 +1070,7 @@ dgc_status dgc_encode(dgc_handle* h, const int32_t* idx, const float* val, const
   ea.capacity = entry_capacity;
   ea.num_tensors = h->num_tensors;
   ea.total_blocks = (int32_t)total_blocks;
+  ea.widest = h->wire_widest;
   if (!hip_ok(launch_encode(ea, stream), "launch encode kernels")) return DGC_ERR_HIP;
   return DGC_OK;
 }

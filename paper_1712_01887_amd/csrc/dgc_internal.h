@@ -97,7 +97,9 @@ constexpr int kWireThreads = 256;
 constexpr int kWireChunk = 4096;
 constexpr int kWireRounds = kWireChunk / kWireThreads;   // rounds of 64 pairs a wavefront takes
 // Block sums that the workgroups of the second pass add up for themselves, sixteen rounds of one load of
-// four per thread at most: a scan launch takes 9.7 us at 8000 sums (66 M elements, regions for 6.25 %).
+// four per thread at most; above, a scan launch.  At the limit (67 M pairs) that takes 232 us where the scan
+// takes 239 if every region is full, and 44 against 56 if one workgroup in eight has pairs; with 512 of them 13
+// against 16.
 constexpr int kWireSelfScan = 16384;
 constexpr int kScanThreads = 1024;
 constexpr int kScanPer = 8;          // block sums per thread and round of the scan
@@ -304,6 +306,8 @@ struct EncodeArgs {
   int64_t capacity;              // entries that fit in runs / vals
   int32_t num_tensors;
   int32_t total_blocks;          // workgroup slots of all tensors
+  int32_t widest;                // of one tensor at most
+  int32_t per_tensor;            // workgroups of every tensor; 0: total_blocks of them, which search
   int32_t self_scan;             // the second pass adds the block sums up itself
 };
 

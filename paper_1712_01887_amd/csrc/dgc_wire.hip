@@ -47,15 +47,26 @@ __device__ __forceinline__ int32_t last_index_before(const EncodeArgs& a, int j)
 }
 
 // Tensor whose region holds workgroup slot `slot`: the last j with first_block[j] <= slot (a tensor with an
-// empty region takes no slot and shares its number with the next one).  One whole wavefront.
-__device__ __forceinline__ int tensor_of_slot(const EncodeArgs& a, uint32_t slot) {
+// empty region takes no slot and shares its number with the next one).  One vote for up to 64 tensors; of
+// more, the first wavefront searches, 64 probes a round, and the others learn it through LDS.
+__device__ __forceinline__ int tensor_of_slot(const EncodeArgs& a, uint32_t slot, int* shared) {
   const int lane = threadIdx.x & 63;
-  int below = 0;
-  for (int base = 0; base < a.num_tensors; base += 64) {
-    const int j = base + lane;
-    below += __popcll(__ballot(j < a.num_tensors && a.first_block[j] <= slot));
+  if (a.num_tensors <= 64) return __popcll(__ballot(lane < a.num_tensors && a.first_block[lane] <= slot)) - 1;
+  if (threadIdx.x < 64) {
+    int lo = 0, end = a.num_tensors;  // the first tensor that starts behind `slot` is in [lo, end]
+    while (lo < end) {
+      const int step = (end - lo + 63) >> 6;
+      const int64_t at = lo + (int64_t)lane * step;
+      const int c = __popcll(__ballot(at < end && a.first_block[at] <= slot));  // a prefix of the lanes
+      if (c == 0) break;
+      const int64_t next = lo + (int64_t)c * step;
+      lo += (c - 1) * step + 1;
+      end = next < end ? (int)next : end;
+    }
+    if (lane == 0) *shared = lo - 1;
   }
-  return below - 1;
+  __syncthreads();
+  return __builtin_amdgcn_readfirstlane(*shared);
 }
 
 // PASS 0: entries needed by the workgroup's pairs.  PASS 1: write them.  One workgroup per kWireChunk
@@ -69,16 +80,26 @@ __global__ __launch_bounds__(kWireThreads) void encode_kernel(EncodeArgs a) {
   __shared__ uint32_t wave_need[kWaves];
   __shared__ uint32_t wave_before[kWaves];
   const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  const int j = tensor_of_slot(a, blockIdx.x);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  __shared__ int tensor;
+  int j;
+  uint32_t slot;
+  if (a.per_tensor > 0) {
+    j = (int)(blockIdx.x / (uint32_t)a.per_tensor);
+    slot = a.first_block[j] + blockIdx.x % (uint32_t)a.per_tensor;
+    if (slot >= a.first_block[j + 1]) return;
+  } else {
+    slot = blockIdx.x;
+    j = tensor_of_slot(a, slot, &tensor);
+  }
   const int64_t region = a.out_offsets[j];
   const int64_t cap = a.out_offsets[j + 1] - region;
   int64_t count = a.counts[j];
   if (count > cap) count = cap;
-  const int64_t begin = (int64_t)(blockIdx.x - a.first_block[j]) * kWireChunk;
-  const bool last_slot = PASS == 1 && a.self_scan && (int)blockIdx.x == a.total_blocks - 1;  // knows how many entries there are
+  const int64_t begin = (int64_t)(slot - a.first_block[j]) * kWireChunk;
+  const bool last_slot = PASS == 1 && a.self_scan && (int)slot == a.total_blocks - 1;  // knows how many entries there are
   if (begin >= count) {
-    if (PASS == 0 && threadIdx.x == 0) a.sums[blockIdx.x] = 0;
+    if (PASS == 0 && threadIdx.x == 0) a.sums[slot] = 0;
     if (!last_slot) return;
   }
   const int32_t* __restrict__ idx = a.idx + region;
@@ -86,9 +107,13 @@ __global__ __launch_bounds__(kWireThreads) void encode_kernel(EncodeArgs a) {
   int32_t prev = -1;                                     // index of the pair before the round
   if (p0 > 0 && p0 <= count) prev = idx[p0 - 1];
   else if (p0 == 0 && count > 0) prev = last_index_before(a, j);
+  const int64_t left = count - p0;
+  const uint32_t pairs = left <= 0 ? 0u : left < 64 * kWireRounds ? (uint32_t)left : (uint32_t)(64 * kWireRounds);
+  const bool one_round = pairs <= 64;  // uniform; small tensors have a pair or two each (20000 of them: 95 -> 60 us)
   int32_t mine[kWireRounds];
 #pragma unroll
   for (int r = 0; r < kWireRounds; ++r) {
+    if (r == 1 && one_round) break;
     const int64_t p = p0 + r * 64 + lane;
     mine[r] = p < count ? idx[p] : 0;
   }
@@ -97,6 +122,7 @@ __global__ __launch_bounds__(kWireThreads) void encode_kernel(EncodeArgs a) {
     const float* __restrict__ val = a.val + region;
 #pragma unroll
     for (int r = 0; r < kWireRounds; ++r) {
+      if (r == 1 && one_round) break;
       const int64_t p = p0 + r * 64 + lane;
       x[r] = p < count ? val[p] : 0.0f;
     }
@@ -106,6 +132,7 @@ __global__ __launch_bounds__(kWireThreads) void encode_kernel(EncodeArgs a) {
   bool unsorted = false;
 #pragma unroll
   for (int r = 0; r < kWireRounds; ++r) {
+    if (r == 1 && one_round) break;
     const bool have = p0 + r * 64 + lane < count;
     int32_t before = __shfl_up(mine[r], 1);
     if (lane == 0) before = prev;
@@ -117,8 +144,6 @@ __global__ __launch_bounds__(kWireThreads) void encode_kernel(EncodeArgs a) {
     }
     fillers += (uint32_t)gap[r] >> 16;
   }
-  const int64_t left = count - p0;
-  const uint32_t pairs = left <= 0 ? 0u : left < 64 * kWireRounds ? (uint32_t)left : (uint32_t)(64 * kWireRounds);
   const uint32_t need = pairs + wave_sum(fillers);  // of the wavefront
   if (lane == 0) wave_need[wave] = need;
   if (PASS == 0) {
@@ -126,7 +151,7 @@ __global__ __launch_bounds__(kWireThreads) void encode_kernel(EncodeArgs a) {
     if (threadIdx.x == 0) {
       uint32_t total = 0;
       for (int w = 0; w < kWaves; ++w) total += wave_need[w];
-      a.sums[blockIdx.x] = total;
+      a.sums[slot] = total;
     }
     if (unsorted) atomicOr(&a.state->flags, (uint32_t)DGC_DIAG_UNSORTED);
     return;
@@ -135,7 +160,7 @@ __global__ __launch_bounds__(kWireThreads) void encode_kernel(EncodeArgs a) {
   if (a.self_scan) {  // few block sums: every workgroup adds up those before its own
     uint32_t mine_before = 0;
     const uint4* __restrict__ four = reinterpret_cast<const uint4*>(a.sums);  // starts on a 256-byte boundary
-    const uint32_t quads = blockIdx.x >> 2;
+    const uint32_t quads = slot >> 2;
     for (uint32_t i = threadIdx.x; i < quads; i += 4 * kWireThreads) {
       uint4 c[4];
 #pragma unroll
@@ -143,7 +168,7 @@ __global__ __launch_bounds__(kWireThreads) void encode_kernel(EncodeArgs a) {
 #pragma unroll
       for (int k = 0; k < 4; ++k) mine_before += (c[k].x + c[k].y) + (c[k].z + c[k].w);
     }
-    if (threadIdx.x < (blockIdx.x & 3u)) mine_before += a.sums[4 * quads + threadIdx.x];
+    if (threadIdx.x < (slot & 3u)) mine_before += a.sums[4 * quads + threadIdx.x];
     mine_before = wave_sum(mine_before);
     if (lane == 0) wave_before[wave] = mine_before;
     __syncthreads();
@@ -151,7 +176,7 @@ __global__ __launch_bounds__(kWireThreads) void encode_kernel(EncodeArgs a) {
     for (int w = 0; w < kWaves; ++w) before_block += wave_before[w];
   } else {
     __syncthreads();
-    before_block = a.sums[blockIdx.x];
+    before_block = a.sums[slot];
   }
   int64_t pos = before_block;
   uint32_t block_total = 0;
@@ -522,7 +547,12 @@ hipError_t launch_encode(EncodeArgs a, hipStream_t stream) {
     return hipGetLastError();
   }
   a.self_scan = a.total_blocks <= kWireSelfScan ? 1 : 0;
-  const dim3 grid((unsigned)a.total_blocks);
+  // As many workgroups for every tensor if few of them stay idle, so that none has to search for its tensor
+  // (20000 tensors of 1500 elements: 60 us, where a search of three dependent rounds of loads took 15 more and
+  // a walk over the tensors, 64 at a time, 1200 more).
+  const int64_t even = (int64_t)a.widest * a.num_tensors;
+  a.per_tensor = even <= 2 * (int64_t)a.total_blocks ? a.widest : 0;
+  const dim3 grid((unsigned)(a.per_tensor > 0 ? even : a.total_blocks));
   hipLaunchKernelGGL(encode_kernel<0>, grid, dim3(kWireThreads), 0, stream, a);
   if (!a.self_scan)
     hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(kScanThreads), 0, stream, a.sums, seg, a.num_entries, (int64_t)0,
