@@ -833,7 +833,7 @@ __device__ __forceinline__ uint32_t mixed_tile_mask(const StreamArgs& a, int64_t
   }
   fill(seg_lo, tile_end, seg_thr);
   fill(tile_end, kWaveTile, __builtin_inff());  // beyond the set: nothing passes
-  __builtin_amdgcn_wave_barrier();              // (LDS operations of one wavefront are carried out in order)
+  wave_lds_fence();
   uint32_t cand = 0;
 #pragma unroll
   for (int r = 0; r < kStreamUnroll; ++r) {
@@ -2134,9 +2134,9 @@ __global__ __launch_bounds__(kEmitThreads) void emit_staged_kernel(EmitArgs a) {
           pos += bit;
         }
       }
-      __builtin_amdgcn_wave_barrier();  // (LDS operations of one wavefront are carried out in order)
+      wave_lds_fence();
       for (int s = 4 * lane; s < total; s += 256) put_indices(tile_idx, s, total, *reinterpret_cast<const int4*>(&list[s]));
-      __builtin_amdgcn_wave_barrier();
+      wave_lds_fence();
       continue;
     }
     // A tile shared between tensors, or one that the region has no room for: element by element.  An

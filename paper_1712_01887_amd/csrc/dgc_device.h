@@ -1,4 +1,4 @@
-// Device code shared by the kernels: wavefront scans and searches.
+// Device code shared by the kernels: wavefront scans, searches and exchange through LDS.
 #ifndef DGC_DEVICE_H_
 #define DGC_DEVICE_H_
 
@@ -36,6 +36,14 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t x) {
   x = larger(x, __builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false));
   x = larger(x, __builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false));
   return wave_last(x);
+}
+
+// Between stores to LDS by some lanes of a wavefront and loads of them by others.  The hardware carries out a
+// wavefront's LDS operations in order; this keeps the compiler from moving them, and costs no instruction.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 }
 
 // Positions [lo, hi) of the list L[0, m) whose values lie in [xa, xb), for a list in which
