@@ -29,7 +29,7 @@ struct dgc_handle {
   std::vector<int64_t> k;            // T
   std::vector<int64_t> draws;        // T
   bool any_band = false;             // some tensor's threshold is found by way of a band (TensorPlan.exact == 2)
-  uint32_t most_bands = 0;           // tensors that take a band at some density
+  uint32_t most_bands = 0;           // tensors that take a band at some density; 0: none does
   std::vector<uint32_t> tile_info;   // ceil(n / kWaveTile)
   std::vector<float> tile_thr_init;  // ceil(n / kWaveTile): NaN where a tile is not wholly inside one tensor
   std::vector<EmitBlock> emit_blocks;  // work list of the emit pass
@@ -153,6 +153,18 @@ int64_t topk_count(double density, int64_t n) {
   return k;
 }
 
+int64_t sample_size(const dgc_config& c, int64_t n) {
+  int64_t want = (int64_t)std::ceil(c.sample_ratio * (double)n);
+  if (want > c.sample_max) want = c.sample_max;
+  if (want < c.sample_min) want = c.sample_min;
+  return want < n ? want : n;
+}
+
+// The threshold comes from all elements of the tensor.
+bool whole_tensor(const dgc_config& c, int64_t n) {
+  return (c.flags & DGC_FLAG_EXACT_SELECT) || sample_size(c, n) >= n || n / c.sample_block < 1;
+}
+
 // Host arithmetic of the sampled threshold (paper: Section 5).  The wanted
 // sample size is ratio * n clamped to [sample_min, sample_max]; a tensor no
 // larger than that is used whole.  Otherwise ceil(s / B) aligned blocks of B
@@ -161,6 +173,14 @@ int64_t topk_count(double density, int64_t n) {
 void build_plan(dgc_handle* h) {
   const dgc_config& c = h->cfg;
   const int64_t B = c.sample_block;
+  int64_t longest = 0, readers = 0;  // of the tensors that are read whole and fill more than a workgroup's registers
+  for (int32_t j = 0; j < h->num_tensors; ++j) {
+    const int64_t n = h->offsets[j + 1] - h->offsets[j];
+    if (n <= kBandSample || !whole_tensor(c, n)) continue;
+    ++readers;
+    if (n > longest) longest = n;
+  }
+  const bool by_bands = longest > (readers >= kBandMany ? kBandFromMany : kBandFrom);
   uint32_t bands = 0;
   h->any_band = false;
   for (int32_t j = 0; j < h->num_tensors; ++j) {
@@ -175,17 +195,14 @@ void build_plan(dgc_handle* h) {
       const double lim = std::floor((double)c.refine_alpha * (double)k);
       p.refine_limit = lim >= 2147483647.0 ? 2147483647 : (int32_t)lim;
     }
-    int64_t want = (int64_t)std::ceil(c.sample_ratio * (double)n);
-    if (want > c.sample_max) want = c.sample_max;
-    if (want < c.sample_min) want = c.sample_min;
-    const int64_t s = want < n ? want : n;
-    if ((c.flags & DGC_FLAG_EXACT_SELECT) || s >= n || n / B < 1) {
+    const int64_t s = sample_size(c, n);
+    if (whole_tensor(c, n)) {
       p.exact = 1;
       p.count = (int32_t)n;
       p.rank = (int32_t)k;
       p.nblocks = 0;
       h->draws[j] = 0;
-      if (n > kBandSample) {  // more than a workgroup of select_kernel holds in registers
+      if (by_bands && n > kBandSample) {  // more than a workgroup of select_kernel holds in registers
         if (k < n) {
           p.exact = 2;
           p.nblocks = bands;

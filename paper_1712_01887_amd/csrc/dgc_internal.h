@@ -131,6 +131,12 @@ constexpr int kSelectInFlight = 8;    // candidates each thread gathers before u
 // 25 %; three workgroup-wide passes over a whole tensor, which are still the way out when a band misses,
 // took 1385 us.
 constexpr int kBandSample = kSelectRegKeys * kSelectThreads;
+// Bands where the longest such tensor has more than this many elements: up to there the passes of one
+// workgroup over it take less than the two launches (one tensor of 33000: 35 against 54 us for the call, 65000: 53 and
+// 55, 80000: 60 and 54; 200 of 60000: 117 and 123, of 80000: 153 and 148).  With as many tensors as compute
+// units a little earlier (256 of 40000: 102 and 121, of 64000: 159 and 147).
+constexpr int64_t kBandFrom = 65536, kBandFromMany = 57344;
+constexpr int64_t kBandMany = 256;
 constexpr int kBandBlockShift = 5;
 constexpr int kBandListShift = 6;       // three list words per 64 elements
 constexpr int kBandThreads = 256;

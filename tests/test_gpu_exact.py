@@ -13,7 +13,8 @@ from tests.parity import Pair, gather_payload
 pytestmark = pytest.mark.gpu
 
 EXACT = B.DGC_FLAG_EXACT_SELECT
-# 32768 fits the registers of a workgroup, 32769 is the smallest that does not; the others share tiles
+# 32768 fits the registers of a workgroup, 32769 is the smallest that does not (a set that has a tensor above
+# 65536 takes bands for all such); the others share tiles
 SIZES = [5, 32769, 32768, 100003, 1, 70001, 262144, 29]
 
 
@@ -39,6 +40,27 @@ def test_exact_thresholds_of_large_tensors(density, flags):
         assert all(int(c) <= O.topk_count(density, s) for c, s in zip(res.counts, SIZES))
     assert p.dgc.dgc_query_plan(3)[:3] == (O.topk_count(density, SIZES[3]), SIZES[3], O.topk_count(density, SIZES[3]))
     p.close()
+
+
+@pytest.mark.parametrize("sizes,listed", [
+    ([65536, 40000, 7, 32769], False),             # no tensor above 65536 elements: a workgroup reads the tensor
+    ([65537, 40000, 7, 32769], True),
+    ([33000], False),
+    ([57344] * 256 + [5], False),
+    ([57345] + [32769] * 256, True),               # as many tensors as compute units, and more: above 57344
+])
+@pytest.mark.parametrize("density", [0.003, 0.3])
+def test_exact_on_both_sides_of_the_rule_for_bands(sizes, listed, density):
+    offsets = np.concatenate([[0], np.cumsum(sizes)])
+    p = Pair(offsets, momentum=0.9, density=density, seed=6, flags=EXACT)
+    sampled = B.Dgc(B.make_config(momentum=0.9, density=density, seed=6), offsets)
+    assert (p.dgc.dgc_workspace_bytes() > sampled.dgc_workspace_bytes()) == listed
+    rng = np.random.default_rng(len(sizes))
+    for it in range(2 if p.n < 1 << 20 else 1):
+        g = (1e-2 * rng.standard_t(3, p.n)).astype(np.float32)
+        p.step(g, it, label=f"exact, {len(sizes)} tensors up to {max(sizes)} d={density} it{it}")
+    p.close()
+    sampled.close()
 
 
 @pytest.mark.parametrize("density", [0.001, 0.25])
