@@ -1955,9 +1955,11 @@ __global__ __launch_bounds__(kEmitThreads) void emit_sorted_kernel(EmitArgs a) {
 // tiles shared between tensors, which the streaming pass leaves alone.
 //
 // Bound by instructions at the lower densities of the warm-up and by the stores at the higher ones.  A
-// wavefront takes eight consecutive tiles; the counts of whole tiles come from the table that the
-// streaming pass has left, not from the mask words; values move four to a lane; the indices of a tile
-// with many selected elements are put in their places in LDS and leave from there four to a lane, too.
+// wavefront takes every fourth tile, eight in all (eight consecutive ones left three wavefronts idle in parts
+// of a few tiles: 4000 tensors of 7500 elements, 6.25 %, 329 us for the call and 307 this way); the counts of
+// whole tiles come from the table that the streaming pass has left, not from the mask words; values move four
+// to a lane; the indices of a tile with many selected elements are put in their places in LDS and leave from
+// there four to a lane, too.
 // 122 M elements: 112 us at 25 %, 44 at 1.6 % (136 and 46 with the counts formed from the mask words and every
 // index stored where it belongs one by one); placing the indices of sparse tiles through LDS as well: 57 us
 // at 1.6 %.  Holding all eight tiles' values and words in registers took 220 of them and 224 us at 25 %.
@@ -1997,7 +1999,7 @@ __global__ __launch_bounds__(kEmitThreads) void emit_staged_kernel(EmitArgs a) {
     uint32_t word[kPerWave];
 #pragma unroll
     for (int i = 0; i < kPerWave; ++i) {
-      const int64_t t = first + wave * kPerWave + i;
+      const int64_t t = first + wave + i * kWaves;
       word[i] = t <= t1 ? tensor_tile_word(a.mask, t, lane, lo, hi) : 0u;
     }
     const int64_t t = first + tid;
@@ -2011,10 +2013,10 @@ __global__ __launch_bounds__(kEmitThreads) void emit_staged_kernel(EmitArgs a) {
   if (lane == 0) sh.base[wave] = pre;
 #pragma unroll 1
   for (int i = 0; i < kPerWave; ++i) {
-    const int64_t t = first + wave * kPerWave + i;
+    const int64_t t = first + wave + i * kWaves;
     if (t <= t1 && !whole(t)) {  // shared with a neighbour, or the ragged end: the tensor's own bits count
       const int c = (int)wave_sum((uint32_t)__popc((uint32_t)words[i * 64]));
-      if (lane == 0) sh.cnt[wave * kPerWave + i] = c;
+      if (lane == 0) sh.cnt[wave + i * kWaves] = c;
     }
   }
   __syncthreads();
@@ -2034,7 +2036,7 @@ __global__ __launch_bounds__(kEmitThreads) void emit_staged_kernel(EmitArgs a) {
   // what a tile of the wavefront is; the slots are counted from the part's first one
   const int64_t part_room = cap - base;
   auto tile_of = [&](int i, int& total, int& slot, int& room) {
-    const int tl = wave * kPerWave + i;
+    const int tl = wave + i * kWaves;
     total = __builtin_amdgcn_readlane(own, tl);
     slot = __builtin_amdgcn_readlane(incl, tl) - total;
     // slots of the tile that exist (the rest of the tile overflows)
@@ -2047,7 +2049,7 @@ __global__ __launch_bounds__(kEmitThreads) void emit_staged_kernel(EmitArgs a) {
     int total, slot, room;
     fvec4u x = {0.0f, 0.0f, 0.0f, 0.0f};
     if (tile_of(i, total, slot, room) && 4 * lane < room)
-      x = *reinterpret_cast<const fvec4u*>(a.stage_v + (first + wave * kPerWave + i) * kWaveTile + 4 * lane);
+      x = *reinterpret_cast<const fvec4u*>(a.stage_v + (first + wave + i * kWaves) * kWaveTile + 4 * lane);
     return x;
   };
   float* __restrict__ part_val = a.out_val + region + base;
@@ -2079,7 +2081,7 @@ __global__ __launch_bounds__(kEmitThreads) void emit_staged_kernel(EmitArgs a) {
     int total, slot, room;
     const bool staged = tile_of(i, total, slot, room);
     if (total == 0) continue;  // uniform, as everything about the tile
-    const int64_t t = first + wave * kPerWave + i;
+    const int64_t t = first + wave + i * kWaves;
     const uint32_t w = words[i * 64];
     const int32_t e_lane = (int32_t)tile_element(t, lane, 0);
     float* __restrict__ tile_val = part_val + slot;
@@ -2139,35 +2141,46 @@ __global__ __launch_bounds__(kEmitThreads) void emit_staged_kernel(EmitArgs a) {
       wave_lds_fence();
       continue;
     }
-    // A tile shared between tensors, or one that the region has no room for: element by element.  An
-    // element's slot is rows before it + bits of its row in lower lanes + lower bits of its nibble.
+    // A tile shared between tensors, or one that the region has no room for: element by element, a row at a
+    // time, the row's loads before its stores.  An element's slot is rows before it + bits of its row in lower
+    // lanes + lower bits of its nibble.
     const float* __restrict__ stage_u = a.stage_u ? a.stage_u + t * kWaveTile : nullptr;
     int row_base = 0;
-#pragma unroll 1
+#pragma unroll
     for (int r = 0; r < kRows; ++r) {
       const uint32_t nib = (w >> (4 * r)) & 0xFu;
       const uint32_t upto = wave_inclusive_sum((uint32_t)__popc(nib));
-      int pos = row_base + (int)upto - __popc(nib);
+      const int pos0 = row_base + (int)upto - __popc(nib);
       row_base += (int)wave_last(upto);
-#pragma unroll 1
+      const int32_t e0 = e_lane + r * 256;
+      float y[4];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const int pos = pos0 + __popc(nib & ((1u << c) - 1u));
+        y[c] = 0.0f;
+        if ((nib >> c) & 1u) {
+          if (!staged && pos < room) y[c] = v[e0 + c];
+          if (staged && pos >= room) y[c] = stage_v[pos];
+        }
+      }
+#pragma unroll
       for (int c = 0; c < 4; ++c) {
         if (!((nib >> c) & 1u)) continue;
-        const int32_t e = e_lane + r * 256 + c;
+        const int pos = pos0 + __popc(nib & ((1u << c) - 1u));
         if (pos < room) {
-          tile_idx[pos] = e;
+          tile_idx[pos] = e0 + c;
           if (!staged) {  // value taken and u, v masked here
-            tile_val[pos] = v[e];
-            v[e] = 0.0f;
-            if (a.factor_masking) u[e] = 0.0f;
+            tile_val[pos] = y[c];
+            v[e0 + c] = 0.0f;
+            if (a.factor_masking) u[e0 + c] = 0.0f;
           }
         } else {
           overflow = true;
           if (staged) {  // region full: the element goes back to where the streaming pass took it from
-            v[e] = stage_v[pos];
-            if (a.factor_masking && stage_u) u[e] = stage_u[pos];
+            v[e0 + c] = y[c];
+            if (a.factor_masking && stage_u) u[e0 + c] = stage_u[pos];
           }
         }
-        ++pos;
       }
     }
   }
