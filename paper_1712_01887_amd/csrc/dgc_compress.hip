@@ -274,10 +274,10 @@ __device__ __forceinline__ uint32_t select_in_registers(SelectShared& sh, const 
   return prefix;
 }
 
-// Key of descending rank `rank` among the keys a workgroup holds in registers (kNoKey marks an empty
+// Key of descending rank `rank` among the `count` keys a workgroup holds in registers (kNoKey marks an empty
 // slot); threads 0 .. holders - 1 have at least one.  Every thread returns the same.
-__device__ __forceinline__ uint32_t rank_registers(SelectShared& sh, const uint32_t (&key)[kSelectRegKeys], int32_t holders,
-                                                   uint32_t rank, int tid) {
+__device__ __forceinline__ uint32_t rank_registers(SelectShared& sh, const uint32_t (&key)[kSelectRegKeys], int32_t count,
+                                                   int32_t holders, uint32_t rank, int tid) {
   // Gradients of one tensor share a few exponents, so a histogram over the leading key
   // bits of all candidates piles tens of thousands of LDS atomics on a handful of bins,
   // and every histogram pass costs half a dozen barriers of 1024 threads (ranking 32 Ki
@@ -294,7 +294,9 @@ __device__ __forceinline__ uint32_t rank_registers(SelectShared& sh, const uint3
   const int wave = tid >> 6;
   const uint32_t full_waves = (uint32_t)holders >= (uint32_t)kSelectThreads ? (uint32_t)kWaves : (uint32_t)holders >> 6;
   const uint32_t t_rounds = full_waves > 0 ? rank / full_waves + 1 : 0;  // full_waves * t_rounds > rank
-  if (t_rounds <= (uint32_t)kSelectFloorRounds) {
+  // (Of a key or two per thread, the list is several hundred long from a rank of 80 or so on: 20000 tensors of
+  // 1500 elements, rank 120, 739 us this way and 553 by histograms, rank 94 618 and 571, rank 45 472 and 535.)
+  if (t_rounds <= (uint32_t)kSelectFloorRounds && (count > 2 * kSelectThreads || rank < 80u)) {
     int32_t top = -1;  // this thread's largest key (an empty slot counts as -1)
 #pragma unroll
     for (int i = 0; i < kSelectRegKeys; ++i) top = (int32_t)key[i] > top ? (int32_t)key[i] : top;
@@ -569,13 +571,13 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectArgs a) {
       const double mid = share * (double)kBandSample;
       const double reach = 32.0 + ceil(7.0 * sqrt(mid * (1.0 - share)));
       const double low = ceil(mid) + reach, high = floor(mid) - reach;
-      const uint32_t floor_key = low < (double)count ? rank_registers(sh, key, holders, (uint32_t)low, tid) : 0xFFFFFFFFu;
-      uint32_t ceil_key = high >= 0.0 ? rank_registers(sh, key, holders, (uint32_t)high, tid) : 0x80000000u;
+      const uint32_t floor_key = low < (double)count ? rank_registers(sh, key, count, holders, (uint32_t)low, tid) : 0xFFFFFFFFu;
+      uint32_t ceil_key = high >= 0.0 ? rank_registers(sh, key, count, holders, (uint32_t)high, tid) : 0x80000000u;
       if (ceil_key == floor_key) ++ceil_key;
       if (tid == 0) *band_state(a, plan) = BandState{floor_key, ceil_key, 0u, 0u, 0u};
       return;
     }
-    thr_bits = rank_registers(sh, key, holders, rank, tid);
+    thr_bits = rank_registers(sh, key, count, holders, rank, tid);
   } else {
     c.scale = settle_scale(a, sh, part, j, tid);
     thr_bits = rank_reevaluated(sh, c, count, rank, tid);

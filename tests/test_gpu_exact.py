@@ -63,6 +63,22 @@ def test_exact_on_both_sides_of_the_rule_for_bands(sizes, listed, density):
     sampled.close()
 
 
+@pytest.mark.parametrize("size", [81, 1000, 1500, 2048, 2049, 4096])
+@pytest.mark.parametrize("rank", [78, 79, 80, 81, 127, 128])
+def test_ranks_where_the_selection_of_small_tensors_changes_over(size, rank):
+    """Up to 2048 elements the largest keys are listed for ranks below 80 only, above that up to rank 127."""
+    offsets = np.arange(6) * size
+    density = min(1.0, (rank - 0.5) / size)
+    p = Pair(offsets, momentum=0.9, density=density, seed=8, flags=EXACT)
+    rng = np.random.default_rng(size)
+    for it in range(2):
+        g = (1e-2 * rng.standard_t(3, p.n)).astype(np.float32)
+        if it:
+            g[: size // 2] = g[0]                      # ties across the rank
+        p.step(g, it, label=f"rank {rank} of {size} it{it}")
+    p.close()
+
+
 @pytest.mark.parametrize("density", [0.001, 0.25])
 @pytest.mark.parametrize("flags", [EXACT, EXACT | B.DGC_FLAG_SORTED_OUTPUT])
 def test_exact_where_the_band_misses(density, flags):
