@@ -244,8 +244,8 @@ dgc_status dgc_compress(dgc_handle* h, const float* g, float* u, float* v, int32
  * errors as dgc_compress otherwise, and
  *   CAPACITY   the handle's tables and scratch exceed the array (dgc_last_error_string says
  *              by how much): use dgc_compress with a workspace of the caller's.  The bound is
- *              dgc_workspace_bytes less the list of exact selection (tensors of more than 32768
- *              elements): the array serves no receive side, whose scratch the list takes;
+ *              dgc_workspace_bytes less the lists of exact selection from large tensors: the
+ *              array serves no receive side, whose scratch the lists take;
  *   HIP        the array's address could not be obtained.
  * The call allocates nothing and frees nothing: it asks the runtime for the array's address the
  * first time it runs on a device and launches the kernels of dgc_compress.  Like dgc_compress, it
@@ -344,7 +344,8 @@ dgc_status dgc_decompress_replace_regions(dgc_handle* h, float* dense, int32_t n
  * dense[idx] = 0 for every pair of the given region-layout payloads: returns a
  * dense aggregate to all-zero after it has been consumed at the cost of the
  * payload size instead of a full fill.  Arguments as above.  Above a density of 0.5 % (or with
- * many payloads, see above), if more than 2 M pairs are expected in all, the regions must be as dgc_compress writes them: the indices of a part are
+ * many payloads, see above), if more than 2 M pairs are expected in all or the set has more than
+ * 32768 tensors, the regions must be as dgc_compress writes them: the indices of a part are
  * marked in a bitmap on chip and every 64-byte sector with a marked element is written
  * once, whole (its other elements are read and written back unchanged).
  */

@@ -119,6 +119,9 @@ constexpr size_t kMergeFewRanges = 256;
 // few there are (23 tensors as above: 7.6 against 3.6 + 14.6 us), and as long as the stores at about this
 // number (122 M elements, 1.9 M pairs: 717 against 712 for the whole pass).
 constexpr double kScatterClearPairs = 2e6;
+// ... and this many tensors, over all of which every workgroup of the scattering launch walks (4 us per 1024):
+// 20000 tensors of 1500 elements, 2 % of eight workers, 106 against 123 us; 50000 of 100, 2 % of two, 184 against 149.
+constexpr int32_t kScatterClearTensors = 32768;
 constexpr double kStagedMinDensity = 0.005;  // compress: staged streaming pass above this density
 constexpr int kProfEvents = 5;
 inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
@@ -980,7 +983,8 @@ static dgc_status scatter_regions(dgc_handle* h, float* dense, int32_t num_paylo
   const int32_t num_parts = (int32_t)h->part_blocks.size();
   void* found = at<char>(workspace, h->lay.part_found);
   if (clear) {
-    if (few || h->cfg.density * (double)h->n * (double)num_payloads <= kScatterClearPairs) {
+    if (few || (h->cfg.density * (double)h->n * (double)num_payloads <= kScatterClearPairs &&
+                h->num_tensors <= kScatterClearTensors)) {
       // the launch is sized for the pairs the density lets expect (the kernel strides over whatever
       // there is), not for regions that were laid out for a higher density
       int64_t expected = 0;

@@ -53,6 +53,8 @@ def time_of(call):
     ([12000000], 0.008, 4, 0.02),
     ([60000, 300, 9000, 60000], 0.02, 4, 0.1),     # no tensor sends more than the accumulator holds
     ([130000, 40000], 0.0094, 4, 0.03),            # ... at its limit
+    ([100] * 32768, 0.02, 2, 0.05),                # the most tensors whose clear is a scattering launch
+    ([100] * 32769, 0.02, 2, 0.05),
 ])
 def test_crowded_pairs_above_half_a_percent(sizes, density, workers, part):
     import torch
