@@ -27,9 +27,10 @@ constexpr int kStreamWaves = kStreamThreads / 64;
 // Workgroups of the streaming pass a compute unit holds at a time.  The pass is faster with few
 // wavefronts in flight than with the 32 a compute unit could hold (fewer streams for the memory side
 // to interleave), so every launch asks for as much LDS as leaves room for this many workgroups in a
-// compute unit's 160 KB.  122 M elements, 0.1 %, average over operand sets (they differ by where they
-// lie): four 387 us, five 378, six 387; workgroups of two wavefronts, two, three, four of them 387, 381
-// to 395, 409; all that fit 404.  25.6 M elements: five 81.6, three of two 82.5.
+// compute unit's 160 KB.  122 M elements, 0.1 %, eight operand sets in one process (mean; they differ by
+// where they lie, by up to 30 us): four 399 us, five 393 (379 to 410), six 400; three workgroups of two wavefronts
+// 400 (391 to 414), each set slower than with five of one.  25.6 M elements: four 86.0, five 83.7, six 84.1, three
+// of two 84.3.
 constexpr int kStreamResidentGroups = 5;
 constexpr int kStreamGroupsAfterNorm = 12;  // with clipping on: see launch_stream
 constexpr size_t kLdsPerComputeUnit = (size_t)160 * 1024;
@@ -126,15 +127,15 @@ constexpr int kSelectInFlight = 8;    // candidates each thread gathers before u
 // the workgroup's registers hold: select_kernel draws kBandSample elements (blocks of 1 << kBandBlockShift)
 // and names a band of keys that holds the wanted rank almost surely, collect_band_kernel reads the
 // tensor once, spread over the chip, and lists the keys inside the band, rank_band_kernel ranks them.
-// The list of a tensor takes three words per 64 elements of an area of its own.  On the 161-tensor set of 25.6 M elements the three kernels take
-// 22 + 55 + 12 us at 0.1 % (the reads, 12 bytes per element, at 5.6 TB/s) and no more than 40 us more at
-// 25 %; three workgroup-wide passes over a whole tensor, which are still the way out when a band misses,
-// took 1385 us.
+// The list of a tensor takes three words per 64 elements of an area of its own.  On the 161-tensor set of
+// 25.6 M elements the three kernels take 22 + 55 + 12 us at 0.1 % (the reads, 12 bytes per element, at 5.6 TB/s)
+// and no more than 40 us more at 25 %; three workgroup-wide passes over a whole tensor, which are still the way
+// out when a band misses, took 1385 us.
 constexpr int kBandSample = kSelectRegKeys * kSelectThreads;
 // Bands where the longest such tensor has more than this many elements: up to there the passes of one
-// workgroup over it take less than the two launches (one tensor of 33000: 35 against 54 us for the call, 65000: 53 and
-// 55, 80000: 60 and 54; 200 of 60000: 117 and 123, of 80000: 153 and 148).  With as many tensors as compute
-// units a little earlier (256 of 40000: 102 and 121, of 64000: 159 and 147).
+// workgroup over it take less than the two launches (one tensor of 33000: 35 against 54 us for the call, 65000:
+// 53 and 55, 80000: 60 and 54; 200 of 60000: 117 and 123, of 80000: 153 and 148).  With as many tensors as
+// compute units a little earlier (256 of 40000: 102 and 121, of 64000: 159 and 147).
 constexpr int64_t kBandFrom = 65536, kBandFromMany = 57344;
 constexpr int64_t kBandMany = 256;
 constexpr int kBandBlockShift = 5;
