@@ -144,7 +144,7 @@ constexpr int kBandThreads = 256;
 constexpr int kBandElements = 8192;     // elements per workgroup of the collecting pass
 constexpr int kBandsPerPart = kEmitElements / kBandElements;
 struct BandState {  // one per tensor, in a line of its own, because atomics on one line are carried out one
-                    // after the other (9 ns each)
+                    // after the other (9 ns each), and 512 bytes from the next (128: the pass 57 instead of 55 us)
   uint32_t floor_key, ceil_key;  // the band: floor_key < key < ceil_key
   uint32_t above, ties, listed;  // keys at or above ceil_key, keys equal to floor_key, keys inside the band
 };
@@ -154,7 +154,7 @@ constexpr int kNormThreads = 256;
 constexpr int kNormMaxBlocks = 512;
 
 constexpr int kMaxPayloads = 64;
-constexpr size_t kBandStride = 128;
+constexpr size_t kBandStride = 512;
 constexpr size_t kPartEntries = 2 * sizeof(int32_t) * kMaxPayloads;  // bytes of a part's entries in the part table
 static_assert(sizeof(BandState) <= kBandStride && kBandStride <= kPartEntries, "a tensor with a band has a part at least");
 static_assert(kMaxPayloads <= 32768, "a payload's number is packed above a 16-bit index");

@@ -70,9 +70,9 @@ int main(void) {
         if (dgc_recommended_payload_layout(e, densities[d], regions) != DGC_OK) return 23;
       }
       if (dgc_workspace_bytes(e, &plain) != DGC_OK || dgc_workspace_bytes_warmup(e, &staged) != DGC_OK) return 24;
-      if (kind > 0) { /* a slot of 128 bytes for each of three tensors, three words per 64 elements */
+      if (kind > 0) { /* a slot of 512 bytes for each of three tensors, three words per 64 elements */
         const size_t list = plain - without_list;
-        if (list < 3 * 128 + 12 * (size_t)(large[5] / 64) || list > 3 * 128 + 12 * (size_t)(large[5] / 64) + 512) return 25;
+        if (list < 3 * 512 + 12 * (size_t)(large[5] / 64) || list > 3 * 512 + 12 * (size_t)(large[5] / 64) + 512) return 25;
       } else {
         without_list = plain;
       }

@@ -207,7 +207,7 @@ def test_exact_selection_in_a_workspace_without_the_list():
     sampled = B.Dgc(B.make_config(**kw), offsets)
     # what a set without exact selection needs, a slot per tensor above 32768 elements, three words per 64 elements
     extra = sides[0][0].dgc_workspace_bytes() - sampled.dgc_workspace_bytes()
-    assert 4 * 128 + 12 * (n // 64) <= extra <= 4 * 128 + 12 * (n // 64) + 512
+    assert 4 * 512 + 12 * (n // 64) <= extra <= 4 * 512 + 12 * (n // 64) + 512
     for it in range(3):
         g = torch.from_numpy((1e-2 * rng.standard_t(3, n)).astype(np.float32)).cuda()
         sides[0][0].dgc_compress(g, *sides[0][1:3], *sides[0][3], it)
