@@ -1964,7 +1964,7 @@ __global__ __launch_bounds__(kEmitThreads) void emit_sorted_kernel(EmitArgs a) {
 // whole tiles come from the table that the streaming pass has left, not from the mask words; values move four
 // to a lane; the indices of a tile with many selected elements are put in their places in LDS and leave from
 // there four to a lane, too.
-// 122 M elements: 112 us at 25 %, 44 at 1.6 % (136 and 46 with the counts formed from the mask words and every
+// 122 M elements: 112 us at 25 %, 42 at 1.6 % (136 and 46 with the counts formed from the mask words and every
 // index stored where it belongs one by one); placing the indices of sparse tiles through LDS as well: 57 us
 // at 1.6 %.  Holding all eight tiles' values and words in registers took 220 of them and 224 us at 25 %.
 struct EmitStagedShared {

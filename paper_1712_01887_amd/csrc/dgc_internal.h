@@ -128,7 +128,7 @@ constexpr int kSelectInFlight = 8;    // candidates each thread gathers before u
 // and names a band of keys that holds the wanted rank almost surely, collect_band_kernel reads the
 // tensor once, spread over the chip, and lists the keys inside the band, rank_band_kernel ranks them.
 // The list of a tensor takes three words per 64 elements of an area of its own.  On the 161-tensor set of
-// 25.6 M elements the three kernels take 22 + 55 + 12 us at 0.1 % (the reads, 12 bytes per element, at 5.6 TB/s)
+// 25.6 M elements the three kernels take 20 + 55 + 12 us at 0.1 % (the reads, 12 bytes per element, at 5.6 TB/s)
 // and no more than 40 us more at 25 %; three workgroup-wide passes over a whole tensor, which are still the way
 // out when a band misses, took 1385 us.
 constexpr int kBandSample = kSelectRegKeys * kSelectThreads;

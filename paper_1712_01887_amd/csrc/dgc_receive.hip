@@ -338,7 +338,7 @@ __device__ __forceinline__ int merge_slot(const MergeShared<CAP>& sh, int32_t r)
 // THREADS: 512 when there are at most eight payloads (one wavefront searches one payload's region,
 // and four workgroups of eight wavefronts fit a compute unit, LDS included: the 970 ranges of a
 // 122 M-element set then run all at once instead of in two rounds), 1024 otherwise.  Bound by latency, the
-// searches before all: replacing calls at 0.1 % 35.2 us on that set and 24.5 on 25.6 M elements with sixteen
+// searches before all: replacing calls at 0.1 % 35.5 us on that set and 25.0 on 25.6 M elements with sixteen
 // payloads.  (A first round of probes around the place that a range has if pairs are spread evenly took 34.9
 // and 23.7, but 49.1 instead of 39.1 where the pairs crowd three tenths of one large tensor: every workgroup
 // goes on from a bracket of its own, where the first rounds over the whole region read the same few sectors.
@@ -625,7 +625,7 @@ struct ProbeRound {
 // its tensor starts, so one bound per part is searched for).  The probes are what this
 // launch costs (each one a 64-byte sector from HBM: 350 MB with 32 probes per round and
 // two bounds per part), so eight lanes share a search: 8 probes per round, about seven
-// rounds for a region of a million pairs, fewer where a first guess is close: 26.7 us on 122 M elements
+// rounds for a region of a million pairs, fewer where a first guess is close: 25.7 us on 122 M elements
 // at 25 %, 30 with searches over the whole region.  The first round probes around the guess and over the
 // whole region at once, so that a wrong guess (pairs that crowd a part of the tensor) costs no round.
 __global__ __launch_bounds__(kFlatThreads) void locate_parts_kernel(RegionPayloads p, int32_t num_payloads,
@@ -904,8 +904,8 @@ __global__ __launch_bounds__(kPartThreads) void merge_parts_kernel(float* __rest
 
 // The sparse clear at the same densities: the indices of all payloads inside the part
 // are marked in an LDS bitmap and zeros stored where a bit is set, every element once.
-// Bound by memory: 25.6 M elements, sixteen payloads of 6.25 %, 204 MB read (the indices, and the sectors, whose
-// other elements are written back) and 102 MB written in 68 us, 4.5 TB/s; 83 us when the workgroup took one
+// Bound by memory: 25.6 M elements, sixteen payloads of 6.25 %, 209 MB read (the indices, and the sectors, whose
+// other elements are written back) and 102 MB written in 69 us, 4.5 TB/s; 83 us when the workgroup took one
 // payload after the other, four indices per thread in flight.
 struct PartClearShared {
   uint32_t bitmap[kEmitElements / 32];
