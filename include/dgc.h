@@ -240,7 +240,7 @@ dgc_status dgc_compress(dgc_handle* h, const float* g, float* u, float* v, int32
  * loops, harnesses that forbid hipMalloc.  dgc_compress with the workspace argument replaced
  * by an array of 8 MiB that is part of the library (static device memory: every GPU the
  * process uses holds its own copy until the process ends), which serves gradient sets of up
- * to about 30 M elements (the ResNet-50-shaped set needs 6 MiB).  Same arguments, results and
+ * to about 30 M elements (the ResNet-50-shaped set needs 5.4 MiB).  Same arguments, results and
  * errors as dgc_compress otherwise, and
  *   CAPACITY   the handle's tables and scratch exceed the array (dgc_last_error_string says
  *              by how much): use dgc_compress with a workspace of the caller's.  The bound is
