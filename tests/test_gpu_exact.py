@@ -193,27 +193,62 @@ def test_exact_compress_leaves_the_scratch_of_the_receive_side_alone():
 
 
 def test_exact_selection_in_a_workspace_without_the_list():
-    """The static array holds the band lists in the place of the receive side's scratch."""
+    """A workspace of the size that a set without exact selection needs holds the band lists in the place of the
+    receive side's scratch, and so does the static array where the whole does not fit it."""
     import torch
     offsets = np.concatenate([[0], np.cumsum(SIZES)])
     n = int(offsets[-1])
     kw = dict(momentum=0.9, density=0.02, seed=3)
     rng = np.random.default_rng(23)
+    sampled = B.Dgc(B.make_config(**kw), offsets)
+    without = sampled.dgc_workspace_bytes()
     sides = []
-    for _ in range(2):
+    for _ in range(3):
         dgc = B.Dgc(B.make_config(flags=EXACT, **kw), offsets)
         dgc.set_layout(dgc.dgc_recommended_payload_layout(0.02))
         sides.append((dgc, torch.zeros(n, device="cuda"), torch.zeros(n, device="cuda"), dgc.alloc_payload("cuda")))
-    sampled = B.Dgc(B.make_config(**kw), offsets)
-    # what a set without exact selection needs, a slot per tensor above 32768 elements, three words per 64 elements
-    extra = sides[0][0].dgc_workspace_bytes() - sampled.dgc_workspace_bytes()
+    # a slot per tensor above 32768 elements, three words per 64 elements
+    extra = sides[0][0].dgc_workspace_bytes() - without
     assert 4 * 512 + 12 * (n // 64) <= extra <= 4 * 512 + 12 * (n // 64) + 512
+    guard = torch.full((without + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+    sides[1][0].workspace = guard
+    sides[1][0]._ws_ptr = (guard.data_ptr() + 255) // 256 * 256
+    sides[1][0]._ws_bytes = without
     for it in range(3):
         g = torch.from_numpy((1e-2 * rng.standard_t(3, n)).astype(np.float32)).cuda()
-        sides[0][0].dgc_compress(g, *sides[0][1:3], *sides[0][3], it)
-        sides[1][0].dgc_compress_static(g, *sides[1][1:3], *sides[1][3], it)
-        for a, b in zip(sides[0][1:3], sides[1][1:3]):
-            assert torch.equal(a, b), it
-        assert torch.equal(sides[0][3][2], sides[1][3][2]) and torch.equal(sides[0][3][3], sides[1][3][3]), it
-    for dgc in (sides[0][0], sides[1][0], sampled):
+        for dgc, u, v, out in sides[:2]:
+            dgc.dgc_compress(g, u, v, *out, it)
+        sides[2][0].dgc_compress_static(g, *sides[2][1:3], *sides[2][3], it)
+        for side in sides[1:]:
+            for a, b in zip(sides[0][1:3] + sides[0][3][2:], side[1:3] + side[3][2:]):
+                assert torch.equal(a, b), it
+    behind = sides[1][0]._ws_ptr - guard.data_ptr() + without
+    assert bool((guard[behind:] == 0xA5).all())
+    sides[1][0]._ws_bytes = without - 256
+    with pytest.raises(B.DgcError):
+        sides[1][0].dgc_compress(g, *sides[1][1:3], *sides[1][3], 3)
+    for dgc in [side[0] for side in sides] + [sampled]:
         dgc.close()
+
+
+@pytest.mark.parametrize("numel", [25000000])
+def test_exact_selection_of_a_large_set_in_the_static_array(numel):
+    """With its lists the set does not fit the static array, without them it does."""
+    import torch
+    offsets = np.array([0, 40001, numel - 70003, numel])
+    kw = dict(momentum=0.9, density=0.001, seed=5)
+    dgc = [B.Dgc(B.make_config(flags=EXACT, **kw), offsets) for _ in range(2)]
+    assert dgc[0].dgc_workspace_bytes() > 8 << 20 > B.Dgc(B.make_config(**kw), offsets).dgc_workspace_bytes()
+    results = []
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    g = torch.randn(numel, device="cuda", generator=gen)
+    for k, d in enumerate(dgc):
+        d.set_layout(d.dgc_recommended_payload_layout(0.001))
+        u, v, out = torch.zeros(numel, device="cuda"), torch.zeros(numel, device="cuda"), d.alloc_payload("cuda")
+        for it in range(2):
+            (d.dgc_compress_static if k else d.dgc_compress)(g, u, v, *out, it)
+        results.append((u, v, out[2], out[3]))
+        d.close()
+    for a, b in zip(*results):
+        assert torch.equal(a, b)
