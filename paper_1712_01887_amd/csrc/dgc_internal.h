@@ -84,8 +84,7 @@ static_assert((kMergeMaxRange / 128) % kMergeMaxThreads == 0, "dealt evenly to t
 // Receive side at warm-up densities: a workgroup owns one emit workgroup's part and keeps
 // the whole range of the dense vector in LDS.
 constexpr int kPartThreads = 1024;
-constexpr int kPartPer = 4;  // pairs a thread holds per round (8: 5 to 15 % slower at every warm-up density; 2: slower at 25 %)
-constexpr int kPartRound = kPartThreads * kPartPer;
+constexpr int kPartChunk = 256;  // slots of a payload a wavefront takes at a time, four consecutive ones to a lane
 constexpr int kPartClearThreads = 256;
 constexpr int kPartClearLoads = 4;  // loads of four indices a lane has on their way
 static_assert(kEmitElements <= 65536 && kEmitElements % kPartThreads == 0 &&
@@ -370,7 +369,7 @@ hipError_t launch_merge_regions(float* dense, const RegionPayloads& p, int32_t n
                                 int32_t num_blocks, int64_t expected_pairs, bool scaled, float scale,
                                 hipStream_t stream);
 hipError_t launch_merge_parts(float* dense, const RegionPayloads& p, int32_t num, const int64_t* out_offsets_dev,
-                              const MergeBlock* parts, int32_t num_parts, void* found, bool replace, bool scaled,
+                              int64_t capacity, const MergeBlock* parts, int32_t num_parts, void* found, bool replace, bool scaled,
                               float scale, hipStream_t stream);
 hipError_t launch_clear_parts(float* dense, const RegionPayloads& p, int32_t num, const int64_t* out_offsets_dev,
                               const MergeBlock* parts, int32_t num_parts, void* found, hipStream_t stream);

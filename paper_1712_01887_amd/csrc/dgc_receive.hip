@@ -612,11 +612,6 @@ struct ProbeRound {
 // payloads of 1.6 %), the pairs are read once, coalesced, and the sums are those of the
 // plain definition, bit for bit.
 //
-// The pairs are taken a round at a time: up to kPartRound consecutive pairs of one
-// payload, kPartPer per thread, with the loads of the next two rounds in flight.  Pairs
-// of one payload have distinct indices and are added without synchronisation; a
-// barrier separates one payload from the next.
-//
 // At these densities a region holds up to millions of pairs and the search for a part's
 // pairs is several rounds of dependent loads: with one workgroup per compute unit (the
 // accumulator fills LDS) nothing else would run meanwhile.  So the searches of all parts
@@ -643,6 +638,7 @@ __global__ __launch_bounds__(kFlatThreads) void locate_parts_kernel(RegionPayloa
   const int b = (int)(wave_id % waves_per_payload) * 7 + group;
   const bool valid = w < num_payloads && b < num_blocks;
   MergeBlock blk{};
+  int64_t region = 0;
   const int32_t* __restrict__ list = nullptr;
   int32_t x = 0;
   int lo = 0, hi = 0;  // the answer lies in [lo, hi]
@@ -650,7 +646,7 @@ __global__ __launch_bounds__(kFlatThreads) void locate_parts_kernel(RegionPayloa
   bool last = true;    // the tensor's last part: it ends where the region's pairs end
   if (valid) {
     blk = blocks[b];
-    const int64_t region = out_offsets[blk.tensor];
+    region = out_offsets[blk.tensor];
     const int64_t cap = out_offsets[blk.tensor + 1] - region;
     int64_t c = p.counts[w][blk.tensor];
     if (c > cap) c = cap;
@@ -693,47 +689,39 @@ __global__ __launch_bounds__(kFlatThreads) void locate_parts_kernel(RegionPayloa
   const int next_lo = __shfl(lo, (lane + 8) & 63);  // of the part after this one (group 7 does not use it)
   if (valid && group < 7 && sub == 0) {
     const int end = last ? cnt : next_lo;
-    found[(int64_t)b * num_payloads + w] = make_int2(lo, end > lo ? end - lo : 0);
+    found[(int64_t)b * num_payloads + w] = make_int2((int)region + lo, end > lo ? end - lo : 0);
   }
 }
-
-// Fills begin[], idx_at[] and val_at[] from that table; returns the number of pairs.
-template <typename Shared>
-__device__ __forceinline__ int located_pairs(Shared& sh, const RegionPayloads& p, int32_t num_payloads, int64_t region,
-                                             const int2* __restrict__ found, int part, int tid) {
-  if (tid < num_payloads) {
-    const int2 f = found[(int64_t)part * num_payloads + tid];
-    sh.idx_at[tid] = p.idx[tid] + region + f.x;
-    sh.val_at[tid] = p.val[tid] ? p.val[tid] + region + f.x : nullptr;
-    sh.begin[tid + 1] = f.y;  // length for now
-  }
-  __syncthreads();
-  if (tid < 64) begins_from_lengths(sh.begin, num_payloads, tid);
-  __syncthreads();
-  return sh.begin[num_payloads];
-}
-
-struct PartShared {
-  alignas(16) float acc[kEmitElements];
-  int32_t begin[kMaxPayloads + 1];  // number of pairs of the payloads before w inside the range
-  const int32_t* idx_at[kMaxPayloads];  // payload w's first pair inside the range
-  const float* val_at[kMaxPayloads];
-};
 
 // REPLACE: `dense` becomes the sum of the payloads: the accumulator starts from zero instead of
 // the range of `dense`, and every range is written, also one that no pair falls into.
+//
+// The pairs of a part are taken in chunks of kPartChunk slots, a wavefront each and four consecutive slots to a
+// lane, that start on 128-byte lines of the payload's index array (the slots before its first pair and behind its
+// last stay empty).  Two things bounded the kernel before: loads of a pair per lane that straddled lines (a bare
+// read of eight payloads' pairs, 1.95 GB in parts of 8192: 284 us in whole lines, 338 half a line off), and
+// instructions, sixteen wavefronts on four SIMDs (chunks of one pair per lane, lines or not: 535 us at 25 %).
+// A round is a chunk for every wavefront, of one payload or of several in their order, and only a change of
+// payload needs a barrier (the indices of one payload are distinct).  While a round is added, the next two are on
+// their way, those of the next part included, so that neither the write-back nor the table look-up leaves the
+// memory pipeline of the unit empty.  122 M elements, eight payloads: 497 -> 426 us at 25 % (2.56 GB, 6.0 TB/s),
+// 242 -> 195 at 1.6 % as the SGD apply (1.1 GB, 5.6 TB/s); 25.6 M elements, sixteen payloads of 6.25 %: 103 -> 95,
+// where 933 parts leave a fourth round of workgroups two thirds full.  Three rounds on their way: 442, 194, 100.
 template <bool REPLACE>
 __global__ __launch_bounds__(kPartThreads) void merge_parts_kernel(float* __restrict__ dense, RegionPayloads p,
-                                                                   int32_t num_payloads,
-                                                                   const int64_t* __restrict__ out_offsets,
+                                                                   int32_t num_payloads, int32_t capacity,
                                                                    const MergeBlock* __restrict__ blocks,
                                                                    int32_t num_blocks,
                                                                    const int2* __restrict__ found, float scale,
                                                                    int32_t scaled) {
   typedef float fvec4u __attribute__((ext_vector_type(4), aligned(4)));  // a range starts anywhere
+  typedef int32_t ivec4 __attribute__((ext_vector_type(4)));
   constexpr int kQuads = kEmitElements / 4 / kPartThreads;
-  __shared__ PartShared sh;
+  constexpr int kWaves = kPartThreads / 64;
+  __shared__ alignas(16) float acc[kEmitElements + 64];  // behind the range a word per lane for what is no pair of it
   const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // four consecutive elements of a range of `len`, from element 4 * (tid + i * kPartThreads) on
   auto load_quad = [&](const float* src, int32_t len, int i) {
     const int e = 4 * (tid + i * kPartThreads);
@@ -757,148 +745,185 @@ __global__ __launch_bounds__(kPartThreads) void merge_parts_kernel(float* __rest
         if (e + c < len) to[e + c] = y[c];
     }
   };
+  auto put_quad = [&](int i, const fvec4u& y) {
+    *reinterpret_cast<float4*>(&acc[4 * (tid + i * kPartThreads)]) = make_float4(y[0], y[1], y[2], y[3]);
+  };
+
   // The accumulator fills LDS, so a workgroup is alone on its compute unit: the grid is one
-  // workgroup per compute unit and every workgroup takes parts b, b + grid, ...; the range of
-  // the next part is requested before the finished one is written back, so that neither
-  // the write-back nor the table look-up leaves the memory pipeline of the unit empty.
+  // workgroup per compute unit and every workgroup takes parts b, b + grid, ...
   int b = blockIdx.x;
   if (b >= num_blocks) return;
-  MergeBlock blk = blocks[b];
-  fvec4u d[kQuads];
-#pragma unroll
-  for (int i = 0; i < kQuads; ++i) d[i] = load_quad(dense + blk.begin, REPLACE ? 0 : (int32_t)(blk.end - blk.begin), i);
-  for (;;) {
-    const int next_b = b + (int)gridDim.x;
-    const bool more = next_b < num_blocks;
-    const MergeBlock next = blocks[more ? next_b : b];
-    const int32_t length = (int32_t)(blk.end - blk.begin);  // <= kEmitElements
-    float* __restrict__ range = dense + blk.begin;
-    const int total = located_pairs(sh, p, num_payloads, out_offsets[blk.tensor], found, b, tid);
-    if (total > 0) {
-#pragma unroll
-      for (int k = 0; k < kQuads; ++k) *reinterpret_cast<float4*>(&sh.acc[4 * (tid + k * kPartThreads)]) = make_float4(d[k][0], d[k][1], d[k][2], d[k][3]);
+  const int step = (int)gridDim.x;
 
-      if (total <= kPartRound) {
-        // Few pairs (many payloads of a low density): all of them at once, whatever payload they
-        // belong to, so that their loads are one wait; then payload after payload from registers.
-        int32_t at[kPartPer];  // payload << 16 | index relative to the range; -1: none
-        float x[kPartPer];
+  // Lane w looks after payload w.
+  const int32_t* const idx_of = lane < num_payloads ? p.idx[lane] : nullptr;
+  const float* const val_of = lane < num_payloads ? p.val[lane] : nullptr;
+  auto entry_of = [&](int part) {
+    return part < num_blocks && lane < num_payloads ? found[(int64_t)part * num_payloads + lane] : make_int2(0, 0);
+  };
+  struct Table {                // of the part that is being fetched
+    const int32_t* idx;         // the lane's payload: start of the line that holds its first pair of the part
+    const float* val;           // ... the value beside it
+    int32_t pos;                // ... its place in the payload's arrays (may lie up to 31 before them)
+    int head, end;              // its pairs are in slots [head, end) from there
+    uint32_t chunk0;            // its first chunk among the part's
+    uint32_t total;             // chunks of the part
+  };
+  auto make_table = [&](const int2& f) {
+    Table t;
+    t.idx = idx_of + f.x;
+    t.head = (int)((reinterpret_cast<uintptr_t>(t.idx) >> 2) & 31u);
+    t.idx -= t.head;
+    t.pos = f.x - t.head;
+    t.val = val_of + f.x - t.head;
+    t.end = t.head + f.y;
+    const uint32_t own = f.y > 0 ? (uint32_t)(t.end + kPartChunk - 1) / (uint32_t)kPartChunk : 0u;
+    const uint32_t upto = wave_inclusive_sum(own);
+    t.total = wave_last(upto);
+    t.chunk0 = lane < num_payloads ? upto - own : 0xFFFFFFFFu;
+    return t;
+  };
+  auto payload_at = [&](const Table& t, uint32_t chunk) { return __popcll(__ballot(t.chunk0 <= chunk)) - 1; };
+  auto of_lane = [&](uint64_t x, int w) {
+    return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, w) |
+           (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), w) << 32;
+  };
+
+  struct Round {
+    ivec4 idx;
+    fvec4u x;
+    int w;              // payload of the wavefront's chunk; -1: none
+    int first, last;    // payloads of the whole round
+    int part;           // -1: there is no round
+  };
+  int fb = b;            // the part that is being fetched
+  Table t = make_table(entry_of(b));
+  int2 next_entry = entry_of(b + step);
+  uint32_t cursor = 0;   // next chunk of it
+  auto fetch = [&](Round& L) {
+    while (cursor >= t.total && fb + step < num_blocks) {
+      fb += step;
+      t = make_table(next_entry);
+      next_entry = entry_of(fb + step);
+      cursor = 0;
+    }
+    L.part = -1;
+    if (cursor >= t.total) return;
+    L.part = fb;
+    const uint32_t until = t.total - cursor < (uint32_t)kWaves ? t.total : cursor + (uint32_t)kWaves;
+    L.first = payload_at(t, cursor);
+    L.last = payload_at(t, until - 1u);
+    const uint32_t c = cursor + (uint32_t)wave;
+    cursor = until;
+    L.w = -1;
+    if (c >= until) return;  // uniform
+    const int w = payload_at(t, c);
+    L.w = w;
+    const int slot0 = (int)(c - (uint32_t)__builtin_amdgcn_readlane((int)t.chunk0, w)) * kPartChunk;
+    const int slot = slot0 + 4 * lane;
+    const int head = __builtin_amdgcn_readlane(t.head, w), end = __builtin_amdgcn_readlane(t.end, w);
+    const int32_t* __restrict__ from = reinterpret_cast<const int32_t*>(of_lane(reinterpret_cast<uint64_t>(t.idx), w));
+    const float* __restrict__ values = reinterpret_cast<const float*>(of_lane(reinterpret_cast<uint64_t>(t.val), w));
+    if (slot0 >= head && slot0 + kPartChunk <= end) {
+      L.idx = __builtin_nontemporal_load(reinterpret_cast<const ivec4*>(from + slot));
+      L.x = __builtin_nontemporal_load(reinterpret_cast<const fvec4u*>(values + slot));
+    } else {
+      // Slots before the first pair and behind the last hold other parts' pairs, or nothing that matters: a
+      // four that has any of the part's is loaded whole if all of it lies inside the arrays.
+      L.idx = ivec4{INT32_MIN, INT32_MIN, INT32_MIN, INT32_MIN};  // outside every range
+      L.x = fvec4u{0.0f, 0.0f, 0.0f, 0.0f};
+      const int32_t pos = __builtin_amdgcn_readlane(t.pos, w) + slot;
+      if (slot + 4 > head && slot < end) {
+        if (pos >= 0 && pos + 4 <= capacity) {
+          const ivec4 y = __builtin_nontemporal_load(reinterpret_cast<const ivec4*>(from + slot));
+          L.x = __builtin_nontemporal_load(reinterpret_cast<const fvec4u*>(values + slot));
 #pragma unroll
-        for (int k = 0; k < kPartPer; ++k) {
-          const int q = tid + k * kPartThreads;
-          at[k] = -1;
-          x[k] = 0.0f;
-          if (q < total) {
-            const int w = payload_of(sh.begin, num_payloads, q);
-            const int src = q - sh.begin[w];
-            const int64_t r = (int64_t)__builtin_nontemporal_load(sh.idx_at[w] + src) - blk.begin;
-            const float value = __builtin_nontemporal_load(sh.val_at[w] + src);
-            x[k] = scaled ? scale * value : value;
-            if (r >= 0 && r < length) at[k] = (int32_t)r | (w << 16);  // anything else: a foreign region
+          for (int k = 0; k < 4; ++k) L.idx[k] = slot + k >= head && slot + k < end ? y[k] : INT32_MIN;
+        } else {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            if (slot + k >= head && slot + k < end) {
+              L.idx[k] = from[slot + k];
+              L.x[k] = values[slot + k];
+            }
           }
         }
-        __syncthreads();  // the accumulator is filled
-        for (int w = 0; w < num_payloads; ++w) {  // payloads in the order given
-          if (sh.begin[w + 1] == sh.begin[w]) continue;
-          float sum[kPartPer];
+      }
+    }
+  };
+
+  Round A, B;
+  bool a_next = true;  // which of the two is added next
+  fetch(A);
+  fetch(B);
+  MergeBlock blk = blocks[b];
+  {
+    fvec4u d[kQuads];
 #pragma unroll
-          for (int k = 0; k < kPartPer; ++k)
-            sum[k] = (at[k] >= 0 && (at[k] >> 16) == w) ? sh.acc[at[k] & 0xFFFF] + x[k] : 0.0f;
+    for (int i = 0; i < kQuads; ++i) d[i] = load_quad(dense + blk.begin, REPLACE ? 0 : (int32_t)(blk.end - blk.begin), i);
 #pragma unroll
-          for (int k = 0; k < kPartPer; ++k)
-            if (at[k] >= 0 && (at[k] >> 16) == w) sh.acc[at[k] & 0xFFFF] = sum[k];
-          __syncthreads();
-        }
-      } else {
-      // A round: up to kPartRound consecutive pairs of one payload.  Two rounds are on their way
-      // while a third is added, and nothing in fetch() depends on the loaded words.
-      struct Loaded {
-        int32_t idx[kPartPer];
-        float x[kPartPer];
-        int w;  // payload
-        int n;  // pairs of the round; 0: there is no further round
-      };
-      int cursor_w = 0, cursor_at = 0;  // next pair to fetch: payload, position among its pairs inside the range
-      auto fetch = [&](Loaded& L) {
-        L.n = 0;
-        L.w = 0;
-        while (cursor_w < num_payloads) {
-          const int len = sh.begin[cursor_w + 1] - sh.begin[cursor_w];
-          if (cursor_at < len) break;
-          ++cursor_w;
-          cursor_at = 0;
-        }
-        if (cursor_w >= num_payloads) return;
-        const int left = sh.begin[cursor_w + 1] - sh.begin[cursor_w] - cursor_at;
-        L.w = cursor_w;
-        L.n = left < kPartRound ? left : kPartRound;
-        const int32_t* __restrict__ ip = sh.idx_at[cursor_w] + cursor_at;
-        const float* __restrict__ vp = sh.val_at[cursor_w] + cursor_at;
-        cursor_at += L.n;
+    for (int i = 0; i < kQuads; ++i) put_quad(i, d[i]);
+  }
+  for (;;) {
+    const bool more = b + step < num_blocks;
+    const MergeBlock next = blocks[more ? b + step : b];
+    const uint32_t begin = (uint32_t)blk.begin;
+    const uint32_t length = (uint32_t)(blk.end - blk.begin);  // <= kEmitElements
+    bool any = false;
+    int last_w = -1;
+    // Adds the round in L and refills L with the next round to fetch.
+    auto add = [&](Round& L) {
+      uint32_t at[4];
+      float x[4];
 #pragma unroll
-        for (int k = 0; k < kPartPer; ++k) {
-          const int q = tid + k * kPartThreads;
-          L.idx[k] = 0;
-          L.x[k] = 0.0f;
-          if (q < L.n) {
-            L.idx[k] = __builtin_nontemporal_load(ip + q);
-            L.x[k] = __builtin_nontemporal_load(vp + q);
-          }
-        }
-      };
-      int last_w = -1;
-      // Adds the round in L and refills L with the next round to fetch.
-      auto add = [&](Loaded& L) {
-        int32_t at[kPartPer];  // index relative to the range; -1: none
-        float x[kPartPer];
-#pragma unroll
-        for (int k = 0; k < kPartPer; ++k) {
-          const int64_t r = (int64_t)L.idx[k] - blk.begin;
-          // an index outside the range can only come from a foreign region
-          at[k] = (tid + k * kPartThreads < L.n && r >= 0 && r < length) ? (int32_t)r : -1;
-          x[k] = scaled ? scale * L.x[k] : L.x[k];
-        }
-        const int w = L.w;
-        fetch(L);
-        if (w != last_w) __syncthreads();  // the payload before is added (the first time: the accumulator is filled)
+      for (int k = 0; k < 4; ++k) {
+        const uint32_t r = (uint32_t)L.idx[k] - begin;
+        at[k] = r < length ? r : (uint32_t)(kEmitElements + lane);  // not a pair of the part, or of a foreign region
+        x[k] = scaled ? scale * L.x[k] : L.x[k];
+      }
+      const int first = L.first, last = L.last, own = L.w;
+      fetch(L);
+      for (int w = first; w <= last; ++w) {  // payloads in the order given
+        if (w != last_w) __syncthreads();    // the payload before is added (the first time: the accumulator is filled)
         last_w = w;
-        // the indices of one payload are distinct: all reads, then all writes, no barrier between its rounds
-        float sum[kPartPer];
+        if (own == w) {
+          // the indices of one payload are distinct: all reads, then all writes, no barrier between its rounds
+          float sum[4];
 #pragma unroll
-        for (int k = 0; k < kPartPer; ++k) sum[k] = at[k] >= 0 ? sh.acc[at[k]] + x[k] : 0.0f;
+          for (int k = 0; k < 4; ++k) sum[k] = acc[at[k]] + x[k];
 #pragma unroll
-        for (int k = 0; k < kPartPer; ++k)
-          if (at[k] >= 0) sh.acc[at[k]] = sum[k];
-      };
-      Loaded A, B;
-      fetch(A);
-      fetch(B);
-      for (;;) {
-        if (A.n == 0) break;
+          for (int k = 0; k < 4; ++k) acc[at[k]] = sum[k];
+        }
+      }
+    };
+    for (;;) {
+      if (a_next) {
+        if (A.part != b) break;
         add(A);
-        if (B.n == 0) break;
+      } else {
+        if (B.part != b) break;
         add(B);
       }
-      __syncthreads();
-      }
+      a_next = !a_next;
+      any = true;
     }
-    // (every d[i] is assigned anew: the old values must not stay alive through the rounds above)
+    // The range is written, and the accumulator takes the next part's: every thread its own elements.
+    fvec4u d[kQuads];
 #pragma unroll
     for (int i = 0; i < kQuads; ++i) d[i] = load_quad(dense + next.begin, (more && !REPLACE) ? (int32_t)(next.end - next.begin) : 0, i);
-    if (total > 0) {
+    __syncthreads();
+    float* __restrict__ range = dense + blk.begin;
 #pragma unroll
-      for (int k = 0; k < kQuads; ++k) {
-        const float4 y = *reinterpret_cast<const float4*>(&sh.acc[4 * (tid + k * kPartThreads)]);
-        store_quad(range, length, k, fvec4u{y.x, y.y, y.z, y.w});
-      }
-    } else if (REPLACE) {
-#pragma unroll
-      for (int k = 0; k < kQuads; ++k) store_quad(range, length, k, fvec4u{0.0f, 0.0f, 0.0f, 0.0f});
+    for (int k = 0; k < kQuads; ++k) {
+      const float4 y = *reinterpret_cast<const float4*>(&acc[4 * (tid + k * kPartThreads)]);
+      if (REPLACE || any) store_quad(range, (int32_t)length, k, fvec4u{y.x, y.y, y.z, y.w});
     }
     if (!more) break;
-    b = next_b;
+#pragma unroll
+    for (int k = 0; k < kQuads; ++k) put_quad(k, d[k]);
+    b += step;
     blk = next;
-    __syncthreads();  // the accumulator and the tables are free again
+    // (no barrier here: the first payload of the next part comes behind one)
   }
 }
 
@@ -907,41 +932,35 @@ __global__ __launch_bounds__(kPartThreads) void merge_parts_kernel(float* __rest
 // Bound by memory: 25.6 M elements, sixteen payloads of 6.25 %, 209 MB read (the indices, and the sectors, whose
 // other elements are written back) and 102 MB written in 69 us, 4.5 TB/s; 83 us when the workgroup took one
 // payload after the other, four indices per thread in flight.
-struct PartClearShared {
-  uint32_t bitmap[kEmitElements / 32];
-  int32_t begin[kMaxPayloads + 1];
-  const int32_t* idx_at[kMaxPayloads];
-  const float* val_at[kMaxPayloads];
-};
-
 __global__ __launch_bounds__(kPartClearThreads) void clear_parts_kernel(float* __restrict__ dense, RegionPayloads p,
                                                                         int32_t num_payloads,
-                                                                        const int64_t* __restrict__ out_offsets,
                                                                         const MergeBlock* __restrict__ blocks,
                                                                         const int2* __restrict__ found) {
   constexpr int kWords = kEmitElements / 32 / kPartClearThreads;
-  __shared__ PartClearShared sh;
+  __shared__ uint32_t bitmap[kEmitElements / 32];
   const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const MergeBlock blk = blocks[blockIdx.x];
-  const int j = blk.tensor;
-  const int64_t region = out_offsets[j];
   const int32_t length = (int32_t)(blk.end - blk.begin);
+  // lane w looks after payload w
+  const int2 entry = lane < num_payloads ? found[(int64_t)blockIdx.x * num_payloads + lane] : make_int2(0, 0);
 #pragma unroll
-  for (int k = 0; k < kWords; ++k) sh.bitmap[tid + k * kPartClearThreads] = 0;
-  const int total = located_pairs(sh, p, num_payloads, region, found, (int)blockIdx.x, tid);
-  if (total == 0) return;
+  for (int k = 0; k < kWords; ++k) bitmap[tid + k * kPartClearThreads] = 0;
+  if (__ballot(entry.y > 0) == 0) return;  // the same in every wavefront
+  __syncthreads();
   // A wavefront takes payloads w, w + waves, ...: the order does not matter here, and no barrier separates
   // them.  Sixteen indices per lane are on their way at a time.
   {
-    const int lane = tid & 63;
     typedef int32_t vec4u __attribute__((ext_vector_type(4), aligned(4)));
     auto mark = [&](int32_t i) {
       const int64_t rr = (int64_t)i - blk.begin;  // outside the range: a foreign region
-      if (rr >= 0 && rr < length) atomicOr(&sh.bitmap[rr >> 5], 1u << (rr & 31));
+      if (rr >= 0 && rr < length) atomicOr(&bitmap[rr >> 5], 1u << (rr & 31));
     };
-    for (int w = tid >> 6; w < num_payloads; w += kPartClearThreads / 64) {
-      const int n = sh.begin[w + 1] - sh.begin[w];
-      const int32_t* __restrict__ ip = sh.idx_at[w];
+    for (int w = wave; w < num_payloads; w += kPartClearThreads / 64) {
+      const int n = __builtin_amdgcn_readlane(entry.y, w);
+      if (n == 0) continue;
+      const int32_t* __restrict__ ip = p.idx[w] + __builtin_amdgcn_readlane(entry.x, w);
       const int quads = n >> 2;
       for (int first = lane; first < quads; first += 64 * kPartClearLoads) {
         vec4u r[kPartClearLoads];
@@ -969,33 +988,35 @@ __global__ __launch_bounds__(kPartClearThreads) void clear_parts_kernel(float* _
   // 16 bytes first unless all of them are cleared.
   const bool aligned = ((reinterpret_cast<uintptr_t>(range) & 15) == 0);
   if (aligned) {
+    typedef float fvec4 __attribute__((ext_vector_type(4)));
     constexpr int kGroups = kEmitElements / 4 / kPartClearThreads;
     constexpr int kBatch = 8;
     for (int i0 = 0; i0 < kGroups; i0 += kBatch) {
       uint32_t nib[kBatch];
       bool touch[kBatch];  // the lane's sector has an element to clear
-      float4 old[kBatch];
+      fvec4 old[kBatch];
 #pragma unroll
       for (int i = 0; i < kBatch; ++i) {
         const int e4 = tid + (i0 + i) * kPartClearThreads;
         const int e = e4 * 4;
-        const uint32_t word = e < length ? sh.bitmap[e4 >> 3] : 0u;
+        const uint32_t word = e < length ? bitmap[e4 >> 3] : 0u;
         nib[i] = (word >> ((e4 & 7) * 4)) & 15u;
         touch[i] = ((word >> ((e4 & 4) * 4)) & 0xFFFFu) != 0;
-        old[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        if (touch[i] && nib[i] != 15u && e + 4 <= length) old[i] = *reinterpret_cast<const float4*>(range + e);
+        old[i] = fvec4{0.0f, 0.0f, 0.0f, 0.0f};
+        if (touch[i] && nib[i] != 15u && e + 4 <= length) old[i] = *reinterpret_cast<const fvec4*>(range + e);
+
       }
 #pragma unroll
       for (int i = 0; i < kBatch; ++i) {
         if (!touch[i]) continue;
         const int e = (tid + (i0 + i) * kPartClearThreads) * 4;
         if (e + 4 <= length) {
-          float4 v = old[i];
-          if (nib[i] & 1u) v.x = 0.0f;
-          if (nib[i] & 2u) v.y = 0.0f;
-          if (nib[i] & 4u) v.z = 0.0f;
-          if (nib[i] & 8u) v.w = 0.0f;
-          *reinterpret_cast<float4*>(range + e) = v;
+          fvec4 v = old[i];
+#pragma unroll
+          for (int c = 0; c < 4; ++c)
+            if ((nib[i] >> c) & 1u) v[c] = 0.0f;
+          *reinterpret_cast<fvec4*>(range + e) = v;
+
         } else {  // the last, incomplete group of the range
 #pragma unroll
           for (int b = 0; b < 4; ++b)
@@ -1005,7 +1026,7 @@ __global__ __launch_bounds__(kPartClearThreads) void clear_parts_kernel(float* _
     }
   } else {
     for (int e4 = tid; e4 * 4 < length; e4 += kPartClearThreads) {
-      const uint32_t nib = (sh.bitmap[e4 >> 3] >> ((e4 & 7) * 4)) & 15u;
+      const uint32_t nib = (bitmap[e4 >> 3] >> ((e4 & 7) * 4)) & 15u;
       const int e = e4 * 4;
 #pragma unroll
       for (int b = 0; b < 4; ++b)
@@ -1079,7 +1100,7 @@ static void launch_locate_parts(const RegionPayloads& p, int32_t num, const int6
 }
 
 hipError_t launch_merge_parts(float* dense, const RegionPayloads& p, int32_t num, const int64_t* out_offsets_dev,
-                              const MergeBlock* parts, int32_t num_parts, void* found, bool replace, bool scaled,
+                              int64_t capacity, const MergeBlock* parts, int32_t num_parts, void* found, bool replace, bool scaled,
                               float scale, hipStream_t stream) {
   if (num <= 0 || num_parts <= 0) return hipSuccess;
   launch_locate_parts(p, num, out_offsets_dev, parts, num_parts, static_cast<int2*>(found), stream);
@@ -1093,10 +1114,10 @@ hipError_t launch_merge_parts(float* dense, const RegionPayloads& p, int32_t num
   const int grid = num_parts < compute_units ? num_parts : compute_units;
   if (replace)
     hipLaunchKernelGGL(merge_parts_kernel<true>, dim3((unsigned)grid), dim3(kPartThreads), 0, stream, dense, p, num,
-                       out_offsets_dev, parts, num_parts, static_cast<const int2*>(found), scale, scaled ? 1 : 0);
+                       (int32_t)capacity, parts, num_parts, static_cast<const int2*>(found), scale, scaled ? 1 : 0);
   else
     hipLaunchKernelGGL(merge_parts_kernel<false>, dim3((unsigned)grid), dim3(kPartThreads), 0, stream, dense, p, num,
-                       out_offsets_dev, parts, num_parts, static_cast<const int2*>(found), scale, scaled ? 1 : 0);
+                       (int32_t)capacity, parts, num_parts, static_cast<const int2*>(found), scale, scaled ? 1 : 0);
   return hipGetLastError();
 }
 
@@ -1105,7 +1126,7 @@ hipError_t launch_clear_parts(float* dense, const RegionPayloads& p, int32_t num
   if (num <= 0 || num_parts <= 0) return hipSuccess;
   launch_locate_parts(p, num, out_offsets_dev, parts, num_parts, static_cast<int2*>(found), stream);
   hipLaunchKernelGGL(clear_parts_kernel, dim3((unsigned)num_parts), dim3(kPartClearThreads), 0, stream, dense, p, num,
-                     out_offsets_dev, parts, static_cast<const int2*>(found));
+                     parts, static_cast<const int2*>(found));
   return hipGetLastError();
 }
 
