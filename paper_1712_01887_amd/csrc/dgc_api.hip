@@ -700,7 +700,6 @@ dgc_status dgc_compress(dgc_handle* h, const float* g, float* u, float* v, int32
   const bool factor_masking = (c.flags & DGC_FLAG_NO_FACTOR_MASKING) == 0;
   const bool staged = c.density > kStagedMinDensity && c.refine_alpha <= 0.0f && workspace_bytes >= h->lay.total_staged;
   ta.factor_masking = factor_masking ? 1 : 0;
-  const bool sorted = (c.flags & DGC_FLAG_SORTED_OUTPUT) != 0;
   // At the densities the method runs at (Section 4.1: 99.9 % sparsity after the warm-up) a tile holds
   // one or two selected elements: the streaming pass parks them in the tile's slots and masks u and v
   // itself, and the emit pass copies, in index order.
@@ -751,7 +750,7 @@ dgc_status dgc_compress(dgc_handle* h, const float* g, float* u, float* v, int32
   ea.stage_v = ta.stage_v;
   ea.stage_u = ta.stage_u;
   ea.slotted = ta.slotted;
-  if (!hip_ok(launch_emit(ea, (int32_t)h->emit_blocks.size(), sorted, stream), "launch emit kernel"))
+  if (!hip_ok(launch_emit(ea, (int32_t)h->emit_blocks.size(), stream), "launch emit kernel"))
     return DGC_ERR_HIP;
   if (ev && !hip_ok(hipEventRecord(ev[4], stream), "record event")) return DGC_ERR_HIP;
   return DGC_OK;

@@ -1670,11 +1670,9 @@ __global__ __launch_bounds__(kRefineThreads) void refine_kernel(RefineArgs a) {
 //
 // The streaming pass has left the number of mask bits of every tile; a workgroup starts
 // after the sum over the tensor's tiles before its own, so the workgroups' parts follow
-// each other in index order and the region is the same on every run.  Inside its part a
-// workgroup places its elements
-//   plain   in the order wavefront, lane, tile, bit (whatever is cheapest), or
-//   sorted  in index order (DGC_FLAG_SORTED_OUTPUT): the whole region ascends, and a
-//           full region keeps the lowest indices.
+// each other in index order and the region is the same on every run.  Inside its part, too, a
+// workgroup places its elements in index order: the whole region ascends, and a full region keeps
+// the lowest indices, whether or not DGC_FLAG_SORTED_OUTPUT asks for it.
 // (A first version reserved slots with one atomic per workgroup in order of arrival; the
 // receive side can find a range of elements in a region by search only if the parts are
 // in order.)
@@ -1696,493 +1694,184 @@ __device__ __forceinline__ uint32_t tensor_tile_word(const uint16_t* __restrict_
   return w;
 }
 
-// Moves the `in_win` elements listed in `list` to slots slot0, slot0 + 1, ... of the
-// tensor's region [region, region + cap): reads v', writes the pair, clears v and u.
-// Returns true if some element found the region full.
-__device__ __forceinline__ bool emit_move(const EmitArgs& a, const int32_t* list, int in_win, int64_t slot0,
-                                          int64_t region, int64_t cap) {
-  float* __restrict__ u = a.u;
-  float* __restrict__ v = a.v;
-  int32_t* __restrict__ out_idx = a.out_idx;
-  float* __restrict__ out_val = a.out_val;
-  bool overflow = false;
-  for (int p0 = threadIdx.x; p0 < in_win; p0 += 4 * kEmitThreads) {
-    int32_t e[4];
-    float x[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int p = p0 + k * kEmitThreads;
-      e[k] = p < in_win ? list[p] : -1;
-      if (e[k] >= 0 && slot0 + p >= cap) {  // region full: leave the element where it is
-        e[k] = -1;
-        overflow = true;
-      }
-      x[k] = e[k] >= 0 ? v[e[k]] : 0.0f;
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      if (e[k] >= 0) {
-        const int64_t slot = slot0 + p0 + k * kEmitThreads;
-        out_idx[region + slot] = e[k];
-        out_val[region + slot] = x[k];
-        v[e[k]] = 0.0f;
-        if (a.factor_masking) u[e[k]] = 0.0f;
-      }
-    }
-  }
-  return overflow;
-}
-
-__global__ __launch_bounds__(kEmitThreads) void emit_kernel(EmitArgs a) {
-  constexpr int kWaves = kEmitThreads / 64;
-  constexpr int kPerWave = kEmitTiles / kWaves;
-  __shared__ int wave_tot[kWaves];
-  __shared__ int pre_tot[kWaves];
-  __shared__ int32_t list[kEmitList];
-
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  const EmitBlock blk = a.blocks[blockIdx.x];
-  const int j = blk.tensor;
-  const int64_t region = a.out_offsets[j];  // asked for early: needed late
-  const int64_t cap = a.out_offsets[j + 1] - region;
-  const int64_t lo = blk.lo;
-  const int64_t hi = blk.hi;
-  const int64_t t0 = lo / kWaveTile;
-  const int64_t t1 = (hi - 1) / kWaveTile;
-  const int64_t first = blk.first_tile;
-
-  // Everything the workgroup needs before it can place its elements is asked for at once: the
-  // mask words of its own tiles, and the mask-bit counts the streaming pass has left for the
-  // tiles of this tensor before them (every tile strictly between the tensor's first tile and
-  // this workgroup's lies wholly inside the tensor; the tensor's share of its first tile is
-  // recounted from the mask words).  A version that summed its own words first and only then,
-  // behind a barrier, asked for the counts had two memory round trips in a row here.
-  uint32_t word[kPerWave];
-#pragma unroll
-  for (int i = 0; i < kPerWave; ++i) {
-    const int64_t t = first + wave + i * kWaves;
-    word[i] = t <= t1 ? tensor_tile_word(a.mask, t, lane, lo, hi) : 0u;
-  }
-  int pre = tile_counts_partial<kEmitThreads>(a.tile_count, t0 + 1, first, threadIdx.x);
-  if (first > t0 && wave == 0) pre += __popc(tensor_tile_word(a.mask, t0, lane, lo, hi));
-  int cnt = 0;
-#pragma unroll
-  for (int i = 0; i < kPerWave; ++i) cnt += __popc(word[i]);
-  const int incl = (int)wave_inclusive_sum((uint32_t)cnt);
-  pre = (int)wave_sum((uint32_t)pre);
-  if (lane == 63) wave_tot[wave] = incl;
-  if (lane == 0) pre_tot[wave] = pre;
-  __syncthreads();
-  // Slots taken by the tensor's tiles before the workgroup's first one, and by the wavefronts
-  // before this one: no atomics, no tickets, the workgroups of a tensor fill its region in index
-  // order, so the region is the same on every run.
-  int before = 0, total = 0, base = 0;
-#pragma unroll
-  for (int w = 0; w < kWaves; ++w) {
-    const int t = wave_tot[w];
-    if (w < wave) before += t;
-    total += t;
-    base += pre_tot[w];
-  }
-  if (threadIdx.x == 0 && (int)((first - t0) / kEmitTiles) == blk.tensor_blocks - 1) a.out_counts[j] = base + total;
-  if (total == 0) return;
-  const int64_t base_slot = base;
-  const int my_first = before + (incl - cnt);  // position of this lane's first element in the workgroup
-  bool overflow = false;
-  // The elements to move are first listed in LDS in their slot order, kEmitList at a
-  // time, then dealt out one per thread: every thread has the same amount of work and
-  // the reads of v are independent of each other.
-  for (int win = 0; win < total; win += kEmitList) {
-    int pos = my_first;
-#pragma unroll
-    for (int i = 0; i < kPerWave; ++i) {
-      uint32_t w = word[i];
-      const int64_t t = first + wave + i * kWaves;
-      while (w) {
-        const int q = __ffs(w) - 1;
-        w &= w - 1;
-        if (pos >= win && pos < win + kEmitList) list[pos - win] = (int32_t)tile_element(t, lane, q);
-        ++pos;
-      }
-    }
-    __syncthreads();
-    const int in_win = total - win < kEmitList ? total - win : kEmitList;
-    overflow |= emit_move(a, list, in_win, base_slot + win, region, cap);
-    __syncthreads();
-  }
-  if (overflow) atomicOr(&a.state->flags, (uint32_t)DGC_DIAG_OVERFLOW);
-}
-
-struct EmitTiles {
-  uint16_t words[kEmitTiles * 64];  // the workgroup's mask words, bits outside the tensor removed
-  int tile_tot[kEmitTiles];         // selected elements per tile
-  int tile_base[kEmitTiles];        // ... and in the workgroup's tiles before it
-  int wave_tot[kEmitThreads / 64];
-  int block_base, block_total;      // slots taken before the workgroup's part; elements of the part
-};
-
-// Parks the workgroup's mask words in LDS, counts per tile, finds where the workgroup's part
-// starts in the tensor's region and, in the tensor's last workgroup, writes the tensor's count.
-__device__ __forceinline__ void emit_tiles(const EmitArgs& a, const EmitBlock& blk, EmitTiles& sh) {
-  constexpr int kWaves = kEmitThreads / 64;
-  constexpr int kPerWave = kEmitTiles / kWaves;
-  static_assert(kEmitTiles <= 64, "one wavefront scans the tile totals");
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  const int j = blk.tensor;
-  const int64_t lo = blk.lo;
-  const int64_t hi = blk.hi;
-  const int64_t t1 = (hi - 1) / kWaveTile;
-  const int64_t first = blk.first_tile;
-
-  // Slots taken by the tiles of this tensor before the workgroup's first one.  Every tile
-  // strictly between the tensor's first tile and this workgroup's lies wholly inside the
-  // tensor, so its count left by the streaming pass (and kept up by the re-threshold pass)
-  // is what it contributes; the tensor's first tile may be shared with the tensor before
-  // and is recounted from its mask words.
-  const int64_t t0 = lo / kWaveTile;
-  const int in_tensor = (int)((first - t0) / kEmitTiles);
-  int before = tile_counts_partial<kEmitThreads>(a.tile_count, t0 + 1, first, threadIdx.x);
-  if (first > t0 && wave == 0) before += __popc(tensor_tile_word(a.mask, t0, lane, lo, hi));
-  static_assert(kPerWave % 2 == 0, "tile totals are reduced two to a register");
-  {
-    uint32_t word[kPerWave];
-#pragma unroll
-    for (int i = 0; i < kPerWave; ++i) {
-      const int64_t t = first + wave + i * kWaves;
-      word[i] = t <= t1 ? tensor_tile_word(a.mask, t, lane, lo, hi) : 0u;
-    }
-    // elements per tile: the lanes' bit counts of two tiles share a register (16 bits each,
-    // a tile holds at most 1024) and are summed over the wavefront together
-    uint32_t pair[kPerWave / 2];
-#pragma unroll
-    for (int i = 0; i < kPerWave; ++i) {
-      sh.words[(wave + i * kWaves) * 64 + lane] = (uint16_t)word[i];
-      if (i & 1) pair[i / 2] |= (uint32_t)__popc(word[i]) << 16;
-      else pair[i / 2] = (uint32_t)__popc(word[i]);
-    }
-#pragma unroll
-    for (int i = 0; i < kPerWave / 2; ++i) pair[i] = wave_sum(pair[i]);
-    before = (int)wave_sum((uint32_t)before);
-    if (lane == 0) {
-      sh.wave_tot[wave] = before;
-#pragma unroll
-      for (int i = 0; i < kPerWave; ++i)
-        sh.tile_tot[wave + i * kWaves] = (int)((pair[i / 2] >> (16 * (i & 1))) & 0xFFFFu);
-    }
-  }
-  __syncthreads();
-  if (wave == 0) {
-    const int own = lane < kEmitTiles ? sh.tile_tot[lane] : 0;
-    const int incl = (int)wave_inclusive_sum((uint32_t)own);
-    if (lane < kEmitTiles) sh.tile_base[lane] = incl - own;
-    if (lane == 63) {
-      int base = 0;
-      for (int w = 0; w < kWaves; ++w) base += sh.wave_tot[w];
-      sh.block_base = base;
-      sh.block_total = incl;
-      if (in_tensor == blk.tensor_blocks - 1) a.out_counts[j] = base + incl;
-    }
-  }
-  __syncthreads();
-}
-
-// Sorted variant.  The workgroup's mask words are parked in LDS; everything that
-// follows walks the tiles one at a time from there, which keeps the register count low
-// (the kernel is latency-bound: what matters is how many workgroups a CU holds).
-__global__ __launch_bounds__(kEmitThreads) void emit_sorted_kernel(EmitArgs a) {
-  constexpr int kWaves = kEmitThreads / 64;
-  constexpr int kPerWave = kEmitTiles / kWaves;
-  constexpr int kRows = kStreamUnroll;  // rounds of 256 elements per tile
-  __shared__ EmitTiles sh;
-  __shared__ int32_t list[kEmitList];
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  const EmitBlock blk = a.blocks[blockIdx.x];
-  const int j = blk.tensor;
-  const int64_t region = a.out_offsets[j];  // asked for early: needed late
-  const int64_t cap = a.out_offsets[j + 1] - region;
-  const int64_t first = blk.first_tile;
-  emit_tiles(a, blk, sh);
-  const int total = sh.block_total;
-  if (total == 0) return;
-  const int64_t base_slot = sh.block_base;
-  bool overflow = false;
-  for (int win = 0; win < total; win += kEmitList) {
-    // Index order inside a tile is row (round of 256 elements), lane, component: an
-    // element's position is the tile's base, plus the rows before it, plus the bits of
-    // its row in lower lanes (counted from the votes), plus the lower bits of its nibble.
-#pragma unroll 1
-    for (int i = 0; i < kPerWave; ++i) {
-      const int tl = wave + i * kWaves;
-      if (sh.tile_tot[tl] == 0) continue;
-      const uint32_t w = sh.words[tl * 64 + lane];
-      const int64_t t = first + tl;
-      int row_base = sh.tile_base[tl];
-#pragma unroll
-      for (int r = 0; r < kRows; ++r) {
-        const uint32_t nib = (w >> (4 * r)) & 0xFu;
-        if (__ballot(nib != 0) == 0) continue;  // nothing in this row of the tile
-        int lower = 0, row = 0;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          const unsigned long long vote = __ballot((nib >> c) & 1u);
-          lower += (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(vote >> 32),
-                                                  __builtin_amdgcn_mbcnt_lo((uint32_t)vote, 0u));
-          row += __popcll(vote);
-        }
-        int pos = row_base + lower;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          if ((nib >> c) & 1u) {
-            if (pos >= win && pos < win + kEmitList) list[pos - win] = (int32_t)tile_element(t, lane, 4 * r + c);
-            ++pos;
-          }
-        }
-        row_base += row;
-      }
-    }
-    __syncthreads();
-    const int in_win = total - win < kEmitList ? total - win : kEmitList;
-    overflow |= emit_move(a, list, in_win, base_slot + win, region, cap);
-    __syncthreads();
-  }
-  if (overflow) atomicOr(&a.state->flags, (uint32_t)DGC_DIAG_OVERFLOW);
-}
-
-// Emit pass after a STAGED streaming pass: the selected values of a tile that lies wholly
-// inside one tensor wait in the tile's slots of the staging array, in index order, and u
-// and v are masked already.  The part's payload is written in index order (as the sorted
-// variant does, with the same positions), values copied from the staging array; u, v are touched
-// only where the region is full (the element is put back: v' and, under factor masking, u') and in
-// tiles shared between tensors, which the streaming pass leaves alone.
+// From mask words, in index order: everything but a slotted streaming pass.  A thread owns 128 consecutive elements
+// of the part, half a row of a tile: it puts their bits together from the mask words (64 bytes), one scan over the
+// workgroup says where in the part they go, and the thread lists them in LDS by a walk over its bits.  Then slots
+// are dealt to threads, so that every thread has as many elements to move however they are spread.
+// STAGED (densities of the warm-up epochs with the staging workspace): the selected values of a tile that lies
+// wholly inside one tensor wait in the tile's slots of the staging array, in index order, and u and v are masked
+// already: values are copied from there, four slots to a thread, u and v touched only where the region is full (the
+// element is put back: v' and, under factor masking, u') and in tiles shared between tensors, which the streaming
+// pass leaves alone.
+// Otherwise every element's v' is read where it is, and v and u are cleared there (neighbouring lanes take
+// neighbouring slots: they meet in the same sectors).
 //
-// Bound by instructions at the lower densities of the warm-up and by the stores at the higher ones.  A
-// wavefront takes every fourth tile, eight in all (eight consecutive ones left three wavefronts idle in parts
-// of a few tiles: 4000 tensors of 7500 elements, 6.25 %, 329 us for the call and 307 this way); the counts of
-// whole tiles come from the table that the streaming pass has left, not from the mask words; values move four
-// to a lane; the indices of a tile with many selected elements are put in their places in LDS and leave from
-// there four to a lane, too.
-// 122 M elements: 112 us at 25 %, 42 at 1.6 % (136 and 46 with the counts formed from the mask words and every
-// index stored where it belongs one by one); placing the indices of sparse tiles through LDS as well: 57 us
-// at 1.6 %.  Holding all eight tiles' values and words in registers took 220 of them and 224 us at 25 %.
-struct EmitStagedShared {
-  int cnt[kEmitTiles];                                // selected elements per tile, this tensor's
-  int base[kEmitThreads / 64];                        // slots taken before the part, by wavefront
-  uint16_t words[kEmitTiles * 64];                    // mask words, bits outside the tensor removed
-  alignas(16) int32_t list[kEmitThreads / 64][kWaveTile + 64];
+// Staged, 122 M elements: 42 -> 17.5 us at 1.6 %, where positions worked out tile by tile in every lane's four
+// rows were bound by instructions; 113 -> 108 at 25 % (pairs stored with the non-temporal hint, which leaves the
+// last-level cache to what follows: the streaming pass of the next call 402 -> 392 us, the merge 430 -> 422; 115
+// without it), of which the walk and the dealing take 42 and the stores, 245 MB, the rest.  From a plain pass,
+// 25.6 M elements, 6.25 %: 65 -> 60.5 us (scattered reads of v and clears of v and u, a sector each), 23 tensors of
+// 0.27 M elements, 1 %: 6.9 -> 5.0.  Also measured at 25 %: four slots to a lane 146 us (a wavefront nearly always
+// has a four that straddles two tiles and takes the long way), a thread's first element found by bisection over the
+// owners and halving of its 128 bits instead of the list 118, and 56 at 1.6 %.
+template <bool STAGED>
+struct EmitOrderedShared {
+  static constexpr int kWindow = STAGED ? 9216 : 4096;  // elements listed at a time
+  uint16_t list[kWindow];                               // offsets from the part's first tile
+  int start[kEmitThreads];                              // elements of the part before those of every thread
+  int wave_tot[kEmitThreads / 64];
+  int pre_tot[kEmitThreads / 64];
 };
 
-__global__ __launch_bounds__(kEmitThreads) void emit_staged_kernel(EmitArgs a) {
-  typedef float fvec4u __attribute__((ext_vector_type(4), aligned(4)));
-  typedef int32_t ivec4u __attribute__((ext_vector_type(4), aligned(4)));
+template <bool STAGED>
+__global__ __launch_bounds__(kEmitThreads) void emit_ordered_kernel(EmitArgs a) {
   constexpr int kWaves = kEmitThreads / 64;
-  constexpr int kPerWave = kEmitTiles / kWaves;
-  constexpr int kRows = kStreamUnroll;
-  constexpr int kWalk = 128;  // tiles with fewer selected elements place their indices by a walk over each lane's bits
-  static_assert(kEmitTiles <= 64 && kWalk < 256, "one wavefront scans the counts; a row's positions fit a byte");
-  __shared__ EmitStagedShared sh;
+  constexpr int kPerTile = kEmitThreads / kEmitTiles;  // threads of a tile
+  constexpr int kOwn = kWaveTile / kPerTile;           // elements of a thread
+  static_assert(kOwn == 128 && kStreamUnroll == 4, "half a row of a tile: 32 mask words, a nibble of each");
+  static_assert(kEmitElements <= 65536, "16-bit offsets");
+  __shared__ EmitOrderedShared<STAGED> sh;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const EmitBlock blk = a.blocks[blockIdx.x];
   const int j = blk.tensor;
-  const int64_t region = a.out_offsets[j];
+  const int64_t region = a.out_offsets[j];  // asked for early: needed late
   const int64_t cap = a.out_offsets[j + 1] - region;
   const int64_t lo = blk.lo;
   const int64_t hi = blk.hi;
   const int64_t t0 = lo / kWaveTile;
   const int64_t t1 = (hi - 1) / kWaveTile;
   const int64_t first = blk.first_tile;
-  auto whole = [&](int64_t t) { return t * kWaveTile >= lo && (t + 1) * kWaveTile <= hi; };
 
-  // this wavefront's mask words, the counts of the part's tiles, and the counts of the tensor's tiles before it
-  uint16_t* words = sh.words + wave * (kPerWave * 64) + lane;  // of this lane: written and read by itself only
-  {
-    uint32_t word[kPerWave];
+  // Everything the workgroup needs before it can place its elements is asked for at once: the mask words of its own
+  // tiles, and the counts the streaming pass has left for the tiles of this tensor before them (every tile strictly
+  // between the tensor's first tile and this workgroup's lies wholly inside the tensor; the tensor's share of its
+  // first tile is recounted from the mask words).
+  const int tl = tid / kPerTile;
+  const int piece = tid % kPerTile;
+  const int64_t tile = first + tl;
+  uint4 raw[4] = {};
+  if (tile <= t1) {
+    const uint4* __restrict__ m = reinterpret_cast<const uint4*>(a.mask + tile * 64 + 32 * (piece & 1));
 #pragma unroll
-    for (int i = 0; i < kPerWave; ++i) {
-      const int64_t t = first + wave + i * kWaves;
-      word[i] = t <= t1 ? tensor_tile_word(a.mask, t, lane, lo, hi) : 0u;
-    }
-    const int64_t t = first + tid;
-    if (tid < kEmitTiles && (t > t1 || whole(t))) sh.cnt[tid] = t <= t1 ? (int)a.tile_count[t] : 0;
-#pragma unroll
-    for (int i = 0; i < kPerWave; ++i) words[i * 64] = (uint16_t)word[i];
+    for (int k = 0; k < 4; ++k) raw[k] = m[k];
   }
   int pre = tile_counts_partial<kEmitThreads>(a.tile_count, t0 + 1, first, tid);
   if (first > t0 && wave == 0) pre += __popc(tensor_tile_word(a.mask, t0, lane, lo, hi));
-  pre = (int)wave_sum((uint32_t)pre);
-  if (lane == 0) sh.base[wave] = pre;
-#pragma unroll 1
-  for (int i = 0; i < kPerWave; ++i) {
-    const int64_t t = first + wave + i * kWaves;
-    if (t <= t1 && !whole(t)) {  // shared with a neighbour, or the ragged end: the tensor's own bits count
-      const int c = (int)wave_sum((uint32_t)__popc((uint32_t)words[i * 64]));
-      if (lane == 0) sh.cnt[wave + i * kWaves] = c;
+  uint32_t bits[4];
+  {
+    const int row4 = 4 * (piece >> 1);
+    auto byte_of = [&](uint32_t two) {  // the row's nibbles of two neighbouring mask words
+      const uint32_t y = (two >> row4) & 0x000F000Fu;
+      return y | (y >> 12);             // (bits 16 to 19 are left over)
+    };
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      bits[k] = (byte_of(raw[k].x) & 0xFFu) | ((byte_of(raw[k].y) & 0xFFu) << 8) | ((byte_of(raw[k].z) & 0xFFu) << 16) |
+                (byte_of(raw[k].w) << 24);
+  }
+  const int64_t e0 = tile * kWaveTile + piece * kOwn;  // the thread's first element
+  if (e0 < lo || e0 + kOwn > hi) {                     // another tensor's elements, or behind the end
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int64_t from = lo - (e0 + 32 * k), until = hi - (e0 + 32 * k);
+      uint32_t keep = until >= 32 ? 0xFFFFFFFFu : until <= 0 ? 0u : (1u << (int)until) - 1u;
+      if (from > 0) keep &= from >= 32 ? 0u : ~((1u << (int)from) - 1u);
+      bits[k] &= keep;
     }
   }
+  const int cnt = __popc(bits[0]) + __popc(bits[1]) + __popc(bits[2]) + __popc(bits[3]);
+  const int incl = (int)wave_inclusive_sum((uint32_t)cnt);
+  pre = (int)wave_sum((uint32_t)pre);
+  if (lane == 63) sh.wave_tot[wave] = incl;
+  if (lane == 0) sh.pre_tot[wave] = pre;
   __syncthreads();
-  int base = 0;
+  int before = 0, total = 0, base = 0;
 #pragma unroll
-  for (int w = 0; w < kWaves; ++w) base += sh.base[w];
-  const int own = lane < kEmitTiles ? sh.cnt[lane] : 0;
-  const int incl = (int)wave_inclusive_sum((uint32_t)own);  // every wavefront scans the counts for itself
-  const int part_total = (int)wave_last((uint32_t)incl);
-  if (tid == 0 && (int)((first - t0) / kEmitTiles) == blk.tensor_blocks - 1) a.out_counts[j] = base + part_total;
-  if (part_total == 0) return;
+  for (int w = 0; w < kWaves; ++w) {
+    const int t = sh.wave_tot[w];
+    if (w < wave) before += t;
+    total += t;
+    base += sh.pre_tot[w];
+  }
+  if (tid == 0 && (int)((first - t0) / kEmitTiles) == blk.tensor_blocks - 1) a.out_counts[j] = base + total;
+  if (total == 0) return;
+  int pos = before + incl - cnt;  // slot of the thread's next element
+  sh.start[tid] = pos;
 
   float* __restrict__ u = a.u;
   float* __restrict__ v = a.v;
-  int32_t* list = sh.list[wave];
-  bool overflow = false;
-  // what a tile of the wavefront is; the slots are counted from the part's first one
-  const int64_t part_room = cap - base;
-  auto tile_of = [&](int i, int& total, int& slot, int& room) {
-    const int tl = wave + i * kWaves;
-    total = __builtin_amdgcn_readlane(own, tl);
-    slot = __builtin_amdgcn_readlane(incl, tl) - total;
-    // slots of the tile that exist (the rest of the tile overflows)
-    room = part_room - slot >= total ? total : (part_room > slot ? (int)(part_room - slot) : 0);
-    return whole(first + tl);
-  };
-  // The first 256 values of a tile are asked for before the tile before it is taken (up to three slots
-  // behind the last value are read with it: they belong to the tile).
-  auto first_values = [&](int i) {
-    int total, slot, room;
-    fvec4u x = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (tile_of(i, total, slot, room) && 4 * lane < room)
-      x = *reinterpret_cast<const fvec4u*>(a.stage_v + (first + wave + i * kWaves) * kWaveTile + 4 * lane);
-    return x;
-  };
-  float* __restrict__ part_val = a.out_val + region + base;
   int32_t* __restrict__ part_idx = a.out_idx + region + base;
-  // four consecutive values, or indices, of which the last `n - s` exist
-  auto put_values = [&](float* to, int s, int n, const fvec4u& y) {
-    if (s + 4 <= n) {
-      *reinterpret_cast<fvec4u*>(to + s) = y;
-    } else {
+  float* __restrict__ part_val = a.out_val + region + base;
+  const int64_t left = cap - base;
+  const int room = left >= total ? total : left > 0 ? (int)left : 0;  // elements that find a slot
+  const int32_t origin = (int32_t)(first * kWaveTile);
+  bool overflow = false;
+  // tiles that the streaming pass has not staged: shared with a neighbour tensor, or the ragged end
+  const int first_shared = t0 * kWaveTile < lo || (t0 + 1) * kWaveTile > hi ? (int)(t0 - first) : -1;
+  const int last_shared = (t1 + 1) * kWaveTile > hi || t1 * kWaveTile < lo ? (int)(t1 - first) : -1;
+  auto is_staged = [&](int t) { return STAGED && t != first_shared && t != last_shared; };
+  for (int win = 0; win < total; win += EmitOrderedShared<STAGED>::kWindow) {
+    const int end = total - win < EmitOrderedShared<STAGED>::kWindow ? total : win + EmitOrderedShared<STAGED>::kWindow;
+    if (win > 0) __syncthreads();
 #pragma unroll
-      for (int c = 0; c < 3; ++c)
-        if (s + c < n) to[s + c] = y[c];
-    }
-  };
-  auto put_indices = [&](int32_t* to, int s, int n, const int4& y) {
-    if (s + 4 <= n) {
-      *reinterpret_cast<ivec4u*>(to + s) = ivec4u{y.x, y.y, y.z, y.w};
-    } else {
-      if (s < n) to[s] = y.x;
-      if (s + 1 < n) to[s + 1] = y.y;
-      if (s + 2 < n) to[s + 2] = y.z;
-    }
-  };
-  fvec4u next = first_values(0);
-#pragma unroll 1
-  for (int i = 0; i < kPerWave; ++i) {
-    const fvec4u x = next;
-    if (i + 1 < kPerWave) next = first_values(i + 1);
-    int total, slot, room;
-    const bool staged = tile_of(i, total, slot, room);
-    if (total == 0) continue;  // uniform, as everything about the tile
-    const int64_t t = first + wave + i * kWaves;
-    const uint32_t w = words[i * 64];
-    const int32_t e_lane = (int32_t)tile_element(t, lane, 0);
-    float* __restrict__ tile_val = part_val + slot;
-    int32_t* __restrict__ tile_idx = part_idx + slot;
-    if (staged) {
-      put_values(tile_val, 4 * lane, room, x);
-      for (int s = 256 + 4 * lane; s < room; s += 256)  // beyond a quarter of the tile
-        put_values(tile_val, s, room, *reinterpret_cast<const fvec4u*>(a.stage_v + t * kWaveTile + s));
-    }
-    if (staged && room == total && total < kWalk) {
-      // The counts of the lane's four rows ride in the bytes of one word (no byte can overflow), one scan
-      // over the lanes gives every row's "bits in lower lanes", the rows' totals shifted up by one, two
-      // and three bytes the "rows before it", and a lane walks its own bits, lowest first.
-      uint32_t y = w - ((w >> 1) & 0x5555u);
-      y = (y & 0x3333u) + ((y >> 2) & 0x3333u);  // a count per nibble
-      const uint32_t cnt = (y & 0xFu) | ((y & 0xF0u) << 4) | ((y & 0xF00u) << 8) | ((y & 0xF000u) << 12);
-      const uint32_t upto = wave_inclusive_sum(cnt);
-      const uint32_t tot = wave_last(upto);
-      uint32_t at = (upto - cnt) + ((tot << 8) + (tot << 16) + (tot << 24));  // next slot of each of the lane's rows
-      uint32_t rem = w;
-      while (__ballot(rem != 0u)) {
-        if (rem != 0u) {
-          const int b = __builtin_ctz(rem);  // bit 4 r + c
-          const int r8 = (b >> 2) * 8;
-          tile_idx[(at >> r8) & 0xFFu] = e_lane + (b >> 2) * 256 + (b & 3);
-          at += 1u << r8;
-          rem &= rem - 1u;
-        }
+    for (int k = 0; k < 4; ++k) {
+      while (bits[k] != 0u && pos < end) {
+        sh.list[pos - win] = (uint16_t)(tid * kOwn + 32 * k + (__ffs((int)bits[k]) - 1));
+        bits[k] &= bits[k] - 1u;
+        ++pos;
       }
-      continue;
     }
-    const float* __restrict__ stage_v = a.stage_v + t * kWaveTile;
-    if (staged && room == total) {
-      // The same for more elements: the counts of two rows to a word, 16 bits each, two scans.  Every one
-      // of the sixteen elements is written to LDS, those not selected to a word of the lane's own behind the
-      // list (no branches).
-      const uint32_t n0 = __popc(w & 0xFu), n1 = __popc(w & 0xF0u), n2 = __popc(w & 0xF00u), n3 = __popc(w & 0xF000u);
-      const uint32_t cnt01 = n0 | (n1 << 16), cnt23 = n2 | (n3 << 16);
-      const uint32_t upto01 = wave_inclusive_sum(cnt01), upto23 = wave_inclusive_sum(cnt23);
-      const uint32_t tot01 = wave_last(upto01), tot23 = wave_last(upto23);
-      const uint32_t at01 = upto01 - cnt01, at23 = upto23 - cnt23;
-      const uint32_t row1 = tot01 & 0xFFFFu, row2 = row1 + (tot01 >> 16), row3 = row2 + (tot23 & 0xFFFFu);
-      const uint32_t row_at[4] = {at01 & 0xFFFFu, row1 + (at01 >> 16), row2 + (at23 & 0xFFFFu), row3 + (at23 >> 16)};
-      const uint32_t spare = (uint32_t)(kWaveTile + lane);
+    __syncthreads();
+    // neighbouring slots to neighbouring lanes, kBatch of them on their way at a time: loads, then stores
+    constexpr int kBatch = 4;
+    for (int s0 = win + tid; s0 < end; s0 += kBatch * kEmitThreads) {
+      int32_t e[kBatch];
+      float x[kBatch];
+      bool parked[kBatch];
+      int64_t at[kBatch];
 #pragma unroll
-      for (int r = 0; r < kRows; ++r) {
-        uint32_t pos = row_at[r];
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          const uint32_t bit = (w >> (4 * r + c)) & 1u;
-          list[bit ? pos : spare] = e_lane + r * 256 + c;
-          pos += bit;
-        }
-      }
-      wave_lds_fence();
-      for (int s = 4 * lane; s < total; s += 256) put_indices(tile_idx, s, total, *reinterpret_cast<const int4*>(&list[s]));
-      wave_lds_fence();
-      continue;
-    }
-    // A tile shared between tensors, or one that the region has no room for: element by element, a row at a
-    // time, the row's loads before its stores.  An element's slot is rows before it + bits of its row in lower
-    // lanes + lower bits of its nibble.
-    const float* __restrict__ stage_u = a.stage_u ? a.stage_u + t * kWaveTile : nullptr;
-    int row_base = 0;
-#pragma unroll
-    for (int r = 0; r < kRows; ++r) {
-      const uint32_t nib = (w >> (4 * r)) & 0xFu;
-      const uint32_t upto = wave_inclusive_sum((uint32_t)__popc(nib));
-      const int pos0 = row_base + (int)upto - __popc(nib);
-      row_base += (int)wave_last(upto);
-      const int32_t e0 = e_lane + r * 256;
-      float y[4];
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const int pos = pos0 + __popc(nib & ((1u << c) - 1u));
-        y[c] = 0.0f;
-        if ((nib >> c) & 1u) {
-          if (!staged && pos < room) y[c] = v[e0 + c];
-          if (staged && pos >= room) y[c] = stage_v[pos];
-        }
-      }
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        if (!((nib >> c) & 1u)) continue;
-        const int pos = pos0 + __popc(nib & ((1u << c) - 1u));
-        if (pos < room) {
-          tile_idx[pos] = e0 + c;
-          if (!staged) {  // value taken and u, v masked here
-            tile_val[pos] = y[c];
-            v[e0 + c] = 0.0f;
-            if (a.factor_masking) u[e0 + c] = 0.0f;
+      for (int k = 0; k < kBatch; ++k) {
+        const int s = s0 + k * kEmitThreads;
+        e[k] = -1;
+        x[k] = 0.0f;
+        parked[k] = false;
+        at[k] = 0;
+        if (s < end) {
+          const int off = sh.list[s - win];
+          const int t = off / kWaveTile;
+          e[k] = origin + off;
+          parked[k] = is_staged(t);
+          if (STAGED && parked[k]) {
+            at[k] = (first + t) * kWaveTile + (s - sh.start[t * kPerTile]);
+            x[k] = a.stage_v[at[k]];
+          } else if (s < room) {
+            x[k] = v[e[k]];
           }
-        } else {
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < kBatch; ++k) {
+        if (e[k] < 0) continue;
+        const int s = s0 + k * kEmitThreads;
+        if (s < room) {
+          if (STAGED) {
+            __builtin_nontemporal_store(e[k], part_idx + s);
+            __builtin_nontemporal_store(x[k], part_val + s);
+          } else {
+            part_idx[s] = e[k];
+            part_val[s] = x[k];
+          }
+          if (!parked[k]) {  // u, v masked here
+            v[e[k]] = 0.0f;
+            if (a.factor_masking) u[e[k]] = 0.0f;
+          }
+        } else {  // region full: what was parked goes back to where the streaming pass took it from, the rest stays
           overflow = true;
-          if (staged) {  // region full: the element goes back to where the streaming pass took it from
-            v[e0 + c] = y[c];
-            if (a.factor_masking && stage_u) u[e0 + c] = stage_u[pos];
+          if (STAGED && parked[k]) {
+            v[e[k]] = x[k];
+            if (a.factor_masking && a.stage_u) u[e[k]] = a.stage_u[at[k]];
           }
         }
       }
@@ -2214,7 +1903,7 @@ __global__ __launch_bounds__(kEmitSlotThreads) void emit_slots_kernel(EmitArgs a
   constexpr int kLanesPerTile = kEmitSlotThreads / kEmitTiles;
   constexpr int kPerLane = kSlotsPerTile / kLanesPerTile;
   static_assert(kPerLane == 2 && kLanesPerTile * kPerLane == kSlotsPerTile, "a thread takes two neighbouring slots");
-  constexpr int kEmitWalk = 6;  // selected elements of one lane the short way takes
+  constexpr int kLaneWalk = 6;  // selected elements of one lane the short way takes
   constexpr int kTilesPerWave = 64 / kLanesPerTile;
   static_assert(kEmitTiles <= 32 && kTilesPerWave * kWaves == kEmitTiles, "tile counts are scanned by half a wavefront");
   __shared__ EmitSlotsShared sh;
@@ -2311,7 +2000,7 @@ __global__ __launch_bounds__(kEmitSlotThreads) void emit_slots_kernel(EmitArgs a
     // its nibble.
     const int most = (int)wave_max((uint32_t)__popc(w));  // bits of the lane that has most (uniform)
     const int tile_count = __shfl(own, k);
-    if (tile_count < 256 && most <= kEmitWalk) {
+    if (tile_count < 256 && most <= kLaneWalk) {
       // The usual case (a tile shared between tensors, or a dozen elements in one tile): positions
       // from one packed scan (the counts of the lane's four rows in the bytes of a word, as in the
       // staged pass), and every lane walks its own bits: all of the tile's reads of v are on their
@@ -2324,11 +2013,11 @@ __global__ __launch_bounds__(kEmitSlotThreads) void emit_slots_kernel(EmitArgs a
       uint32_t next = (inc - cnt) + ((tot << 8) + (tot << 16) + (tot << 24));  // next position of each of the lane's rows
       const int32_t e_lane = (int32_t)tile_element(tk, lane, 0);
       uint32_t rem = w;
-      int32_t e[kEmitWalk];
-      int ps[kEmitWalk];
-      float x[kEmitWalk];
+      int32_t e[kLaneWalk];
+      int ps[kLaneWalk];
+      float x[kLaneWalk];
 #pragma unroll
-      for (int i = 0; i < kEmitWalk; ++i) {
+      for (int i = 0; i < kLaneWalk; ++i) {
         e[i] = -1;
         ps[i] = 0;
         x[i] = 0.0f;
@@ -2346,7 +2035,7 @@ __global__ __launch_bounds__(kEmitSlotThreads) void emit_slots_kernel(EmitArgs a
         }
       }
 #pragma unroll
-      for (int i = 0; i < kEmitWalk; ++i) {
+      for (int i = 0; i < kLaneWalk; ++i) {
         if (i < most && e[i] >= 0) {
           out_idx[tile_slot + ps[i]] = e[i];
           out_val[tile_slot + ps[i]] = x[i];
@@ -2498,15 +2187,13 @@ hipError_t launch_refine(const RefineArgs& a, int32_t num_tensors, hipStream_t s
   return hipGetLastError();
 }
 
-hipError_t launch_emit(const EmitArgs& a, int32_t num_blocks, bool sorted, hipStream_t stream) {
+hipError_t launch_emit(const EmitArgs& a, int32_t num_blocks, hipStream_t stream) {
   if (a.stage_v)
-    hipLaunchKernelGGL(emit_staged_kernel, dim3((unsigned)num_blocks), dim3(kEmitThreads), 0, stream, a);
+    hipLaunchKernelGGL(emit_ordered_kernel<true>, dim3((unsigned)num_blocks), dim3(kEmitThreads), 0, stream, a);
   else if (a.slotted)
     hipLaunchKernelGGL(emit_slots_kernel, dim3((unsigned)num_blocks), dim3(kEmitSlotThreads), 0, stream, a);
-  else if (sorted)
-    hipLaunchKernelGGL(emit_sorted_kernel, dim3((unsigned)num_blocks), dim3(kEmitThreads), 0, stream, a);
   else
-    hipLaunchKernelGGL(emit_kernel, dim3((unsigned)num_blocks), dim3(kEmitThreads), 0, stream, a);
+    hipLaunchKernelGGL(emit_ordered_kernel<false>, dim3((unsigned)num_blocks), dim3(kEmitThreads), 0, stream, a);
   return hipGetLastError();
 }
 
