@@ -159,17 +159,45 @@ __global__ __launch_bounds__(kFlatThreads) void scatter_regions_kernel(float* de
 // belongs to one workgroup, so plain loads and stores do.  (Float atomics complete at
 // about 20 G/s on this part wherever they are executed, plain scattered stores at 80 G/s.)
 
-// wave_equal_range for two lists at once, with the probes of both in flight together (`safe` is any
-// readable word: it is read in place of a probe that has nothing left to ask).
-__device__ __forceinline__ void wave_equal_range2(const int32_t* __restrict__ L0, int m0, const int32_t* __restrict__ L1,
+// Positions of xa and xb (the first values not below them) in two lists at once, for lists in which "value < x" is
+// monotone; `safe` is any readable word, read in place of a probe that has nothing left to ask.  The probes of
+// both lists are in flight together.  In the first round all lanes probe for both bounds, so that up to 2112 values
+// leave brackets of 32 and one more round, half the lanes to a bound, is the last; up to 4224 with two probes each
+// (161 tensors, the longest of 2.36 M elements, sixteen payloads: 25.6 -> 24.2 us).  Longer lists take three rounds
+// anyway, and the fewer the different sectors that the first one reads, the better: 62 tensors of up to 10 M
+// elements, eight payloads, 32 probes 37 us, 64 probes 38, 128 probes 41.
+__device__ __forceinline__ void wave_equal_ranges(const int32_t* __restrict__ L0, int m0, const int32_t* __restrict__ L1,
                                                   int m1, const int32_t* __restrict__ safe, int32_t xa, int32_t xb,
                                                   int lane, int& lo_0, int& hi_0, int& lo_1, int& hi_1) {
-  const int half = lane >> 5;
+  const int half = lane >> 5;  // 0: xa, 1: xb
   const int sub = lane & 31;
   const int32_t x = half ? xb : xa;
   const int32_t* __restrict__ A = m0 > 0 ? L0 : safe;
   const int32_t* __restrict__ B = m1 > 0 ? L1 : safe;
-  int lo0 = 0, hi0 = m0, lo1 = 0, hi1 = m1;
+  int lo0, hi0, lo1, hi1;  // of the lane's half
+  {
+    const bool twice = (m0 > 64 * 33 && m0 <= 128 * 33) || (m1 > 64 * 33 && m1 <= 128 * 33);  // uniform
+    const int shift = twice ? 7 : m0 > 128 * 33 || m1 > 128 * 33 ? 5 : 6;  // log2 of the probes
+    const int step0 = (m0 + (1 << shift) - 1) >> shift, step1 = (m1 + (1 << shift) - 1) >> shift;
+    const int p0 = lane * step0, p1 = lane * step1, q0 = p0 + 64 * step0, q1 = p1 + 64 * step1;
+    const bool ask0 = p0 < m0, ask1 = p1 < m1, more0 = twice && q0 < m0, more1 = twice && q1 < m1;
+    const int32_t v0 = A[ask0 ? p0 : 0], v1 = B[ask1 ? p1 : 0];
+    int32_t w0 = 0, w1 = 0;
+    if (twice) {
+      w0 = A[more0 ? q0 : 0];
+      w1 = B[more1 ? q1 : 0];
+    }
+    auto below = [&](int32_t bound, bool ask, int32_t v, bool more, int32_t w) {  // probes below the bound: a prefix
+      return __popcll(__ballot(ask && v < bound)) + __popcll(__ballot(more && w < bound));
+    };
+    const int ca0 = below(xa, ask0, v0, more0, w0), cb0 = below(xb, ask0, v0, more0, w0);
+    const int ca1 = below(xa, ask1, v1, more1, w1), cb1 = below(xb, ask1, v1, more1, w1);
+    const int c0 = half ? cb0 : ca0, c1 = half ? cb1 : ca1;
+    lo0 = c0 > 0 ? (c0 - 1) * step0 + 1 : 0;
+    hi0 = c0 > 0 ? (c0 * step0 < m0 ? c0 * step0 : m0) : 0;
+    lo1 = c1 > 0 ? (c1 - 1) * step1 + 1 : 0;
+    hi1 = c1 > 0 ? (c1 * step1 < m1 ? c1 * step1 : m1) : 0;
+  }
   while (__ballot(hi0 > lo0 || hi1 > lo1)) {
     const int span0 = hi0 - lo0, span1 = hi1 - lo1;
     const int step0 = (span0 + 31) >> 5, step1 = (span1 + 31) >> 5;
@@ -200,10 +228,10 @@ __device__ __forceinline__ void wave_equal_range2(const int32_t* __restrict__ L0
       }
     }
   }
-  lo_0 = __shfl(lo0, 0);
-  hi_0 = __shfl(lo0, 32);
-  lo_1 = __shfl(lo1, 0);
-  hi_1 = __shfl(lo1, 32);
+  lo_0 = __builtin_amdgcn_readlane(lo0, 0);
+  hi_0 = __builtin_amdgcn_readlane(lo0, 32);
+  lo_1 = __builtin_amdgcn_readlane(lo1, 0);
+  hi_1 = __builtin_amdgcn_readlane(lo1, 32);
 }
 
 // begin[1 .. num] holds lengths; afterwards begin[w] is the sum of the lengths before w.  One wavefront.
@@ -216,72 +244,56 @@ __device__ __forceinline__ void begins_from_lengths(int32_t* begin, int num, int
 
 // Finds every payload's pairs inside [blk.begin, blk.end) and fills begin[], idx_at[] and
 // val_at[] (in LDS: a payload's pointers looked up per pair in the kernel's argument block
-// would put a load from memory in front of every pair load).
-template <typename Shared>
-__device__ __forceinline__ int locate_pairs(Shared& sh, const RegionPayloads& p, int32_t num_payloads, int64_t region,
-                                            int64_t cap, const MergeBlock& blk, int tid, int waves) {
+// would put a load from memory in front of every pair load).  BOTH: of two sets of payloads at
+// once (the new ones and the previous ones of a replacing merge); `total2` gets the second set's number
+// of pairs, the first set's is returned.  Wavefront w looks after payload w; its number is uniform, and nothing
+// is asked for conditionally, so that all its pointers come from one round of scalar loads and both counts from the
+// next (a lane-wise payload number made six rounds of dependent loads of them).
+template <bool BOTH, typename Shared, typename Shared2>
+__device__ __forceinline__ int locate_pairs(Shared& sh, const RegionPayloads& p, int32_t num_payloads, Shared2& sh2,
+                                            const RegionPayloads& p2, int32_t num_payloads2, const int64_t* __restrict__ out_offsets,
+                                            const MergeBlock& blk, const int32_t* __restrict__ safe, int tid, int waves,
+                                            int& total2) {
   const int lane = tid & 63;
-  const int wave = tid >> 6;
-  for (int w = wave; w < num_payloads; w += waves) {
-    int64_t cnt = p.counts[w][blk.tensor];
-    if (cnt > cap) cnt = cap;
-    if (cnt < 0) cnt = 0;
-    int lo = 0, hi = (int)cnt;
-    if (blk.begin != blk.lo || blk.end != blk.hi)  // (a range that is a whole tensor has all its pairs)
-      wave_equal_range(p.idx[w] + region, (int)cnt, blk.begin, blk.end, lane, lo, hi);
-    if (lane == 0) {
-      sh.idx_at[w] = p.idx[w] + region + lo;
-      sh.val_at[w] = p.val[w] ? p.val[w] + region + lo : nullptr;
-      sh.begin[w + 1] = hi - lo;  // length for now
-    }
-  }
-  __syncthreads();
-  if (tid < 64) begins_from_lengths(sh.begin, num_payloads, tid);
-  __syncthreads();
-  return sh.begin[num_payloads];
-}
-
-// Two sets of payloads at once (the new ones and the previous ones of a replacing merge):
-// wavefront w searches payload w of both sets with the probes of the two searches in flight
-// together.  `total2` gets the second set's number of pairs, the first set's is returned.
-template <typename Shared, typename Shared2>
-__device__ __forceinline__ int locate_pairs2(Shared& sh, const RegionPayloads& p, int32_t num_payloads, Shared2& sh2,
-                                             const RegionPayloads& p2, int32_t num_payloads2, int64_t region,
-                                             int64_t cap, const MergeBlock& blk, const int32_t* __restrict__ safe,
-                                             int tid, int waves, int& total2) {
-  const int lane = tid & 63;
-  const int wave = tid >> 6;
-  const int most = num_payloads > num_payloads2 ? num_payloads : num_payloads2;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int most = BOTH && num_payloads2 > num_payloads ? num_payloads2 : num_payloads;
   for (int w = wave; w < most; w += waves) {
-    int64_t cnt = w < num_payloads ? (int64_t)p.counts[w][blk.tensor] : 0;
-    int64_t cnt2 = w < num_payloads2 ? (int64_t)p2.counts[w][blk.tensor] : 0;
-    if (cnt > cap) cnt = cap;
-    if (cnt < 0) cnt = 0;
-    if (cnt2 > cap) cnt2 = cap;
-    if (cnt2 < 0) cnt2 = 0;
-    const int32_t* __restrict__ list = w < num_payloads ? p.idx[w] + region : safe;
-    const int32_t* __restrict__ list2 = w < num_payloads2 ? p2.idx[w] + region : safe;
+    const bool have = w < num_payloads, have2 = BOTH && w < num_payloads2;
+    const int at = have ? w : 0, at2 = have2 ? w : 0;
+    const int32_t* __restrict__ idx = p.idx[at];
+    const float* __restrict__ val = p.val[at];
+    const int32_t* __restrict__ counts = p.counts[at];
+    const int32_t* __restrict__ idx2 = BOTH ? p2.idx[at2] : idx;
+    const int32_t* __restrict__ counts2 = BOTH ? p2.counts[at2] : counts;
+    if (!have2) counts2 = counts;  // (there may be no second set at all)
+    const int64_t region = out_offsets[blk.tensor];
+    const int64_t cap = out_offsets[blk.tensor + 1] - region;
+    const int32_t both = (lane & 1 ? counts2 : counts)[blk.tensor];  // one load for the two
+    const int32_t count = __builtin_amdgcn_readlane(both, 0), count2 = __builtin_amdgcn_readlane(both, 1);
+    const int64_t cnt = !have || count < 0 ? 0 : count > cap ? cap : count;
+    const int64_t cnt2 = !have2 || count2 < 0 ? 0 : count2 > cap ? cap : count2;
+    idx += region;
+    idx2 += region;
     int lo = 0, hi = (int)cnt, lo2 = 0, hi2 = (int)cnt2;
     if (blk.begin != blk.lo || blk.end != blk.hi)  // (a range that is a whole tensor has all its pairs)
-      wave_equal_range2(list, (int)cnt, list2, (int)cnt2, safe, blk.begin, blk.end, lane, lo, hi, lo2, hi2);
+      wave_equal_ranges(idx, (int)cnt, idx2, (int)cnt2, safe, blk.begin, blk.end, lane, lo, hi, lo2, hi2);
     if (lane == 0) {
-      if (w < num_payloads) {
-        sh.idx_at[w] = list + lo;
-        sh.val_at[w] = p.val[w] ? p.val[w] + region + lo : nullptr;
+      if (have) {
+        sh.idx_at[w] = idx + lo;
+        sh.val_at[w] = val + region + lo;
         sh.begin[w + 1] = hi - lo;  // length for now
       }
-      if (w < num_payloads2) {
-        sh2.idx_at[w] = list2 + lo2;
-        sh2.val_at[w] = nullptr;
+      if (have2) {
+        sh2.idx_at[w] = idx2 + lo2;
         sh2.begin[w + 1] = hi2 - lo2;
       }
     }
   }
   __syncthreads();
   if (tid < 64) begins_from_lengths(sh.begin, num_payloads, tid);
-  if (tid >= 64 && tid < 128) begins_from_lengths(sh2.begin, num_payloads2, tid - 64);
+  if (BOTH && tid >= 64 && tid < 128) begins_from_lengths(sh2.begin, num_payloads2, tid - 64);
   __syncthreads();
-  total2 = sh2.begin[num_payloads2];
+  total2 = BOTH ? sh2.begin[num_payloads2] : 0;
   return sh.begin[num_payloads];
 }
 
@@ -318,7 +330,6 @@ struct MergeShared {
 struct OldLists {
   int32_t begin[kMaxPayloads + 1];
   const int32_t* idx_at[kMaxPayloads];
-  const float* val_at[kMaxPayloads];  // unused
 };
 
 // Number of the distinct index r (relative to the range) among those of the range: the indices
@@ -338,8 +349,9 @@ __device__ __forceinline__ int merge_slot(const MergeShared<CAP>& sh, int32_t r)
 // THREADS: 512 when there are at most eight payloads (one wavefront searches one payload's region,
 // and four workgroups of eight wavefronts fit a compute unit, LDS included: the 970 ranges of a
 // 122 M-element set then run all at once instead of in two rounds), 1024 otherwise.  Bound by latency, the
-// searches before all: replacing calls at 0.1 % 35.5 us on that set and 25.0 on 25.6 M elements with sixteen
-// payloads.  (A first round of probes around the place that a range has if pairs are spread evenly took 34.9
+// searches before all: replacing calls at 0.1 % 36 us on that set (37.5 with the pointers of a wavefront's payload fetched one after the
+// other) and 24.2 on 25.6 M elements with sixteen payloads (25.5; 66 M with four 20.3 against 22.2, 1 M with four 8.9
+// against 10.7).  (A first round of probes around the place that a range has if pairs are spread evenly took 34.9
 // and 23.7, but 49.1 instead of 39.1 where the pairs crowd three tenths of one large tensor: every workgroup
 // goes on from a bracket of its own, where the first rounds over the whole region read the same few sectors.
 // Both sets of probes in one round: no gain where pairs are spread evenly.)  kMergeCap:
@@ -364,17 +376,12 @@ __global__ __launch_bounds__(THREADS) void merge_regions_kernel(float* __restric
   const int lane = tid & 63;
   const int wave = tid >> 6;
   const MergeBlock blk = blocks[blockIdx.x];
-  const int j = blk.tensor;
-  const int64_t region = out_offsets[j];
-  const int64_t cap = out_offsets[j + 1] - region;
   const int32_t length = (int32_t)(blk.end - blk.begin);  // <= kMergeMaxRange
 #pragma unroll
   for (int k = 0; k < kWordsPerThread; ++k) sh.bitmap[tid * kWordsPerThread + k] = 0;
   int old_total = 0;
-  const int total = (REPLACE && num_old > 0)
-                        ? locate_pairs2(sh, p, num_payloads, was, old, num_old, region, cap, blk,
-                                        reinterpret_cast<const int32_t*>(blocks), tid, kMergeWaves, old_total)
-                        : locate_pairs(sh, p, num_payloads, region, cap, blk, tid, kMergeWaves);
+  const int total = locate_pairs<REPLACE>(sh, p, num_payloads, was, old, num_old, out_offsets, blk,
+                                          reinterpret_cast<const int32_t*>(blocks), tid, kMergeWaves, old_total);
   if (total == 0 && old_total == 0) return;
   // Whether the accumulator may start from zero: the earlier set's indices of this range fit
   // the registers too.  Otherwise they are cleared in `dense` first and the sum is added
@@ -407,12 +414,14 @@ __global__ __launch_bounds__(THREADS) void merge_regions_kernel(float* __restric
     int pw[kPerThread];
     int32_t rel[kPerThread];
     float x[kPerThread];
+    float held[kPerThread];  // what the element's slot starts from: asked for before the indices are numbered
 #pragma unroll
     for (int k = 0; k < kPerThread; ++k) {
       const int q = tid + k * kMergeThreads;
       rel[k] = -1;
       pw[k] = 0;
       x[k] = 0.0f;
+      held[k] = 0.0f;
       if (q < total) {
         int w = 0, e = num_payloads;  // largest w with begin[w] <= q
         while (e - w > 1) {
@@ -427,6 +436,7 @@ __global__ __launch_bounds__(THREADS) void merge_regions_kernel(float* __restric
         pw[k] = w;
         if (r >= 0 && r < length) {  // anything else can only come from a region that does not ascend
           rel[k] = (int32_t)r;
+          if (!from_zero) held[k] = dense[blk.begin + r];
           atomicOr(&sh.bitmap[r >> 5], 1u << (r & 31));
         }
       }
@@ -467,7 +477,7 @@ __global__ __launch_bounds__(THREADS) void merge_regions_kernel(float* __restric
       if (rel[k] >= 0) {
         id[k] = merge_slot(sh, rel[k]);
         // pairs of several payloads with one index write the same
-        sh.acc[id[k]] = from_zero ? 0.0f : dense[blk.begin + rel[k]];
+        sh.acc[id[k]] = held[k];
       }
     }
     __syncthreads();
