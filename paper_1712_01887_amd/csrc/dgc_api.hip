@@ -29,6 +29,7 @@ struct dgc_handle {
   std::vector<int64_t> k;            // T
   std::vector<int64_t> draws;        // T
   bool any_band = false;             // some tensor's threshold is found by way of a band (TensorPlan.exact == 2)
+  bool bands_in_pass = false;        // ... whose floor the streaming pass compares with
   uint32_t most_bands = 0;           // tensors that take a band at some density; 0: none does
   std::vector<uint32_t> tile_info;   // ceil(n / kWaveTile)
   std::vector<float> tile_thr_init;  // ceil(n / kWaveTile): NaN where a tile is not wholly inside one tensor
@@ -168,6 +169,12 @@ bool whole_tensor(const dgc_config& c, int64_t n) {
   return (c.flags & DGC_FLAG_EXACT_SELECT) || sample_size(c, n) >= n || n / c.sample_block < 1;
 }
 
+// Rank in the band's sample that the floor of a band in the pass is taken at, as select_kernel forms it (within one).
+int64_t band_floor_rank(double density) {
+  const double mid = density * (double)kBandSample;
+  return (int64_t)(std::ceil(mid) + 16.0 + std::ceil(5.0 * std::sqrt(mid * (1.0 - density))));
+}
+
 // Host arithmetic of the sampled threshold (paper: Section 5).  The wanted
 // sample size is ratio * n clamped to [sample_min, sample_max]; a tensor no
 // larger than that is used whole.  Otherwise ceil(s / B) aligned blocks of B
@@ -186,6 +193,8 @@ void build_plan(dgc_handle* h) {
   const bool by_bands = longest > (readers >= kBandMany ? kBandFromMany : kBandFrom);
   uint32_t bands = 0;
   h->any_band = false;
+  // What lies above the band's floor in the longest of these tensors has to fit the list of one workgroup.
+  h->bands_in_pass = by_bands && c.density <= kBandInPassDensity && longest * band_floor_rank(c.density) / kBandSample <= kBandInPassList;
   for (int32_t j = 0; j < h->num_tensors; ++j) {
     const int64_t n = h->offsets[j + 1] - h->offsets[j];
     TensorPlan& p = h->plans[j];
@@ -668,8 +677,10 @@ dgc_status dgc_compress(dgc_handle* h, const float* g, float* u, float* v, int32
   sa.seed_hi = (uint32_t)(c.seed >> 32);
   sa.iter_lo = (uint32_t)(iteration & 0xFFFFFFFFu);
   sa.iter_hi = (uint32_t)(iteration >> 32);
+  const bool bands_in_pass = h->any_band && h->bands_in_pass;
+  sa.bands_in_pass = bands_in_pass ? 1 : 0;
   if (!hip_ok(launch_select(sa, h->num_tensors, stream), "launch select kernel")) return DGC_ERR_HIP;
-  if (h->any_band &&
+  if (h->any_band && !bands_in_pass &&
       !hip_ok(launch_band(sa, at<EmitBlock>(workspace, h->lay.emit_blocks), (int32_t)h->emit_blocks.size(),
                           h->num_tensors, stream),
               "launch band kernels"))
@@ -709,13 +720,18 @@ dgc_status dgc_compress(dgc_handle* h, const float* g, float* u, float* v, int32
     ta.stage_u = (factor_masking && h->layout_may_overflow) ? at<float>(workspace, h->lay.stage_u) : nullptr;
   }
   ta.slotted = slotted ? 1 : 0;
+  static_assert(kBandInPassDensity <= kStagedMinDensity, "bands in the pass go by records");
+  ta.bands_in_pass = sa.bands_in_pass;
+  ta.plans = sa.plans;
   if (!hip_ok(launch_stream(ta, stream), "launch stream kernel")) return DGC_ERR_HIP;
   if (ev && !hip_ok(hipEventRecord(ev[3], stream), "record event")) return DGC_ERR_HIP;
 
   // paper: Section 5 -- a tensor that lets through far more elements than wanted gets an exact
   // threshold, computed among the elements that passed
-  if (c.refine_alpha > 0.0f) {
+  if (c.refine_alpha > 0.0f || bands_in_pass) {
     RefineArgs ra{};
+    ra.on_excess = c.refine_alpha > 0.0f ? 1 : 0;
+    ra.bands_in_pass = sa.bands_in_pass;
     ra.plans = sa.plans;
     ra.v = v;
     ra.mask = ta.mask;
@@ -750,6 +766,7 @@ dgc_status dgc_compress(dgc_handle* h, const float* g, float* u, float* v, int32
   ea.stage_v = ta.stage_v;
   ea.stage_u = ta.stage_u;
   ea.slotted = ta.slotted;
+  ea.settled = slotted && (c.refine_alpha > 0.0f || bands_in_pass) ? sa.thr : nullptr;
   if (!hip_ok(launch_emit(ea, (int32_t)h->emit_blocks.size(), stream), "launch emit kernel"))
     return DGC_ERR_HIP;
   if (ev && !hip_ok(hipEventRecord(ev[4], stream), "record event")) return DGC_ERR_HIP;

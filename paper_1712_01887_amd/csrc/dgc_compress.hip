@@ -231,6 +231,8 @@ __device__ __forceinline__ uint32_t rank_directly(SelectShared& sh, int tid, uin
 // thread), ignoring empty slots (kNoKey) and keys below `floor_key`; the caller
 // guarantees that more than `rank` keys are considered.  Every thread returns the same.
 constexpr uint32_t kNoKey = 0xFFFFFFFFu;  // real keys have the sign bit clear
+constexpr uint32_t kInfinity = 0x7F800000u;  // the keys of NaNs lie above: they are ranked, and not sent
+__device__ __forceinline__ bool sent(uint32_t key, uint32_t thr) { return key > thr && key <= kInfinity; }
 
 template <int NKEYS>
 __device__ __forceinline__ uint32_t select_in_registers(SelectShared& sh, const uint32_t (&key)[NKEYS],
@@ -570,8 +572,15 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectArgs a) {
       const double share = (double)plan.rank / (double)plan.n;
       const double mid = share * (double)kBandSample;
       const double reach = 32.0 + ceil(7.0 * sqrt(mid * (1.0 - share)));
-      const double low = ceil(mid) + reach, high = floor(mid) - reach;
+      // (in the pass, where every element above the floor costs, five and 16: a miss costs one workgroup four walks
+      // over the tensor)
+      const double low = ceil(mid) + (a.bands_in_pass ? 16.0 + ceil(5.0 * sqrt(mid * (1.0 - share))) : reach);
+      const double high = floor(mid) - reach;
       const uint32_t floor_key = low < (double)count ? rank_registers(sh, key, count, holders, (uint32_t)low, tid) : 0xFFFFFFFFu;
+      if (a.bands_in_pass) {  // what exceeds the floor passes, and refine_kernel ranks it
+        write_threshold(a, j, plan, __uint_as_float(floor_key < kInfinity ? floor_key : kInfinity), tid);
+        return;
+      }
       uint32_t ceil_key = high >= 0.0 ? rank_registers(sh, key, count, holders, (uint32_t)high, tid) : 0x80000000u;
       if (ceil_key == floor_key) ++ceil_key;
       if (tid == 0) *band_state(a, plan) = BandState{floor_key, ceil_key, 0u, 0u, 0u};
@@ -848,6 +857,22 @@ __device__ __forceinline__ uint32_t mixed_tile_mask(const StreamArgs& a, int64_t
   return cand;
 }
 
+// Mask bits of the lane's NaNs that belong to tensors with a band.  (Rare: `j0` is the tensor of the tile's first
+// element, those behind it are walked over.)
+__device__ __forceinline__ uint32_t band_nans(const StreamArgs& a, int64_t base, int lane, int32_t j0, const vec4 (&z)[kStreamUnroll]) {
+  uint32_t found = 0;
+#pragma unroll
+  for (int q = 0; q < 4 * kStreamUnroll; ++q) {
+    const float v = z[q >> 2][q & 3];
+    const int64_t e = base + (q >> 2) * 256 + lane * 4 + (q & 3);
+    if (v == v || e >= a.n) continue;
+    int32_t j = j0;
+    while (a.offsets[j + 1] <= e) ++j;
+    if (a.plans[j].exact == 2) found |= 1u << q;
+  }
+  return found;
+}
+
 // NESTEROV and SCALED are compile-time so that the sixteen updates of a lane are straight
 // code: SCALED = false is the case scale == 1 exactly (no clipping), where g * 1.0f == g
 // bit for bit and the multiplication is left out.  The kernel is memory-bound but a
@@ -878,11 +903,18 @@ __device__ __forceinline__ uint32_t mixed_tile_mask(const StreamArgs& a, int64_t
 // place of the tile's mask words, in index order, and stores u and v masked: the emit pass copies
 // from the record and neither decodes a mask word nor reads or rewrites u and v for such a tile.  Tiles with more selected elements, and tiles shared between tensors, are
 // left to the emit pass as in the plain case (u', v' unmasked, mask bits set).
-enum StreamMode : int { kStreamPlain = 0, kStreamStaged = 1, kStreamSlotted = 2 };
+//
+// BAND (exact selection at those densities): the threshold is a floor under the exact one, and refine_kernel settles
+// which of the elements that pass are sent.  NaNs, which rank above everything, have to pass with them (those of
+// tensors whose threshold comes from a band: the comparison lets none pass).
+enum StreamMode : int { kStreamPlain = 0, kStreamStaged = 1, kStreamSlotted = 2, kStreamBand = 3 };
+
+
 
 template <bool NESTEROV, bool SCALED, int MODE>
 __global__ __launch_bounds__(kStreamThreads) void stream_kernel(StreamArgs a) {
   constexpr bool STAGED = MODE == kStreamStaged;
+  constexpr bool SLOTTED = MODE == kStreamSlotted || MODE == kStreamBand;
   __shared__ alignas(16) float mixed_thr[kStreamWaves][kWaveTile];  // for tiles shared between tensors only
   constexpr int U = kStreamUnroll;
   const int lane = threadIdx.x & 63;
@@ -940,6 +972,13 @@ __global__ __launch_bounds__(kStreamThreads) void stream_kernel(StreamArgs a) {
       z[r][c] = v1;
     }
   }
+  uint32_t nans = 0;
+  if (MODE == kStreamBand) {
+    float sum = 0.0f;  // a NaN if any of the elements is one (or there are infinities of both signs)
+#pragma unroll
+    for (int q = 0; q < 4 * U; ++q) sum += z[q >> 2][q & 3];
+    if (__ballot(sum != sum) != 0) nans = band_nans(a, base, lane, j0, z);
+  }
   if (STAGED && thr == thr) {  // wholly inside one tensor (and so a whole tile)
     uint32_t cand = 0;
 #pragma unroll
@@ -981,8 +1020,8 @@ __global__ __launch_bounds__(kStreamThreads) void stream_kernel(StreamArgs a) {
     if (lane == 0) a.tile_count[tile] = (uint32_t)row_base;
     return;
   }
-  if (MODE == kStreamSlotted && thr == thr) {  // wholly inside one tensor (and so a whole tile)
-    uint32_t cand = 0;
+  if (SLOTTED && thr == thr) {  // wholly inside one tensor (and so a whole tile)
+    uint32_t cand = nans;
 #pragma unroll
     for (int q = 0; q < 4 * U; ++q)
       if (fabsf(z[q >> 2][q & 3]) > thr) cand |= 1u << q;
@@ -1085,7 +1124,7 @@ __global__ __launch_bounds__(kStreamThreads) void stream_kernel(StreamArgs a) {
     for (int q = 0; q < 4 * U; ++q)
       if (fabsf(z[q >> 2][q & 3]) > thr) cand |= 1u << q;
   } else {
-    cand = mixed_tile_mask(a, base, lane, j0, z, mixed_thr[wave]);
+    cand = mixed_tile_mask(a, base, lane, j0, z, mixed_thr[wave]) | nans;
   }
   a.mask[tile * 64 + lane] = (uint16_t)cand;
   // bits set in the tile, for the index-ordered emit pass (measured: no cost here)
@@ -1169,14 +1208,18 @@ __device__ __forceinline__ int tile_counts_partial(const uint32_t* __restrict__ 
 // tensor.  (A first version ran over the emit work list: every workgroup recounted its part's
 // mask words and took a ticket on the tensor's counter, the last to arrive went on; 17 us on the
 // 161-tensor set and 34 us on the 122 M-element set for what the per-tile counts already say.)
+// EXACT SELECTION at densities up to kBandInPassDensity comes here, too: select_kernel has named a floor that lies below
+// the exact threshold almost surely, the pass took what exceeds it, and every such tensor is ranked here.  The streaming
+// pass is then the only one over g, u, v: 161 tensors of 25.6 M elements, 0.1 %, 174 -> 128 us (select 19, pass 82,
+// refine 20, emit 7) where collect_band_kernel read them once more and rank_band_kernel followed (20, 81, 5, and 55
+// + 12).  Above 0.2 % too many tiles hold more than a record does: 12 tensors of 1 M elements, 0.4 %, 71 against 57.
 // A workgroup lists up to kRefineList selected elements in LDS (index and key) and ranks them by one
 // histogram; the over-selection of a big tensor goes to the payload region, which is free until the emit
 // pass, and through three histogram passes.  Bound by latency, a chain of dependent steps in the dozen
-// workgroups that go on: 15 us on the 161-tensor set, 23 with the list always in the payload region.  The lists
+// workgroups that go on: 13 us on the 161-tensor set (15.4 with one addition to the list's length per tile and with
+// what is dropped put back from here; 23 with the list always in the payload region).  The lists
 // (and 16 wavefronts of more than 64 registers) leave one workgroup per compute unit; 20000 tensors, most of which
 // only add up their counts, take 133 us as they did without the lists.
-constexpr int kRefinePer = 12;
-constexpr int kRefineList = kRefinePer * kRefineThreads;
 struct RefineShared {
   SelectShared s;
   uint32_t list[kRefineList];
@@ -1220,6 +1263,8 @@ __global__ __launch_bounds__(kRefineThreads) void refine_kernel(RefineArgs a) {
   const int64_t hi = plan.offset + plan.n;
   const int64_t t0 = lo / kWaveTile;
   const int64_t t1 = (hi - 1) / kWaveTile;
+  // Exact selection: the pass took whatever exceeds a floor, NaNs too, and the threshold is settled here in any case.
+  const bool banded = a.bands_in_pass != 0 && plan.exact == 2;
 
   // How many elements of the tensor passed: the counts the streaming pass has left for the tiles
   // that lie wholly inside the tensor, and the tensor's share of a first or last tile that it
@@ -1240,7 +1285,7 @@ __global__ __launch_bounds__(kRefineThreads) void refine_kernel(RefineArgs a) {
     int total = 0;
     for (int w = 0; w < kWaves; ++w) total += sh.red[w];
     sh.passed = (uint32_t)total;
-    sh.go = (uint32_t)total > (uint32_t)plan.refine_limit;
+    sh.go = banded || (a.on_excess && (uint32_t)total > (uint32_t)plan.refine_limit);
   }
   __syncthreads();
   if (!sh.go) return;
@@ -1262,12 +1307,72 @@ __global__ __launch_bounds__(kRefineThreads) void refine_kernel(RefineArgs a) {
     return c >= 1u && c <= (uint32_t)kSlotsPerTile;
   };
   constexpr uint32_t kFromRecord = 0x80000000u;  // list entry: the element sits in a record (indices are below 2^31)
+  const float floor = a.thr[j];  // every selected element exceeds it
+
+  if (banded && passed <= (int64_t)rank && floor > 0.0f) {
+    // The floor lies above the threshold (the sample missed): everything goes back to u and v, the whole tensor is
+    // ranked as it stands there, and its tiles get mask words.  One workgroup over the tensor four times; this
+    // takes values that are large where the sample looks.
+    for (int64_t tile = t0 + tid; tile <= t1; tile += kRefineThreads) {
+      if (!is_record(tile)) continue;
+      const int c = (int)a.tile_count[tile];
+      for (int q = 0; q < c; ++q) {
+        const int32_t* r = records + tile * kSlotRecord + q;
+        a.v_out[r[0]] = __int_as_float(r[kSlotsPerTile]);
+        if (a.factor_masking) a.u_out[r[0]] = __int_as_float(r[2 * kSlotsPerTile]);
+      }
+    }
+    __syncthreads();
+    auto key_at = [&](int64_t e) { return __float_as_uint(a.v_out[e]) & 0x7FFFFFFFu; };
+#pragma unroll 1
+    for (int pass = 0; pass < 3; ++pass) {
+      const int bits = pass == 2 ? 9 : 11;
+      const int shift = 31 - consumed - bits;
+      const uint32_t digit_mask = (1u << bits) - 1u;
+      for (int i = tid; i < kSelectBins; i += kRefineThreads) sh.s.hist[i] = 0;
+      __syncthreads();
+      for (int64_t e = lo + tid; e < hi; e += kRefineThreads) {
+        const uint32_t key = key_at(e);
+        if (pass == 0 || (key >> (shift + bits)) == prefix) atomicAdd(&sh.s.hist[(key >> shift) & digit_mask], 1u);
+      }
+      __syncthreads();
+      uint32_t bin, above, members;
+      find_bin<kRefineThreads>(sh.s.hist, sh.s.wave_tot, sh.s.sel, tid, rank, bin, above, members);
+      prefix = (prefix << bits) | bin;
+      rank -= above;
+      consumed += bits;
+    }
+    for (int64_t tile = t0 + wave; tile <= t1; tile += kWaves) {
+      uint32_t own = 0, word = 0;  // the lane's elements that belong to the tensor, and those that are sent
+      for (int q = 0; q < 4 * kStreamUnroll; ++q) {
+        const int64_t e = tile_element(tile, lane, q);
+        if (e < lo || e >= hi) continue;
+        own |= 1u << q;
+        if (sent(key_at(e), prefix)) word |= 1u << q;
+      }
+      if (tile * kWaveTile >= lo && (tile + 1) * kWaveTile <= hi) {
+        a.mask[tile * 64 + lane] = (uint16_t)word;
+        const uint32_t c = wave_sum((uint32_t)__popc(word));
+        if (lane == 0) a.tile_count[tile] = c ? c | kTileCountHasMask : 0u;
+      } else {  // shared with a neighbour, whose bits stay (counts of such tiles are formed from the words)
+        const int64_t h = tile * 64 + lane;
+        const int sh16 = 16 * (int)(h & 1);
+        atomicAnd(&mask32[h >> 1], ~(own << sh16));
+        atomicOr(&mask32[h >> 1], word << sh16);
+      }
+    }
+    if (tid == 0) {
+      const float thr = __uint_as_float(prefix);
+      a.thr[j] = thr;
+      if (a.out_thr) a.out_thr[j] = thr;
+    }
+    return;
+  }
 
   if (passed <= kRefineList) {
     // From the records: one thread per tile, the counts of four tiles and then their records in flight
     // together; from the mask words of the other tiles: by the wavefront whose lanes met them.
     if (tid == 0) sh.listed = 0;
-    const float floor = a.thr[j];  // every selected element exceeds it
     __syncthreads();
     auto list_words = [&](int64_t tile, int l, uint32_t w) {  // a lane's mask word, this tensor's bits only
       int pos = (int)atomicAdd(&sh.listed, (uint32_t)__popc(w));
@@ -1305,10 +1410,21 @@ __global__ __launch_bounds__(kRefineThreads) void refine_kernel(RefineArgs a) {
             }
           }
         }
+        // one addition to the list's length per wavefront: those of its lanes would be carried out one by one
+        uint32_t at[kTilesInFlight], all = 0;
+#pragma unroll
+        for (int k = 0; k < kTilesInFlight; ++k) {
+          at[k] = all;
+          all += c[k];
+        }
+        const uint32_t upto = wave_inclusive_sum(all);
+        uint32_t from = 0;
+        if (lane == 63 && upto > 0u) from = atomicAdd(&sh.listed, upto);
+        from = wave_last(from) + upto - all;
 #pragma unroll
         for (int k = 0; k < kTilesInFlight; ++k) {
           if (c[k] == 0u) continue;
-          const uint32_t pos = atomicAdd(&sh.listed, c[k]);
+          const uint32_t pos = from + at[k];
           const int32_t ee[8] = {e[k][0].x, e[k][0].y, e[k][0].z, e[k][0].w, e[k][1].x, e[k][1].y, e[k][1].z, e[k][1].w};
           const int32_t xx[8] = {x[k][0].x, x[k][0].y, x[k][0].z, x[k][0].w, x[k][1].x, x[k][1].y, x[k][1].z, x[k][1].w};
 #pragma unroll
@@ -1381,7 +1497,7 @@ __global__ __launch_bounds__(kRefineThreads) void refine_kernel(RefineArgs a) {
         key[q] = (e & kFromRecord) ? sh.keys[p] : (__float_as_uint(a.v[e]) & 0x7FFFFFFFu);
       }
     }
-    {
+    if (passed > (int64_t)rank) {
       // One histogram over the four octaves above the sampled threshold, where the wanted rank nearly always
       // is (the last bin takes everything beyond), and direct ranking of its bin; if that does not fit, the
       // passes over the key's bits.
@@ -1409,7 +1525,7 @@ __global__ __launch_bounds__(kRefineThreads) void refine_kernel(RefineArgs a) {
         __syncthreads();
         prefix = select_in_registers<kRefinePer>(sh.s, key, 0u, rank, tid);
       }
-    }
+    }  // (else the floor is zero, and so is the threshold: fewer elements than wanted are anything else)
     // Clear the mask bit of every selected element that does not exceed the new threshold.
     // A 16-bit mask word of a tile shared with a neighbour tensor also holds that tensor's
     // bits, and its re-threshold may run at the same time: atomic AND on the 32-bit word.
@@ -1417,7 +1533,7 @@ __global__ __launch_bounds__(kRefineThreads) void refine_kernel(RefineArgs a) {
 #pragma unroll
     for (int q = 0; q < kRefinePer; ++q) {
       const int p = tid + q * kRefineThreads;
-      if (p < count && !(key[q] > prefix) && !(sh.list[p] & kFromRecord)) {
+      if (p < count && !sent(key[q], prefix) && !(sh.list[p] & kFromRecord)) {
         const int64_t e = sh.list[p];
         const int64_t tile = e / kWaveTile;
         const int r = (int)(e % kWaveTile);
@@ -1526,7 +1642,7 @@ __global__ __launch_bounds__(kRefineThreads) void refine_kernel(RefineArgs a) {
     }
     // mask bits as above
     for (int p = tid; p < count; p += kRefineThreads) {
-      if (!(keys[p] > prefix) && !(list[p] & kFromRecord)) {
+      if (!sent(keys[p], prefix) && !(list[p] & kFromRecord)) {
         const int64_t e = list[p];
         const int64_t tile = e / kWaveTile;
         const int r = (int)(e % kWaveTile);
@@ -1586,7 +1702,7 @@ __global__ __launch_bounds__(kRefineThreads) void refine_kernel(RefineArgs a) {
         const int q = __ffs(w) - 1;
         w &= w - 1;
         const uint32_t key = __float_as_uint(a.v[tile_element(tile, l, q)]) & 0x7FFFFFFFu;
-        if (!(key > prefix)) drop |= 1u << q;
+        if (!sent(key, prefix)) drop |= 1u << q;
       }
       if (drop) {
         const int64_t h = tile * 64 + l;  // index of the 16-bit word
@@ -1595,58 +1711,37 @@ __global__ __launch_bounds__(kRefineThreads) void refine_kernel(RefineArgs a) {
       }
     }
   }
-  // Records: an element that does not exceed the new threshold goes back to where the streaming
-  // pass took it from (v', and u' under factor masking), the others close ranks in the record, in
-  // their order.  One thread per tile: a record belongs to this tensor alone.  (Whether a tile has
-  // a record is read off its count, which this loop changes: each tile is looked at once, by one
-  // thread, and a count that falls to zero makes the emit pass skip the tile.)
+  // Records: a tile's count becomes the elements that exceed the new threshold, with the number that the record holds
+  // beside it, and the emit pass tells them apart and puts the others back.  (Put back from here, 2400 elements of one
+  // tensor took 16 us: one compute unit stores to half a scattered word per ns.)  One thread per tile: a record belongs
+  // to this tensor alone.
   if (a.slotted) {
     __syncthreads();  // every walk over records and counts above is over
-    int32_t* rec = reinterpret_cast<int32_t*>(a.mask);
-    constexpr int kTilesInFlight = 2;
+    constexpr int kTilesInFlight = 4;
 #pragma unroll 1
     for (int64_t first = t0; first <= t1; first += kTilesInFlight * kRefineThreads) {
       uint32_t c[kTilesInFlight];
-      int4 e[kTilesInFlight][2], x[kTilesInFlight][2], y[kTilesInFlight][2];
+      int4 x[kTilesInFlight][2];
 #pragma unroll
       for (int k = 0; k < kTilesInFlight; ++k) {
         // the counts of the tiles and their lines (a record only if the count says so) are asked for together
         const int64_t tile = first + k * kRefineThreads + tid;
         const bool whole = tile <= t1 && tile * kWaveTile >= lo && (tile + 1) * kWaveTile <= hi;
-        const int4* line = reinterpret_cast<const int4*>(rec + tile * kSlotRecord);
-        c[k] = whole ? a.tile_count[tile] : 0u;
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          e[k][h] = whole ? line[h] : make_int4(0, 0, 0, 0);
-          x[k][h] = whole ? line[kSlotsPerTile / 4 + h] : make_int4(0, 0, 0, 0);
-          y[k][h] = whole ? line[2 * kSlotsPerTile / 4 + h] : make_int4(0, 0, 0, 0);
-        }
+        const int64_t from = tile <= t1 ? tile : t0;
+        const int4* line = reinterpret_cast<const int4*>(records + from * kSlotRecord + kSlotsPerTile);
+        const uint32_t count = a.tile_count[from];
+        x[k][0] = line[0];
+        x[k][1] = line[1];
+        c[k] = whole && count <= (uint32_t)kSlotsPerTile ? count : 0u;
       }
 #pragma unroll
       for (int k = 0; k < kTilesInFlight; ++k) {
-        if (c[k] < 1u || c[k] > (uint32_t)kSlotsPerTile) continue;
-        const int64_t tile = first + k * kRefineThreads + tid;
-        int32_t* r = rec + tile * kSlotRecord;
-        const int32_t ee[8] = {e[k][0].x, e[k][0].y, e[k][0].z, e[k][0].w, e[k][1].x, e[k][1].y, e[k][1].z, e[k][1].w};
         const int32_t xx[8] = {x[k][0].x, x[k][0].y, x[k][0].z, x[k][0].w, x[k][1].x, x[k][1].y, x[k][1].z, x[k][1].w};
-        const int32_t yy[8] = {y[k][0].x, y[k][0].y, y[k][0].z, y[k][0].w, y[k][1].x, y[k][1].y, y[k][1].z, y[k][1].w};
         uint32_t kept = 0;
 #pragma unroll
-        for (int q = 0; q < kSlotsPerTile; ++q) {
-          if ((uint32_t)q >= c[k]) continue;
-          if (((uint32_t)xx[q] & 0x7FFFFFFFu) > prefix) {
-            if (kept != (uint32_t)q) {
-              r[kept] = ee[q];
-              r[kSlotsPerTile + kept] = xx[q];
-              r[2 * kSlotsPerTile + kept] = yy[q];
-            }
-            ++kept;
-          } else {
-            a.v_out[ee[q]] = __int_as_float(xx[q]);
-            if (a.factor_masking) a.u_out[ee[q]] = __int_as_float(yy[q]);
-          }
-        }
-        if (kept != c[k]) a.tile_count[tile] = kept;
+        for (int q = 0; q < kSlotsPerTile; ++q)
+          if ((uint32_t)q < c[k] && sent((uint32_t)xx[q] & 0x7FFFFFFFu, prefix)) ++kept;
+        if (kept != c[k]) a.tile_count[first + k * kRefineThreads + tid] = kept | (c[k] << kTileCountHeldShift);
       }
     }
   }
@@ -1929,10 +2024,12 @@ __global__ __launch_bounds__(kEmitSlotThreads) void emit_slots_kernel(EmitArgs a
   const uint32_t c_own = c_raw & kTileCountMask;
   int2 e_slot = make_int2(0, 0);
   int2 x_slot = make_int2(0, 0);  // bits of the values
+  int2 y_slot = make_int2(0, 0);  // ... and of u', for what a settled threshold drops
   const int32_t* __restrict__ records = reinterpret_cast<const int32_t*>(a.mask);  // see the streaming pass
   if (inside) {  // (a record only if the count says so; loaded before the count is known)
     e_slot = *reinterpret_cast<const int2*>(records + t * kSlotRecord + s);
     x_slot = *reinterpret_cast<const int2*>(records + t * kSlotRecord + kSlotsPerTile + s);
+    if (a.settled) y_slot = *reinterpret_cast<const int2*>(records + t * kSlotRecord + 2 * kSlotsPerTile + s);
   }
   // Slots taken by the tensor's tiles before the workgroup's first one.  The tensor's first tile
   // counts like the others when it lies wholly inside the tensor (its line may hold a record);
@@ -1943,7 +2040,7 @@ __global__ __launch_bounds__(kEmitSlotThreads) void emit_slots_kernel(EmitArgs a
   pre = (int)wave_sum((uint32_t)pre);
   if (lane == 0) sh.pre_tot[wave] = pre;
 
-  const bool from_slots = inside && c_raw <= (uint32_t)kSlotsPerTile;  // (a flagged count is a large number)
+  const bool from_slots = inside && !(c_raw & kTileCountHasMask);
   // tiles of this wavefront that are taken from their mask words: one bit per tile, at its first lane
   const unsigned long long others = __ballot(exists && !from_slots && s == 0);
   if (from_slots && s == 0) sh.cnt[tl] = (int)c_own;
@@ -1964,7 +2061,7 @@ __global__ __launch_bounds__(kEmitSlotThreads) void emit_slots_kernel(EmitArgs a
   const int incl = (int)wave_inclusive_sum((uint32_t)own);
   const int total = __builtin_amdgcn_readlane(incl, kEmitTiles - 1);
   if (tid == 0 && (int)((first - t0) / kEmitTiles) == blk.tensor_blocks - 1) a.out_counts[j] = base + total;
-  if (total == 0) return;
+  if (total == 0 && !a.settled) return;
   const int excl = incl - own;
   int32_t* __restrict__ out_idx = a.out_idx + region;
   float* __restrict__ out_val = a.out_val + region;
@@ -1973,12 +2070,42 @@ __global__ __launch_bounds__(kEmitSlotThreads) void emit_slots_kernel(EmitArgs a
   bool overflow = false;
   {
     const int tile_start = __shfl(excl, tl & 31);
+    // Where refine_kernel has settled the threshold, a record may hold more than is sent: the rest goes back to where
+    // the streaming pass took it from, and what is sent closes ranks (places from the votes of the tile's lanes).
+    int place[kPerLane] = {s, s + 1};
+    bool goes[kPerLane] = {s < (int)c_own, s + 1 < (int)c_own};
+    if (a.settled) {
+      const int held = (int)((c_raw >> kTileCountHeldShift) & 0xFu);
+      if (__ballot(from_slots && held > 0) != 0) {
+        const uint32_t thr = __float_as_uint(a.settled[j]);
+        const unsigned long long lower = ((1ull << (lane % kLanesPerTile)) - 1ull) << (lane & ~(kLanesPerTile - 1));
+        const bool some = from_slots && held > 0;
+        const bool keep0 = some && s < held && sent((uint32_t)x_slot.x & 0x7FFFFFFFu, thr);
+        const bool keep1 = some && s + 1 < held && sent((uint32_t)x_slot.y & 0x7FFFFFFFu, thr);
+        const unsigned long long votes0 = __ballot(keep0), votes1 = __ballot(keep1);
+        if (some) {
+          place[0] = __popcll(votes0 & lower) + __popcll(votes1 & lower);
+          place[1] = place[0] + (keep0 ? 1 : 0);
+          goes[0] = keep0;
+          goes[1] = keep1;
+          if (s < held && !keep0) {
+            v[e_slot.x] = __int_as_float(x_slot.x);
+            if (a.factor_masking) u[e_slot.x] = __int_as_float(y_slot.x);
+          }
+          if (s + 1 < held && !keep1) {
+            v[e_slot.y] = __int_as_float(x_slot.y);
+            if (a.factor_masking) u[e_slot.y] = __int_as_float(y_slot.y);
+          }
+        }
+      }
+      if (total == 0) return;
+    }
 #pragma unroll
     for (int q = 0; q < kPerLane; ++q) {
       const int32_t e_q = q == 0 ? e_slot.x : e_slot.y;
       const float x_q = __int_as_float(q == 0 ? x_slot.x : x_slot.y);
-      if (from_slots && s + q < (int)c_own) {
-        const int64_t slot = (int64_t)base + tile_start + s + q;
+      if (from_slots && goes[q]) {
+        const int64_t slot = (int64_t)base + tile_start + place[q];
         if (slot < cap) {
           out_idx[slot] = e_q;
           out_val[slot] = x_q;
@@ -2152,6 +2279,7 @@ static void launch_stream_mode(const StreamArgs& a, int mode, int groups, dim3 g
   const size_t pad = stream_lds_pad(groups, kStreamStaticLds);
   if (mode == kStreamStaged) hipLaunchKernelGGL((stream_kernel<NESTEROV, SCALED, kStreamStaged>), grid, block, pad, stream, a);
   else if (mode == kStreamSlotted) hipLaunchKernelGGL((stream_kernel<NESTEROV, SCALED, kStreamSlotted>), grid, block, pad, stream, a);
+  else if (mode == kStreamBand) hipLaunchKernelGGL((stream_kernel<NESTEROV, SCALED, kStreamBand>), grid, block, pad, stream, a);
   else hipLaunchKernelGGL((stream_kernel<NESTEROV, SCALED, kStreamPlain>), grid, block, pad, stream, a);
 }
 
@@ -2161,7 +2289,7 @@ hipError_t launch_stream(const StreamArgs& a, hipStream_t stream) {
   // scale is known to be exactly 1 when neither the norm kernel nor an override supplies it
   const bool scaled = a.scale_from_state != 0 || a.scale_const != 1.0f;
   const dim3 grid((unsigned)blocks), block(kStreamThreads);
-  const int mode = a.stage_v ? kStreamStaged : a.slotted ? kStreamSlotted : kStreamPlain;
+  const int mode = a.stage_v ? kStreamStaged : a.bands_in_pass ? kStreamBand : a.slotted ? kStreamSlotted : kStreamPlain;
   // right after the norm pass part of g comes from the last-level cache, and more wavefronts pay
   const int groups = a.scale_from_state ? kStreamGroupsAfterNorm : kStreamResidentGroups;
   if (a.nesterov) {

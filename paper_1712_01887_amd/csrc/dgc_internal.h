@@ -55,11 +55,16 @@ constexpr int kSlotRecord = 32;  // 32-bit words per tile: the 128 bytes of the 
 // Per-tile count of the slotted pass: the top bit says that the tile's line holds mask words although
 // the tile lies wholly inside one tensor (it selected more elements than a record holds).
 constexpr uint32_t kTileCountHasMask = 0x80000000u;
-constexpr uint32_t kTileCountMask = 0x7FFFFFFFu;
+constexpr uint32_t kTileCountMask = 0xFFFFu;
+// Where the re-threshold lowers the count of a tile with a record, the number of elements that the record holds.
+constexpr int kTileCountHeldShift = 16;
+static_assert(kWaveTile <= (int)kTileCountMask && kSlotsPerTile <= 15, "a count in 16 bits, a record's in four");
 static_assert(3 * kSlotsPerTile <= kSlotRecord, "index, v' and u' of every slot");
 constexpr int kEmitSlotThreads = 128;  // emit pass over records: two slots per thread
 static_assert(kEmitTiles * kSlotsPerTile == 2 * kEmitSlotThreads, "two slots of the workgroup's tiles per emit thread");
 constexpr int kRefineThreads = 1024;                  // the re-threshold pass: one workgroup per tensor
+constexpr int kRefinePer = 12;
+constexpr int kRefineList = kRefinePer * kRefineThreads;  // selected elements a workgroup lists in LDS
 
 // Receive side: pairs of one payload handled by one workgroup (kFlatPer per thread) and
 // tensors whose counts a workgroup stages in LDS at a time.
@@ -137,6 +142,10 @@ constexpr int kBandSample = kSelectRegKeys * kSelectThreads;
 // compute units a little earlier (256 of 40000: 102 and 121, of 64000: 159 and 147).
 constexpr int64_t kBandFrom = 65536, kBandFromMany = 57344;
 constexpr int64_t kBandMany = 256;
+// At the lowest densities the band's floor is the threshold of a slotted streaming pass, and refine_kernel finds the
+// exact one among what passes and puts the rest back: no pass of its own over g, u, v.
+constexpr double kBandInPassDensity = 0.002;  // (the floor lets two to three times as many pass: 4 of a tile's 1024 there)
+constexpr int64_t kBandInPassList = kRefineList * 3 / 4;
 constexpr int kBandBlockShift = 5;
 constexpr int kBandListShift = 6;       // three list words per 64 elements
 constexpr int kBandThreads = 256;
@@ -207,6 +216,7 @@ struct SelectArgs {
   int32_t block_shift;  // log2(sample_block)
   BandState* bands;     // device, a slot of kBandStride bytes per tensor that has a band; null: none has
   uint32_t* band_list;  // device, see band_list_begin
+  int32_t bands_in_pass;  // the band's floor is the pass's threshold, refine_kernel ranks what passes: no list
   uint32_t seed_lo, seed_hi, iter_lo, iter_hi;
 };
 
@@ -232,6 +242,8 @@ struct StreamArgs {
   float* stage_u;              // device, n floats, or null: no region can overflow, or no factor masking
   int32_t factor_masking;
   int32_t slotted;             // slotted pass (densities up to 0.5 %): records in place of mask words
+  int32_t bands_in_pass;       // as in SelectArgs; implies `slotted`
+  const TensorPlan* plans;     // device, T: looked at for NaNs with bands_in_pass
 };
 
 struct EmitBlock {
@@ -257,6 +269,8 @@ struct RefineArgs {
   int32_t factor_masking;
   float* u_out;                // u and v, to put back what is dropped from a record
   float* v_out;
+  int32_t on_excess;           // re-threshold tensors that let more than refine_limit pass
+  int32_t bands_in_pass;       // as in SelectArgs: settle the threshold of tensors with a band
 };
 
 struct EmitArgs {
@@ -275,6 +289,7 @@ struct EmitArgs {
   const float* stage_v;        // as in StreamArgs; null: the streaming pass was a plain one
   const float* stage_u;
   int32_t slotted;             // as in StreamArgs
+  const float* settled;        // device, T: the thresholds, where refine_kernel has run on records; else null
 };
 
 struct MergeBlock {

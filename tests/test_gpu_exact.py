@@ -252,3 +252,35 @@ def test_exact_selection_of_a_large_set_in_the_static_array(numel):
         d.close()
     for a, b in zip(*results):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("whole_regions", [False, True])
+@pytest.mark.parametrize("flags", [EXACT, EXACT | B.DGC_FLAG_SORTED_OUTPUT | B.DGC_FLAG_NO_FACTOR_MASKING])
+@pytest.mark.parametrize("many", [9000, 12500, 30000])
+def test_exact_at_low_densities_where_many_pass_the_floor(many, flags, whole_regions):
+    """Large values where the band's sample did not look: up to 12288 that pass are listed on chip, more in the payload
+    region if they fit there, and otherwise the tiles are walked over."""
+    sizes = [500, 200001, 90000, 64]
+    offsets = np.concatenate([[0], np.cumsum(sizes)])
+    caps = list(sizes) if whole_regions else None
+    p = Pair(offsets, capacities=caps, momentum=0.0, density=0.002, seed=14, flags=flags)
+    rng = np.random.default_rng(many)
+    for it in range(2):
+        g = (1e-3 * rng.standard_normal(p.n)).astype(np.float32)
+        unseen = np.setdiff1d(np.arange(sizes[1]), np.unique(band_sample(sizes[1], 14, it, 1)))
+        pos = rng.choice(unseen, many, replace=False)
+        g[offsets[1] + pos] = rng.standard_normal(many).astype(np.float32) + 3.0
+        p.step(g, it, label=f"exact, {many} unseen flags={flags} it{it}")
+    p.close()
+
+
+@pytest.mark.parametrize("density", [0.001, 0.002, 0.0021])
+@pytest.mark.parametrize("size", [3_000_000, 4_600_000])
+def test_exact_on_both_sides_of_the_rule_for_bands_in_the_pass(density, size):
+    """Up to 0.2 % and as long as what exceeds the floor fits one workgroup's list; with the re-threshold beside it."""
+    offsets = [0, 40000, 40000 + size]
+    p = Pair(offsets, momentum=0.9, density=density, seed=15, flags=EXACT, refine_alpha=2.0)
+    rng = np.random.default_rng(size)
+    g = (1e-2 * rng.standard_t(3, p.n)).astype(np.float32)
+    p.step(g, 0, label=f"exact, n={size} d={density}")
+    p.close()
