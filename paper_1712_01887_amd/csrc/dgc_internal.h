@@ -113,6 +113,10 @@ constexpr int kScanPer = 8;          // block sums per thread and round of the s
 constexpr int kDecodePer = 8;
 constexpr int kDecodeBlock = 64 * kDecodePer;
 static_assert((kWireChunk >> 3) == kDecodeBlock, "s goes up to 3: the blocks the workspace is sized for");
+// Payloads of the direct form that are decoded in one launch: kDecodeGroupsMax workgroups of kDecodeGroup entries at most.
+constexpr int kDecodeGroupThreads = 512;
+constexpr int kDecodeGroup = kDecodeGroupThreads * kDecodePer;
+constexpr int kDecodeGroupsMax = 8;
 // Range form of the decoder: a workgroup owns a range of elements and adds the entries that fall into it
 // in LDS, payloads in order (32 KB: four workgroups per compute unit), then touches `dense` once per element.
 constexpr int kDecodeRange = 8192;
