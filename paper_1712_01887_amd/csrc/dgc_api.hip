@@ -190,11 +190,14 @@ void build_plan(dgc_handle* h) {
     ++readers;
     if (n > longest) longest = n;
   }
-  const bool by_bands = longest > (readers >= kBandMany ? kBandFromMany : kBandFrom);
+  // The lists of bands have areas in the workspace, whose size must not depend on the density.
+  const bool by_lists = longest > (readers >= kBandMany ? kBandFromMany : kBandFrom);
   uint32_t bands = 0;
   h->any_band = false;
   // What lies above the band's floor in the longest of these tensors has to fit the list of one workgroup.
-  h->bands_in_pass = by_bands && c.density <= kBandInPassDensity && longest * band_floor_rank(c.density) / kBandSample <= kBandInPassList;
+  h->bands_in_pass = longest > kBandFromInPass && c.density <= kBandInPassDensity &&
+                     longest * band_floor_rank(c.density) / kBandSample <= kBandInPassList;
+  const bool by_bands = by_lists || h->bands_in_pass;
   for (int32_t j = 0; j < h->num_tensors; ++j) {
     const int64_t n = h->offsets[j + 1] - h->offsets[j];
     TensorPlan& p = h->plans[j];
@@ -220,7 +223,7 @@ void build_plan(dgc_handle* h) {
           p.nblocks = bands;
           h->any_band = true;
         }
-        ++bands;
+        if (by_lists) ++bands;
       }
     } else {
       const int64_t draws = (s + B - 1) / B;
@@ -727,7 +730,8 @@ dgc_status dgc_compress(dgc_handle* h, const float* g, float* u, float* v, int32
   if (ev && !hip_ok(hipEventRecord(ev[3], stream), "record event")) return DGC_ERR_HIP;
 
   // paper: Section 5 -- a tensor that lets through far more elements than wanted gets an exact
-  // threshold, computed among the elements that passed
+  // threshold, computed among the elements that passed; so does, at the lowest densities, every large tensor
+  // whose threshold is to be exact in the first place
   if (c.refine_alpha > 0.0f || bands_in_pass) {
     RefineArgs ra{};
     ra.on_excess = c.refine_alpha > 0.0f ? 1 : 0;

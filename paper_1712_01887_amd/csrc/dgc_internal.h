@@ -44,7 +44,6 @@ constexpr int kEmitThreads = 256;
 constexpr int kEmitElements = 32768;                  // elements per workgroup
 constexpr int kEmitTiles = kEmitElements / kWaveTile;
 static_assert(kEmitTiles % (kEmitThreads / 64) == 0, "tiles are dealt round-robin to wavefronts");
-constexpr int kEmitList = 4096;                       // elements listed in LDS at a time
 // Slots: at the densities the method runs at, a tile of 1024 elements holds one or two selected
 // elements.  The streaming pass parks up to kSlotsPerTile of them in a record (kSlotsPerTile
 // indices, their v', their u', padding) that it writes in place of the tile's mask words, and
@@ -56,7 +55,7 @@ constexpr int kSlotRecord = 32;  // 32-bit words per tile: the 128 bytes of the 
 // the tile lies wholly inside one tensor (it selected more elements than a record holds).
 constexpr uint32_t kTileCountHasMask = 0x80000000u;
 constexpr uint32_t kTileCountMask = 0xFFFFu;
-// Where the re-threshold lowers the count of a tile with a record, the number of elements that the record holds.
+// Where the re-threshold (or the settling of an exact threshold) lowers the count of a tile with a record, the number of elements that the record holds.
 constexpr int kTileCountHeldShift = 16;
 static_assert(kWaveTile <= (int)kTileCountMask && kSlotsPerTile <= 15, "a count in 16 bits, a record's in four");
 static_assert(3 * kSlotsPerTile <= kSlotRecord, "index, v' and u' of every slot");
@@ -148,7 +147,14 @@ constexpr int64_t kBandFrom = 65536, kBandFromMany = 57344;
 constexpr int64_t kBandMany = 256;
 // At the lowest densities the band's floor is the threshold of a slotted streaming pass, and refine_kernel finds the
 // exact one among what passes and puts the rest back: no pass of its own over g, u, v.
-constexpr double kBandInPassDensity = 0.002;  // (the floor lets two to three times as many pass: 4 of a tile's 1024 there)
+// (The floor lets two to three times as many pass: 4 of a tile's 1024 elements at 0.2 %.  30 tensors of 8 M elements,
+// 0.1 %: 91 against 75 us for the call, 0.2 %: 95 and 86; at 0.4 %, where a tile in five holds more than a record,
+// 60 of 8 M: 98 and 108, 12 of 1 M: 57 and 71.)
+constexpr double kBandInPassDensity = 0.002;
+// ... and from a shorter tensor on, because no pass is added (calls at 0.1 %, the passes of one workgroup against this:
+// one tensor of 33000 31.2 and 32.0 us, of 50000 39.0 and 31.5, of 65000 46 and 33; 20 of 33000 36 and 44; 500 of
+// 40000 173 and 137; 100 of 60000 72 and 59).
+constexpr int64_t kBandFromInPass = 40960;
 constexpr int64_t kBandInPassList = kRefineList * 3 / 4;
 constexpr int kBandBlockShift = 5;
 constexpr int kBandListShift = 6;       // three list words per 64 elements

@@ -275,12 +275,15 @@ def test_exact_at_low_densities_where_many_pass_the_floor(many, flags, whole_reg
 
 
 @pytest.mark.parametrize("density", [0.001, 0.002, 0.0021])
-@pytest.mark.parametrize("size", [3_000_000, 4_600_000])
+@pytest.mark.parametrize("size", [40960, 40961, 65537, 3_000_000, 4_600_000])
 def test_exact_on_both_sides_of_the_rule_for_bands_in_the_pass(density, size):
-    """Up to 0.2 % and as long as what exceeds the floor fits one workgroup's list; with the re-threshold beside it."""
+    """Up to 0.2 %, from 40961 elements on and as long as what exceeds the floor fits one workgroup's list; with the
+    re-threshold beside it, and with a density that changes under one handle and workspace."""
     offsets = [0, 40000, 40000 + size]
-    p = Pair(offsets, momentum=0.9, density=density, seed=15, flags=EXACT, refine_alpha=2.0)
+    p = Pair(offsets, layout_density=0.02, momentum=0.9, density=density, seed=15, flags=EXACT, refine_alpha=2.0)
     rng = np.random.default_rng(size)
-    g = (1e-2 * rng.standard_t(3, p.n)).astype(np.float32)
-    p.step(g, 0, label=f"exact, n={size} d={density}")
+    for it, d in enumerate((density, 0.02, density)):
+        p.set_density(d)
+        g = (1e-2 * rng.standard_t(3, p.n)).astype(np.float32)
+        p.step(g, it, label=f"exact, n={size} d={d}")
     p.close()
