@@ -287,3 +287,30 @@ def test_exact_on_both_sides_of_the_rule_for_bands_in_the_pass(density, size):
         g = (1e-2 * rng.standard_t(3, p.n)).astype(np.float32)
         p.step(g, it, label=f"exact, n={size} d={d}")
     p.close()
+
+
+@pytest.mark.parametrize("kind", ["one magnitude", "four levels", "few of one magnitude", "ties at the end", "rows"])
+@pytest.mark.parametrize("size", [50_000, 400_001])
+def test_floor_in_the_pass_with_ties_and_rows(kind, size):
+    """The floor is itself the threshold: found among the first elements, far into the tensor, or nowhere but at its end;
+    and large values side by side, so that tiles lose many elements at once.  A NaN beside them."""
+    rng = np.random.default_rng(size)
+    offsets = [0, 333, 333 + size]
+    p = Pair(offsets, layout_density=0.02, momentum=0.0, density=0.002, seed=16, flags=EXACT)
+    g = rng.standard_normal(offsets[-1]).astype(np.float32)
+    where = np.arange(offsets[-1])
+    if kind == "one magnitude":
+        g = np.sign(g)
+    elif kind == "four levels":
+        g = np.clip(np.round(g), -2, 2)
+    elif kind == "few of one magnitude":
+        g = np.sign(g) * (rng.random(g.size) < 0.01)
+    elif kind == "ties at the end":
+        g = np.where(where >= offsets[-1] - size // 100, np.sign(g), 0.0)
+    else:
+        g = g * np.where(where // 650 % 100 == 0, 100.0, 1.0)
+    g = g.astype(np.float32)
+    p.step(g, 0, label=f"exact, {kind}, n={size}")
+    g[offsets[-1] // 2] = np.nan
+    p.step(g, 1, label=f"exact, {kind} and a NaN, n={size}")
+    p.close()
