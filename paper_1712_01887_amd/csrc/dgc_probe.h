@@ -1,0 +1,24 @@
+// First round of probes of a search in a list of up to 2^31 - 1 values: plain arithmetic, for the host too.
+#ifndef DGC_PROBE_H_
+#define DGC_PROBE_H_
+
+#include <stdint.h>
+
+namespace dgc {
+
+// 1 << shift probes (32 at least), evenly spaced over a list of m values.  The last probe's position stays below
+// m + 2^shift, and every product below in 32 bits without a sign, because a probe beyond the last is told by its
+// number, not by where it would lie: in a list of 2^30 values and more, 63 steps of a round of 32 are 2^31.
+struct FirstRound {
+  uint32_t m, step, probes;
+  constexpr FirstRound(int length, int shift)
+      : m((uint32_t)length), step((m + (1u << shift) - 1u) >> shift), probes(1u << shift) {}
+  constexpr bool asks(uint32_t probe) const { return probe < probes && probe * step < m; }
+  constexpr int at(uint32_t probe) const { return asks(probe) ? (int)(probe * step) : 0; }
+  // the answer lies in [lo, hi] if `below` probes, a prefix of those that ask, are less than what is looked for
+  constexpr int lo(int below) const { return below > 0 ? (int)((uint32_t)(below - 1) * step + 1u) : 0; }
+  constexpr int hi(int below) const { return below > 0 ? (int)((uint32_t)below * step < m ? (uint32_t)below * step : m) : 0; }
+};
+
+}  // namespace dgc
+#endif  // DGC_PROBE_H_

@@ -4,6 +4,7 @@
 
 #include "dgc_device.h"
 #include "dgc_internal.h"
+#include "dgc_probe.h"
 
 namespace dgc {
 namespace {
@@ -178,14 +179,13 @@ __device__ __forceinline__ void wave_equal_ranges(const int32_t* __restrict__ L0
   {
     const bool twice = (m0 > 64 * 33 && m0 <= 128 * 33) || (m1 > 64 * 33 && m1 <= 128 * 33);  // uniform
     const int shift = twice ? 7 : m0 > 128 * 33 || m1 > 128 * 33 ? 5 : 6;  // log2 of the probes
-    const int step0 = (m0 + (1 << shift) - 1) >> shift, step1 = (m1 + (1 << shift) - 1) >> shift;
-    const int p0 = lane * step0, p1 = lane * step1, q0 = p0 + 64 * step0, q1 = p1 + 64 * step1;
-    const bool ask0 = p0 < m0, ask1 = p1 < m1, more0 = twice && q0 < m0, more1 = twice && q1 < m1;
-    const int32_t v0 = A[ask0 ? p0 : 0], v1 = B[ask1 ? p1 : 0];
+    const FirstRound r0(m0, shift), r1(m1, shift);
+    const bool ask0 = r0.asks(lane), ask1 = r1.asks(lane), more0 = r0.asks(lane + 64), more1 = r1.asks(lane + 64);
+    const int32_t v0 = A[r0.at(lane)], v1 = B[r1.at(lane)];
     int32_t w0 = 0, w1 = 0;
     if (twice) {
-      w0 = A[more0 ? q0 : 0];
-      w1 = B[more1 ? q1 : 0];
+      w0 = A[r0.at(lane + 64)];
+      w1 = B[r1.at(lane + 64)];
     }
     auto below = [&](int32_t bound, bool ask, int32_t v, bool more, int32_t w) {  // probes below the bound: a prefix
       return __popcll(__ballot(ask && v < bound)) + __popcll(__ballot(more && w < bound));
@@ -193,10 +193,10 @@ __device__ __forceinline__ void wave_equal_ranges(const int32_t* __restrict__ L0
     const int ca0 = below(xa, ask0, v0, more0, w0), cb0 = below(xb, ask0, v0, more0, w0);
     const int ca1 = below(xa, ask1, v1, more1, w1), cb1 = below(xb, ask1, v1, more1, w1);
     const int c0 = half ? cb0 : ca0, c1 = half ? cb1 : ca1;
-    lo0 = c0 > 0 ? (c0 - 1) * step0 + 1 : 0;
-    hi0 = c0 > 0 ? (c0 * step0 < m0 ? c0 * step0 : m0) : 0;
-    lo1 = c1 > 0 ? (c1 - 1) * step1 + 1 : 0;
-    hi1 = c1 > 0 ? (c1 * step1 < m1 ? c1 * step1 : m1) : 0;
+    lo0 = r0.lo(c0);
+    hi0 = r0.hi(c0);
+    lo1 = r1.lo(c1);
+    hi1 = r1.hi(c1);
   }
   while (__ballot(hi0 > lo0 || hi1 > lo1)) {
     const int span0 = hi0 - lo0, span1 = hi1 - lo1;
