@@ -294,6 +294,8 @@ dgc_status dgc_decompress_accumulate(dgc_handle* h, float* dense, int64_t n, int
  * `out_offsets_host`; counts_w is the device int32[num_tensors] written by
  * dgc_compress (clamped to each region's capacity here).
  *   workspace    device workspace of this handle (holds the layout copy)
+ * A payload's arrays need not go on behind the last pair of its last region that has one; slots before it that
+ * hold no pair may be read, and are not used.
  * The regions must be as dgc_compress of this library writes them (the parts of
  * consecutive blocks of 32768 elements of a tensor follow each other in index order; the
  * order inside a part is free, the indices of one payload are distinct).  The payloads are

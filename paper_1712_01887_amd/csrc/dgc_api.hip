@@ -1024,7 +1024,7 @@ static dgc_status scatter_regions(dgc_handle* h, float* dense, int32_t num_paylo
                                      expected_pairs, sgd, scale, stream),
                 "launch merge kernel"))
       return DGC_ERR_HIP;
-  } else if (!hip_ok(launch_merge_parts(dense, p, num_payloads, oo, widest, parts, num_parts, found, replace, sgd, scale,
+  } else if (!hip_ok(launch_merge_parts(dense, p, num_payloads, oo, parts, num_parts, found, replace, sgd, scale,
                                         stream),
                      "launch merge kernel")) {
     return DGC_ERR_HIP;

@@ -394,7 +394,7 @@ hipError_t launch_merge_regions(float* dense, const RegionPayloads& p, int32_t n
                                 int32_t num_blocks, int64_t expected_pairs, bool scaled, float scale,
                                 hipStream_t stream);
 hipError_t launch_merge_parts(float* dense, const RegionPayloads& p, int32_t num, const int64_t* out_offsets_dev,
-                              int64_t capacity, const MergeBlock* parts, int32_t num_parts, void* found, bool replace, bool scaled,
+                              const MergeBlock* parts, int32_t num_parts, void* found, bool replace, bool scaled,
                               float scale, hipStream_t stream);
 hipError_t launch_clear_parts(float* dense, const RegionPayloads& p, int32_t num, const int64_t* out_offsets_dev,
                               const MergeBlock* parts, int32_t num_parts, void* found, hipStream_t stream);

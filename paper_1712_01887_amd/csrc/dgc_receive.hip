@@ -708,7 +708,7 @@ __global__ __launch_bounds__(kFlatThreads) void locate_parts_kernel(RegionPayloa
 //
 // The pairs of a part are taken in chunks of kPartChunk slots, a wavefront each and four consecutive slots to a
 // lane, that start on 128-byte lines of the payload's index array (the slots before its first pair and behind its
-// last stay empty).  Two things bounded the kernel before: loads of a pair per lane that straddled lines (a bare
+// last stay empty, and no load goes beyond the last).  Two things bounded the kernel before: loads of a pair per lane that straddled lines (a bare
 // read of eight payloads' pairs, 1.95 GB in parts of 8192: 284 us in whole lines, 338 half a line off), and
 // instructions, sixteen wavefronts on four SIMDs (chunks of one pair per lane, lines or not: 535 us at 25 %).
 // A round is a chunk for every wavefront, of one payload or of several in their order, and only a change of
@@ -719,13 +719,14 @@ __global__ __launch_bounds__(kFlatThreads) void locate_parts_kernel(RegionPayloa
 // where 933 parts leave a fourth round of workgroups two thirds full.  Three rounds on their way: 442, 194, 100.
 template <bool REPLACE>
 __global__ __launch_bounds__(kPartThreads) void merge_parts_kernel(float* __restrict__ dense, RegionPayloads p,
-                                                                   int32_t num_payloads, int32_t capacity,
+                                                                   int32_t num_payloads,
                                                                    const MergeBlock* __restrict__ blocks,
                                                                    int32_t num_blocks,
                                                                    const int2* __restrict__ found, float scale,
                                                                    int32_t scaled) {
   typedef float fvec4u __attribute__((ext_vector_type(4), aligned(4)));  // a range starts anywhere
   typedef int32_t ivec4 __attribute__((ext_vector_type(4)));
+  typedef int32_t ivec4u __attribute__((ext_vector_type(4), aligned(4)));
   constexpr int kQuads = kEmitElements / 4 / kPartThreads;
   constexpr int kWaves = kPartThreads / 64;
   __shared__ alignas(16) float acc[kEmitElements + 64];  // behind the range a word per lane for what is no pair of it
@@ -786,8 +787,9 @@ __global__ __launch_bounds__(kPartThreads) void merge_parts_kernel(float* __rest
     t.idx -= t.head;
     t.pos = f.x - t.head;
     t.val = val_of + f.x - t.head;
-    t.end = t.head + f.y;
-    const uint32_t own = f.y > 0 ? (uint32_t)(t.end + kPartChunk - 1) / (uint32_t)kPartChunk : 0u;
+    const uint32_t until = (uint32_t)t.head + (uint32_t)f.y;  // (beyond 2^31 - 1: a foreign region)
+    t.end = (int)(until < 0x7FFFFFFFu ? until : 0x7FFFFFFFu);
+    const uint32_t own = f.y > 0 ? ((uint32_t)t.end + (uint32_t)kPartChunk - 1u) / (uint32_t)kPartChunk : 0u;
     const uint32_t upto = wave_inclusive_sum(own);
     t.total = wave_last(upto);
     t.chunk0 = lane < num_payloads ? upto - own : 0xFFFFFFFFu;
@@ -805,6 +807,9 @@ __global__ __launch_bounds__(kPartThreads) void merge_parts_kernel(float* __rest
     int w;              // payload of the wavefront's chunk; -1: none
     int first, last;    // payloads of the whole round
     int part;           // -1: there is no round
+    bool edge;          // the chunk holds slots that are no pairs of the part:
+    uint32_t wanted;    // ... a bit for each of the lane's four that is one,
+    int back;           // ... and how many places behind its own each was loaded
   };
   int fb = b;            // the part that is being fetched
   Table t = make_table(entry_of(b));
@@ -826,6 +831,7 @@ __global__ __launch_bounds__(kPartThreads) void merge_parts_kernel(float* __rest
     const uint32_t c = cursor + (uint32_t)wave;
     cursor = until;
     L.w = -1;
+    L.edge = false;
     if (c >= until) return;  // uniform
     const int w = payload_at(t, c);
     L.w = w;
@@ -834,28 +840,27 @@ __global__ __launch_bounds__(kPartThreads) void merge_parts_kernel(float* __rest
     const int head = __builtin_amdgcn_readlane(t.head, w), end = __builtin_amdgcn_readlane(t.end, w);
     const int32_t* __restrict__ from = reinterpret_cast<const int32_t*>(of_lane(reinterpret_cast<uint64_t>(t.idx), w));
     const float* __restrict__ values = reinterpret_cast<const float*>(of_lane(reinterpret_cast<uint64_t>(t.val), w));
-    if (slot0 >= head && slot0 + kPartChunk <= end) {
+    if (slot0 >= head && end - slot0 >= kPartChunk) {
       L.idx = __builtin_nontemporal_load(reinterpret_cast<const ivec4*>(from + slot));
       L.x = __builtin_nontemporal_load(reinterpret_cast<const fvec4u*>(values + slot));
     } else {
-      // Slots before the first pair and behind the last hold other parts' pairs, or nothing that matters: a
-      // four that has any of the part's is loaded whole if all of it lies inside the arrays.
-      L.idx = ivec4{INT32_MIN, INT32_MIN, INT32_MIN, INT32_MIN};  // outside every range
-      L.x = fvec4u{0.0f, 0.0f, 0.0f, 0.0f};
-      const int32_t pos = __builtin_amdgcn_readlane(t.pos, w) + slot;
-      if (slot + 4 > head && slot < end) {
-        if (pos >= 0 && pos + 4 <= capacity) {
-          const ivec4 y = __builtin_nontemporal_load(reinterpret_cast<const ivec4*>(from + slot));
-          L.x = __builtin_nontemporal_load(reinterpret_cast<const fvec4u*>(values + slot));
+      // Slots before the first pair and behind the last hold other parts' pairs, or nothing that matters, or do not
+      // exist.  (What is loaded is sorted out when the round is added: nothing here waits for it.)
+      const EdgeFour four(slot, head, end, __builtin_amdgcn_readlane(t.pos, w) + slot);
+      L.edge = true;
+      L.wanted = 0;
 #pragma unroll
-          for (int k = 0; k < 4; ++k) L.idx[k] = slot + k >= head && slot + k < end ? y[k] : INT32_MIN;
-        } else {
+      for (int k = 0; k < 4; ++k) L.wanted |= EdgeFour::wanted(slot + k, head, end) ? 1u << k : 0u;
+      L.back = four.whole ? four.back : 0;
+      if (four.whole) {
+        L.idx = __builtin_nontemporal_load(reinterpret_cast<const ivec4u*>(from + slot - four.back));
+        L.x = __builtin_nontemporal_load(reinterpret_cast<const fvec4u*>(values + slot - four.back));
+      } else if (four.any) {
 #pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            if (slot + k >= head && slot + k < end) {
-              L.idx[k] = from[slot + k];
-              L.x[k] = values[slot + k];
-            }
+        for (int k = 0; k < 4; ++k) {
+          if ((L.wanted >> k) & 1u) {
+            L.idx[k] = from[slot + k];
+            L.x[k] = values[slot + k];
           }
         }
       }
@@ -885,6 +890,19 @@ __global__ __launch_bounds__(kPartThreads) void merge_parts_kernel(float* __rest
     auto add = [&](Round& L) {
       uint32_t at[4];
       float x[4];
+      if (L.edge) {  // uniform
+        if (L.back & 1) {
+          L.idx = ivec4{L.idx[1], L.idx[2], L.idx[3], L.idx[3]};
+          L.x = fvec4u{L.x[1], L.x[2], L.x[3], L.x[3]};
+        }
+        if (L.back & 2) {
+          L.idx = ivec4{L.idx[2], L.idx[3], L.idx[3], L.idx[3]};
+          L.x = fvec4u{L.x[2], L.x[3], L.x[3], L.x[3]};
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          if (!((L.wanted >> k) & 1u)) L.idx[k] = INT32_MIN;  // outside every range
+      }
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         const uint32_t r = (uint32_t)L.idx[k] - begin;
@@ -1110,7 +1128,7 @@ static void launch_locate_parts(const RegionPayloads& p, int32_t num, const int6
 }
 
 hipError_t launch_merge_parts(float* dense, const RegionPayloads& p, int32_t num, const int64_t* out_offsets_dev,
-                              int64_t capacity, const MergeBlock* parts, int32_t num_parts, void* found, bool replace, bool scaled,
+                              const MergeBlock* parts, int32_t num_parts, void* found, bool replace, bool scaled,
                               float scale, hipStream_t stream) {
   if (num <= 0 || num_parts <= 0) return hipSuccess;
   launch_locate_parts(p, num, out_offsets_dev, parts, num_parts, static_cast<int2*>(found), stream);
@@ -1124,10 +1142,10 @@ hipError_t launch_merge_parts(float* dense, const RegionPayloads& p, int32_t num
   const int grid = num_parts < compute_units ? num_parts : compute_units;
   if (replace)
     hipLaunchKernelGGL(merge_parts_kernel<true>, dim3((unsigned)grid), dim3(kPartThreads), 0, stream, dense, p, num,
-                       (int32_t)capacity, parts, num_parts, static_cast<const int2*>(found), scale, scaled ? 1 : 0);
+                       parts, num_parts, static_cast<const int2*>(found), scale, scaled ? 1 : 0);
   else
     hipLaunchKernelGGL(merge_parts_kernel<false>, dim3((unsigned)grid), dim3(kPartThreads), 0, stream, dense, p, num,
-                       (int32_t)capacity, parts, num_parts, static_cast<const int2*>(found), scale, scaled ? 1 : 0);
+                       parts, num_parts, static_cast<const int2*>(found), scale, scaled ? 1 : 0);
   return hipGetLastError();
 }
 
