@@ -20,6 +20,11 @@ struct FirstRound {
   constexpr int hi(int below) const { return below > 0 ? (int)((uint32_t)below * step < m ? (uint32_t)below * step : m) : 0; }
 };
 
+// log2 of the probes that the range merge's first round makes in a list of m values, whatever other list is searched
+// beside it: enough to leave brackets of 32, for which one more round of 32 is the last, in up to 4224 values; in
+// longer lists, which take three rounds anyway, the fewest.
+constexpr int first_round_shift(int m) { return m > 128 * 33 ? 5 : m > 64 * 33 ? 7 : 6; }
+
 // Four consecutive slots of which some lie outside [head, end), the slots that hold a part's pairs.  Those behind
 // `end` may not exist: a payload need not go on behind its last pair.  Those before `head` do, as far back as the
 // payload's first slot (`pos` is the place of `slot` in the payload).  So one load of four that ends at `end` gets all

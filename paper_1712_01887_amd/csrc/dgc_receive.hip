@@ -166,7 +166,8 @@ __global__ __launch_bounds__(kFlatThreads) void scatter_regions_kernel(float* de
 // leave brackets of 32 and one more round, half the lanes to a bound, is the last; up to 4224 with two probes each
 // (161 tensors, the longest of 2.36 M elements, sixteen payloads: 25.6 -> 24.2 us).  Longer lists take three rounds
 // anyway, and the fewer the different sectors that the first one reads, the better: 62 tensors of up to 10 M
-// elements, eight payloads, 32 probes 37 us, 64 probes 38, 128 probes 41.
+// elements, eight payloads, 32 probes 37 us, 64 probes 38, 128 probes 41.  The two lists of one payload choose for
+// themselves: with one number for both, the longer list's, that set took 36.0 us and takes 35.3.
 __device__ __forceinline__ void wave_equal_ranges(const int32_t* __restrict__ L0, int m0, const int32_t* __restrict__ L1,
                                                   int m1, const int32_t* __restrict__ safe, int32_t xa, int32_t xb,
                                                   int lane, int& lo_0, int& hi_0, int& lo_1, int& hi_1) {
@@ -177,9 +178,8 @@ __device__ __forceinline__ void wave_equal_ranges(const int32_t* __restrict__ L0
   const int32_t* __restrict__ B = m1 > 0 ? L1 : safe;
   int lo0, hi0, lo1, hi1;  // of the lane's half
   {
-    const bool twice = (m0 > 64 * 33 && m0 <= 128 * 33) || (m1 > 64 * 33 && m1 <= 128 * 33);  // uniform
-    const int shift = twice ? 7 : m0 > 128 * 33 || m1 > 128 * 33 ? 5 : 6;  // log2 of the probes
-    const FirstRound r0(m0, shift), r1(m1, shift);
+    const FirstRound r0(m0, first_round_shift(m0)), r1(m1, first_round_shift(m1));
+    const bool twice = r0.probes > 64u || r1.probes > 64u;  // uniform
     const bool ask0 = r0.asks(lane), ask1 = r1.asks(lane), more0 = r0.asks(lane + 64), more1 = r1.asks(lane + 64);
     const int32_t v0 = A[r0.at(lane)], v1 = B[r1.at(lane)];
     int32_t w0 = 0, w1 = 0;

@@ -15,6 +15,9 @@ int main() {
   for (int d = 0; d <= 70; ++d) lengths.push_back(2147483647 - d);
   long checked = 0;
   for (int m : lengths) {
+    const dgc::FirstRound own(m, dgc::first_round_shift(m));
+    if (m <= 4224 && own.step > 33) return std::printf("m %d: brackets of %u\n", m, own.step - 1), 1;
+    if (m > 4224 && own.probes != 32) return std::printf("m %d: %u probes\n", m, own.probes), 1;
     for (int shift = 5; shift <= 7; ++shift) {
       const dgc::FirstRound r(m, shift);
       std::vector<int> asked;

@@ -63,3 +63,27 @@ def test_lists_of_every_shape(workers, previous, crowded):
             expect[pos] = (expect[pos] + val).astype(np.float32)
         assert np.array_equal(dense.cpu().numpy(), expect), turn
         dgc.close()
+
+
+@pytest.mark.parametrize("new,old", [(2113, 8600), (4224, 17000), (3000, 20000), (900, 9000), (8600, 2500), (20000, 4224), (2112, 4225), (40, 3000)])
+def test_new_and_previous_lists_of_very_different_lengths(new, old):
+    """As after a change of density: the two are searched together, each with its own number of probes."""
+    import torch
+    rng = np.random.default_rng([new, old])
+    offsets = np.concatenate([[0], np.cumsum(SIZES)])
+    n = int(offsets[-1])
+    layout = [0, 900, 900 + 20500, 900 + 20500 + 5]
+    dgc = B.Dgc(B.make_config(density=0.003, num_workers=3), offsets)
+    dgc.set_layout(layout)
+    fresh = [payload(m, rng, False, layout, offsets) for m in (new, new, 0)]
+    last = [payload(m, rng, False, layout, offsets) for m in (old, 7, old)]
+    was, expect = np.zeros(n, np.float32), np.zeros(n, np.float32)
+    for (pos, val), _ in last:
+        was[pos] += val
+    for (pos, val), _ in fresh:
+        expect[pos] = (expect[pos] + val).astype(np.float32)
+    dense = torch.from_numpy(was).cuda()
+    lists = tuple([d[i] for _, d in fresh] for i in range(3))
+    dgc.dgc_decompress_replace_regions(dense, *lists, [d[0] for _, d in last], [d[2] for _, d in last])
+    assert np.array_equal(dense.cpu().numpy(), expect)
+    dgc.close()
