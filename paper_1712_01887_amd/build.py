@@ -20,7 +20,8 @@ LIB_PATH = os.path.join(HERE, "libdgc.so")
 SOURCES = [os.path.join(HERE, "csrc", name) for name in
            ("dgc_api.hip", "dgc_compress.hip", "dgc_receive.hip", "dgc_wire.hip")]
 HEADERS = [os.path.join(HERE, "csrc", "dgc_internal.h"), os.path.join(HERE, "csrc", "dgc_device.h"),
-           os.path.join(HERE, "csrc", "dgc_probe.h"), os.path.join(ROOT, "include", "dgc.h")]
+           os.path.join(HERE, "csrc", "dgc_probe.h"),
+           os.path.join(HERE, "csrc", "dgc_band.h"), os.path.join(ROOT, "include", "dgc.h")]
 
 
 def hipcc_path() -> str:

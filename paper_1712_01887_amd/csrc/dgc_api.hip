@@ -30,6 +30,7 @@ struct dgc_handle {
   std::vector<int64_t> draws;        // T
   bool any_band = false;             // some tensor's threshold is found by way of a band (TensorPlan.exact == 2)
   bool bands_in_pass = false;        // ... whose floor the streaming pass compares with
+  int64_t band_elements = 0;         // elements of these tensors
   uint32_t most_bands = 0;           // tensors that take a band at some density; 0: none does
   std::vector<uint32_t> tile_info;   // ceil(n / kWaveTile)
   std::vector<float> tile_thr_init;  // ceil(n / kWaveTile): NaN where a tile is not wholly inside one tensor
@@ -169,12 +170,6 @@ bool whole_tensor(const dgc_config& c, int64_t n) {
   return (c.flags & DGC_FLAG_EXACT_SELECT) || sample_size(c, n) >= n || n / c.sample_block < 1;
 }
 
-// Rank in the band's sample that the floor of a band in the pass is taken at, as select_kernel forms it (within one).
-int64_t band_floor_rank(double density) {
-  const double mid = density * (double)kBandSample;
-  return (int64_t)(std::ceil(mid) + 16.0 + std::ceil(5.0 * std::sqrt(mid * (1.0 - density))));
-}
-
 // Host arithmetic of the sampled threshold (paper: Section 5).  The wanted
 // sample size is ratio * n clamped to [sample_min, sample_max]; a tensor no
 // larger than that is used whole.  Otherwise ceil(s / B) aligned blocks of B
@@ -183,20 +178,22 @@ int64_t band_floor_rank(double density) {
 void build_plan(dgc_handle* h) {
   const dgc_config& c = h->cfg;
   const int64_t B = c.sample_block;
-  int64_t longest = 0, readers = 0;  // of the tensors that are read whole and fill more than a workgroup's registers
+  int64_t longest = 0, readers = 0, read_whole = 0;  // of the tensors that are read whole and fill more than a workgroup's registers
   for (int32_t j = 0; j < h->num_tensors; ++j) {
     const int64_t n = h->offsets[j + 1] - h->offsets[j];
     if (n <= kBandSample || !whole_tensor(c, n)) continue;
     ++readers;
+    read_whole += n;
     if (n > longest) longest = n;
   }
   // The lists of bands have areas in the workspace, whose size must not depend on the density.
   const bool by_lists = longest > (readers >= kBandMany ? kBandFromMany : kBandFrom);
   uint32_t bands = 0;
   h->any_band = false;
-  // What lies above the band's floor in the longest of these tensors has to fit the list of one workgroup.
+  h->band_elements = 0;
   h->bands_in_pass = longest > kBandFromInPass && c.density <= kBandInPassDensity &&
-                     longest * band_floor_rank(c.density) / kBandSample <= kBandInPassList;
+                     longest * (int64_t)BandRanks(c.density, (double)kBandSample).floor_in_pass() / kBandSample <= kBandInPassList &&
+                     (!by_lists || read_whole > kBandInPassElements);
   const bool by_bands = by_lists || h->bands_in_pass;
   for (int32_t j = 0; j < h->num_tensors; ++j) {
     const int64_t n = h->offsets[j + 1] - h->offsets[j];
@@ -222,6 +219,7 @@ void build_plan(dgc_handle* h) {
           p.exact = 2;
           p.nblocks = bands;
           h->any_band = true;
+          h->band_elements += n;
         }
         if (by_lists) ++bands;
       }
@@ -675,15 +673,17 @@ dgc_status dgc_compress(dgc_handle* h, const float* g, float* u, float* v, int32
   sa.block_shift = shift;
   const bool band_areas = workspace_bytes >= h->lay.total;
   sa.bands = h->any_band ? at<BandState>(workspace, band_areas ? h->lay.bands : h->lay.part_found) : nullptr;
-  sa.band_list = at<uint32_t>(workspace, band_areas ? h->lay.band_list : h->lay.wire_sums);
+  sa.band_list = h->most_bands == 0 ? nullptr : at<uint32_t>(workspace, band_areas ? h->lay.band_list : h->lay.wire_sums);
   sa.seed_lo = (uint32_t)(c.seed & 0xFFFFFFFFu);
   sa.seed_hi = (uint32_t)(c.seed >> 32);
   sa.iter_lo = (uint32_t)(iteration & 0xFFFFFFFFu);
   sa.iter_hi = (uint32_t)(iteration >> 32);
   const bool bands_in_pass = h->any_band && h->bands_in_pass;
-  sa.bands_in_pass = bands_in_pass ? 1 : 0;
+  sa.floor.in_pass = bands_in_pass ? 1 : 0;
+  sa.floor.collected = out_counts;
+  sa.floor.elements = h->band_elements;
   if (!hip_ok(launch_select(sa, h->num_tensors, stream), "launch select kernel")) return DGC_ERR_HIP;
-  if (h->any_band && !bands_in_pass &&
+  if (h->any_band && h->most_bands > 0 &&
       !hip_ok(launch_band(sa, at<EmitBlock>(workspace, h->lay.emit_blocks), (int32_t)h->emit_blocks.size(),
                           h->num_tensors, stream),
               "launch band kernels"))
@@ -724,7 +724,7 @@ dgc_status dgc_compress(dgc_handle* h, const float* g, float* u, float* v, int32
   }
   ta.slotted = slotted ? 1 : 0;
   static_assert(kBandInPassDensity <= kStagedMinDensity, "bands in the pass go by records");
-  ta.bands_in_pass = sa.bands_in_pass;
+  ta.floor = sa.floor;
   ta.plans = sa.plans;
   if (!hip_ok(launch_stream(ta, stream), "launch stream kernel")) return DGC_ERR_HIP;
   if (ev && !hip_ok(hipEventRecord(ev[3], stream), "record event")) return DGC_ERR_HIP;
@@ -735,7 +735,8 @@ dgc_status dgc_compress(dgc_handle* h, const float* g, float* u, float* v, int32
   if (c.refine_alpha > 0.0f || bands_in_pass) {
     RefineArgs ra{};
     ra.on_excess = c.refine_alpha > 0.0f ? 1 : 0;
-    ra.bands_in_pass = sa.bands_in_pass;
+    ra.floor = sa.floor;
+    ra.state = state;
     ra.plans = sa.plans;
     ra.v = v;
     ra.mask = ta.mask;

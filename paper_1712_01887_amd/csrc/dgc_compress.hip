@@ -276,6 +276,31 @@ __device__ __forceinline__ uint32_t select_in_registers(SelectShared& sh, const 
   return prefix;
 }
 
+// The smallest of what the first `full_waves` wavefronts name as the t-th largest of their threads' largest keys: a key that
+// t * full_waves keys at least do not lie below.  `top` gets this thread's largest key (-1: it has none).
+__device__ __forceinline__ uint32_t floor_of_waves(SelectShared& sh, const uint32_t (&key)[kSelectRegKeys], uint32_t full_waves,
+                                                   uint32_t t, int tid, int32_t& top) {
+  constexpr int kWaves = kSelectThreads / 64;
+  const int lane = tid & 63;
+  const int wave = tid >> 6;
+  top = -1;  // (an empty slot counts as -1)
+#pragma unroll
+  for (int i = 0; i < kSelectRegKeys; ++i) top = (int32_t)key[i] > top ? (int32_t)key[i] : top;
+  uint32_t rest = top > 0 ? (uint32_t)top : 0u;
+  uint32_t tth = 0;
+  for (uint32_t round = 0; round < t; ++round) {
+    tth = wave_max(rest);
+    const unsigned long long holding = __ballot(rest == tth);
+    if (lane == __ffsll((long long)holding) - 1) rest = 0;  // one holder of the maximum steps down
+  }
+  if (lane == 0) sh.wave_tot[wave] = (uint32_t)wave < full_waves ? tth : 0x7FFFFFFFu;
+  __syncthreads();
+  uint32_t floor_key = sh.wave_tot[0];
+#pragma unroll
+  for (int w = 1; w < kWaves; ++w) floor_key = sh.wave_tot[w] < floor_key ? sh.wave_tot[w] : floor_key;
+  return full_waves == 0 ? 0u : floor_key;
+}
+
 // Key of descending rank `rank` among the `count` keys a workgroup holds in registers (kNoKey marks an empty
 // slot); threads 0 .. holders - 1 have at least one.  Every thread returns the same.
 __device__ __forceinline__ uint32_t rank_registers(SelectShared& sh, const uint32_t (&key)[kSelectRegKeys], int32_t count,
@@ -292,31 +317,15 @@ __device__ __forceinline__ uint32_t rank_registers(SelectShared& sh, const uint3
   // and ranked by direct counting.  Anything that does not fit this pattern takes the
   // histogram passes.
   constexpr int kWaves = kSelectThreads / 64;
-  const int lane = tid & 63;
-  const int wave = tid >> 6;
   const uint32_t full_waves = (uint32_t)holders >= (uint32_t)kSelectThreads ? (uint32_t)kWaves : (uint32_t)holders >> 6;
   const uint32_t t_rounds = full_waves > 0 ? rank / full_waves + 1 : 0;  // full_waves * t_rounds > rank
   // (Of a key or two per thread, the list is several hundred long from a rank of 80 or so on: 20000 tensors of
   // 1500 elements, rank 120, 739 us this way and 553 by histograms, rank 94 618 and 571, rank 45 472 and 535.)
   if (t_rounds <= (uint32_t)kSelectFloorRounds && (count > 2 * kSelectThreads || rank < 80u)) {
-    int32_t top = -1;  // this thread's largest key (an empty slot counts as -1)
-#pragma unroll
-    for (int i = 0; i < kSelectRegKeys; ++i) top = (int32_t)key[i] > top ? (int32_t)key[i] : top;
-    uint32_t rest = top > 0 ? (uint32_t)top : 0u;
-    uint32_t tth = 0;
-    for (uint32_t round = 0; round < t_rounds; ++round) {
-      tth = wave_max(rest);
-      const unsigned long long holding = __ballot(rest == tth);
-      if (lane == __ffsll((long long)holding) - 1) rest = 0;  // one holder of the maximum steps down
-    }
-    if (lane == 0) sh.wave_tot[wave] = (uint32_t)wave < full_waves ? tth : 0x7FFFFFFFu;
+    int32_t top;
     if (tid == 0) sh.surv_n = 0;
     sh.surv[tid] = 0;
-    __syncthreads();
-    uint32_t floor_key = sh.wave_tot[0];
-#pragma unroll
-    for (int w = 1; w < kWaves; ++w) floor_key = sh.wave_tot[w] < floor_key ? sh.wave_tot[w] : floor_key;
-    if (full_waves == 0) floor_key = 0;
+    const uint32_t floor_key = floor_of_waves(sh, key, full_waves, t_rounds, tid, top);
     if (top >= (int32_t)floor_key) {
 #pragma unroll
       for (int i = 0; i < kSelectRegKeys; ++i)
@@ -335,6 +344,49 @@ __device__ __forceinline__ uint32_t rank_registers(SelectShared& sh, const uint3
     __syncthreads();
   }
   return select_in_registers<kSelectRegKeys>(sh, key, 0u, rank, tid);
+}
+
+// How many keys of a band's sample lie above `floor_key`, how many do not lie below it, and the sum over the sampled
+// blocks of the squares of the latter's numbers.  Eight neighbouring threads hold the 32 keys of a block, four to a
+// thread, and eight blocks (see the gather).
+__device__ __forceinline__ void keys_by_block(SelectShared& sh, const uint32_t (&key)[kSelectRegKeys], uint32_t floor_key,
+                                              int tid, uint32_t& above, uint32_t& keys, uint32_t& squares) {
+  static_assert(kBandBlockShift == 5 && kSelectRegKeys == 32 && kBandSample == kSelectRegKeys * kSelectThreads, "every thread is full");
+  uint32_t four[2] = {0u, 0u};  // of the thread's eight blocks, a byte each
+  uint32_t strict = 0;
+#pragma unroll
+  for (int i = 0; i < kSelectRegKeys; ++i) {
+    four[i >> 4] += key[i] >= floor_key ? 1u << (8 * ((i >> 2) & 3)) : 0u;
+    strict += key[i] > floor_key ? 1u : 0u;
+  }
+  uint32_t own = 0;  // a wavefront's 64 blocks: up to 2048 keys, squares up to 65536
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {  // over the eight lanes: up to 32 in a byte
+    uint32_t x = four[h];
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xf, 0xf, false);   // the neighbour's
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x4E, 0xf, 0xf, false);   // the other pair's of the quad
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x141, 0xf, 0xf, false);  // the other quad's of the half row
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      const uint32_t n = (x >> (8 * b)) & 0xFFu;
+      own += (n << 20) + n * n;
+    }
+  }
+  own = wave_sum((tid & 7) == 0 ? own : 0u);
+  strict = wave_sum(strict);
+  if ((tid & 63) == 0) {
+    sh.wave_tot[tid >> 6] = own;
+    sh.surv[tid >> 6] = strict;
+  }
+  __syncthreads();
+  above = keys = squares = 0;
+#pragma unroll
+  for (int w = 0; w < kSelectThreads / 64; ++w) {
+    keys += sh.wave_tot[w] >> 20;
+    squares += sh.wave_tot[w] & 0xFFFFFu;
+    above += sh.surv[w];
+  }
+  __syncthreads();
 }
 
 // The same among `count` candidates that are evaluated from g, u, v anew in every pass.
@@ -417,6 +469,13 @@ __device__ __forceinline__ Candidates candidates_of(const SelectArgs& a, int j, 
   return c;
 }
 
+// For a tensor with a band, after select_kernel.
+__device__ __forceinline__ bool floor_went_into_pass(const FloorArgs& f, const DeviceState* state, int j) {
+  const int64_t crowded = state->crowded;
+  const int32_t collected = f.collected[j];  // (asked for in any case: no chain of loads)
+  return f.in_pass != 0 && collected == 0 && (crowded == 0 || f.elements - crowded > kBandMixedElements);
+}
+
 __device__ __forceinline__ BandState* band_state(const SelectArgs& a, const TensorPlan& plan) {
   return reinterpret_cast<BandState*>(reinterpret_cast<char*>(a.bands) + (size_t)plan.nblocks * kBandStride);
 }
@@ -463,8 +522,10 @@ __device__ __forceinline__ float settle_scale(const SelectArgs& a, SelectShared&
 // Bound by latency: the gather of the candidates, then the ranking, in one workgroup per tensor.  17 us on the
 // 122 M-element set, 13.6 on the 161-tensor set, 10.5 on 23 tensors of 0.27 M elements in all (19.2, 14.3, 12.2
 // with the wavefronts' maxima taken through LDS and one key per LDS read).
-// BANDS: some tensors are ranked by way of a band (TensorPlan.exact == 2).
-template <bool NESTEROV, bool BANDS>
+// MODE: whether some tensors are ranked by way of a band (TensorPlan.exact == 2), and whether its floor may go into the pass.
+enum SelectMode : int { kSelectNoBands = 0, kSelectLists = 1, kSelectInPass = 2 };
+
+template <bool NESTEROV, int MODE>
 __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectArgs a) {
   __shared__ SelectShared sh;
   const int tid = threadIdx.x;
@@ -481,13 +542,13 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectArgs a) {
   }
 
   Candidates c = candidates_of(a, j, plan, a.scale_const, NESTEROV);
-  if (BANDS && plan.exact == 2) {  // a sample for the band of an exact selection
+  if (MODE != kSelectNoBands && plan.exact == 2) {  // a sample for the band of an exact selection
     c.exact = 0;
     c.block_shift = kBandBlockShift;
     c.nblocks = (uint32_t)(plan.n >> kBandBlockShift);
   }
 
-  const int32_t count = (BANDS && plan.exact == 2) ? kBandSample : plan.count;
+  const int32_t count = (MODE != kSelectNoBands && plan.exact == 2) ? kBandSample : plan.count;
   const uint32_t rank = (uint32_t)plan.rank;
   uint32_t thr_bits = 0;
 
@@ -565,22 +626,41 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectArgs a) {
         }
       }
     }
-    if (BANDS && plan.exact == 2) {
-      // A band that holds the rank unless the number of sampled elements above the exact threshold is
-      // seven standard deviations off (and 32 more, for small ranks and for values that come in
-      // clusters).  Nothing depends on it but the time: a band that misses is noticed.
-      const double share = (double)plan.rank / (double)plan.n;
-      const double mid = share * (double)kBandSample;
-      const double reach = 32.0 + ceil(7.0 * sqrt(mid * (1.0 - share)));
-      // (in the pass, where every element above the floor costs, five and 16: a miss costs one workgroup four walks
-      // over the tensor)
-      const double low = ceil(mid) + (a.bands_in_pass ? 16.0 + ceil(5.0 * sqrt(mid * (1.0 - share))) : reach);
-      const double high = floor(mid) - reach;
-      const uint32_t floor_key = low < (double)count ? rank_registers(sh, key, count, holders, (uint32_t)low, tid) : 0xFFFFFFFFu;
-      if (a.bands_in_pass) {  // what exceeds the floor passes, and refine_kernel ranks it
+    if (MODE != kSelectNoBands && plan.exact == 2) {
+      // A band that holds the wanted rank almost surely.  Nothing depends on it but the time: a band that misses is
+      // noticed.  In the pass it is a floor alone, and only for values that the sample can be relied on for; the
+      // others are collected.
+      const BandRanks at((double)plan.rank / (double)plan.n, (double)kBandSample);
+      if (MODE == kSelectInPass) {
+        const uint32_t floor_key = rank_registers(sh, key, count, holders, (uint32_t)at.floor_in_pass(), tid);
+        bool reliable = true, in_clusters = false;
+        if (a.band_list) {  // (a set without lists has no tensor so long that a miss would cost more than looking)
+          uint32_t above, keys, squares;
+          keys_by_block(sh, key, floor_key, tid, above, keys, squares);
+          in_clusters = at.clustered(keys, squares);
+          reliable = !in_clusters && !at.tied(above, floor_key);
+        }
+        if (tid == 0) {
+          a.floor.collected[j] = reliable ? 0 : 1;
+          if (!reliable) atomicAdd(&a.state->crowded, (uint32_t)plan.n);
+        }
+        // What exceeds the floor passes, and refine_kernel ranks it ...
         write_threshold(a, j, plan, __uint_as_float(floor_key < kInfinity ? floor_key : kInfinity), tid);
+        // ... or the band is collected, and rank_band_kernel writes the threshold.  Ties at the floor are counted then.
+        // Clusters need a floor further down: they fill eight lanes each and so spare some wavefront, whose own floor is the
+        // smallest; the list gets two or three times the keys that the rank below asks for, and which they are does
+        // not matter.  No ceiling: at the densities of the pass it would lie above everything.
+        if (a.band_list) {
+          uint32_t band_floor = floor_key;
+          int32_t top;
+          if (in_clusters) band_floor = floor_of_waves(sh, key, kSelectThreads / 64, (uint32_t)(ceil(at.mid) + at.reach()) / (kSelectThreads / 64) + 1u, tid, top);
+          if (tid == 0) *band_state(a, plan) = BandState{band_floor, 0x80000000u, 0u, 0u, 0u};
+        }
         return;
       }
+      const double reach = at.reach();
+      const double low = ceil(at.mid) + reach, high = floor(at.mid) - reach;
+      const uint32_t floor_key = low < (double)count ? rank_registers(sh, key, count, holders, (uint32_t)low, tid) : 0xFFFFFFFFu;
       uint32_t ceil_key = high >= 0.0 ? rank_registers(sh, key, count, holders, (uint32_t)high, tid) : 0x80000000u;
       if (ceil_key == floor_key) ++ceil_key;
       if (tid == 0) *band_state(a, plan) = BandState{floor_key, ceil_key, 0u, 0u, 0u};
@@ -615,7 +695,8 @@ __global__ __launch_bounds__(kBandThreads) void collect_band_kernel(SelectArgs a
   __shared__ uint32_t base_sh;
   const EmitBlock blk = blocks[blockIdx.x / kBandsPerPart];
   const TensorPlan plan = a.plans[blk.tensor];
-  if (plan.exact != 2) return;
+  const bool into_pass = floor_went_into_pass(a.floor, a.state, blk.tensor);
+  if (plan.exact != 2 || into_pass) return;
   const int64_t base = (int64_t)blk.first_tile * kWaveTile + (int64_t)(blockIdx.x % kBandsPerPart) * kBandElements;
   if (base >= blk.hi || base + kBandElements <= blk.lo) return;
   const int tid = threadIdx.x;
@@ -709,7 +790,8 @@ __global__ __launch_bounds__(kSelectThreads) void rank_band_kernel(SelectArgs a)
   const int tid = threadIdx.x;
   const int j = blockIdx.x;
   const TensorPlan plan = a.plans[j];
-  if (plan.exact != 2) return;
+  const bool into_pass = floor_went_into_pass(a.floor, a.state, j);
+  if (plan.exact != 2 || into_pass) return;
   const BandState st = *band_state(a, plan);
   const int64_t begin = band_list_begin(plan.offset);
   const int64_t cap = band_list_begin(plan.offset + plan.n) - begin;
@@ -857,7 +939,7 @@ __device__ __forceinline__ uint32_t mixed_tile_mask(const StreamArgs& a, int64_t
   return cand;
 }
 
-// Mask bits of the lane's NaNs that belong to tensors with a band.  (Rare: `j0` is the tensor of the tile's first
+// Mask bits of the lane's NaNs that belong to tensors with a floor.  (Rare: `j0` is the tensor of the tile's first
 // element, those behind it are walked over.)
 __device__ __forceinline__ uint32_t band_nans(const StreamArgs& a, int64_t base, int lane, int32_t j0, const vec4 (&z)[kStreamUnroll]) {
   uint32_t found = 0;
@@ -868,7 +950,7 @@ __device__ __forceinline__ uint32_t band_nans(const StreamArgs& a, int64_t base,
     if (v == v || e >= a.n) continue;
     int32_t j = j0;
     while (a.offsets[j + 1] <= e) ++j;
-    if (a.plans[j].exact == 2) found |= 1u << q;
+    if (a.plans[j].exact == 2 && floor_went_into_pass(a.floor, a.state, j)) found |= 1u << q;
   }
   return found;
 }
@@ -1210,9 +1292,10 @@ __device__ __forceinline__ int tile_counts_partial(const uint32_t* __restrict__ 
 // 161-tensor set and 34 us on the 122 M-element set for what the per-tile counts already say.)
 // EXACT SELECTION at densities up to kBandInPassDensity comes here, too: select_kernel has named a floor that lies below
 // the exact threshold almost surely, the pass took what exceeds it, and every such tensor is ranked here.  The streaming
-// pass is then the only one over g, u, v: 161 tensors of 25.6 M elements, 0.1 %, 174 -> 128 us (select 19, pass 82,
-// refine 20, emit 7) where collect_band_kernel read them once more and rank_band_kernel followed (20, 81, 5, and 55
-// + 12).  Above 0.2 % too many tiles hold more than a record does: 12 tensors of 1 M elements, 0.4 %, 71 against 57.
+// pass is then the only one over g, u, v: 161 tensors of 25.6 M elements, 0.1 %, call 176 -> 148 us where bands were
+// collected by another pass.  (Tensors whose sample does not bear the floor out still are: with large values in rows of
+// every second large tensor, placed anew every third call, the median of the calls is 195 us and the worst 215, where bands
+// alone take 187 and 1467; with such rows in one tensor of fifty 159, against 178.)
 // A workgroup lists up to kRefineList selected elements in LDS (index and key) and ranks them by one
 // histogram; the over-selection of a big tensor goes to the payload region, which is free until the emit
 // pass, and through three histogram passes.  Bound by latency, a chain of dependent steps in the dozen
@@ -1264,7 +1347,9 @@ __global__ __launch_bounds__(kRefineThreads) void refine_kernel(RefineArgs a) {
   const int64_t t0 = lo / kWaveTile;
   const int64_t t1 = (hi - 1) / kWaveTile;
   // Exact selection: the pass took whatever exceeds a floor, NaNs too, and the threshold is settled here in any case.
-  const bool banded = a.bands_in_pass != 0 && plan.exact == 2;
+  const bool into_pass = floor_went_into_pass(a.floor, a.state, j);
+  const bool banded = plan.exact == 2 && into_pass;
+  if (!banded && !a.on_excess) return;
 
   // How many elements of the tensor passed: the counts the streaming pass has left for the tiles
   // that lie wholly inside the tensor, and the tensor's share of a first or last tile that it
@@ -1285,7 +1370,7 @@ __global__ __launch_bounds__(kRefineThreads) void refine_kernel(RefineArgs a) {
     int total = 0;
     for (int w = 0; w < kWaves; ++w) total += sh.red[w];
     sh.passed = (uint32_t)total;
-    sh.go = banded || (a.on_excess && (uint32_t)total > (uint32_t)plan.refine_limit);
+    sh.go = banded || (uint32_t)total > (uint32_t)plan.refine_limit;
   }
   __syncthreads();
   if (!sh.go) return;
@@ -1310,8 +1395,7 @@ __global__ __launch_bounds__(kRefineThreads) void refine_kernel(RefineArgs a) {
   const float floor = a.thr[j];  // every selected element exceeds it
   // Takes the mask bit of element e away, and one from the count of its tile; by whole wavefronts.  Neighbours in a
   // list mostly lie in one tile, and additions to words of one line are carried out one by one: one per tile and
-  // wavefront (3.8 M elements whose largest values fill 20 rows of 650, exact 0.1 %: call
-  // 167 -> 105 us; by way of bands 79, and 72 against 70 where they are spread).
+  // wavefront (3.8 M elements whose largest values fill 20 rows of 650, all above the floor: call 167 -> 105 us).
   auto drop_bit = [&](bool drop, uint32_t e) {
     const uint32_t tile = e / kWaveTile, r = e % kWaveTile;
     if (drop) {
@@ -1332,8 +1416,7 @@ __global__ __launch_bounds__(kRefineThreads) void refine_kernel(RefineArgs a) {
   if (missed) {
     // Values that occur many times (rounded or ternary gradients): the floor is itself the threshold if enough
     // elements equal it, and what has passed is what is sent.  As much of the tensor is looked at as that takes
-    // (3.8 M elements, 0.1 %, call: all of one magnitude 11.3 ms without
-    // this, now 144 us; 0.5 % of them and zeros 7.4 ms, now 162; by way of bands 147 and 94).
+    // (A set without lists, see select_kernel; in others such tensors do not come here.)
     constexpr int kPer = 32;
     const uint32_t floor_key = __float_as_uint(floor);
     const uint32_t enough = rank - (uint32_t)passed + 1u;
@@ -1361,8 +1444,9 @@ __global__ __launch_bounds__(kRefineThreads) void refine_kernel(RefineArgs a) {
   }
   if (missed) {
     // The floor lies above the threshold (the sample missed): everything goes back to u and v, the whole tensor is
-    // ranked as it stands there, and its tiles get mask words.  One workgroup over the tensor four times; this
-    // takes values that are large where the sample looks.
+    // ranked as it stands there, and its tiles get mask words.  One workgroup over the tensor four times, 1.9 ms for
+    // 3 M elements; this
+    // takes single values that are large where the sample looks, or the chance of one in a million.
     for (int64_t tile = t0 + tid; tile <= t1; tile += kRefineThreads) {
       if (!is_record(tile)) continue;
       const int c = (int)a.tile_count[tile];
@@ -1381,9 +1465,19 @@ __global__ __launch_bounds__(kRefineThreads) void refine_kernel(RefineArgs a) {
       const uint32_t digit_mask = (1u << bits) - 1u;
       for (int i = tid; i < kSelectBins; i += kRefineThreads) sh.s.hist[i] = 0;
       __syncthreads();
-      for (int64_t e = lo + tid; e < hi; e += kRefineThreads) {
-        const uint32_t key = key_at(e);
-        if (pass == 0 || (key >> (shift + bits)) == prefix) atomicAdd(&sh.s.hist[(key >> shift) & digit_mask], 1u);
+      constexpr int kPer = 16;  // loads on their way
+#pragma unroll 1
+      for (int64_t first = lo; first < hi; first += kPer * kRefineThreads) {
+        uint32_t key[kPer];
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) {
+          const int64_t e = first + q * kRefineThreads + tid;
+          key[q] = key_at(e < hi ? e : hi - 1);
+          if (e >= hi) key[q] = kNoKey;
+        }
+#pragma unroll
+        for (int q = 0; q < kPer; ++q)
+          if (key[q] != kNoKey && (pass == 0 || (key[q] >> (shift + bits)) == prefix)) atomicAdd(&sh.s.hist[(key[q] >> shift) & digit_mask], 1u);
       }
       __syncthreads();
       uint32_t bin, above, members;
@@ -1394,12 +1488,16 @@ __global__ __launch_bounds__(kRefineThreads) void refine_kernel(RefineArgs a) {
     }
     for (int64_t tile = t0 + wave; tile <= t1; tile += kWaves) {
       uint32_t own = 0, word = 0;  // the lane's elements that belong to the tensor, and those that are sent
+      uint32_t key[4 * kStreamUnroll];
+#pragma unroll
       for (int q = 0; q < 4 * kStreamUnroll; ++q) {
         const int64_t e = tile_element(tile, lane, q);
-        if (e < lo || e >= hi) continue;
-        own |= 1u << q;
-        if (sent(key_at(e), prefix)) word |= 1u << q;
+        key[q] = key_at(e < lo ? lo : e < hi ? e : hi - 1);
+        if (e >= lo && e < hi) own |= 1u << q;
       }
+#pragma unroll
+      for (int q = 0; q < 4 * kStreamUnroll; ++q)
+        if (sent(key[q], prefix)) word |= (own >> q & 1u) << q;
       if (tile * kWaveTile >= lo && (tile + 1) * kWaveTile <= hi) {
         a.mask[tile * 64 + lane] = (uint16_t)word;
         const uint32_t c = wave_sum((uint32_t)__popc(word));
@@ -2098,6 +2196,7 @@ __global__ __launch_bounds__(kEmitSlotThreads) void emit_slots_kernel(EmitArgs a
   const int incl = (int)wave_inclusive_sum((uint32_t)own);
   const int total = __builtin_amdgcn_readlane(incl, kEmitTiles - 1);
   if (tid == 0 && (int)((first - t0) / kEmitTiles) == blk.tensor_blocks - 1) a.out_counts[j] = base + total;
+  if (a.settled && blockIdx.x == 0 && tid == 0) a.state->crowded = 0;  // (nothing behind reads it)
   if (total == 0 && !a.settled) return;
   const int excl = incl - own;
   int32_t* __restrict__ out_idx = a.out_idx + region;
@@ -2279,13 +2378,10 @@ hipError_t launch_norm(const float* g, int64_t n, double* partials, hipStream_t 
 
 hipError_t launch_select(const SelectArgs& a, int32_t num_tensors, hipStream_t stream) {
   const dim3 grid((unsigned)num_tensors), block(kSelectThreads);
-  if (a.bands) {
-    if (a.nesterov) hipLaunchKernelGGL((select_kernel<true, true>), grid, block, 0, stream, a);
-    else hipLaunchKernelGGL((select_kernel<false, true>), grid, block, 0, stream, a);
-  } else {
-    if (a.nesterov) hipLaunchKernelGGL((select_kernel<true, false>), grid, block, 0, stream, a);
-    else hipLaunchKernelGGL((select_kernel<false, false>), grid, block, 0, stream, a);
-  }
+  const auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, stream, a); };
+  const int mode = a.floor.in_pass ? kSelectInPass : a.bands ? kSelectLists : kSelectNoBands;
+  if (a.nesterov) launch(mode == kSelectInPass ? select_kernel<true, kSelectInPass> : mode == kSelectLists ? select_kernel<true, kSelectLists> : select_kernel<true, kSelectNoBands>);
+  else launch(mode == kSelectInPass ? select_kernel<false, kSelectInPass> : mode == kSelectLists ? select_kernel<false, kSelectLists> : select_kernel<false, kSelectNoBands>);
   return hipGetLastError();
 }
 
@@ -2326,7 +2422,7 @@ hipError_t launch_stream(const StreamArgs& a, hipStream_t stream) {
   // scale is known to be exactly 1 when neither the norm kernel nor an override supplies it
   const bool scaled = a.scale_from_state != 0 || a.scale_const != 1.0f;
   const dim3 grid((unsigned)blocks), block(kStreamThreads);
-  const int mode = a.stage_v ? kStreamStaged : a.bands_in_pass ? kStreamBand : a.slotted ? kStreamSlotted : kStreamPlain;
+  const int mode = a.stage_v ? kStreamStaged : a.floor.in_pass ? kStreamBand : a.slotted ? kStreamSlotted : kStreamPlain;
   // right after the norm pass part of g comes from the last-level cache, and more wavefronts pay
   const int groups = a.scale_from_state ? kStreamGroupsAfterNorm : kStreamResidentGroups;
   if (a.nesterov) {

@@ -7,6 +7,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "dgc_band.h"
+
 #include "dgc.h"
 
 namespace dgc {
@@ -138,6 +140,8 @@ constexpr int kSelectInFlight = 8;    // candidates each thread gathers before u
 // 25.6 M elements the three kernels take 20 + 55 + 12 us at 0.1 % (the reads, 12 bytes per element, at 5.6 TB/s)
 // and no more than 40 us more at 25 %; three workgroup-wide passes over a whole tensor, which are still the way
 // out when a band misses, took 1385 us.
+// (The sample's blocks are 32 neighbours, so a band misses more often than its seven standard deviations say where
+// large values come in clusters: with 2 large rows of 1500 in 3 M elements two calls in a hundred.)
 constexpr int kBandSample = kSelectRegKeys * kSelectThreads;
 // Bands where the longest such tensor has more than this many elements: up to there the passes of one
 // workgroup over it take less than the two launches (one tensor of 33000: 35 against 54 us for the call, 65000:
@@ -147,15 +151,27 @@ constexpr int64_t kBandFrom = 65536, kBandFromMany = 57344;
 constexpr int64_t kBandMany = 256;
 // At the lowest densities the band's floor is the threshold of a slotted streaming pass, and refine_kernel finds the
 // exact one among what passes and puts the rest back: no pass of its own over g, u, v.
-// (The floor lets two to three times as many pass: 4 of a tile's 1024 elements at 0.2 %.  30 tensors of 8 M elements,
-// 0.1 %: 91 against 75 us for the call, 0.2 %: 95 and 86; at 0.4 %, where a tile in five holds more than a record,
-// 60 of 8 M: 98 and 108, 12 of 1 M: 57 and 71.)
+// (The floor lets two to three times as many pass: 4 of a tile's 1024 elements at 0.2 %.  At 0.4 %, where a tile in five
+// holds more than a record, 60 tensors of 8 M elements in all take 98 us with bands collected and 108 this way, 12 of 1 M 57 and 71.)
 constexpr double kBandInPassDensity = 0.002;
 // ... and from a shorter tensor on, because no pass is added (calls at 0.1 %, the passes of one workgroup against this:
 // one tensor of 33000 31.2 and 32.0 us, of 50000 39.0 and 31.5, of 65000 46 and 33; 20 of 33000 36 and 44; 500 of
 // 40000 173 and 137; 100 of 60000 72 and 59).
 constexpr int64_t kBandFromInPass = 40960;
+// What lies above the floor in the longest tensor, as far as the sample tells, has to fit the list of refine_kernel's
+// workgroup, with room for large values that the sample has seen none of.  (A list of 16384: the re-threshold 0.8 us slower.)
 constexpr int64_t kBandInPassList = kRefineList * 3 / 4;
+// Values that come in rows or runs, or in few magnitudes, are not for a floor (see BandRanks), and which tensors have such
+// is known on the device only: a set with tensors so long that a miss would cost a millisecond launches the
+// two kernels that collect bands in any case, 7 us where they find nothing to do.  So in such a set the floors
+// go into the pass only if the tensors hold more than this in all (calls at 0.1 %, bands collected against this: 6 tensors of
+// 1 M 72 and 72 us, 8 of 1 M 82 and 78, 2 of 3.8 M 90 and 95; 12 of 1 M 104 and 92, 8 of 3 M 170 and 146,
+// 300 of 70000 190 and 163) ...
+constexpr int64_t kBandInPassElements = 8 << 20;
+// ... and if some are collected, only if the others hold more than this; otherwise all are.  (4 tensors of 3.8 M, one of
+// them with large values in 20 rows, 11.4 M elements in the others: 158 us with their floors in the pass, 150
+// without; 161 tensors of 25.6 M, one in fifty with such rows: 159, and 185 without.)
+constexpr int64_t kBandMixedElements = 16 << 20;
 constexpr int kBandBlockShift = 5;
 constexpr int kBandListShift = 6;       // three list words per 64 elements
 constexpr int kBandThreads = 256;
@@ -182,7 +198,8 @@ struct DeviceState {
   double norm;           // L2 norm of g (clipping on)
   float scale;           // factor applied to g
   uint32_t flags;        // DGC_DIAG_*
-  uint32_t pad[4];
+  uint32_t crowded;      // exact selection in the pass: elements of the tensors whose floor does not go there; zero between calls
+  uint32_t pad[3];
 };
 
 // Per-tensor selection plan (host arithmetic, uploaded when the density changes).
@@ -205,6 +222,14 @@ struct WorkspaceLayout {
       stage_v, stage_u, total_staged;  // staging arrays lie behind `total`: a workspace may end before them
 };
 
+// Exact selection with the bands' floors in the streaming pass.
+struct FloorArgs {
+  int32_t in_pass;        // 0: bands are collected, if there are any
+  int32_t* collected;     // device, T: not zero for a tensor whose floor does not go into the pass (the call's counts, which the
+                          // emit pass writes last)
+  int64_t elements;       // of all tensors with a band
+};
+
 struct SelectArgs {
   const float* g;
   const float* u;
@@ -225,8 +250,8 @@ struct SelectArgs {
   int32_t nesterov;
   int32_t block_shift;  // log2(sample_block)
   BandState* bands;     // device, a slot of kBandStride bytes per tensor that has a band; null: none has
-  uint32_t* band_list;  // device, see band_list_begin
-  int32_t bands_in_pass;  // the band's floor is the pass's threshold, refine_kernel ranks what passes: no list
+  uint32_t* band_list;  // device, see band_list_begin; null: the set has none
+  FloorArgs floor;
   uint32_t seed_lo, seed_hi, iter_lo, iter_hi;
 };
 
@@ -252,8 +277,8 @@ struct StreamArgs {
   float* stage_u;              // device, n floats, or null: no region can overflow, or no factor masking
   int32_t factor_masking;
   int32_t slotted;             // slotted pass (densities up to 0.5 %): records in place of mask words
-  int32_t bands_in_pass;       // as in SelectArgs; implies `slotted`
-  const TensorPlan* plans;     // device, T: looked at for NaNs with bands_in_pass
+  FloorArgs floor;             // implies `slotted`
+  const TensorPlan* plans;     // device, T: looked at for NaNs with floors in the pass
 };
 
 struct EmitBlock {
@@ -280,7 +305,8 @@ struct RefineArgs {
   float* u_out;                // u and v, to put back what is dropped from a record
   float* v_out;
   int32_t on_excess;           // re-threshold tensors that let more than refine_limit pass
-  int32_t bands_in_pass;       // as in SelectArgs: settle the threshold of tensors with a band
+  FloorArgs floor;             // settle the threshold of tensors whose floor went into the pass
+  const DeviceState* state;
 };
 
 struct EmitArgs {

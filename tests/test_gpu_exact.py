@@ -314,3 +314,45 @@ def test_floor_in_the_pass_with_ties_and_rows(kind, size):
     g[offsets[-1] // 2] = np.nan
     p.step(g, 1, label=f"exact, {kind} and a NaN, n={size}")
     p.close()
+
+
+def in_rows(g, lo, hi, width, rows, rng):
+    """Large values in rows of a matrix that fills [lo, hi)."""
+    for r in rng.choice((hi - lo) // width, rows, replace=False):
+        g[lo + r * width:lo + (r + 1) * width] *= 100
+
+
+@pytest.mark.parametrize("kind", ["spread", "one in rows", "all in rows", "few magnitudes", "misses", "mostly zero", "unseen rows"])
+@pytest.mark.parametrize("tensors", [3, 7])
+def test_exact_of_sets_that_decide_on_the_device(kind, tensors):
+    """Sets large enough for floors in the pass, with tensors so long that the sample has to bear the floor out: all
+    floors in the pass, some, or (with fewer elements beside a tensor that cannot) none.  A NaN in every tensor in the second
+    call, another density in the third."""
+    sizes = [333] + [3_000_000] * tensors + [40_001, 20]
+    offsets = np.concatenate([[0], np.cumsum(sizes)])
+    flags = EXACT | (B.DGC_FLAG_NO_FACTOR_MASKING if kind == "misses" else 0)
+    p = Pair(offsets, layout_density=0.004, momentum=0.0, density=0.001, seed=21, flags=flags)
+    rng = np.random.default_rng([tensors, len(kind)])
+    for it, d in enumerate((0.001, 0.001, 0.004) if tensors == 3 else (0.0005, 0.001)):
+        p.set_density(d)
+        g = rng.standard_normal(p.n, dtype=np.float32)
+        lo, hi = int(offsets[1]), int(offsets[2])
+        if kind == "one in rows":
+            in_rows(g, lo, hi, 1500, 3, rng)
+        elif kind == "all in rows":
+            for j in range(1, tensors + 1):
+                in_rows(g, int(offsets[j]), int(offsets[j + 1]), 1500, 3, rng)
+        elif kind == "few magnitudes":
+            g[lo:hi] = np.clip(np.round(g[lo:hi]), -2, 2)
+        elif kind == "mostly zero":
+            g[lo:hi] *= np.arange(hi - lo) // 1500 % 50 == 0
+        elif kind == "misses":                       # one large value to a sampled block: fewer than k, more than the floor's rank
+            first = np.unique(band_sample(sizes[1], 21, it, 1) // 32 * 32)
+            g[lo + first + rng.integers(0, 32, first.size)] = 50.0 + rng.random(first.size, dtype=np.float32)
+        elif kind == "unseen rows":                  # many more pass than the sample lets expect: the list in LDS does not hold them
+            unseen = np.setdiff1d(np.arange(sizes[1] // 32), band_sample(sizes[1], 21, it, 1) // 32)
+            g[lo + (rng.choice(unseen, 700, replace=False)[:, None] * 32 + np.arange(32)).ravel()] *= 100
+        if it == 1:
+            g[(offsets[:-1] + offsets[1:]) // 2] = np.nan
+        p.step(g, it, label=f"exact, {kind}, {tensors} tensors, d={d} it{it}")
+    p.close()
