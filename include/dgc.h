@@ -180,8 +180,8 @@ dgc_status dgc_workspace_bytes(const dgc_handle* h, size_t* bytes);
  * warm-up training: 25 % down to 0.4 % of the elements are sent during the first epochs).
  * Given a workspace of at least this size, dgc_compress at a density above 0.5 % masks u
  * and v inside its streaming pass and parks the selected values in the staging arrays, so
- * that the emit pass does not come back to u and v (1017 -> about 600 us at 25 % on a
- * 122 M-element set); every region of the payload is then in ascending index order.  With
+ * that the emit pass does not come back to u and v (916 -> 517 us at 25 % on a
+ * 122 M-element set, 779 -> 450 at 6.25 %).  With
  * the smaller workspace, or with refine_alpha > 0, the same results are computed the slower
  * way.  Results do not depend on which workspace is given.
  */
@@ -199,7 +199,9 @@ dgc_status dgc_recommended_payload_layout(const dgc_handle* h, double density,
  *   scale  = clip ? min(1, (thr_G / sqrt N) / ||g||_2) : 1          (Appendix C)
  *   u'     = m u + scale g ;  v' = v + u'                            (equation 7)
  *   thr_j  = magnitude of descending rank r_j among the sampled |v'| of tensor j,
- *            or of the whole tensor when it is small or EXACT_SELECT (Section 5)
+ *            or of the whole tensor when it is small or EXACT_SELECT (Section 5; up to a
+ *            density of 0.2 % it may be settled among what a lower one lets pass, which
+ *            changes no result)
  *   if refine_alpha > 0 and more than refine_alpha * k_j elements pass: thr_j =
  *            magnitude of descending rank k_j among those that passed    (Section 5)
  *   keep   = |v'| > thr_j  (strict)                                  (Algorithm 3)
@@ -216,9 +218,9 @@ dgc_status dgc_recommended_payload_layout(const dgc_handle* h, double density,
  *              mask.  Pairs [out_offsets[j], out_offsets[j] + min(count_j, capacity_j))
  *              are valid: the same pairs in the same order on every run, the parts of
  *              consecutive blocks of 32768 elements in index order, ascending throughout
- *              with DGC_FLAG_SORTED_OUTPUT (and, as it happens, whenever the staging arrays of
- *              dgc_workspace_bytes_warmup are in use, and up to a density of 0.5 % without the
- *              re-threshold: only the flag is a promise).  An element that passed but found
+ *              with DGC_FLAG_SORTED_OUTPUT (today without it, too: only the flag is a
+ *              promise).  Until the emit pass writes them, the counts are scratch of the call.
+ *              An element that passed but found
  *              the region full is neither emitted nor cleared (it stays in u, v) and
  *              DGC_DIAG_OVERFLOW is raised; in an ascending region those are the highest
  *              indices.

@@ -1299,7 +1299,7 @@ __device__ __forceinline__ int tile_counts_partial(const uint32_t* __restrict__ 
 // A workgroup lists up to kRefineList selected elements in LDS (index and key) and ranks them by one
 // histogram; the over-selection of a big tensor goes to the payload region, which is free until the emit
 // pass, and through three histogram passes.  Bound by latency, a chain of dependent steps in the dozen
-// workgroups that go on: 13 us on the 161-tensor set (15.4 with one addition to the list's length per tile and with
+// workgroups that go on: 14 us on the 161-tensor set (16 with one addition to the list's length per tile and with
 // what is dropped put back from here; 23 with the list always in the payload region).  The lists
 // (and 16 wavefronts of more than 64 registers) leave one workgroup per compute unit; 20000 tensors, most of which
 // only add up their counts, take 133 us as they did without the lists.

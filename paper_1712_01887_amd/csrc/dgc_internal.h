@@ -115,6 +115,8 @@ constexpr int kDecodePer = 8;
 constexpr int kDecodeBlock = 64 * kDecodePer;
 static_assert((kWireChunk >> 3) == kDecodeBlock, "s goes up to 3: the blocks the workspace is sized for");
 // Payloads of the direct form that are decoded in one launch: kDecodeGroupsMax workgroups of kDecodeGroup entries at most.
+// (Calls in two launches and in one: one payload of 16000 entries 11.0 and 9.6 us, of 32700 11.0 and 10.6, and if it took up to
+// 65536 of 45000 10.9 and 11.3; eight payloads 13.3 and 11.0, 18.0 and 16.4, 22.8 and 21.0.)
 constexpr int kDecodeGroupThreads = 512;
 constexpr int kDecodeGroup = kDecodeGroupThreads * kDecodePer;
 constexpr int kDecodeGroupsMax = 8;
@@ -155,8 +157,8 @@ constexpr int64_t kBandMany = 256;
 // holds more than a record, 60 tensors of 8 M elements in all take 98 us with bands collected and 108 this way, 12 of 1 M 57 and 71.)
 constexpr double kBandInPassDensity = 0.002;
 // ... and from a shorter tensor on, because no pass is added (calls at 0.1 %, the passes of one workgroup against this:
-// one tensor of 33000 31.2 and 32.0 us, of 50000 39.0 and 31.5, of 65000 46 and 33; 20 of 33000 36 and 44; 500 of
-// 40000 173 and 137; 100 of 60000 72 and 59).
+// one tensor of 33000 31.2 and 32.0 us, of 50000 39.0 and 32.4, of 65000 46 and 33; 20 of 33000 36 and 44; 100 of 60000
+// 75 and 62; one of 50000 with a large row of 100 in the mean of 150 calls, misses and all, 49 and 44).
 constexpr int64_t kBandFromInPass = 40960;
 // What lies above the floor in the longest tensor, as far as the sample tells, has to fit the list of refine_kernel's
 // workgroup, with room for large values that the sample has seen none of.  (A list of 16384: the re-threshold 0.8 us slower.)

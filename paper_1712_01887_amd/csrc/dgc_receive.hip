@@ -151,7 +151,7 @@ __global__ __launch_bounds__(kFlatThreads) void scatter_regions_kernel(float* de
 // workgroups; in every payload's region those parts follow each other in index order
 // (inside a part the order is free), so "index below the range's end" is monotone along
 // a region and the payload's pairs inside the range are found by search: one wavefront
-// per payload, both ends at once (half the lanes probe for each, 32 probes per round).
+// per payload, both ends at once (from the same probes in the first round, half the lanes for each end from then on).
 // Every thread then takes a few of the pairs into registers and marks their indices in
 // an LDS bitmap of the range; a prefix sum over the bitmap numbers the distinct
 // indices, which gives every index a slot in an LDS accumulator.  The slots start from
@@ -349,7 +349,7 @@ __device__ __forceinline__ int merge_slot(const MergeShared<CAP>& sh, int32_t r)
 // THREADS: 512 when there are at most eight payloads (one wavefront searches one payload's region,
 // and four workgroups of eight wavefronts fit a compute unit, LDS included: the 970 ranges of a
 // 122 M-element set then run all at once instead of in two rounds), 1024 otherwise.  Bound by latency, the
-// searches before all: replacing calls at 0.1 % 36 us on that set (37.5 with the pointers of a wavefront's payload fetched one after the
+// searches before all: replacing calls at 0.1 % 35.3 us on that set (37.5 with the pointers of a wavefront's payload fetched one after the
 // other) and 24.2 on 25.6 M elements with sixteen payloads (25.5; 66 M with four 20.3 against 22.2, 1 M with four 8.9
 // against 10.7).  (A first round of probes around the place that a range has if pairs are spread evenly took 34.9
 // and 23.7, but 49.1 instead of 39.1 where the pairs crowd three tenths of one large tensor: every workgroup
@@ -715,8 +715,9 @@ __global__ __launch_bounds__(kFlatThreads) void locate_parts_kernel(RegionPayloa
 // payload needs a barrier (the indices of one payload are distinct).  While a round is added, the next two are on
 // their way, those of the next part included, so that neither the write-back nor the table look-up leaves the
 // memory pipeline of the unit empty.  122 M elements, eight payloads: 497 -> 426 us at 25 % (2.56 GB, 6.0 TB/s),
-// 242 -> 195 at 1.6 % as the SGD apply (1.1 GB, 5.6 TB/s); 25.6 M elements, sixteen payloads of 6.25 %: 103 -> 95,
-// where 933 parts leave a fourth round of workgroups two thirds full.  Three rounds on their way: 442, 194, 100.
+// 242 -> 191 at 1.6 % as the SGD apply (1.1 GB, 5.7 TB/s); 25.6 M elements, sixteen payloads of 6.25 %: 103 -> 86.5
+// (95 with the first and last loads of a part sorted out, and so waited for, when they are asked for),
+// where 933 parts leave a fourth round of workgroups two thirds full.  Three rounds on their way: 442, 194, 100 against 426, 195, 95.
 template <bool REPLACE>
 __global__ __launch_bounds__(kPartThreads) void merge_parts_kernel(float* __restrict__ dense, RegionPayloads p,
                                                                    int32_t num_payloads,

@@ -356,3 +356,31 @@ def test_exact_of_sets_that_decide_on_the_device(kind, tensors):
             g[(offsets[:-1] + offsets[1:]) // 2] = np.nan
         p.step(g, it, label=f"exact, {kind}, {tensors} tensors, d={d} it{it}")
     p.close()
+
+
+def test_floors_in_the_pass_and_collected_bands_in_the_static_array():
+    """The static array has no areas for bands: those that are collected beside floors in the pass lie in other scratch."""
+    import torch
+    offsets = np.concatenate([[0], np.cumsum([777] + [3_000_000] * 7 + [50_001])])
+    n = int(offsets[-1])
+    rng = np.random.default_rng(11)
+    sides = []
+    for _ in range(2):
+        dgc = B.Dgc(B.make_config(momentum=0.9, density=0.001, seed=31, flags=EXACT), offsets)
+        dgc.set_layout(dgc.dgc_recommended_payload_layout(0.001))
+        sides.append((dgc, torch.zeros(n, device="cuda"), torch.zeros(n, device="cuda"), dgc.alloc_payload("cuda")))
+    for it in range(3):
+        g = rng.standard_normal(n, dtype=np.float32)
+        in_rows(g, int(offsets[2]), int(offsets[3]), 1500, 3, rng)
+        if it == 2:
+            for j in range(1, 7):
+                in_rows(g, int(offsets[j]), int(offsets[j + 1]), 1500, 5, rng)
+        g = torch.from_numpy(g).cuda()
+        sides[0][0].dgc_compress(g, *sides[0][1:3], *sides[0][3], it)
+        sides[1][0].dgc_compress_static(g, *sides[1][1:3], *sides[1][3], it)
+        for a, b in zip(sides[0][1:3] + sides[0][3][2:], sides[1][1:3] + sides[1][3][2:]):
+            assert torch.equal(a, b), it
+        (ia, va, _), (ib, vb, _) = (gather_payload(side[0]._layout, *side[3][:3]) for side in sides)
+        assert all(np.array_equal(a, b) for a, b in zip(ia + va, ib + vb)), it
+    for side in sides:
+        side[0].close()
