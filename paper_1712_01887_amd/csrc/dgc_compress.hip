@@ -693,6 +693,7 @@ __global__ __launch_bounds__(kBandThreads) void collect_band_kernel(SelectArgs a
   __shared__ uint32_t list[kBandElements];
   __shared__ uint32_t counts[3][kWaves];
   __shared__ uint32_t base_sh;
+  if (a.floor.in_pass && a.state->crowded == 0) return;  // every floor went into the pass
   const EmitBlock blk = blocks[blockIdx.x / kBandsPerPart];
   const TensorPlan plan = a.plans[blk.tensor];
   const bool into_pass = floor_went_into_pass(a.floor, a.state, blk.tensor);
@@ -789,6 +790,7 @@ __global__ __launch_bounds__(kSelectThreads) void rank_band_kernel(SelectArgs a)
   __shared__ SelectShared sh;
   const int tid = threadIdx.x;
   const int j = blockIdx.x;
+  if (a.floor.in_pass && a.state->crowded == 0) return;  // every floor went into the pass
   const TensorPlan plan = a.plans[j];
   const bool into_pass = floor_went_into_pass(a.floor, a.state, j);
   if (plan.exact != 2 || into_pass) return;
