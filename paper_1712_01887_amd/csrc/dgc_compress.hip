@@ -1294,10 +1294,10 @@ __device__ __forceinline__ int tile_counts_partial(const uint32_t* __restrict__ 
 // 161-tensor set and 34 us on the 122 M-element set for what the per-tile counts already say.)
 // EXACT SELECTION at densities up to kBandInPassDensity comes here, too: select_kernel has named a floor that lies below
 // the exact threshold almost surely, the pass took what exceeds it, and every such tensor is ranked here.  The streaming
-// pass is then the only one over g, u, v: 161 tensors of 25.6 M elements, 0.1 %, call 176 -> 148 us where bands were
+// pass is then the only one over g, u, v: 161 tensors of 25.6 M elements, 0.1 %, call 175 -> 146 us where bands were
 // collected by another pass.  (Tensors whose sample does not bear the floor out still are: with large values in rows of
-// every second large tensor, placed anew every third call, the median of the calls is 195 us and the worst 215, where bands
-// alone take 187 and 1467; with such rows in one tensor of fifty 159, against 178.)
+// every second large tensor, placed anew every third call, the median of the calls is 195 us and the worst 220, where bands
+// alone take 187 and 1467; with such rows in one tensor of fifty 158, against 178.)
 // A workgroup lists up to kRefineList selected elements in LDS (index and key) and ranks them by one
 // histogram; the over-selection of a big tensor goes to the payload region, which is free until the emit
 // pass, and through three histogram passes.  Bound by latency, a chain of dependent steps in the dozen

@@ -172,7 +172,7 @@ constexpr int64_t kBandInPassList = kRefineList * 3 / 4;
 constexpr int64_t kBandInPassElements = 8 << 20;
 // ... and if some are collected, only if the others hold more than this; otherwise all are.  (4 tensors of 3.8 M, one of
 // them with large values in 20 rows, 11.4 M elements in the others: 158 us with their floors in the pass, 150
-// without; 161 tensors of 25.6 M, one in fifty with such rows: 159, and 185 without.)
+// without; 161 tensors of 25.6 M, one in fifty with such rows: 158, and 185 without.)
 constexpr int64_t kBandMixedElements = 16 << 20;
 constexpr int kBandBlockShift = 5;
 constexpr int kBandListShift = 6;       // three list words per 64 elements

@@ -322,7 +322,8 @@ def in_rows(g, lo, hi, width, rows, rng):
         g[lo + r * width:lo + (r + 1) * width] *= 100
 
 
-@pytest.mark.parametrize("kind", ["spread", "one in rows", "all in rows", "few magnitudes", "misses", "mostly zero", "unseen rows"])
+@pytest.mark.parametrize("kind", ["spread", "one in rows", "all in rows", "few magnitudes", "misses", "mostly zero", "unseen rows",
+                                  "rows of NaNs", "many NaNs"])
 @pytest.mark.parametrize("tensors", [3, 7])
 def test_exact_of_sets_that_decide_on_the_device(kind, tensors):
     """Sets large enough for floors in the pass, with tensors so long that the sample has to bear the floor out: all
@@ -349,6 +350,10 @@ def test_exact_of_sets_that_decide_on_the_device(kind, tensors):
         elif kind == "misses":                       # one large value to a sampled block: fewer than k, more than the floor's rank
             first = np.unique(band_sample(sizes[1], 21, it, 1) // 32 * 32)
             g[lo + first + rng.integers(0, 32, first.size)] = 50.0 + rng.random(first.size, dtype=np.float32)
+        elif kind == "rows of NaNs" and it == 1:     # more than k: the threshold is one, and nothing is sent
+            g[lo + 30_000:lo + 36_000] = np.nan
+        elif kind == "many NaNs" and it == 1:
+            g[lo + rng.choice(hi - lo, 6000, replace=False)] = np.nan
         elif kind == "unseen rows":                  # many more pass than the sample lets expect: the list in LDS does not hold them
             unseen = np.setdiff1d(np.arange(sizes[1] // 32), band_sample(sizes[1], 21, it, 1) // 32)
             g[lo + (rng.choice(unseen, 700, replace=False)[:, None] * 32 + np.arange(32)).ravel()] *= 100
