@@ -1011,7 +1011,8 @@ static dgc_status scatter_regions(dgc_handle* h, float* dense, int32_t num_paylo
       int64_t expected = 0;
       for (int32_t j = 0; j < h->num_tensors; ++j) expected += 8 * h->k[j] + 256;
       const int64_t sized_for = expected < widest ? expected : widest;
-      if (!hip_ok(launch_scatter_regions(dense, h->n, p, 0, num_payloads, oo, h->num_tensors, sized_for,
+      const int64_t longest = (int64_t)std::ceil(1.25 * h->cfg.density * (double)h->longest_tensor);
+      if (!hip_ok(launch_scatter_regions(dense, h->n, p, 0, num_payloads, oo, h->num_tensors, sized_for, longest,
                                          kScatterClear, 0.0f, nullptr, stream),
                   "launch scatter kernel"))
         return DGC_ERR_HIP;

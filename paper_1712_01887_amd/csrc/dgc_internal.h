@@ -73,6 +73,13 @@ constexpr int kFlatThreads = 256;
 constexpr int kFlatPer = 4;
 constexpr int kFlatChunk = kFlatThreads * kFlatPer;
 constexpr int kFlatTensors = 1024;
+// A sparse clear has a workgroup at least for every tensor of every payload up to kClearGroups of them (launches
+// by tensors against numbered pairs, us: 1000 tensors, sixteen workers 8.8 and 9.5; 4000, four 8.7 and 13.2; 8000, two 10.0
+// and 20.0), as many as the longest tensor's pairs ask for up to half as many (500 tensors of 20 M elements, 1 % of
+// eight workers: 24.7, with twice as many 29.5, numbered 27.5), and none that would take more than
+// kClearRounds chunks one after the other, as where one tensor holds nearly everything.
+constexpr int64_t kClearGroups = 16384;
+constexpr int64_t kClearRounds = 4;
 
 // Receive side without atomics: a workgroup owns a range of one tensor's elements (a
 // whole number of emit workgroups' parts, which follow each other in index order in
@@ -414,7 +421,7 @@ hipError_t launch_scatter_pairs(float* dense, int64_t n, const PairPayloads& p, 
                                 uint32_t* diag_flags, hipStream_t stream);
 hipError_t launch_scatter_regions(float* dense, int64_t n, const RegionPayloads& p, int32_t first,
                                   int32_t num, const int64_t* out_offsets_dev, int32_t num_tensors,
-                                  int64_t total_capacity, ScatterMode mode, float scale,
+                                  int64_t total_capacity, int64_t longest, ScatterMode mode, float scale,
                                   uint32_t* diag_flags, hipStream_t stream);
 
 hipError_t launch_merge_regions(float* dense, const RegionPayloads& p, int32_t num, const RegionPayloads* old,
