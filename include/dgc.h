@@ -306,7 +306,8 @@ dgc_status dgc_decompress_accumulate(dgc_handle* h, float* dense, int64_t n, int
  * density: up to 0.5 %, as long as the payloads together let expect no more than 6144 pairs
  * in the longest range (density x payloads x its elements x 1.25), and above it, unless an aggregate
  * is replaced, in sets of up to 256 ranges that let expect no more than 6144 in the longest
- * tensor, a workgroup touches only the elements that occur in a range of up to 131072; otherwise (the warm-up densities of
+ * tensor, a workgroup touches only the elements that occur in a range of up to 131072 (in sets of up to 256 parts whose
+ * payloads let expect few pairs per element, in one part); otherwise (the warm-up densities of
  * Section 4, or many payloads) it keeps one part's whole range of
  * `dense` on chip, after a launch that finds every payload's pairs of every part.  A
  * region laid out otherwise gives wrong sums (never an access out of bounds); for

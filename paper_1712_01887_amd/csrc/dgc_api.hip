@@ -40,6 +40,7 @@ struct dgc_handle {
   int64_t longest_tensor = 0;
   std::vector<MergeBlock> part_blocks;   // the same with one emit part per range (warm-up densities)
   bool layout_may_overflow = true;       // some region of the registered layout is smaller than its tensor
+  double last_replace_share = 0.0;       // pairs per element that they let expect
   int64_t last_replace_expected = 0;     // pairs per range the payloads of the last dgc_decompress_replace_regions call let expect
   WorkspaceLayout lay{};
   // what the bound workspace currently holds
@@ -117,6 +118,11 @@ constexpr double kMergeMaxDensity = 0.005;   // receive side: merge by element r
 // is two orders of magnitude slower (30 M elements, 0.8 %, four workers, pairs in a fiftieth of the tensor:
 // 5700 us by ranges, 45 by parts; 1 M elements, pairs in an eighth: 146 and 14).
 constexpr size_t kMergeFewRanges = 256;
+// Sets of up to as many parts have a word of LDS for every element, if the payloads let expect at most this many pairs
+// per element.  Against the part kernels in one launch (us): accumulating, 30 tensors of 7 M elements, 0.4 % of sixteen
+// workers (0.064) 16.2 and 18.2, 1 M, 1 % of sixteen (0.16) 17.7 and 13.9; replacing, 1 % of four (0.04) 13.7 and 12.8,
+// of two (0.02) 10.0 and 12.2, 1 M, of four 9.5 and 9.6.
+constexpr double kDirectMaxShare = 0.08, kDirectMaxShareReplacing = 0.03;
 // Sparse clear by scattered stores (80 G/s) up to this many pairs in all; the part kernels take 18 us however
 // few there are (23 tensors as above: 7.6 against 3.6 + 14.6 us), and as long as the stores at about this
 // number (122 M elements, 1.9 M pairs: 717 against 712 for the whole pass).
@@ -1003,6 +1009,10 @@ static dgc_status scatter_regions(dgc_handle* h, float* dense, int32_t num_paylo
   const MergeBlock* parts = at<MergeBlock>(workspace, h->lay.part_blocks);
   const int32_t num_parts = (int32_t)h->part_blocks.size();
   void* found = at<char>(workspace, h->lay.part_found);
+  const double share = h->cfg.density * (double)num_payloads;
+  const double share_old = (replace && num_old > 0) ? h->last_replace_share : 0.0;
+  const bool direct = h->part_blocks.size() <= kMergeFewRanges && (share > share_old ? share : share_old) <= (replace ? kDirectMaxShareReplacing : kDirectMaxShare);
+  if (replace) h->last_replace_share = share;
   if (clear) {
     if (few || (h->cfg.density * (double)h->n * (double)num_payloads <= kScatterClearPairs &&
                 h->num_tensors <= kScatterClearTensors)) {
@@ -1020,6 +1030,11 @@ static dgc_status scatter_regions(dgc_handle* h, float* dense, int32_t num_paylo
                        "launch clear kernel")) {
       return DGC_ERR_HIP;
     }
+  } else if (direct) {
+    if (!hip_ok(launch_merge_direct(dense, p, num_payloads, replace ? &was : nullptr, num_old, oo, parts, num_parts, sgd,
+                                    scale, stream),
+                "launch merge kernel"))
+      return DGC_ERR_HIP;
   } else if (few) {
     if (!hip_ok(launch_merge_regions(dense, p, num_payloads, replace ? &was : nullptr, num_old, oo,
                                      at<MergeBlock>(workspace, h->lay.merge_blocks), (int32_t)h->merge_blocks.size(),

@@ -94,6 +94,10 @@ constexpr int kMergeCapSmall = 4096;
 constexpr int kMergeCapLarge = 6144;
 static_assert((kMergeMaxRange / 128) % kMergeMaxThreads == 0, "dealt evenly to threads");
 
+// Where the accumulator has a word per element: pairs of a part that a workgroup takes into registers (more are
+// read again for every step).
+constexpr int kDirectPairs = 4096;
+
 // Receive side at warm-up densities: a workgroup owns one emit workgroup's part and keeps
 // the whole range of the dense vector in LDS.
 constexpr int kPartThreads = 1024;
@@ -428,6 +432,9 @@ hipError_t launch_merge_regions(float* dense, const RegionPayloads& p, int32_t n
                                 int32_t num_old, const int64_t* out_offsets_dev, const MergeBlock* blocks,
                                 int32_t num_blocks, int64_t expected_pairs, bool scaled, float scale,
                                 hipStream_t stream);
+hipError_t launch_merge_direct(float* dense, const RegionPayloads& p, int32_t num, const RegionPayloads* old,
+                               int32_t num_old, const int64_t* out_offsets_dev, const MergeBlock* parts,
+                               int32_t num_parts, bool scaled, float scale, hipStream_t stream);
 hipError_t launch_merge_parts(float* dense, const RegionPayloads& p, int32_t num, const int64_t* out_offsets_dev,
                               const MergeBlock* parts, int32_t num_parts, void* found, bool replace, bool scaled,
                               float scale, hipStream_t stream);

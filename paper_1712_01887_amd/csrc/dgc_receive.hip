@@ -606,6 +606,138 @@ __global__ __launch_bounds__(THREADS) void merge_regions_kernel(float* __restric
   }
 }
 
+// The same sums where every emit workgroup's part of the set has a compute unit to itself: the part's range of `dense`
+// then has a word of LDS for every element, and the pairs need no numbering (no bitmap, no prefix sum over it, no
+// look-up of slots).  Only words of elements that occur are ever touched.  Parts are a quarter as long as the ranges
+// above, so that a set of a few million elements keeps four times as many compute units busy, and a crowded part
+// just takes longer.
+// Bound by latency, as the range kernel: launch included, in a graph, 0.1 % of four workers, replacing: 1 M elements 8.2
+// -> 6.7 us, 7 M in two tensors 8.9 -> 7.6; of sixteen 14.8 -> 9.5 and 16.6 -> 12.0; accumulating 1 % of four workers,
+// 23 tensors of 0.27 M 8.6 -> 6.8, 1 M 12.1 -> 7.4 (part kernels).
+// REPLACE: the indices of the earlier payloads are elements that start from zero and get no pair: what the new ones
+// share with them gets its sum, the others zero.
+struct DirectShared {
+  float acc[kEmitElements];
+  int32_t begin[kMaxPayloads + 1];
+  const int32_t* idx_at[kMaxPayloads];
+  const float* val_at[kMaxPayloads];
+};
+
+template <bool REPLACE, int THREADS>
+__global__ __launch_bounds__(THREADS) void merge_direct_kernel(float* __restrict__ dense, RegionPayloads p,
+                                                               int32_t num_payloads, RegionPayloads old,
+                                                               int32_t num_old,
+                                                               const int64_t* __restrict__ out_offsets,
+                                                               const MergeBlock* __restrict__ blocks,
+                                                               float scale, int32_t scaled) {
+  constexpr int kPer = kDirectPairs / THREADS;
+  __shared__ DirectShared sh;
+  __shared__ OldLists was;
+  const int tid = threadIdx.x;
+  const MergeBlock blk = blocks[blockIdx.x];
+  const uint32_t length = (uint32_t)(blk.end - blk.begin);  // <= kEmitElements
+  float* __restrict__ range = dense + blk.begin;
+  int old_total = 0;
+  const int total = locate_pairs<REPLACE>(sh, p, num_payloads, was, old, num_old, out_offsets, blk,
+                                          reinterpret_cast<const int32_t*>(blocks), tid, THREADS / 64, old_total);
+  if (total == 0 && old_total == 0) return;
+  const uint32_t nowhere = 0xFFFFFFFFu;  // (an index outside the range: of a region that does not ascend)
+  auto old_at = [&](int q) {
+    const int w = payload_of(was.begin, num_old, q);
+    const uint32_t r = (uint32_t)was.idx_at[w][q - was.begin[w]] - (uint32_t)blk.begin;
+    return r < length ? r : nowhere;
+  };
+  if (total <= kDirectPairs && old_total <= kDirectPairs) {
+    // everything in registers, all loads on their way together
+    uint32_t old_rel[kPer], rel[kPer];
+    int pw[kPer];
+    float x[kPer];
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      const int q = tid + k * THREADS;
+      old_rel[k] = nowhere;
+      if (REPLACE && k * THREADS < old_total && q < old_total) old_rel[k] = old_at(q);
+    }
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      const int q = tid + k * THREADS;
+      rel[k] = nowhere;
+      pw[k] = 0;
+      x[k] = 0.0f;
+      if (k * THREADS < total && q < total) {
+        const int w = payload_of(sh.begin, num_payloads, q);
+        const int src = q - sh.begin[w];
+        const uint32_t r = (uint32_t)sh.idx_at[w][src] - (uint32_t)blk.begin;
+        const float value = sh.val_at[w][src];
+        rel[k] = r < length ? r : nowhere;
+        x[k] = scaled ? scale * value : value;
+        pw[k] = w;
+      }
+    }
+    float held[kPer];
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      held[k] = 0.0f;
+      if (!REPLACE && k * THREADS < total && rel[k] != nowhere) held[k] = range[rel[k]];
+    }
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      if (REPLACE && k * THREADS < old_total && old_rel[k] != nowhere) sh.acc[old_rel[k]] = 0.0f;
+      if (k * THREADS < total && rel[k] != nowhere) sh.acc[rel[k]] = held[k];  // pairs of several payloads with one index write the same
+    }
+    __syncthreads();
+    for (int w = 0; w < num_payloads; ++w) {  // payloads in the order given
+#pragma unroll
+      for (int k = 0; k < kPer; ++k)
+        if (k * THREADS < total && rel[k] != nowhere && pw[k] == w) sh.acc[rel[k]] = sh.acc[rel[k]] + x[k];
+      __syncthreads();
+    }
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      if (k * THREADS < total && rel[k] != nowhere) range[rel[k]] = sh.acc[rel[k]];
+      if (REPLACE && k * THREADS < old_total && old_rel[k] != nowhere) range[old_rel[k]] = sh.acc[old_rel[k]];
+    }
+    return;
+  }
+  auto pair_at = [&](int q) {
+    const int w = payload_of(sh.begin, num_payloads, q);
+    const uint32_t r = (uint32_t)sh.idx_at[w][q - sh.begin[w]] - (uint32_t)blk.begin;
+    return r < length ? r : nowhere;
+  };
+  if (REPLACE) {
+    for (int q = tid; q < old_total; q += THREADS) {
+      const uint32_t r = old_at(q);
+      if (r != nowhere) sh.acc[r] = 0.0f;
+    }
+  }
+  for (int q = tid; q < total; q += THREADS) {
+    const uint32_t r = pair_at(q);
+    if (r != nowhere) sh.acc[r] = REPLACE ? 0.0f : range[r];
+  }
+  __syncthreads();
+  for (int w = 0; w < num_payloads; ++w) {  // payloads in the order given
+    const int len = sh.begin[w + 1] - sh.begin[w];
+    const int32_t* __restrict__ idx = sh.idx_at[w];
+    const float* __restrict__ val = sh.val_at[w];
+    for (int q = tid; q < len; q += THREADS) {
+      const uint32_t r = (uint32_t)idx[q] - (uint32_t)blk.begin;
+      const float x = scaled ? scale * val[q] : val[q];
+      if (r < length) sh.acc[r] = sh.acc[r] + x;
+    }
+    __syncthreads();
+  }
+  for (int q = tid; q < total; q += THREADS) {
+    const uint32_t r = pair_at(q);
+    if (r != nowhere) range[r] = sh.acc[r];
+  }
+  if (REPLACE) {
+    for (int q = tid; q < old_total; q += THREADS) {
+      const uint32_t r = old_at(q);
+      if (r != nowhere) range[r] = sh.acc[r];
+    }
+  }
+}
+
 // Where to look first for x in an ascending list of m values that lie in [from, to): the place it has if they
 // are spread evenly, and the standard deviation of that place if they are spread at random.  Only the number
 // of probes depends on it.
@@ -1156,6 +1288,23 @@ hipError_t launch_merge_regions(float* dense, const RegionPayloads& p, int32_t n
     else
       hipLaunchKernelGGL((merge_regions_kernel<false, 1024>), grid, dim3(1024), 0, stream, dense, p, num, p, 0,
                          out_offsets_dev, blocks, scale, sc);
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_merge_direct(float* dense, const RegionPayloads& p, int32_t num, const RegionPayloads* old,
+                               int32_t num_old, const int64_t* out_offsets_dev, const MergeBlock* parts,
+                               int32_t num_parts, bool scaled, float scale, hipStream_t stream) {
+  if (num <= 0 || num_parts <= 0) return hipSuccess;
+  const dim3 grid((unsigned)num_parts);
+  const int sc = scaled ? 1 : 0;
+  const bool few = num <= 8 && num_old <= 8;  // one wavefront per payload in a workgroup of eight
+  if (old) {
+    if (few) hipLaunchKernelGGL((merge_direct_kernel<true, 512>), grid, dim3(512), 0, stream, dense, p, num, *old, num_old, out_offsets_dev, parts, scale, sc);
+    else hipLaunchKernelGGL((merge_direct_kernel<true, 1024>), grid, dim3(1024), 0, stream, dense, p, num, *old, num_old, out_offsets_dev, parts, scale, sc);
+  } else {
+    if (few) hipLaunchKernelGGL((merge_direct_kernel<false, 512>), grid, dim3(512), 0, stream, dense, p, num, p, 0, out_offsets_dev, parts, scale, sc);
+    else hipLaunchKernelGGL((merge_direct_kernel<false, 1024>), grid, dim3(1024), 0, stream, dense, p, num, p, 0, out_offsets_dev, parts, scale, sc);
   }
   return hipGetLastError();
 }
