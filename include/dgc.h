@@ -309,7 +309,7 @@ dgc_status dgc_decompress_accumulate(dgc_handle* h, float* dense, int64_t n, int
  * tensor, a workgroup touches only the elements that occur in a range of up to 131072 (in sets of up to 256 parts whose
  * payloads let expect few pairs per element, in one part); otherwise (the warm-up densities of
  * Section 4, or many payloads) it keeps one part's whole range of
- * `dense` on chip, after a launch that finds every payload's pairs of every part.  A
+ * `dense` on chip, after a launch that finds every payload's pairs of every part (or, in small sets, a search of its own).  A
  * region laid out otherwise gives wrong sums (never an access out of bounds); for
  * arbitrary pair lists there is dgc_decompress_accumulate.
  */

@@ -102,6 +102,11 @@ constexpr int kDirectPairs = 4096;
 // the whole range of the dense vector in LDS.
 constexpr int kPartThreads = 1024;
 constexpr int kPartChunk = 256;  // slots of a payload a wavefront takes at a time, four consecutive ones to a lane
+// Parts times payloads up to which the workgroups of the part kernel, one to a part, search for themselves.  In one
+// launch and in two, replacing: 1 M elements (32 parts), four workers, 6.25 %: 10.2 and 11.7 us, sixteen 19.8 and 20.6;
+// 7 M (215 parts), four: 13.7 and 15.5, but sixteen 26.4 and 25.4, at 25 % 57.7 and 52.8: without the first guess of the
+// searching launch, every wavefront takes five rounds of probes.
+constexpr int64_t kPartSearches = 2048;
 constexpr int kPartClearThreads = 256;
 constexpr int kPartClearLoads = 4;  // loads of four indices a lane has on their way
 static_assert(kEmitElements <= 65536 && kEmitElements % kPartThreads == 0 &&

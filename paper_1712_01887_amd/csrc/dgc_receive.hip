@@ -880,12 +880,15 @@ __global__ __launch_bounds__(kFlatThreads) void locate_parts_kernel(RegionPayloa
 // 242 -> 191 at 1.6 % as the SGD apply (1.1 GB, 5.7 TB/s); 25.6 M elements, sixteen payloads of 6.25 %: 103 -> 86.5
 // (95 with the first and last loads of a part sorted out, and so waited for, when they are asked for),
 // where 933 parts leave a fourth round of workgroups two thirds full.  Three rounds on their way: 442, 194, 100 against 426, 195, 95.
-template <bool REPLACE>
+//
+// SEARCH: every part has a workgroup of its own, which finds its payloads' pairs itself, a payload to a wavefront (two
+// from seventeen on), instead of reading them from the table of a launch before (see kPartSearches).
+template <bool REPLACE, bool SEARCH>
 __global__ __launch_bounds__(kPartThreads) void merge_parts_kernel(float* __restrict__ dense, RegionPayloads p,
                                                                    int32_t num_payloads,
+                                                                   const int64_t* __restrict__ out_offsets,
                                                                    const MergeBlock* __restrict__ blocks,
-                                                                   int32_t num_blocks,
-                                                                   const int2* __restrict__ found, float scale,
+                                                                   int32_t num_blocks, int2* __restrict__ found, float scale,
                                                                    int32_t scaled) {
   typedef float fvec4u __attribute__((ext_vector_type(4), aligned(4)));  // a range starts anywhere
   typedef int32_t ivec4 __attribute__((ext_vector_type(4)));
@@ -932,7 +935,33 @@ __global__ __launch_bounds__(kPartThreads) void merge_parts_kernel(float* __rest
   // Lane w looks after payload w.
   const int32_t* const idx_of = lane < num_payloads ? p.idx[lane] : nullptr;
   const float* const val_of = lane < num_payloads ? p.val[lane] : nullptr;
+  __shared__ int2 own_entry[SEARCH ? kMaxPayloads : 1];
+  if (SEARCH) {
+    const MergeBlock blk = blocks[b];
+    const int64_t region = out_offsets[blk.tensor];
+    const int64_t cap = out_offsets[blk.tensor + 1] - region;
+    for (int w = wave; w < num_payloads; w += 2 * kWaves) {  // uniform
+      const bool two = w + kWaves < num_payloads;
+      const int w2 = two ? w + kWaves : w;
+      const int32_t* __restrict__ list = p.idx[w] + region;
+      const int32_t* __restrict__ list2 = p.idx[w2] + region;
+      const int32_t* __restrict__ counts = p.counts[w];
+      const int32_t* __restrict__ counts2 = p.counts[w2];
+      const int32_t both = (lane & 1 ? counts2 : counts)[blk.tensor];  // one load for the two
+      const int32_t count = __builtin_amdgcn_readlane(both, 0), count2 = __builtin_amdgcn_readlane(both, 1);
+      int lo = 0, hi = count < 0 ? 0 : count > cap ? (int)cap : count;
+      int lo2 = 0, hi2 = !two || count2 < 0 ? 0 : count2 > cap ? (int)cap : count2;
+      if (blk.begin != blk.lo || blk.end != blk.hi)  // (a part that is a whole tensor has all its pairs)
+        wave_equal_ranges(list, hi, list2, hi2, reinterpret_cast<const int32_t*>(blocks), blk.begin, blk.end, lane, lo, hi, lo2, hi2);
+      if (lane == 0) {  // (the table says the same after either way)
+        found[(int64_t)b * num_payloads + w] = own_entry[w] = make_int2((int)region + lo, hi > lo ? hi - lo : 0);
+        if (two) found[(int64_t)b * num_payloads + w2] = own_entry[w2] = make_int2((int)region + lo2, hi2 > lo2 ? hi2 - lo2 : 0);
+      }
+    }
+    __syncthreads();
+  }
   auto entry_of = [&](int part) {
+    if (SEARCH) return part == (int)blockIdx.x && lane < num_payloads ? own_entry[lane] : make_int2(0, 0);
     return part < num_blocks && lane < num_payloads ? found[(int64_t)part * num_payloads + lane] : make_int2(0, 0);
   };
   struct Table {                // of the part that is being fetched
@@ -1320,7 +1349,6 @@ hipError_t launch_merge_parts(float* dense, const RegionPayloads& p, int32_t num
                               const MergeBlock* parts, int32_t num_parts, void* found, bool replace, bool scaled,
                               float scale, hipStream_t stream) {
   if (num <= 0 || num_parts <= 0) return hipSuccess;
-  launch_locate_parts(p, num, out_offsets_dev, parts, num_parts, static_cast<int2*>(found), stream);
   static int compute_units = 0;  // one workgroup of this kernel fits a compute unit
   if (compute_units <= 0) {
     int dev = 0;
@@ -1329,12 +1357,14 @@ hipError_t launch_merge_parts(float* dense, const RegionPayloads& p, int32_t num
       compute_units = 256;
   }
   const int grid = num_parts < compute_units ? num_parts : compute_units;
-  if (replace)
-    hipLaunchKernelGGL(merge_parts_kernel<true>, dim3((unsigned)grid), dim3(kPartThreads), 0, stream, dense, p, num,
-                       parts, num_parts, static_cast<const int2*>(found), scale, scaled ? 1 : 0);
-  else
-    hipLaunchKernelGGL(merge_parts_kernel<false>, dim3((unsigned)grid), dim3(kPartThreads), 0, stream, dense, p, num,
-                       parts, num_parts, static_cast<const int2*>(found), scale, scaled ? 1 : 0);
+  const bool search = num_parts <= compute_units && (int64_t)num_parts * num <= kPartSearches;
+  if (!search) launch_locate_parts(p, num, out_offsets_dev, parts, num_parts, static_cast<int2*>(found), stream);
+  const auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(kPartThreads), 0, stream, dense, p, num, out_offsets_dev,
+                       parts, num_parts, static_cast<int2*>(found), scale, scaled ? 1 : 0);
+  };
+  if (search) launch(replace ? merge_parts_kernel<true, true> : merge_parts_kernel<false, true>);
+  else launch(replace ? merge_parts_kernel<true, false> : merge_parts_kernel<false, false>);
   return hipGetLastError();
 }
 

@@ -102,3 +102,28 @@ def test_replacing_across_a_change_of_density(first, then):
         assert np.array_equal(dense.cpu().numpy(), expect)
         previous = (lists[0], lists[2])
     dgc.close()
+
+
+@pytest.mark.parametrize("workers,more", [(7, 0), (64, 0), (64, 25)])
+def test_part_kernel_that_searches_and_that_looks_up(workers, more):
+    """Dense payloads, parts times payloads on both sides of the line between one launch and two."""
+    import torch
+    rng = np.random.default_rng([workers, more])
+    sizes = SIZES + [3] * more                       # 10 parts, 35
+    offsets = np.concatenate([[0], np.cumsum(sizes)])
+    dgc = B.Dgc(B.make_config(density=0.25, num_workers=workers), offsets)
+    layout = offsets.tolist()
+    dgc.set_layout(layout)
+    new = [payload(0.25 if w % 3 else 0.01, rng, offsets, layout, 0) for w in range(workers)]
+    lists = tuple([d[i] for _, d in new] for i in range(3))
+    start = rng.standard_normal(int(offsets[-1])).astype(np.float32)
+    expect, fresh = start.copy(), np.zeros_like(start)
+    for (e, x), _ in new:
+        expect[e] = (expect[e] + x).astype(np.float32)
+        fresh[e] = (fresh[e] + x).astype(np.float32)
+    dense = torch.from_numpy(start).cuda()
+    dgc.dgc_decompress_accumulate_regions(dense, *lists)
+    assert np.array_equal(dense.cpu().numpy(), expect)
+    dgc.dgc_decompress_replace_regions(dense, *lists)
+    assert np.array_equal(dense.cpu().numpy(), fresh)
+    dgc.close()
