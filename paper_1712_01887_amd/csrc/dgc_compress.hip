@@ -208,18 +208,27 @@ __device__ __forceinline__ void find_bin(const uint32_t* hist, uint32_t* wave_to
 }
 
 // The `m` <= kSelectThreads keys in sh.surv, which is zero behind them up to a multiple of four: the one of
-// descending rank `rank`.  Every thread compares one key with all, four to an LDS read.  (Splitting the
-// comparisons of one key over several threads, with the partial counts added in LDS, was measured:
-// no faster for the 100 to 200 keys that get here.)
+// descending rank `rank`.  Up to 256 keys, the usual case, have four neighbouring threads each, which compare it with a
+// quarter of the keys, four to an LDS read, and add up through the vector unit; more have one.
 __device__ __forceinline__ uint32_t rank_directly(SelectShared& sh, int tid, uint32_t m, uint32_t rank) {
-  if (tid < (int)m) {
-    const uint32_t x = sh.surv[tid];
+  const uint4* __restrict__ four = reinterpret_cast<const uint4*>(sh.surv);
+  const bool shared = 4 * m <= (uint32_t)kSelectThreads;  // uniform
+  const uint32_t own = shared ? (uint32_t)tid >> 2 : (uint32_t)tid;
+  if (own < m) {
+    const uint32_t x = sh.surv[own];
     uint32_t greater = 0, equal = 0;  // (a zero behind the keys can only add to the last rank's ties)
-    const uint4* __restrict__ four = reinterpret_cast<const uint4*>(sh.surv);
-    for (uint32_t i = 0; 4 * i < m; ++i) {
+    const uint32_t step = shared ? 4 : 1;
+    for (uint32_t i = shared ? tid & 3 : 0; 4 * i < m; i += step) {
       const uint4 y = four[i];
       greater += (y.x > x) + (y.y > x) + (y.z > x) + (y.w > x);
       equal += (y.x == x) + (y.y == x) + (y.z == x) + (y.w == x);
+    }
+    if (shared) {
+      uint32_t both = greater | (equal << 16);
+      both += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)both, 0xB1, 0xf, 0xf, false);  // the neighbour's
+      both += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)both, 0x4E, 0xf, 0xf, false);  // the other pair's
+      greater = both & 0xFFFFu;
+      equal = both >> 16;
     }
     if (greater <= rank && rank < greater + equal) sh.result = x;  // ties write the same value
   }
@@ -278,14 +287,17 @@ __device__ __forceinline__ uint32_t select_in_registers(SelectShared& sh, const 
 
 // The smallest of what the first `full_waves` wavefronts name as the t-th largest of their threads' largest keys: a key that
 // t * full_waves keys at least do not lie below.  `top` gets this thread's largest key (-1: it has none).
-__device__ __forceinline__ uint32_t floor_of_waves(SelectShared& sh, const uint32_t (&key)[kSelectRegKeys], uint32_t full_waves,
-                                                   uint32_t t, int tid, int32_t& top) {
+__device__ __forceinline__ uint32_t floor_of_waves(SelectShared& sh, const uint32_t (&key)[kSelectRegKeys], int live,
+                                                   uint32_t full_waves, uint32_t t, int tid, int32_t& top) {
   constexpr int kWaves = kSelectThreads / 64;
   const int lane = tid & 63;
   const int wave = tid >> 6;
   top = -1;  // (an empty slot counts as -1)
 #pragma unroll
-  for (int i = 0; i < kSelectRegKeys; ++i) top = (int32_t)key[i] > top ? (int32_t)key[i] : top;
+  for (int i = 0; i < kSelectRegKeys; ++i) {
+    if (i % 4 == 0 && i >= live) break;  // uniform
+    top = (int32_t)key[i] > top ? (int32_t)key[i] : top;
+  }
   uint32_t rest = top > 0 ? (uint32_t)top : 0u;
   uint32_t tth = 0;
   for (uint32_t round = 0; round < t; ++round) {
@@ -302,9 +314,9 @@ __device__ __forceinline__ uint32_t floor_of_waves(SelectShared& sh, const uint3
 }
 
 // Key of descending rank `rank` among the `count` keys a workgroup holds in registers (kNoKey marks an empty
-// slot); threads 0 .. holders - 1 have at least one.  Every thread returns the same.
+// slot); threads 0 .. holders - 1 have at least one, none has one behind its first `live`.  Every thread returns the same.
 __device__ __forceinline__ uint32_t rank_registers(SelectShared& sh, const uint32_t (&key)[kSelectRegKeys], int32_t count,
-                                                   int32_t holders, uint32_t rank, int tid) {
+                                                   int32_t holders, int live, uint32_t rank, int tid) {
   // Gradients of one tensor share a few exponents, so a histogram over the leading key
   // bits of all candidates piles tens of thousands of LDS atomics on a handful of bins,
   // and every histogram pass costs half a dozen barriers of 1024 threads (ranking 32 Ki
@@ -325,22 +337,32 @@ __device__ __forceinline__ uint32_t rank_registers(SelectShared& sh, const uint3
     int32_t top;
     if (tid == 0) sh.surv_n = 0;
     sh.surv[tid] = 0;
-    const uint32_t floor_key = floor_of_waves(sh, key, full_waves, t_rounds, tid, top);
-    if (top >= (int32_t)floor_key) {
+    const uint32_t floor_key = floor_of_waves(sh, key, live, full_waves, t_rounds, tid, top);
+    // One addition to the list's length per wavefront.  Most threads that have a key to list have one, their largest.
+    uint32_t mine = 0;
 #pragma unroll
-      for (int i = 0; i < kSelectRegKeys; ++i)
-        if ((int32_t)key[i] >= (int32_t)floor_key) {
-          const uint32_t pos = atomicAdd(&sh.surv_n, 1u);
+    for (int i = 0; i < kSelectRegKeys; ++i) {
+      if (i % 4 == 0 && i >= live) break;  // uniform
+      mine += (int32_t)key[i] >= (int32_t)floor_key ? 1u : 0u;
+    }
+    const uint32_t upto = wave_inclusive_sum(mine);
+    uint32_t pos = 0;
+    if ((tid & 63) == 63 && upto > 0u) pos = atomicAdd(&sh.surv_n, upto);
+    pos = wave_last(pos) + upto - mine;
+    if (mine == 1u && pos < (uint32_t)kSelectThreads) sh.surv[pos] = (uint32_t)top;
+    if (__ballot(mine > 1u) != 0) {
+#pragma unroll
+      for (int i = 0; i < kSelectRegKeys; ++i) {
+        if (i % 4 == 0 && i >= live) break;  // uniform
+        if (mine > 1u && (int32_t)key[i] >= (int32_t)floor_key) {
           if (pos < (uint32_t)kSelectThreads) sh.surv[pos] = key[i];
+          ++pos;
         }
+      }
     }
     __syncthreads();
     const uint32_t listed = sh.surv_n;
-    if (listed <= (uint32_t)kSelectThreads) {
-      const uint32_t found = rank_directly(sh, tid, listed, rank);
-      __syncthreads();
-      return found;
-    }
+    if (listed <= (uint32_t)kSelectThreads) return rank_directly(sh, tid, listed, rank);
     __syncthreads();
   }
   return select_in_registers<kSelectRegKeys>(sh, key, 0u, rank, tid);
@@ -495,8 +517,7 @@ __device__ __forceinline__ float settle_scale(const SelectArgs& a, SelectShared&
     }
     return a.scale_const;
   }
-  double s = part;
-  for (int d = 32; d >= 1; d >>= 1) s += __shfl_down(s, d);
+  const double s = wave_sum_down(part);
   if ((tid & 63) == 0) sh.red[tid >> 6] = s;
   __syncthreads();
   if (tid == 0) {
@@ -521,7 +542,10 @@ __device__ __forceinline__ float settle_scale(const SelectArgs& a, SelectShared&
 
 // Bound by latency: the gather of the candidates, then the ranking, in one workgroup per tensor.  17 us on the
 // 122 M-element set, 13.6 on the 161-tensor set, 10.5 on 23 tensors of 0.27 M elements in all (19.2, 14.3, 12.2
-// with the wavefronts' maxima taken through LDS and one key per LDS read).
+// with the wavefronts' maxima taken through LDS and one key per LDS read).  Inside the workgroup, 1 M elements, from its start:
+// 8.0 -> 6.6 us with the list's length asked for once per wavefront and not per key, four threads to a listed key, no
+// walk over empty slots, and the scale's sum over the lanes inside the vector unit; the step of that set 27.5 ->
+// 26.3, of the 23 tensors 33.9 -> 31.9.
 // MODE: whether some tensors are ranked by way of a band (TensorPlan.exact == 2), and whether its floor may go into the pass.
 enum SelectMode : int { kSelectNoBands = 0, kSelectLists = 1, kSelectInPass = 2 };
 
@@ -559,6 +583,8 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectArgs a) {
     for (int i = 0; i < kSelectRegKeys; ++i) key[i] = kNoKey;
     const bool quads_of_blocks = !c.exact && c.block_shift >= 2;
     const int32_t holders = quads_of_blocks ? count >> 2 : count;  // threads with at least one candidate
+    // candidates of a thread that has most
+    const int live = quads_of_blocks ? 4 * (((count >> 2) + kSelectThreads - 1) / kSelectThreads) : (count + kSelectThreads - 1) / kSelectThreads;
     // The gather is written without branches around the loads and without conditional stores into
     // key[]: a candidate beyond the count reads candidate 0 instead and its key is replaced by the
     // empty mark afterwards.  (With `if (p < count)` around them the compiler copied the whole
@@ -632,7 +658,7 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectArgs a) {
       // others are collected.
       const BandRanks at((double)plan.rank / (double)plan.n, (double)kBandSample);
       if (MODE == kSelectInPass) {
-        const uint32_t floor_key = rank_registers(sh, key, count, holders, (uint32_t)at.floor_in_pass(), tid);
+        const uint32_t floor_key = rank_registers(sh, key, count, holders, live, (uint32_t)at.floor_in_pass(), tid);
         bool reliable = true, in_clusters = false;
         if (a.band_list) {  // (a set without lists has no tensor so long that a miss would cost more than looking)
           uint32_t above, keys, squares;
@@ -653,20 +679,20 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectArgs a) {
         if (a.band_list) {
           uint32_t band_floor = floor_key;
           int32_t top;
-          if (in_clusters) band_floor = floor_of_waves(sh, key, kSelectThreads / 64, (uint32_t)(ceil(at.mid) + at.reach()) / (kSelectThreads / 64) + 1u, tid, top);
+          if (in_clusters) band_floor = floor_of_waves(sh, key, live, kSelectThreads / 64, (uint32_t)(ceil(at.mid) + at.reach()) / (kSelectThreads / 64) + 1u, tid, top);
           if (tid == 0) *band_state(a, plan) = BandState{band_floor, 0x80000000u, 0u, 0u, 0u};
         }
         return;
       }
       const double reach = at.reach();
       const double low = ceil(at.mid) + reach, high = floor(at.mid) - reach;
-      const uint32_t floor_key = low < (double)count ? rank_registers(sh, key, count, holders, (uint32_t)low, tid) : 0xFFFFFFFFu;
-      uint32_t ceil_key = high >= 0.0 ? rank_registers(sh, key, count, holders, (uint32_t)high, tid) : 0x80000000u;
+      const uint32_t floor_key = low < (double)count ? rank_registers(sh, key, count, holders, live, (uint32_t)low, tid) : 0xFFFFFFFFu;
+      uint32_t ceil_key = high >= 0.0 ? rank_registers(sh, key, count, holders, live, (uint32_t)high, tid) : 0x80000000u;
       if (ceil_key == floor_key) ++ceil_key;
       if (tid == 0) *band_state(a, plan) = BandState{floor_key, ceil_key, 0u, 0u, 0u};
       return;
     }
-    thr_bits = rank_registers(sh, key, count, holders, rank, tid);
+    thr_bits = rank_registers(sh, key, count, holders, live, rank, tid);
   } else {
     c.scale = settle_scale(a, sh, part, j, tid);
     thr_bits = rank_reevaluated(sh, c, count, rank, tid);

@@ -38,6 +38,23 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t x) {
   return wave_last(x);
 }
 
+// In lane 0 the sum over the wavefront, every lane's value added to that of the lane half as far away as there are lanes
+// left (32, 16, 8, 4, 2, 1).  Halves and rows change places in one instruction, the rest are shifts inside a row.
+__device__ __forceinline__ double wave_sum_down(double x) {
+  auto add = [&](auto move) {
+    const uint64_t b = (uint64_t)__double_as_longlong(x);
+    const uint64_t o = (uint64_t)(uint32_t)move((int)(uint32_t)b) | (uint64_t)(uint32_t)move((int)(uint32_t)(b >> 32)) << 32;
+    x += __longlong_as_double((long long)o);
+  };
+  add([](int v) { return (int)__builtin_amdgcn_permlane32_swap((unsigned)v, (unsigned)v, false, false)[1]; });
+  add([](int v) { return (int)__builtin_amdgcn_permlane16_swap((unsigned)v, (unsigned)v, false, false)[1]; });
+  add([](int v) { return __builtin_amdgcn_update_dpp(0, v, 0x108, 0xf, 0xf, false); });  // row_shl:8
+  add([](int v) { return __builtin_amdgcn_update_dpp(0, v, 0x104, 0xf, 0xf, false); });
+  add([](int v) { return __builtin_amdgcn_update_dpp(0, v, 0x102, 0xf, 0xf, false); });
+  add([](int v) { return __builtin_amdgcn_update_dpp(0, v, 0x101, 0xf, 0xf, false); });
+  return x;
+}
+
 // Between stores to LDS by some lanes of a wavefront and loads of them by others.  The hardware carries out a
 // wavefront's LDS operations in order; this keeps the compiler from moving them, and costs no instruction.
 __device__ __forceinline__ void wave_lds_fence() {
