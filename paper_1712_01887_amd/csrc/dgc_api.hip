@@ -119,9 +119,9 @@ constexpr double kMergeMaxDensity = 0.005;   // receive side: merge by element r
 // 5700 us by ranges, 45 by parts; 1 M elements, pairs in an eighth: 146 and 14).
 constexpr size_t kMergeFewRanges = 256;
 // Sets of up to as many parts have a word of LDS for every element, if the payloads let expect at most this many pairs
-// per element.  Against the part kernels in one launch (us): accumulating, 30 tensors of 7 M elements, 0.4 % of sixteen
-// workers (0.064) 16.2 and 18.2, 1 M, 1 % of sixteen (0.16) 17.7 and 13.9; replacing, 1 % of four (0.04) 13.7 and 12.8,
-// of two (0.02) 10.0 and 12.2, 1 M, of four 9.5 and 9.6.
+// per element.  Against the part kernels (us): accumulating, two tensors of 7 M elements, 0.4 % of sixteen
+// workers (0.064) 15.6 and 18.3, 1 M, 1 % of sixteen (0.16) 17.7 and 13.9; replacing, 7 M, 1 % of four (0.04) 15.1 and 11.1,
+// of two (0.02) 10.3 and 12.4.
 constexpr double kDirectMaxShare = 0.08, kDirectMaxShareReplacing = 0.03;
 // Sparse clear by scattered stores (80 G/s) up to this many pairs in all; the part kernels take 18 us however
 // few there are (23 tensors as above: 7.6 against 3.6 + 14.6 us), and as long as the stores at about this

@@ -55,6 +55,16 @@ __device__ __forceinline__ double wave_sum_down(double x) {
   return x;
 }
 
+// A pointer to global memory that the compiler cannot tell to be one, because it comes from LDS or was put together
+// from registers.  Through a generic pointer every load is a FLAT one, which counts as an LDS operation, too: the next
+// wait for LDS then waits for all such loads that are on their way.
+template <typename T>
+using global_ptr = const __attribute__((address_space(1))) T*;
+template <typename T>
+__device__ __forceinline__ global_ptr<T> in_global(const T* p) {
+  return (global_ptr<T>)p;
+}
+
 // Between stores to LDS by some lanes of a wavefront and loads of them by others.  The hardware carries out a
 // wavefront's LDS operations in order; this keeps the compiler from moving them, and costs no instruction.
 __device__ __forceinline__ void wave_lds_fence() {

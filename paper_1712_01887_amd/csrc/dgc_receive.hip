@@ -309,12 +309,12 @@ __device__ __forceinline__ int locate_pairs(Shared& sh, const RegionPayloads& p,
       wave_equal_ranges(idx, (int)cnt, idx2, (int)cnt2, safe, blk.begin, blk.end, lane, lo, hi, lo2, hi2);
     if (lane == 0) {
       if (have) {
-        sh.idx_at[w] = idx + lo;
-        sh.val_at[w] = val + region + lo;
+        sh.idx_at[w] = in_global(idx + lo);
+        sh.val_at[w] = in_global(val + region + lo);
         sh.begin[w + 1] = hi - lo;  // length for now
       }
       if (have2) {
-        sh2.idx_at[w] = idx2 + lo2;
+        sh2.idx_at[w] = in_global(idx2 + lo2);
         sh2.begin[w + 1] = hi2 - lo2;
       }
     }
@@ -323,8 +323,8 @@ __device__ __forceinline__ int locate_pairs(Shared& sh, const RegionPayloads& p,
   if (tid < 64) begins_from_lengths(sh.begin, num_payloads, tid);
   if (BOTH && tid >= 64 && tid < 128) begins_from_lengths(sh2.begin, num_payloads2, tid - 64);
   __syncthreads();
-  total2 = BOTH ? sh2.begin[num_payloads2] : 0;
-  return sh.begin[num_payloads];
+  total2 = BOTH ? __builtin_amdgcn_readfirstlane(sh2.begin[num_payloads2]) : 0;  // (uniform, for the compiler as well)
+  return __builtin_amdgcn_readfirstlane(sh.begin[num_payloads]);
 }
 
 // Largest w with begin[w] <= q.
@@ -338,6 +338,22 @@ __device__ __forceinline__ int payload_of(const int32_t* begin, int num_payloads
   return w;
 }
 
+// The same for the 64 neighbouring numbers q0, q0 + 1, ... of a wavefront's lanes, q0 below the number of all pairs: lane
+// w of `own` holds begin[w] (behind the payloads: the largest number there is).  One vote says whose q0 is, and the payloads
+// that start among the lanes, mostly one or none, are gone through, instead of a chain of reads from LDS in every lane.
+// `last`: that of the last lane.
+__device__ __forceinline__ int payloads_of(int32_t own, int num_payloads, int q0, int lane, int& first, int& last) {
+  first = __popcll(__ballot(own <= q0)) - 1;
+  int w = first;
+  for (last = first; last + 1 < num_payloads; ++last) {
+    const int32_t next = __builtin_amdgcn_readlane(own, last + 1);
+    if (next > q0 + 63) break;
+    w += q0 + lane >= next ? 1 : 0;
+  }
+  return w;
+}
+__device__ __forceinline__ uint64_t payload_bits(int first, int last) { return (~0ull >> (63 - last)) & (~0ull << first); }
+
 template <int CAP>
 struct MergeShared {
   alignas(16) uint32_t bitmap[kMergeMaxRange / 32];
@@ -345,8 +361,8 @@ struct MergeShared {
   float acc[CAP];
   uint32_t wave_sums[kMergeMaxThreads / 64];
   int32_t begin[kMaxPayloads + 1];  // number of pairs of the payloads before w inside the range
-  const int32_t* idx_at[kMaxPayloads];  // payload w's first pair inside the range
-  const float* val_at[kMaxPayloads];
+  global_ptr<int32_t> idx_at[kMaxPayloads];  // payload w's first pair inside the range
+  global_ptr<float> val_at[kMaxPayloads];
 };
 
 // `scale` multiplies every value first (1 for the plain sum; -learning rate for the SGD
@@ -359,7 +375,7 @@ struct MergeShared {
 // none of the new payloads gets a zero: one launch instead of a clear and an accumulate.
 struct OldLists {
   int32_t begin[kMaxPayloads + 1];
-  const int32_t* idx_at[kMaxPayloads];
+  global_ptr<int32_t> idx_at[kMaxPayloads];
 };
 
 // Number of the distinct index r (relative to the range) among those of the range: the indices
@@ -384,7 +400,11 @@ __device__ __forceinline__ int merge_slot(const MergeShared<CAP>& sh, int32_t r)
 // against 10.7).  (A first round of probes around the place that a range has if pairs are spread evenly took 34.9
 // and 23.7, but 49.1 instead of 39.1 where the pairs crowd three tenths of one large tensor: every workgroup
 // goes on from a bracket of its own, where the first rounds over the whole region read the same few sectors.
-// Both sets of probes in one round: no gain where pairs are spread evenly.)  kMergeCap:
+// Both sets of probes in one round: no gain where pairs are spread evenly.)  Behind the searches, the steps of the
+// 346 ranges of the 25.6 M elements with sixteen payloads from their start, 19.9 -> 18.0 us, call 123.2 -> 121.3: pairs loaded through
+// pointers that are known to be global (FLAT loads before), whose payload a vote tells (four dependent reads of LDS
+// before), a wavefront that goes through its slots for payloads that it has pairs of only, and the wavefronts' sums read together.
+// kMergeCap:
 // pairs a workgroup takes into registers, slots of its LDS accumulator (a range with more takes
 // the slow way at the end of the kernel).
 template <bool REPLACE, int THREADS>
@@ -404,7 +424,7 @@ __global__ __launch_bounds__(THREADS) void merge_regions_kernel(float* __restric
   __shared__ OldLists was;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wave = tid >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const MergeBlock blk = blocks[blockIdx.x];
   const int32_t length = (int32_t)(blk.end - blk.begin);  // <= kMergeMaxRange
 #pragma unroll
@@ -431,13 +451,17 @@ __global__ __launch_bounds__(THREADS) void merge_regions_kernel(float* __restric
     // the earlier set's indices of this range, asked for first and not looked at before the
     // new pairs are in: their loads are in flight together with those of the pairs
     int32_t was_idx[kPerThread];
+    {
+      const int32_t own = lane < num_old ? was.begin[lane] : INT32_MAX;
 #pragma unroll
-    for (int k = 0; k < kPerThread; ++k) {
-      const int q = tid + k * kMergeThreads;
-      was_idx[k] = 0;
-      if (from_zero && q < old_total) {
-        const int w = payload_of(was.begin, num_old, q);
-        was_idx[k] = was.idx_at[w][q - was.begin[w]];
+      for (int k = 0; k < kPerThread; ++k) {
+        const int q0 = wave * 64 + k * kMergeThreads, q = q0 + lane;
+        was_idx[k] = 0;
+        if (from_zero && q0 < old_total) {  // uniform
+          int first, last;
+          const int w = payloads_of(own, num_old, q0, lane, first, last);
+          if (q < old_total) was_idx[k] = was.idx_at[w][q - was.begin[w]];
+        }
       }
     }
     // this thread's pairs: payload, index relative to the range (-1: none), value
@@ -445,26 +469,26 @@ __global__ __launch_bounds__(THREADS) void merge_regions_kernel(float* __restric
     int32_t rel[kPerThread];
     float x[kPerThread];
     float held[kPerThread];  // what the element's slot starts from: asked for before the indices are numbered
+    uint64_t mine = 0;  // payloads of the wavefront's pairs, a bit each (uniform)
+    const int32_t own = lane < num_payloads ? sh.begin[lane] : INT32_MAX;
 #pragma unroll
     for (int k = 0; k < kPerThread; ++k) {
-      const int q = tid + k * kMergeThreads;
+      const int q0 = wave * 64 + k * kMergeThreads, q = q0 + lane;
       rel[k] = -1;
-      pw[k] = 0;
+      pw[k] = -1;
       x[k] = 0.0f;
       held[k] = 0.0f;
+      if (q0 >= total) continue;  // uniform
+      int first, last;
+      const int w = payloads_of(own, num_payloads, q0, lane, first, last);
+      mine |= payload_bits(first, last);
       if (q < total) {
-        int w = 0, e = num_payloads;  // largest w with begin[w] <= q
-        while (e - w > 1) {
-          const int mid = (w + e) >> 1;
-          if (sh.begin[mid] <= q) w = mid;
-          else e = mid;
-        }
         const int src = q - sh.begin[w];
         const int64_t r = (int64_t)sh.idx_at[w][src] - blk.begin;
         const float value = sh.val_at[w][src];
         x[k] = scaled ? scale * value : value;
-        pw[k] = w;
         if (r >= 0 && r < length) {  // anything else can only come from a region that does not ascend
+          pw[k] = w;
           rel[k] = (int32_t)r;
           if (!from_zero) held[k] = dense[blk.begin + r];
           atomicOr(&sh.bitmap[r >> 5], 1u << (r & 31));
@@ -492,7 +516,11 @@ __global__ __launch_bounds__(THREADS) void merge_regions_kernel(float* __restric
       if (lane == 63) sh.wave_sums[wave] = incl;
       __syncthreads();
       uint32_t run = incl - mine;
-      for (int v = 0; v < wave; ++v) run += sh.wave_sums[v];
+#pragma unroll
+      for (int v = 0; v < kMergeWaves; ++v) {  // (all asked for together)
+        const uint32_t t = sh.wave_sums[v];
+        run += v < wave ? t : 0u;
+      }
 #pragma unroll
       for (int k = 0; k < kWordsPerThread; ++k) {
         if ((k & 3) == 0) sh.prefix[(tid * kWordsPerThread + k) >> 2] = run;
@@ -512,9 +540,11 @@ __global__ __launch_bounds__(THREADS) void merge_regions_kernel(float* __restric
     }
     __syncthreads();
     for (int w = 0; w < num_payloads; ++w) {  // payloads in the order given
+      if ((mine >> w) & 1u) {
 #pragma unroll
-      for (int k = 0; k < kPerThread; ++k)
-        if (id[k] >= 0 && pw[k] == w) sh.acc[id[k]] = sh.acc[id[k]] + x[k];
+        for (int k = 0; k < kPerThread; ++k)
+          if (pw[k] == w) sh.acc[id[k]] = sh.acc[id[k]] + x[k];
+      }
       __syncthreads();
     }
 #pragma unroll
@@ -612,15 +642,15 @@ __global__ __launch_bounds__(THREADS) void merge_regions_kernel(float* __restric
 // above, so that a set of a few million elements keeps four times as many compute units busy, and a crowded part
 // just takes longer.
 // Bound by latency, as the range kernel: launch included, in a graph, 0.1 % of four workers, replacing: 1 M elements 8.2
-// -> 6.7 us, 7 M in two tensors 8.9 -> 7.6; of sixteen 14.8 -> 9.5 and 16.6 -> 12.0; accumulating 1 % of four workers,
-// 23 tensors of 0.27 M 8.6 -> 6.8, 1 M 12.1 -> 7.4 (part kernels).
+// -> 6.3 us, 7 M in two tensors 8.9 -> 7.3; of sixteen 14.8 -> 8.6 and 16.6 -> 11.3; accumulating 1 % of four workers,
+// 23 tensors of 0.27 M 8.6 -> 6.5, 1 M 12.1 -> 7.1 (part kernels).
 // REPLACE: the indices of the earlier payloads are elements that start from zero and get no pair: what the new ones
 // share with them gets its sum, the others zero.
 struct DirectShared {
   float acc[kEmitElements];
   int32_t begin[kMaxPayloads + 1];
-  const int32_t* idx_at[kMaxPayloads];
-  const float* val_at[kMaxPayloads];
+  global_ptr<int32_t> idx_at[kMaxPayloads];
+  global_ptr<float> val_at[kMaxPayloads];
 };
 
 template <bool REPLACE, int THREADS>
@@ -634,6 +664,8 @@ __global__ __launch_bounds__(THREADS) void merge_direct_kernel(float* __restrict
   __shared__ DirectShared sh;
   __shared__ OldLists was;
   const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const MergeBlock blk = blocks[blockIdx.x];
   const uint32_t length = (uint32_t)(blk.end - blk.begin);  // <= kEmitElements
   float* __restrict__ range = dense + blk.begin;
@@ -652,26 +684,40 @@ __global__ __launch_bounds__(THREADS) void merge_direct_kernel(float* __restrict
     uint32_t old_rel[kPer], rel[kPer];
     int pw[kPer];
     float x[kPer];
+    uint64_t mine = 0;  // payloads of the wavefront's pairs, a bit each (uniform)
+    const int32_t own_old = REPLACE && lane < num_old ? was.begin[lane] : INT32_MAX;
+    const int32_t own = lane < num_payloads ? sh.begin[lane] : INT32_MAX;
 #pragma unroll
     for (int k = 0; k < kPer; ++k) {
-      const int q = tid + k * THREADS;
+      const int q0 = wave * 64 + k * THREADS, q = q0 + lane;
       old_rel[k] = nowhere;
-      if (REPLACE && k * THREADS < old_total && q < old_total) old_rel[k] = old_at(q);
+      if (!REPLACE || q0 >= old_total) continue;  // uniform
+      int first, last;
+      const int w = payloads_of(own_old, num_old, q0, lane, first, last);
+      if (q < old_total) {
+        const uint32_t r = (uint32_t)was.idx_at[w][q - was.begin[w]] - (uint32_t)blk.begin;
+        old_rel[k] = r < length ? r : nowhere;
+      }
     }
 #pragma unroll
     for (int k = 0; k < kPer; ++k) {
-      const int q = tid + k * THREADS;
+      const int q0 = wave * 64 + k * THREADS, q = q0 + lane;
       rel[k] = nowhere;
-      pw[k] = 0;
+      pw[k] = -1;
       x[k] = 0.0f;
-      if (k * THREADS < total && q < total) {
-        const int w = payload_of(sh.begin, num_payloads, q);
+      if (q0 >= total) continue;  // uniform
+      int first, last;
+      const int w = payloads_of(own, num_payloads, q0, lane, first, last);
+      mine |= payload_bits(first, last);
+      if (q < total) {
         const int src = q - sh.begin[w];
         const uint32_t r = (uint32_t)sh.idx_at[w][src] - (uint32_t)blk.begin;
         const float value = sh.val_at[w][src];
-        rel[k] = r < length ? r : nowhere;
         x[k] = scaled ? scale * value : value;
-        pw[k] = w;
+        if (r < length) {
+          rel[k] = r;
+          pw[k] = w;
+        }
       }
     }
     float held[kPer];
@@ -687,9 +733,11 @@ __global__ __launch_bounds__(THREADS) void merge_direct_kernel(float* __restrict
     }
     __syncthreads();
     for (int w = 0; w < num_payloads; ++w) {  // payloads in the order given
+      if ((mine >> w) & 1u) {
 #pragma unroll
-      for (int k = 0; k < kPer; ++k)
-        if (k * THREADS < total && rel[k] != nowhere && pw[k] == w) sh.acc[rel[k]] = sh.acc[rel[k]] + x[k];
+        for (int k = 0; k < kPer; ++k)
+          if (pw[k] == w) sh.acc[rel[k]] = sh.acc[rel[k]] + x[k];
+      }
       __syncthreads();
     }
 #pragma unroll
@@ -717,8 +765,8 @@ __global__ __launch_bounds__(THREADS) void merge_direct_kernel(float* __restrict
   __syncthreads();
   for (int w = 0; w < num_payloads; ++w) {  // payloads in the order given
     const int len = sh.begin[w + 1] - sh.begin[w];
-    const int32_t* __restrict__ idx = sh.idx_at[w];
-    const float* __restrict__ val = sh.val_at[w];
+    const global_ptr<int32_t> idx = sh.idx_at[w];
+    const global_ptr<float> val = sh.val_at[w];
     for (int q = tid; q < len; q += THREADS) {
       const uint32_t r = (uint32_t)idx[q] - (uint32_t)blk.begin;
       const float x = scaled ? scale * val[q] : val[q];
