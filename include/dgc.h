@@ -431,7 +431,7 @@ dgc_status dgc_decode_accumulate(dgc_handle* h, float* dense, int64_t n, int32_t
  * Kernel timing for measurement harnesses.  After dgc_profile_enable the next
  * `max_calls` dgc_compress calls record HIP events on the caller's stream before
  * the norm kernel, after it, after the select kernel, after the streaming kernel
- * and after the emit kernel.  dgc_profile_collect waits for the recorded calls, returns how
+ * and after the emit kernel (in small sets the select kernel forms the norm as well: its time is all of the two then).  dgc_profile_collect waits for the recorded calls, returns how
  * many there were and the summed durations (milliseconds) of the four kernels, and starts a
  * new batch.  Enabling creates events (a runtime allocation); the hot path itself
  * allocates nothing.  Errors: INVALID_ARG, STATE (collect without enable), HIP.

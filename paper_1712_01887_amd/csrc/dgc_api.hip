@@ -41,6 +41,7 @@ struct dgc_handle {
   std::vector<MergeBlock> part_blocks;   // the same with one emit part per range (warm-up densities)
   bool layout_may_overflow = true;       // some region of the registered layout is smaller than its tensor
   double last_replace_share = 0.0;       // pairs per element that they let expect
+  int32_t norm_looks = kNormLooks;       // how often the selection looks for a share of the norm before it sums it itself
   int64_t last_replace_expected = 0;     // pairs per range the payloads of the last dgc_decompress_replace_regions call let expect
   WorkspaceLayout lay{};
   // what the bound workspace currently holds
@@ -130,6 +131,13 @@ constexpr double kScatterClearPairs = 2e6;
 // ... and this many tensors, over all of which every workgroup of the scattering launch walks (4 us per 1024):
 // 20000 tensors of 1500 elements, 2 % of eight workers, 106 against 123 us; 50000 of 100, 2 % of two, 184 against 149.
 constexpr int32_t kScatterClearTensors = 32768;
+// Clipping: the norm's sums by workgroups of the selection's own launch in sets of up to this many elements and tensors.
+// A launch fewer, but the workgroups that sum fill a compute unit each, and those of the tensors behind them start late or wait
+// long (calls in one launch and in two, in a graph, us: 100 K elements 15.1 and 16.4, 23 tensors of 0.27 M 17.6 and 18.9,
+// 1 M 16.7 and 17.4, 5 of 3 M 29.2 and 32.9, 200 of 1 M 21.9 and 22.3; 150 of 3 M 30.5 and 30.3, 30 of 7 M 43.4 and 42.8, 200 of 7 M
+// 45.7 and 41.8, 11 of 66 M 277 and 260).
+constexpr int64_t kNormInSelectElements = 4 << 20;
+constexpr int32_t kNormInSelectTensors = 64;
 constexpr double kStagedMinDensity = 0.005;  // compress: staged streaming pass above this density
 constexpr int kProfEvents = 5;
 inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
@@ -338,7 +346,8 @@ dgc_status sync_workspace(dgc_handle* h, void* ws, size_t ws_bytes, const int64_
   }
   if (!h->ws_static_valid) {
     workspace_claim(ws, h->id);
-    if (!hip_ok(launch_clear_words(at<uint32_t>(ws, h->lay.state), sizeof(DeviceState) / sizeof(uint32_t), stream),
+    // (the record, and the places of the norm's shares behind it, which every call leaves empty)
+    if (!hip_ok(launch_clear_words(at<uint32_t>(ws, h->lay.state), (h->lay.offsets - h->lay.state) / sizeof(uint32_t), stream),
                 "clear workspace state"))
       return DGC_ERR_HIP;
     if (!hip_ok(hipMemcpyAsync(at<char>(ws, h->lay.offsets), h->offsets.data(),
@@ -525,6 +534,11 @@ dgc_status dgc_create(dgc_handle** out, const dgc_config* cfg, int32_t num_tenso
   return DGC_OK;
 }
 
+// Test hook (not part of the interface): a selection that sums all the shares of the norm that it does not find at once.
+__attribute__((visibility("default"))) void dgc_test_set_norm_looks(dgc_handle* h, int32_t looks) {
+  if (h && looks >= 0) h->norm_looks = looks;
+}
+
 static void profile_release(dgc_handle* h);
 
 dgc_status dgc_destroy(dgc_handle* h) {
@@ -650,7 +664,8 @@ dgc_status dgc_compress(dgc_handle* h, const float* g, float* u, float* v, int32
 
   // paper: Appendix C equation 12 -- the local threshold is N^-1/2 times the global one.
   const double thr_local = clip ? (double)c.clip_threshold / std::sqrt((double)c.num_workers) : 0.0;
-  if (clip) {
+  const bool with_norm = clip && h->n <= kNormInSelectElements && h->num_tensors <= kNormInSelectTensors;
+  if (clip && !with_norm) {
     if (!hip_ok(launch_norm(g, h->n, at<double>(workspace, h->lay.partials), stream), "launch norm kernel"))
       return DGC_ERR_HIP;
   }
@@ -668,7 +683,9 @@ dgc_status dgc_compress(dgc_handle* h, const float* g, float* u, float* v, int32
   sa.tile_thr = at<float>(workspace, h->lay.tile_thr);
   sa.partials = at<double>(workspace, h->lay.partials);
   sa.thr_local = thr_local;
-  sa.num_partials = clip ? norm_blocks(h->n) : 0;
+  sa.num_partials = with_norm ? norm_shares(h->n) : clip ? norm_blocks(h->n) : 0;
+  sa.n = h->n;
+  sa.looks = h->norm_looks;
   sa.scale_override = c.scale_override;
   sa.momentum = c.momentum;
   sa.scale_const = scale_const;
@@ -688,7 +705,16 @@ dgc_status dgc_compress(dgc_handle* h, const float* g, float* u, float* v, int32
   sa.floor.in_pass = bands_in_pass ? 1 : 0;
   sa.floor.collected = out_counts;
   sa.floor.elements = h->band_elements;
-  if (!hip_ok(launch_select(sa, h->num_tensors, stream), "launch select kernel")) return DGC_ERR_HIP;
+  // The emit pass empties the places of the norm's shares again: a call that does not get so far leaves a workspace that
+  // has to be set up anew.
+  struct Unfinished {
+    dgc_handle* h;
+    bool armed;
+    ~Unfinished() {
+      if (armed) h->ws_static_valid = false;
+    }
+  } unfinished{h, with_norm};
+  if (!hip_ok(launch_select(sa, h->num_tensors, with_norm, stream), "launch select kernel")) return DGC_ERR_HIP;
   if (h->any_band && h->most_bands > 0 &&
       !hip_ok(launch_band(sa, at<EmitBlock>(workspace, h->lay.emit_blocks), (int32_t)h->emit_blocks.size(),
                           h->num_tensors, stream),
@@ -777,9 +803,12 @@ dgc_status dgc_compress(dgc_handle* h, const float* g, float* u, float* v, int32
   ea.stage_v = ta.stage_v;
   ea.stage_u = ta.stage_u;
   ea.slotted = ta.slotted;
+  ea.norm_shares = at<unsigned long long>(workspace, h->lay.partials);
+  ea.shares = with_norm ? sa.num_partials : 0;
   ea.settled = slotted && (c.refine_alpha > 0.0f || bands_in_pass) ? sa.thr : nullptr;
   if (!hip_ok(launch_emit(ea, (int32_t)h->emit_blocks.size(), stream), "launch emit kernel"))
     return DGC_ERR_HIP;
+  unfinished.armed = false;
   if (ev && !hip_ok(hipEventRecord(ev[4], stream), "record event")) return DGC_ERR_HIP;
   return DGC_OK;
 }

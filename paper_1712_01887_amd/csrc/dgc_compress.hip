@@ -52,7 +52,7 @@ __global__ __launch_bounds__(256) void clear_words_kernel(uint32_t* __restrict__
 // so that the result does not depend on scheduling and no workgroup has to wait for
 // another: a version in which the last workgroup to arrive finished the sum needed two
 // chained device-scope atomics per workgroup and ran 6 us longer (52 against 46 us on
-// 66 M elements).
+// 66 M elements).  (Small sets have no launch for it: see select_kernel.)
 __global__ __launch_bounds__(kNormThreads) void norm_kernel(const float* __restrict__ g, int64_t n,
                                                             double* __restrict__ partials) {
   __shared__ double red[kNormThreads / 64];
@@ -157,7 +157,8 @@ struct Candidates {
 // thread gathers its own once and keeps them); a larger candidate set (exact
 // selection on a big tensor) is re-evaluated from g, u, v in every pass.
 struct SelectShared {
-  double red[kSelectThreads / 64];
+  alignas(16) double red[kSelectThreads / 64];
+  unsigned long long missing[kSelectThreads / 64];
   float scale;
   uint32_t hist[kSelectBins];
   uint32_t wave_tot[kSelectThreads / 64];
@@ -503,11 +504,54 @@ __device__ __forceinline__ BandState* band_state(const SelectArgs& a, const Tens
 }
 __device__ __forceinline__ int64_t band_list_begin(int64_t offset) { return 3 * (offset >> kBandListShift); }
 
+// Sum of squares of share `c` of `shares` of g by a workgroup of select_kernel's size; every thread returns it.
+__device__ __forceinline__ double norm_share(const float* __restrict__ g, int64_t n, int c, int shares, SelectShared& sh, int tid) {
+  constexpr int kInFlight = 4;
+  const int64_t nvec = n >> 2;
+  const float4* __restrict__ g4 = reinterpret_cast<const float4*>(g);
+  const int64_t stride = (int64_t)shares * kSelectThreads;
+  double a[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int64_t i = (int64_t)c * kSelectThreads + tid; i < nvec; i += kInFlight * stride) {
+    float4 x[kInFlight];
+#pragma unroll
+    for (int q = 0; q < kInFlight; ++q) {
+      const int64_t at = i + q * stride;
+      x[q] = at < nvec ? g4[at] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    }
+#pragma unroll
+    for (int q = 0; q < kInFlight; ++q) {
+      a[0] += (double)x[q].x * (double)x[q].x;
+      a[1] += (double)x[q].y * (double)x[q].y;
+      a[2] += (double)x[q].z * (double)x[q].z;
+      a[3] += (double)x[q].w * (double)x[q].w;
+    }
+  }
+  if (c == 0 && tid < (int)(n & 3)) {
+    const double x = (double)g[(nvec << 2) + tid];
+    a[0] += x * x;
+  }
+  const double s = wave_sum_down((a[0] + a[1]) + (a[2] + a[3]));
+  __syncthreads();  // (`red` may be in use)
+  if ((tid & 63) == 0) sh.red[tid >> 6] = s;
+  __syncthreads();
+  double total = 0.0;
+#pragma unroll
+  for (int w = 0; w < kSelectThreads / 64; ++w) total += sh.red[w];
+  return total;
+}
+
+// A share's place holds zero until its sum is there, which is stored with the sign turned: a sum of nothing is -0.
+__device__ __forceinline__ unsigned long long share_word(double sum) { return (unsigned long long)__double_as_longlong(-sum); }
+
 // Clipping scale (paper: Appendix C equation 12).  With clipping on, the norm kernel has left its partial
 // sums, of which `part` is this thread's (thread t has partial t, or zero); every workgroup adds them in the
 // same fixed order (lanes, then wavefronts, in order), so all of them get the same bits, and the first one
 // also files the result for the streaming pass and for the diagnostics.
+// FUSED: other workgroups of this launch form the partial sums.  A workgroup looks for them for a while (they are there by
+// the time the candidates are, in a set that this is done for); what is missing then, because those workgroups
+// have found no place on the device, say, it forms itself.  So nothing here waits without an end, whatever else runs.
 static_assert(kNormMaxBlocks <= kSelectThreads, "a partial sum per thread");
+template <bool FUSED>
 __device__ __forceinline__ float settle_scale(const SelectArgs& a, SelectShared& sh, double part, int j, int tid) {
   if (!a.scale_from_state) {
     if (tid == 0 && j == 0) {  // no clipping: start a clean record
@@ -517,11 +561,43 @@ __device__ __forceinline__ float settle_scale(const SelectArgs& a, SelectShared&
     }
     return a.scale_const;
   }
+  if (FUSED) {
+    unsigned long long word = ~0ull;
+    if (tid < a.num_partials) {
+      word = 0;
+      for (int look = 0; look < a.looks; ++look) {
+        word = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(a.partials) + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (word != 0) break;
+        __builtin_amdgcn_s_sleep(1);
+      }
+      part = -__longlong_as_double((long long)word);
+    }
+    const unsigned long long lacking = __ballot(word == 0);
+    if ((tid & 63) == 0) sh.missing[tid >> 6] = lacking;
+  }
   const double s = wave_sum_down(part);
   if ((tid & 63) == 0) sh.red[tid >> 6] = s;
   __syncthreads();
+  if (FUSED) {
+    unsigned long long any = 0;
+#pragma unroll
+    for (int w = 0; w < kSelectThreads / 64; ++w) any |= sh.missing[w];
+    if (__builtin_amdgcn_readfirstlane((int)(any != 0)) != 0) {  // the same in every wavefront
+      for (int c = 0; c < a.num_partials; ++c) {
+        if ((sh.missing[c >> 6] >> (c & 63)) & 1u) {
+          const double sum = norm_share(a.g, a.n, c, a.num_partials, sh, tid);
+          if (tid == c) part = sum;
+        }
+      }
+      const double again = wave_sum_down(part);
+      __syncthreads();
+      if ((tid & 63) == 0) sh.red[tid >> 6] = again;
+      __syncthreads();
+    }
+  }
   if (tid == 0) {
     double total = 0.0;
+#pragma unroll
     for (int w = 0; w < kSelectThreads / 64; ++w) total += sh.red[w];
     const double norm = sqrt(total);
     float sc = 1.0f;
@@ -546,21 +622,29 @@ __device__ __forceinline__ float settle_scale(const SelectArgs& a, SelectShared&
 // 8.0 -> 6.6 us with the list's length asked for once per wavefront and not per key, four threads to a listed key, no
 // walk over empty slots, and the scale's sum over the lanes inside the vector unit; the step of that set 27.5 ->
 // 26.3, of the 23 tensors 33.9 -> 31.9.
+// FUSED: the norm's partial sums are formed by the first workgroups of the launch, while the others gather (rule and
+// figures at kNormInSelectElements; steps with clipping: 23 tensors of 0.27 M elements 31.7 -> 30.1 us, 1 M 26.0 -> 24.4).
 // MODE: whether some tensors are ranked by way of a band (TensorPlan.exact == 2), and whether its floor may go into the pass.
 enum SelectMode : int { kSelectNoBands = 0, kSelectLists = 1, kSelectInPass = 2 };
 
-template <bool NESTEROV, int MODE>
+template <bool NESTEROV, int MODE, bool FUSED>
 __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectArgs a) {
   __shared__ SelectShared sh;
   const int tid = threadIdx.x;
-  const int j = blockIdx.x;
+  if (FUSED && (int)blockIdx.x < a.num_partials) {  // the first workgroups form the partial sums of the norm
+    const double sum = norm_share(a.g, a.n, blockIdx.x, a.num_partials, sh, tid);
+    if (tid == 0)
+      __hip_atomic_store(reinterpret_cast<unsigned long long*>(a.partials) + blockIdx.x, share_word(sum), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return;
+  }
+  const int j = FUSED ? (int)blockIdx.x - a.num_partials : (int)blockIdx.x;
   const TensorPlan plan = a.plans[j];
   // Asked for before the candidates and used after their first loads are on their way, so that the scale's
   // chain of steps (sum over the lanes, over the wavefronts, square root) runs while those are outstanding.
-  const double part = a.scale_from_state && tid < a.num_partials ? a.partials[tid] : 0.0;
+  const double part = !FUSED && a.scale_from_state && tid < a.num_partials ? a.partials[tid] : 0.0;
 
   if (plan.rank >= plan.count) {  // the strict comparison then passes everything
-    settle_scale(a, sh, part, j, tid);
+    settle_scale<FUSED>(a, sh, part, j, tid);
     write_threshold(a, j, plan, -1.0f, tid);
     return;
   }
@@ -614,7 +698,7 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectArgs a) {
             uu[q] = *reinterpret_cast<const vec4u*>(c.u + e);
             vv[q] = *reinterpret_cast<const vec4u*>(c.v + e);
           }
-          if (r == 0) c.scale = settle_scale(a, sh, part, j, tid);
+          if (r == 0) c.scale = settle_scale<FUSED>(a, sh, part, j, tid);
 #pragma unroll
           for (int q = 0; q < kQuadsInFlight; ++q) {
             const bool ok = tid + (r * kQuadsInFlight + q) * kSelectThreads < quads;
@@ -641,7 +725,7 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectArgs a) {
             uu[q] = c.u[e];
             vv[q] = c.v[e];
           }
-          if (r == 0) c.scale = settle_scale(a, sh, part, j, tid);
+          if (r == 0) c.scale = settle_scale<FUSED>(a, sh, part, j, tid);
 #pragma unroll
           for (int q = 0; q < kSelectInFlight; ++q) {
             const bool ok = tid + (r * kSelectInFlight + q) * kSelectThreads < count;
@@ -694,7 +778,7 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectArgs a) {
     }
     thr_bits = rank_registers(sh, key, count, holders, live, rank, tid);
   } else {
-    c.scale = settle_scale(a, sh, part, j, tid);
+    c.scale = settle_scale<FUSED>(a, sh, part, j, tid);
     thr_bits = rank_reevaluated(sh, c, count, rank, tid);
   }
   write_threshold(a, j, plan, __uint_as_float(thr_bits), tid);
@@ -1935,6 +2019,12 @@ __global__ __launch_bounds__(kRefineThreads) void refine_kernel(RefineArgs a) {
 // receive side can find a range of elements in a region by search only if the parts are
 // in order.)
 
+// The places of the norm's shares for the next call (see share_word): nothing behind the selection reads them.
+template <int THREADS>
+__device__ __forceinline__ void clear_shares(const EmitArgs& a, int tid) {
+  for (int c = tid; c < a.shares; c += THREADS) a.norm_shares[c] = 0;
+}
+
 // This lane's mask word of tile t with the bits outside tensor [lo, hi) removed.
 __device__ __forceinline__ uint32_t tensor_tile_word(const uint16_t* __restrict__ mask, int64_t t, int lane,
                                                      int64_t lo, int64_t hi) {
@@ -2054,6 +2144,7 @@ __global__ __launch_bounds__(kEmitThreads) void emit_ordered_kernel(EmitArgs a) 
     base += sh.pre_tot[w];
   }
   if (tid == 0 && (int)((first - t0) / kEmitTiles) == blk.tensor_blocks - 1) a.out_counts[j] = base + total;
+  if (blockIdx.x == 0) clear_shares<kEmitThreads>(a, tid);
   if (total == 0) return;
   int pos = before + incl - cnt;  // slot of the thread's next element
   sh.start[tid] = pos;
@@ -2225,6 +2316,7 @@ __global__ __launch_bounds__(kEmitSlotThreads) void emit_slots_kernel(EmitArgs a
   const int total = __builtin_amdgcn_readlane(incl, kEmitTiles - 1);
   if (tid == 0 && (int)((first - t0) / kEmitTiles) == blk.tensor_blocks - 1) a.out_counts[j] = base + total;
   if (a.settled && blockIdx.x == 0 && tid == 0) a.state->crowded = 0;  // (nothing behind reads it)
+  if (blockIdx.x == 0) clear_shares<kEmitSlotThreads>(a, tid);
   if (total == 0 && !a.settled) return;
   const int excl = incl - own;
   int32_t* __restrict__ out_idx = a.out_idx + region;
@@ -2404,12 +2496,28 @@ hipError_t launch_norm(const float* g, int64_t n, double* partials, hipStream_t 
   return hipGetLastError();
 }
 
-hipError_t launch_select(const SelectArgs& a, int32_t num_tensors, hipStream_t stream) {
-  const dim3 grid((unsigned)num_tensors), block(kSelectThreads);
-  const auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, stream, a); };
-  const int mode = a.floor.in_pass ? kSelectInPass : a.bands ? kSelectLists : kSelectNoBands;
-  if (a.nesterov) launch(mode == kSelectInPass ? select_kernel<true, kSelectInPass> : mode == kSelectLists ? select_kernel<true, kSelectLists> : select_kernel<true, kSelectNoBands>);
-  else launch(mode == kSelectInPass ? select_kernel<false, kSelectInPass> : mode == kSelectLists ? select_kernel<false, kSelectLists> : select_kernel<false, kSelectNoBands>);
+int32_t norm_shares(int64_t n) {
+  const int64_t shares = ceil_div(n >> 2, (int64_t)kSelectThreads * 4);
+  return (int32_t)(shares < 1 ? 1 : shares > kNormMaxShares ? kNormMaxShares : shares);
+}
+
+template <bool NESTEROV, bool FUSED>
+static void launch_select_mode(const SelectArgs& a, dim3 grid, hipStream_t stream) {
+  const auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(kSelectThreads), 0, stream, a); };
+  if (a.floor.in_pass) launch(select_kernel<NESTEROV, kSelectInPass, FUSED>);
+  else if (a.bands) launch(select_kernel<NESTEROV, kSelectLists, FUSED>);
+  else launch(select_kernel<NESTEROV, kSelectNoBands, FUSED>);
+}
+
+hipError_t launch_select(const SelectArgs& a, int32_t num_tensors, bool with_norm, hipStream_t stream) {
+  const dim3 grid((unsigned)(num_tensors + (with_norm ? a.num_partials : 0)));
+  if (a.nesterov) {
+    if (with_norm) launch_select_mode<true, true>(a, grid, stream);
+    else launch_select_mode<true, false>(a, grid, stream);
+  } else {
+    if (with_norm) launch_select_mode<false, true>(a, grid, stream);
+    else launch_select_mode<false, false>(a, grid, stream);
+  }
   return hipGetLastError();
 }
 

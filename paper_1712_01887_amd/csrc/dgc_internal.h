@@ -204,6 +204,10 @@ struct BandState {  // one per tensor, in a line of its own, because atomics on 
 // Clipping norm: a fixed number of partial sums keeps the result reproducible.
 constexpr int kNormThreads = 256;
 constexpr int kNormMaxBlocks = 512;
+// The same by workgroups of the selection's launch: shares at most, and how often a workgroup looks for one (a look
+// takes about half a microsecond; what is still missing then it sums itself).
+constexpr int kNormMaxShares = 128;
+constexpr int kNormLooks = 4096;
 
 constexpr int kMaxPayloads = 64;
 constexpr size_t kBandStride = 512;
@@ -258,7 +262,9 @@ struct SelectArgs {
   float* out_thr;       // may be null
   float* tile_thr;      // device, one word per wave tile: the threshold of every tile that lies
                         // wholly inside one tensor; the others hold a NaN put there once by the host
-  const double* partials;  // partial sums of the squared norm (clipping on)
+  double* partials;        // partial sums of the squared norm (clipping on)
+  int64_t n;               // elements of g
+  int32_t looks;           // norm and selection in one launch: how often a workgroup looks for a partial sum
   double thr_local;        // thr_G / sqrt(N)
   int32_t num_partials;
   float scale_override;    // NaN: unused
@@ -344,6 +350,8 @@ struct EmitArgs {
   const float* stage_u;
   int32_t slotted;             // as in StreamArgs
   const float* settled;        // device, T: the thresholds, where refine_kernel has run on records; else null
+  unsigned long long* norm_shares;  // device: cleared for the next call
+  int32_t shares;                   // 0: the norm had a launch of its own, or there was none
 };
 
 struct MergeBlock {
@@ -418,7 +426,8 @@ enum ScatterMode : int32_t {
 hipError_t launch_clear_words(uint32_t* p, size_t words, hipStream_t stream);  // p[0 .. words) <- 0
 int32_t norm_blocks(int64_t n);  // partial sums launch_norm leaves
 hipError_t launch_norm(const float* g, int64_t n, double* partials, hipStream_t stream);
-hipError_t launch_select(const SelectArgs& a, int32_t num_tensors, hipStream_t stream);
+int32_t norm_shares(int64_t n);  // partial sums of launch_select with the norm
+hipError_t launch_select(const SelectArgs& a, int32_t num_tensors, bool with_norm, hipStream_t stream);
 hipError_t launch_band(const SelectArgs& a, const EmitBlock* blocks, int32_t num_blocks, int32_t num_tensors,
                        hipStream_t stream);
 hipError_t launch_stream(const StreamArgs& a, hipStream_t stream);
