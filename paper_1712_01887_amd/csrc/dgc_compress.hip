@@ -176,7 +176,7 @@ __device__ __forceinline__ void find_bin(const uint32_t* hist, uint32_t* wave_to
                                          uint32_t& members) {
   constexpr int PER = kSelectBins / THREADS;  // consecutive bins owned by a thread
   const int lane = tid & 63;
-  const int wave = tid >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   uint32_t h[PER];
   uint32_t local = 0;
 #pragma unroll
@@ -184,15 +184,15 @@ __device__ __forceinline__ void find_bin(const uint32_t* hist, uint32_t* wave_to
     h[i] = hist[PER * tid + i];
     local += h[i];
   }
-  uint32_t incl = local;  // suffix sum: this thread's bins and everything above
-  for (int d = 1; d < 64; d <<= 1) {
-    const uint32_t t = __shfl_down(incl, d);
-    if (lane + d < 64) incl += t;
-  }
-  if (lane == 0) wave_tot[wave] = incl;
+  const uint32_t incl = wave_inclusive_sum(local);
+  if (lane == 63) wave_tot[wave] = incl;
   __syncthreads();
-  uint32_t run = incl - local;  // candidates above this thread's bins
-  for (int w = wave + 1; w < THREADS / 64; ++w) run += wave_tot[w];
+  uint32_t run = wave_last(incl) - incl;  // candidates above this thread's bins: in its wavefront, and in those behind
+#pragma unroll
+  for (int w = 0; w < THREADS / 64; ++w) {  // (all asked for together)
+    const uint32_t t = wave_tot[w];
+    run += w > wave ? t : 0u;
+  }
 #pragma unroll
   for (int i = PER - 1; i >= 0; --i) {
     if (run <= rank && rank < run + h[i]) {
@@ -1404,24 +1404,25 @@ __device__ __forceinline__ int tile_counts_partial(const uint32_t* __restrict__ 
 // 161-tensor set and 34 us on the 122 M-element set for what the per-tile counts already say.)
 // EXACT SELECTION at densities up to kBandInPassDensity comes here, too: select_kernel has named a floor that lies below
 // the exact threshold almost surely, the pass took what exceeds it, and every such tensor is ranked here.  The streaming
-// pass is then the only one over g, u, v: 161 tensors of 25.6 M elements, 0.1 %, call 175 -> 146 us where bands were
+// pass is then the only one over g, u, v: 161 tensors of 25.6 M elements, 0.1 %, call 175 -> 139 us where bands were
 // collected by another pass.  (Tensors whose sample does not bear the floor out still are: with large values in rows of
 // every second large tensor, placed anew every third call, the median of the calls is 195 us and the worst 220, where bands
 // alone take 187 and 1467; with such rows in one tensor of fifty 158, against 178.)
-// A workgroup lists up to kRefineList selected elements in LDS (index and key) and ranks them by one
-// histogram; the over-selection of a big tensor goes to the payload region, which is free until the emit
+// After a slotted pass over a tensor of up to 4096 tiles the keys of the records stay in registers, from the one read of the
+// lines to the lowered counts; what mask words say, and the elements of larger tensors or of other passes, up to
+// kRefineList of them, is listed in LDS.  One histogram and a direct ranking settle the threshold; the over-selection of a big
+// tensor goes to the payload region, which is free until the emit
 // pass, and through three histogram passes.  Bound by latency, a chain of dependent steps in the dozen
-// workgroups that go on: 14 us on the 161-tensor set (16 with one addition to the list's length per tile and with
-// what is dropped put back from here; 23 with the list always in the payload region).  The lists
+// workgroups that go on: 11 us on the 161-tensor set (14.4 with the records' elements listed in LDS and read again for the
+// counts, two look-ups of every line, and a prefix over the bins through LDS; 23 with the list always in the payload region),
+// and with exact selection there, where every large tensor goes on, 14.5 (21.5).  The lists
 // (and 16 wavefronts of more than 64 registers) leave one workgroup per compute unit; 20000 tensors, most of which
 // only add up their counts, take 133 us as they did without the lists.
 struct RefineShared {
   SelectShared s;
   uint32_t list[kRefineList];
   uint32_t keys[kRefineList];
-  int red[kRefineThreads / 64];
-  int go;
-  uint32_t passed;
+  alignas(16) int red[kRefineThreads / 64];
   uint32_t listed;
 };
 static_assert(kRefineThreads == kSelectThreads, "the ranking is shared with select_kernel");
@@ -1468,31 +1469,69 @@ __global__ __launch_bounds__(kRefineThreads) void refine_kernel(RefineArgs a) {
   // shares with a neighbour (or that is the ragged end of the set), recounted from the mask words.
   const bool shared0 = t0 * kWaveTile < lo || (t0 == t1 && (t1 + 1) * kWaveTile > hi);
   const bool shared1 = t1 != t0 && (t1 + 1) * kWaveTile > hi;
-  int cnt = tile_counts_partial<kRefineThreads>(a.tile_count, shared0 ? t0 + 1 : t0, shared1 ? t1 : t1 + 1, tid);
+  // After a slotted pass over up to kRefineHeld / 2 tiles per thread the counts stay in registers, and the keys of the records
+  // will, which are asked for before the counts are there where they are wanted in any case.  Two neighbouring threads share a
+  // tile, half a record's keys each: a line is looked up once for both.
+  constexpr int kHalf = kSlotsPerTile / 2;
+  const int half = tid & 1;
+  auto tile_of = [&](int k) { return t0 + ((k * kRefineThreads + tid) >> 1); };
+  const int groups = (int)((2 * (t1 - t0) + 1) / kRefineThreads) + 1;  // of items to a thread that are in use
+  const bool held = a.slotted && groups <= kRefineHeld;
+  uint32_t held_count[kRefineHeld];     // elements in a record
+  bool held_words[kRefineHeld];         // the tile has mask words, and the thread looks after them
+  int4 held_keys[kRefineHeld];
+  auto load_keys = [&](int k) {
+    const int64_t tile = tile_of(k);
+    held_keys[k] = reinterpret_cast<const int4*>(a.mask)[(tile <= t1 ? tile : t1) * (kSlotRecord / 4) + kSlotsPerTile / 4 + half];
+  };
+  int cnt = 0;
+  if (held) {
+    uint32_t c[kRefineHeld];
+#pragma unroll
+    for (int k = 0; k < kRefineHeld; ++k) {
+      c[k] = 0;
+      held_keys[k] = make_int4(0, 0, 0, 0);
+      if (k >= groups) continue;  // uniform
+      const int64_t tile = tile_of(k);
+      c[k] = a.tile_count[tile <= t1 ? tile : t1];
+    }
+    if (banded) {
+#pragma unroll
+      for (int k = 0; k < kRefineHeld; ++k)
+        if (k < groups) load_keys(k);  // uniform
+    }
+#pragma unroll
+    for (int k = 0; k < kRefineHeld; ++k) {
+      const int64_t tile = tile_of(k);
+      const bool whole = tile <= t1 && tile * kWaveTile >= lo && (tile + 1) * kWaveTile <= hi;
+      held_words[k] = half == 0 && tile <= t1 && (!whole || c[k] > (uint32_t)kSlotsPerTile);
+      held_count[k] = whole && c[k] <= (uint32_t)kSlotsPerTile ? c[k] : 0u;
+      if (whole && half == 0) cnt += (int)(c[k] & kTileCountMask);
+    }
+  } else {
+    cnt = tile_counts_partial<kRefineThreads>(a.tile_count, shared0 ? t0 + 1 : t0, shared1 ? t1 : t1 + 1, tid);
+  }
   {
     int64_t tile;
     int l;
     if (shared0 && wave == 0) cnt += __popc(tensor_mask_word(a.mask, t0, lane, lo, hi, tile, l));
     if (shared1 && wave == 1) cnt += __popc(tensor_mask_word(a.mask, t0, (t1 - t0) * 64 + lane, lo, hi, tile, l));
   }
-  for (int d = 32; d >= 1; d >>= 1) cnt += __shfl_down(cnt, d);
+  cnt = (int)wave_sum((uint32_t)cnt);
   if (lane == 0) sh.red[wave] = cnt;
+  if (tid == 0) sh.listed = 0;
   __syncthreads();
-  if (tid == 0) {
-    int total = 0;
-    for (int w = 0; w < kWaves; ++w) total += sh.red[w];
-    sh.passed = (uint32_t)total;
-    sh.go = banded || (uint32_t)total > (uint32_t)plan.refine_limit;
-  }
-  __syncthreads();
-  if (!sh.go) return;
+  int total = 0;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) total += sh.red[w];
+  if (!banded && (uint32_t)total <= (uint32_t)plan.refine_limit) return;
 
   // ---- exact threshold among the selected elements of tensor j (rare) ---------------
   // After a slotted streaming pass a tile that lies wholly inside the tensor and selected 1 to
   // kSlotsPerTile elements holds a record in place of its mask words (indices, v', u'), and u and
   // v are masked there already; every other tile has mask words and u', v' as they were.
   const int64_t words = (t1 - t0 + 1) * 64;
-  const int64_t passed = sh.passed;
+  const int64_t passed = total;
   uint32_t prefix = 0;
   uint32_t rank = (uint32_t)plan.k;
   int consumed = 0;
@@ -1532,8 +1571,6 @@ __global__ __launch_bounds__(kRefineThreads) void refine_kernel(RefineArgs a) {
     constexpr int kPer = 32;
     const uint32_t floor_key = __float_as_uint(floor);
     const uint32_t enough = rank - (uint32_t)passed + 1u;
-    if (tid == 0) sh.listed = 0;
-    __syncthreads();
 #pragma unroll 1
     for (int64_t first = lo; missed && first < hi; first += kPer * kRefineThreads) {
       uint32_t key[kPer];
@@ -1552,7 +1589,11 @@ __global__ __launch_bounds__(kRefineThreads) void refine_kernel(RefineArgs a) {
       missed = sh.listed < enough;
       __syncthreads();
     }
-    if (!missed) prefix = floor_key;
+    if (!missed) {
+      prefix = floor_key;
+      if (tid == 0) sh.listed = 0;
+      __syncthreads();
+    }
   }
   if (missed) {
     // The floor lies above the threshold (the sample missed): everything goes back to u and v, the whole tensor is
@@ -1629,19 +1670,120 @@ __global__ __launch_bounds__(kRefineThreads) void refine_kernel(RefineArgs a) {
     return;
   }
 
+  auto list_words = [&](int64_t tile, int l, uint32_t w) {  // a lane's mask word, this tensor's bits only
+    int pos = (int)atomicAdd(&sh.listed, (uint32_t)__popc(w));
+    while (w) {
+      const int q = __ffs(w) - 1;
+      w &= w - 1;
+      sh.list[pos++] = (uint32_t)tile_element(tile, l, q);
+    }
+  };
+  // One histogram over the four octaves above the sampled threshold, where the wanted rank nearly always
+  // is (the last bin takes everything beyond), and direct ranking of its bin; if that does not fit, the
+  // passes over the key's bits.  `sh.s.hist` and `sh.s.surv_n` are zero.
+  // `in_use(q)`, uniform: some thread may have a key in slot q.
+  auto settle = [&](const auto& key, auto in_use) {
+    constexpr int kKeys = sizeof(key) / sizeof(uint32_t);
+    constexpr int kShift = 14;
+    const uint32_t low = floor >= 0.0f ? __float_as_uint(floor) : 0u;  // -1: everything was let through
+#pragma unroll
+    for (int q = 0; q < kKeys; ++q) {
+      if (!in_use(q)) continue;
+      const uint32_t b = (key[q] - low) >> kShift;
+      if (key[q] != kNoKey) atomicAdd(&sh.s.hist[b < (uint32_t)kSelectBins ? b : (uint32_t)kSelectBins - 1u], 1u);
+    }
+    __syncthreads();
+    uint32_t bin, above, members;
+    find_bin<kRefineThreads>(sh.s.hist, sh.s.wave_tot, sh.s.sel, tid, rank, bin, above, members);
+    if (members <= (uint32_t)kSelectDirect) {
+      if (tid < 4) sh.s.surv[(members & ~3u) + tid] = 0;
+      __syncthreads();
+      const uint32_t first = low + (bin << kShift);  // the bin's keys: this one, and `span` behind it
+      const uint32_t span = bin < (uint32_t)kSelectBins - 1u ? (1u << kShift) - 1u : kNoKey - 1u - first;
+#pragma unroll
+      for (int q = 0; q < kKeys; ++q)
+        if (in_use(q) && key[q] - first <= span) sh.s.surv[atomicAdd(&sh.s.surv_n, 1u)] = key[q];
+      __syncthreads();
+      return rank_directly(sh.s, tid, members, rank - above);
+    }
+    __syncthreads();
+    return select_in_registers<kKeys>(sh.s, key, 0u, rank, tid);
+  };
+  auto clear_bins = [&]() {
+    for (int b = tid; b < kSelectBins; b += kRefineThreads) sh.s.hist[b] = 0;
+    if (tid == 0) sh.s.surv_n = 0;
+  };
+
+  if (held && passed <= kRefineList) {
+    // The keys of the records in registers, where they stay until the tiles' counts are lowered; what mask words say, which
+    // is little as a rule, is listed.
+    constexpr int kRecordKeys = kRefineHeld * kHalf;
+    constexpr int kWordKeys = 4;
+    clear_bins();
+#pragma unroll
+    for (int k = 0; k < kRefineHeld; ++k) {
+      if (k >= groups) continue;  // uniform
+      if (!banded) load_keys(k);
+      for (unsigned long long m = __ballot(held_words[k]); m; m &= m - 1) {
+        const int64_t wi = (((int64_t)k * kRefineThreads + wave * 64 + (__ffsll((long long)m) - 1)) >> 1) * 64 + lane;
+        int64_t tile;
+        int l;
+        const uint32_t w = tensor_mask_word(a.mask, t0, wi, lo, hi, tile, l);
+        if (w) list_words(tile, l, w);
+      }
+    }
+    __syncthreads();
+    const uint32_t listed = sh.listed;
+    if (listed <= (uint32_t)(kWordKeys * kRefineThreads)) {
+      uint32_t key[kRecordKeys + kWordKeys];
+      uint32_t from[kWordKeys];
+#pragma unroll
+      for (int q = 0; q < kWordKeys; ++q) {
+        const uint32_t p = (uint32_t)(tid + q * kRefineThreads);
+        from[q] = p < listed ? sh.list[p] : 0u;
+        key[kRecordKeys + q] = kNoKey;
+        if (p < listed) key[kRecordKeys + q] = __float_as_uint(a.v[from[q]]) & 0x7FFFFFFFu;
+      }
+#pragma unroll
+      for (int k = 0; k < kRefineHeld; ++k) {
+        const int32_t x[kHalf] = {held_keys[k].x, held_keys[k].y, held_keys[k].z, held_keys[k].w};
+#pragma unroll
+        for (int q = 0; q < kHalf; ++q)
+          key[k * kHalf + q] = (uint32_t)(half * kHalf + q) < held_count[k] ? (uint32_t)x[q] & 0x7FFFFFFFu : kNoKey;
+      }
+      auto in_use = [&](int q) {
+        return q < kRecordKeys ? q / kHalf < groups : (q - kRecordKeys) * kRefineThreads < (int)listed;
+      };
+      if (passed > (int64_t)rank) prefix = settle(key, in_use);  // (else: see below)
+#pragma unroll
+      for (int q = 0; q < kWordKeys; ++q) {
+        const bool drop = (uint32_t)(tid + q * kRefineThreads) < listed && !sent(key[kRecordKeys + q], prefix);
+        if (q * kRefineThreads < (int)listed) drop_bit(drop, from[q]);  // uniform
+      }
+#pragma unroll
+      for (int k = 0; k < kRefineHeld; ++k) {
+        if (k >= groups) break;  // uniform
+        uint32_t kept = 0;
+#pragma unroll
+        for (int q = 0; q < kHalf; ++q) kept += sent(key[k * kHalf + q], prefix) ? 1u : 0u;
+        kept += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)kept, 0xB1, 0xf, 0xf, false);  // the neighbour's
+        if (half == 0 && kept != held_count[k]) a.tile_count[tile_of(k)] = kept | (held_count[k] << kTileCountHeldShift);
+      }
+      if (tid == 0) {
+        const float thr = __uint_as_float(prefix);
+        a.thr[j] = thr;
+        if (a.out_thr) a.out_thr[j] = thr;
+      }
+      return;
+    }
+    __syncthreads();  // (the list's length is read before it is formed anew)
+  }
+
   if (passed <= kRefineList) {
     // From the records: one thread per tile, the counts of four tiles and then their records in flight
     // together; from the mask words of the other tiles: by the wavefront whose lanes met them.
     if (tid == 0) sh.listed = 0;
     __syncthreads();
-    auto list_words = [&](int64_t tile, int l, uint32_t w) {  // a lane's mask word, this tensor's bits only
-      int pos = (int)atomicAdd(&sh.listed, (uint32_t)__popc(w));
-      while (w) {
-        const int q = __ffs(w) - 1;
-        w &= w - 1;
-        sh.list[pos++] = (uint32_t)tile_element(tile, l, q);
-      }
-    };
     if (a.slotted) {
       constexpr int kTilesInFlight = 4;
 #pragma unroll 1
@@ -1743,8 +1885,7 @@ __global__ __launch_bounds__(kRefineThreads) void refine_kernel(RefineArgs a) {
         }
       }
     }
-    for (int b = tid; b < kSelectBins; b += kRefineThreads) sh.s.hist[b] = 0;
-    if (tid == 0) sh.s.surv_n = 0;
+    clear_bins();
     __syncthreads();
     const int count = (int)passed;
     uint32_t key[kRefinePer];
@@ -1757,35 +1898,8 @@ __global__ __launch_bounds__(kRefineThreads) void refine_kernel(RefineArgs a) {
         key[q] = (e & kFromRecord) ? sh.keys[p] : (__float_as_uint(a.v[e]) & 0x7FFFFFFFu);
       }
     }
-    if (passed > (int64_t)rank) {
-      // One histogram over the four octaves above the sampled threshold, where the wanted rank nearly always
-      // is (the last bin takes everything beyond), and direct ranking of its bin; if that does not fit, the
-      // passes over the key's bits.
-      constexpr int kShift = 14;
-      const uint32_t low = floor >= 0.0f ? __float_as_uint(floor) : 0u;  // -1: everything was let through
-      auto bin_of = [&](uint32_t k) {
-        const uint32_t b = (k - low) >> kShift;
-        return b < (uint32_t)kSelectBins ? b : (uint32_t)kSelectBins - 1u;
-      };
-#pragma unroll
-      for (int q = 0; q < kRefinePer; ++q)
-        if (key[q] != kNoKey) atomicAdd(&sh.s.hist[bin_of(key[q])], 1u);
-      __syncthreads();
-      uint32_t bin, above, members;
-      find_bin<kRefineThreads>(sh.s.hist, sh.s.wave_tot, sh.s.sel, tid, rank, bin, above, members);
-      if (members <= (uint32_t)kSelectDirect) {
-        if (tid < 4) sh.s.surv[(members & ~3u) + tid] = 0;
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < kRefinePer; ++q)
-          if (key[q] != kNoKey && bin_of(key[q]) == bin) sh.s.surv[atomicAdd(&sh.s.surv_n, 1u)] = key[q];
-        __syncthreads();
-        prefix = rank_directly(sh.s, tid, members, rank - above);
-      } else {
-        __syncthreads();
-        prefix = select_in_registers<kRefinePer>(sh.s, key, 0u, rank, tid);
-      }
-    }  // (else the floor is the threshold: settled above, or zero, with fewer elements than wanted anything else)
+    if (passed > (int64_t)rank) prefix = settle(key, [](int) { return true; });
+    // (else the floor is the threshold: settled above, or zero, with fewer elements than wanted anything else)
     // Clear the mask bit of every selected element that does not exceed the new threshold.
     // A 16-bit mask word of a tile shared with a neighbour tensor also holds that tensor's
     // bits, and its re-threshold may run at the same time: atomic AND on the 32-bit word.

@@ -65,6 +65,7 @@ constexpr int kEmitSlotThreads = 128;  // emit pass over records: two slots per 
 static_assert(kEmitTiles * kSlotsPerTile == 2 * kEmitSlotThreads, "two slots of the workgroup's tiles per emit thread");
 constexpr int kRefineThreads = 1024;                  // the re-threshold pass: one workgroup per tensor
 constexpr int kRefinePer = 12;
+constexpr int kRefineHeld = 8;   // halves of tiles' records whose keys a thread keeps in registers
 constexpr int kRefineList = kRefinePer * kRefineThreads;  // selected elements a workgroup lists in LDS
 
 // Receive side: pairs of one payload handled by one workgroup (kFlatPer per thread) and
