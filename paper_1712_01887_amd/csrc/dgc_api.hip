@@ -41,7 +41,7 @@ struct dgc_handle {
   std::vector<MergeBlock> part_blocks;   // the same with one emit part per range (warm-up densities)
   bool layout_may_overflow = true;       // some region of the registered layout is smaller than its tensor
   double last_replace_share = 0.0;       // pairs per element that they let expect
-  int32_t norm_looks = kNormLooks;       // how often the selection looks for a share of the norm before it sums it itself
+  int32_t looks = kNormLooks;            // how often a workgroup looks for what another one leaves before it does it itself
   int64_t last_replace_expected = 0;     // pairs per range the payloads of the last dgc_decompress_replace_regions call let expect
   WorkspaceLayout lay{};
   // what the bound workspace currently holds
@@ -305,6 +305,11 @@ T* at(void* ws, size_t off) {
   return reinterpret_cast<T*>(static_cast<char*>(ws) + off);
 }
 
+// The encoder's needs: the last 2 * kWireOnce block sums, from an even one on.
+unsigned long long* wire_needs(const dgc_handle* h, void* ws) {
+  return at<unsigned long long>(ws, h->lay.wire_sums + sizeof(uint32_t) * ((h->wire_slots - 2 * (size_t)kWireOnce) & ~(size_t)1));
+}
+
 bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
 
 dgc_status check_layout(const dgc_handle* h, const int64_t* oo) {
@@ -349,6 +354,9 @@ dgc_status sync_workspace(dgc_handle* h, void* ws, size_t ws_bytes, const int64_
     // (the record, and the places of the norm's shares behind it, which every call leaves empty)
     if (!hip_ok(launch_clear_words(at<uint32_t>(ws, h->lay.state), (h->lay.offsets - h->lay.state) / sizeof(uint32_t), stream),
                 "clear workspace state"))
+      return DGC_ERR_HIP;
+    if (h->wire_slots >= 2 * (size_t)kWireOnce &&
+        !hip_ok(launch_clear_words(reinterpret_cast<uint32_t*>(wire_needs(h, ws)), 2 * (size_t)kWireOnce, stream), "clear encoder needs"))
       return DGC_ERR_HIP;
     if (!hip_ok(hipMemcpyAsync(at<char>(ws, h->lay.offsets), h->offsets.data(),
                                sizeof(int64_t) * (T + 1), hipMemcpyHostToDevice, stream),
@@ -534,9 +542,9 @@ dgc_status dgc_create(dgc_handle** out, const dgc_config* cfg, int32_t num_tenso
   return DGC_OK;
 }
 
-// Test hook (not part of the interface): a selection that sums all the shares of the norm that it does not find at once.
-__attribute__((visibility("default"))) void dgc_test_set_norm_looks(dgc_handle* h, int32_t looks) {
-  if (h && looks >= 0) h->norm_looks = looks;
+// Test hook (not part of the interface): workgroups that do themselves whatever of others they do not find at once.
+__attribute__((visibility("default"))) void dgc_test_set_looks(dgc_handle* h, int32_t looks) {
+  if (h && looks >= 0) h->looks = looks;
 }
 
 static void profile_release(dgc_handle* h);
@@ -685,7 +693,7 @@ dgc_status dgc_compress(dgc_handle* h, const float* g, float* u, float* v, int32
   sa.thr_local = thr_local;
   sa.num_partials = with_norm ? norm_shares(h->n) : clip ? norm_blocks(h->n) : 0;
   sa.n = h->n;
-  sa.looks = h->norm_looks;
+  sa.looks = h->looks;
   sa.scale_override = c.scale_override;
   sa.momentum = c.momentum;
   sa.scale_const = scale_const;
@@ -1158,6 +1166,9 @@ dgc_status dgc_encode(dgc_handle* h, const int32_t* idx, const float* val, const
   ea.num_tensors = h->num_tensors;
   ea.total_blocks = (int32_t)total_blocks;
   ea.widest = h->wire_widest;
+  if (total_blocks > 0 && total_blocks <= (uint32_t)kWireOnce && h->wire_slots >= 2 * (size_t)kWireOnce)
+    ea.needs = wire_needs(h, workspace);
+  ea.looks = h->looks;
   if (!hip_ok(launch_encode(ea, stream), "launch encode kernels")) return DGC_ERR_HIP;
   return DGC_OK;
 }

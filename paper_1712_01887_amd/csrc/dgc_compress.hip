@@ -209,25 +209,25 @@ __device__ __forceinline__ void find_bin(const uint32_t* hist, uint32_t* wave_to
 }
 
 // The `m` <= kSelectThreads keys in sh.surv, which is zero behind them up to a multiple of four: the one of
-// descending rank `rank`.  Up to 256 keys, the usual case, have four neighbouring threads each, which compare it with a
-// quarter of the keys, four to an LDS read, and add up through the vector unit; more have one.
+// descending rank `rank`.  Up to 256 keys, the usual case, have four neighbouring threads each, up to 512 two, which compare
+// it with a share of the keys, four to an LDS read, and add up through the vector unit; more have one.
 __device__ __forceinline__ uint32_t rank_directly(SelectShared& sh, int tid, uint32_t m, uint32_t rank) {
   const uint4* __restrict__ four = reinterpret_cast<const uint4*>(sh.surv);
-  const bool shared = 4 * m <= (uint32_t)kSelectThreads;  // uniform
-  const uint32_t own = shared ? (uint32_t)tid >> 2 : (uint32_t)tid;
+  const uint32_t shift = 4 * m <= (uint32_t)kSelectThreads ? 2u : 2 * m <= (uint32_t)kSelectThreads ? 1u : 0u;  // uniform
+  const uint32_t own = (uint32_t)tid >> shift, step = 1u << shift;
   if (own < m) {
     const uint32_t x = sh.surv[own];
     uint32_t greater = 0, equal = 0;  // (a zero behind the keys can only add to the last rank's ties)
-    const uint32_t step = shared ? 4 : 1;
-    for (uint32_t i = shared ? tid & 3 : 0; 4 * i < m; i += step) {
+    for (uint32_t i = (uint32_t)tid & (step - 1u); 4 * i < m; i += step) {
       const uint4 y = four[i];
       greater += (y.x > x) + (y.y > x) + (y.z > x) + (y.w > x);
       equal += (y.x == x) + (y.y == x) + (y.z == x) + (y.w == x);
     }
-    if (shared) {
+    if (shift > 0) {
       uint32_t both = greater | (equal << 16);
       both += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)both, 0xB1, 0xf, 0xf, false);  // the neighbour's
-      both += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)both, 0x4E, 0xf, 0xf, false);  // the other pair's
+      const uint32_t other = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)both, 0x4E, 0xf, 0xf, false);  // the other pair's
+      both += shift > 1 ? other : 0u;
       greater = both & 0xFFFFu;
       equal = both >> 16;
     }

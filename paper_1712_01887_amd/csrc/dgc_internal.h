@@ -124,6 +124,13 @@ constexpr int kWireRounds = kWireChunk / kWireThreads;   // rounds of 64 pairs a
 // takes 239 if every region is full, and 44 against 56 if one workgroup in eight has pairs; with 512 of them 13
 // against 16.
 constexpr int kWireSelfScan = 16384;
+// Up to as many workgroup slots the encoder is one launch; their needs lie at the end of the block sums, a word of 64 bits
+// each with the call's number above (and a bit that no block sum has).  (Calls in two launches and in one, in a graph, us: one
+// slot 7.1 and 5.3, 60 8.8 and 7.4, 174 11.1 and 9.1, 216 10.8 and 10.2, 243 10.3 and 10.4: every workgroup
+// looks for all the needs before its own.)
+constexpr int kWireOnce = 256;
+constexpr uint32_t kWireCall = 0x80000000u;
+static_assert(kWireOnce <= kWireThreads, "a thread looks for each slot before its own");
 constexpr int kScanThreads = 1024;
 constexpr int kScanPer = 8;          // block sums per thread and round of the scan
 // Decoder: entries a wavefront decodes at a time (eight per lane: one 16-byte load of runs), positions
@@ -222,7 +229,9 @@ struct DeviceState {
   float scale;           // factor applied to g
   uint32_t flags;        // DGC_DIAG_*
   uint32_t crowded;      // exact selection in the pass: elements of the tensors whose floor does not go there; zero between calls
-  uint32_t pad[3];
+  uint32_t wire_call;    // encoder in one launch: number of the next call, and
+  uint32_t wire_arrived; // workgroups of this one that have what they need from the others; zero between calls
+  uint32_t pad;
 };
 
 // Per-tensor selection plan (host arithmetic, uploaded when the density changes).
@@ -393,6 +402,8 @@ struct EncodeArgs {
   int32_t widest;                // of one tensor at most
   int32_t per_tensor;            // workgroups of every tensor; 0: total_blocks of them, which search
   int32_t self_scan;             // the second pass adds the block sums up itself
+  unsigned long long* needs;     // device, total_blocks: one launch; null: two
+  int32_t looks;                 // how often a workgroup looks for what another one leaves
 };
 
 // Segments of the block-sum array handed to the scan kernel: segment s is

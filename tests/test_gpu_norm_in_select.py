@@ -17,7 +17,7 @@ MOST = 4 << 20
 
 
 def never_look(p):
-    hook = B.load().dgc_test_set_norm_looks
+    hook = B.load().dgc_test_set_looks
     hook.argtypes, hook.restype = [C.c_void_p, C.c_int32], None
     hook(p.dgc._h, 0)
 
