@@ -148,10 +148,9 @@ struct Candidates {
 
 // One workgroup per tensor finds the candidate key of a given descending rank
 // exactly.  Keys are the bit patterns of |v'| (order-isomorphic to the
-// magnitudes).  Up to three histogram passes over 11 + 11 + 9 key bits, most
-// significant first, narrow the key down; as soon as the bin that holds the
-// rank has few enough members they are gathered and ranked directly, which at
-// the paper's densities happens after the first pass.
+// magnitudes).  Histograms of 2048 bins narrow the interval that holds the key down; as soon as the bin that holds the
+// rank has few enough members they are gathered and ranked directly, mostly after the first.  Low ranks are ranked
+// from a list of the largest keys without any.
 //
 // Up to kSelectRegKeys * kSelectThreads candidates live in registers (each
 // thread gathers its own once and keeps them); a larger candidate set (exact
@@ -635,12 +634,12 @@ __device__ __forceinline__ float settle_scale(const SelectArgs& a, SelectShared&
   return sh.scale;
 }
 
-// Bound by latency: the gather of the candidates, then the ranking, in one workgroup per tensor.  17 us on the
-// 122 M-element set, 13.6 on the 161-tensor set, 10.5 on 23 tensors of 0.27 M elements in all (19.2, 14.3, 12.2
-// with the wavefronts' maxima taken through LDS and one key per LDS read).  Inside the workgroup, 1 M elements, from its start:
+// Bound by latency: the gather of the candidates, then the ranking, in one workgroup per tensor.  16.2 us on eleven tensors of
+// 66 M elements, 12.7 on 161 of 25.6 M (13.7 with chains as they were before the next sentence).  Inside the workgroup,
+// 1 M elements, from its start:
 // 8.0 -> 6.6 us with the list's length asked for once per wavefront and not per key, four threads to a listed key, no
 // walk over empty slots, and the scale's sum over the lanes inside the vector unit; the step of that set 27.5 ->
-// 26.3, of the 23 tensors 33.9 -> 31.9.
+// 26.3, of 23 tensors of 0.27 M elements in all 33.9 -> 31.9.
 // FUSED: the norm's partial sums are formed by the first workgroups of the launch, while the others gather (rule and
 // figures at kNormInSelectElements; steps with clipping: 23 tensors of 0.27 M elements 31.7 -> 30.1 us, 1 M 26.0 -> 24.4).
 // MODE: whether some tensors are ranked by way of a band (TensorPlan.exact == 2), and whether its floor may go into the pass.
