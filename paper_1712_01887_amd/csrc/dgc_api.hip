@@ -40,7 +40,6 @@ struct dgc_handle {
   int64_t longest_tensor = 0;
   std::vector<MergeBlock> part_blocks;   // the same with one emit part per range (warm-up densities)
   bool layout_may_overflow = true;       // some region of the registered layout is smaller than its tensor
-  double last_replace_share = 0.0;       // pairs per element that they let expect
   int32_t looks = kNormLooks;            // how often a workgroup looks for what another one leaves before it does it itself
   int64_t last_replace_expected = 0;     // pairs per range the payloads of the last dgc_decompress_replace_regions call let expect
   WorkspaceLayout lay{};
@@ -121,9 +120,10 @@ constexpr double kMergeMaxDensity = 0.005;   // receive side: merge by element r
 constexpr size_t kMergeFewRanges = 256;
 // Sets of up to as many parts have a word of LDS for every element, if the payloads let expect at most this many pairs
 // per element.  Against the part kernels (us): accumulating, two tensors of 7 M elements, 0.4 % of sixteen
-// workers (0.064) 15.6 and 18.3, 1 M, 1 % of sixteen (0.16) 17.7 and 13.9; replacing, 7 M, 1 % of four (0.04) 15.1 and 11.1,
-// of two (0.02) 10.3 and 12.4.
-constexpr double kDirectMaxShare = 0.08, kDirectMaxShareReplacing = 0.03;
+// workers (0.064) 15.6 and 18.3, 1 M, 1 % of sixteen (0.16) 17.7 and 13.9.  Replacing, wherever the range kernel would do it:
+// against that, one tensor of 7 M, 0.1 % of sixteen (0.016) 11.9 and 15.6, 0.4 % of eight (0.032) 14.6 and 18.8, 1 M 10.1 and
+// 15.4, 30 of 0.1 M 10.8 and 14.5.
+constexpr double kDirectMaxShare = 0.08;
 // Sparse clear by scattered stores (80 G/s) up to this many pairs in all; the part kernels take 18 us however
 // few there are (23 tensors as above: 7.6 against 3.6 + 14.6 us), and as long as the stores at about this
 // number (122 M elements, 1.9 M pairs: 717 against 712 for the whole pass).
@@ -1046,10 +1046,10 @@ static dgc_status scatter_regions(dgc_handle* h, float* dense, int32_t num_paylo
   const MergeBlock* parts = at<MergeBlock>(workspace, h->lay.part_blocks);
   const int32_t num_parts = (int32_t)h->part_blocks.size();
   void* found = at<char>(workspace, h->lay.part_found);
-  const double share = h->cfg.density * (double)num_payloads;
-  const double share_old = (replace && num_old > 0) ? h->last_replace_share : 0.0;
-  const bool direct = h->part_blocks.size() <= kMergeFewRanges && (share > share_old ? share : share_old) <= (replace ? kDirectMaxShareReplacing : kDirectMaxShare);
-  if (replace) h->last_replace_share = share;
+  // (Replacing, only where the range kernel would do it: elsewhere the previous payloads are not looked at and the whole of
+  // `dense` is written, which callers may count on.)
+  const bool direct = h->part_blocks.size() <= kMergeFewRanges && (few || !replace) &&
+                      h->cfg.density * (double)num_payloads <= kDirectMaxShare;
   if (clear) {
     if (few || (h->cfg.density * (double)h->n * (double)num_payloads <= kScatterClearPairs &&
                 h->num_tensors <= kScatterClearTensors)) {

@@ -104,6 +104,30 @@ def test_replacing_across_a_change_of_density(first, then):
     dgc.close()
 
 
+@pytest.mark.parametrize("share,workers,then", [(0.01, 2, 0.01), (0.02, 1, 0.02), (0.01, 2, 0.001), (0.02, 1, 0.004)])
+def test_replacing_above_half_a_percent_reads_nothing(share, workers, then):
+    """The whole of `dense` is written whatever it holds and whatever the previous payloads name, and so it is in the call
+    behind such a one."""
+    import torch
+    rng = np.random.default_rng([workers, int(1000 * then)])
+    offsets = np.concatenate([[0], np.cumsum(SIZES)])
+    layout = offsets.tolist()
+    dgc = B.Dgc(B.make_config(density=share, num_workers=workers), offsets)
+    dgc.set_layout(layout)
+    dense = torch.empty(int(offsets[-1]), device="cuda")
+    stale = [torch.zeros(layout[-1], dtype=torch.int32, device="cuda")], [torch.zeros(len(SIZES), dtype=torch.int32, device="cuda")]
+    for density in (share, then):
+        dgc.dgc_set_density(density)
+        new = [payload(density, rng, offsets, layout, 0) for _ in range(workers)]
+        expect = np.zeros(dense.numel(), np.float32)
+        for (e, x), _ in new:
+            expect[e] = (expect[e] + x).astype(np.float32)
+        dense.fill_(7.0)
+        dgc.dgc_decompress_replace_regions(dense, *(tuple([d[i] for _, d in new] for i in range(3))), *stale)
+        assert np.array_equal(dense.cpu().numpy(), expect), density
+    dgc.close()
+
+
 @pytest.mark.parametrize("workers,more", [(7, 0), (64, 0), (64, 25)])
 def test_part_kernel_that_searches_and_that_looks_up(workers, more):
     """Dense payloads, parts times payloads on both sides of the line between one launch and two."""
