@@ -39,6 +39,7 @@ struct dgc_handle {
   int64_t longest_range = 0;             // elements of the longest of them
   int64_t longest_tensor = 0;
   std::vector<MergeBlock> part_blocks;   // the same with one emit part per range (warm-up densities)
+  int64_t searched_parts = 0;            // parts that are not a whole tensor
   bool layout_may_overflow = true;       // some region of the registered layout is smaller than its tensor
   int32_t looks = kNormLooks;            // how often a workgroup looks for what another one leaves before it does it itself
   int64_t last_replace_expected = 0;     // pairs per range the payloads of the last dgc_decompress_replace_regions call let expect
@@ -119,11 +120,16 @@ constexpr double kMergeMaxDensity = 0.005;   // receive side: merge by element r
 // 5700 us by ranges, 45 by parts; 1 M elements, pairs in an eighth: 146 and 14).
 constexpr size_t kMergeFewRanges = 256;
 // Sets of up to as many parts have a word of LDS for every element, if the payloads let expect at most this many pairs
-// per element.  Against the part kernels (us): accumulating, two tensors of 7 M elements, 0.4 % of sixteen
-// workers (0.064) 15.6 and 18.3, 1 M, 1 % of sixteen (0.16) 17.7 and 13.9.  Replacing, wherever the range kernel would do it:
-// against that, one tensor of 7 M, 0.1 % of sixteen (0.016) 11.9 and 15.6, 0.4 % of eight (0.032) 14.6 and 18.8, 1 M 10.1 and
-// 15.4, 30 of 0.1 M 10.8 and 14.5.
+// per element.  Against the part kernels (us): accumulating, two tensors of 3.5 M elements, 0.4 % of sixteen
+// workers (0.064) 15.2 and 17.9, 1 % of eight (0.08) 15.2 and 17.3, 30 of 0.1 M 11.1 and 13.9, 1 M 9.2 and 12.5, but 1 % of
+// sixteen (0.16) 17.7 and 13.9.  Replacing, wherever the range kernel would do it:
+// against that, one tensor of 7 M, 0.1 % of sixteen (0.016) 11.1 and 15.6, two of 3.5 M, 0.4 % of eight (0.032) 13.2 and 18.4,
+// 1 M 9.2 and 15.4, 30 of 0.1 M 9.8 and 14.5.
 constexpr double kDirectMaxShare = 0.08;
+// ... and, where the part kernels are the other way, this many searches of a payload for a part: with 64 workers of 0.1 % (0.064) one
+// tensor of 1 M elements (2048 searches) takes 19.3 and 20.3, of 3 M (5888) 23.5 and 22.1, two of 3.5 M (13824) 29.4 and 26.1;
+// 200 of 30 K, which are a part each, 19.3 and 27.9.
+constexpr int64_t kDirectSearches = 4096;
 // Sparse clear by scattered stores (80 G/s) up to this many pairs in all; the part kernels take 18 us however
 // few there are (23 tensors as above: 7.6 against 3.6 + 14.6 us), and as long as the stores at about this
 // number (122 M elements, 1.9 M pairs: 717 against 712 for the whole pass).
@@ -529,6 +535,7 @@ dgc_status dgc_create(dgc_handle** out, const dgc_config* cfg, int32_t num_tenso
       if (end > h->offsets[eb.tensor + 1]) end = h->offsets[eb.tensor + 1];
       h->part_blocks.push_back(MergeBlock{(int32_t)begin, (int32_t)end, eb.tensor, (int32_t)h->offsets[eb.tensor],
                                           (int32_t)h->offsets[eb.tensor + 1], 0});
+      if (begin != h->offsets[eb.tensor] || end != h->offsets[eb.tensor + 1]) ++h->searched_parts;
     }
     h->ws_out_offsets.resize(num_tensors + 1);
     h->wire_first_block.resize(num_tensors + 1);
@@ -1048,8 +1055,8 @@ static dgc_status scatter_regions(dgc_handle* h, float* dense, int32_t num_paylo
   void* found = at<char>(workspace, h->lay.part_found);
   // (Replacing, only where the range kernel would do it: elsewhere the previous payloads are not looked at and the whole of
   // `dense` is written, which callers may count on.)
-  const bool direct = h->part_blocks.size() <= kMergeFewRanges && (few || !replace) &&
-                      h->cfg.density * (double)num_payloads <= kDirectMaxShare;
+  const bool direct = h->part_blocks.size() <= kMergeFewRanges && h->cfg.density * (double)num_payloads <= kDirectMaxShare &&
+                      (few || (!replace && h->searched_parts * num_payloads <= kDirectSearches));
   if (clear) {
     if (few || (h->cfg.density * (double)h->n * (double)num_payloads <= kScatterClearPairs &&
                 h->num_tensors <= kScatterClearTensors)) {

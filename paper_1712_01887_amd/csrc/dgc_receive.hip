@@ -636,18 +636,172 @@ __global__ __launch_bounds__(THREADS) void merge_regions_kernel(float* __restric
   }
 }
 
+// Pairs of a part in the chunks that merge_parts_kernel takes (see there): a table of where they are, lane w looking after
+// payload w, and rounds of a chunk for every wavefront.
+typedef float fvec4u __attribute__((ext_vector_type(4), aligned(4)));  // a range starts anywhere
+typedef int32_t ivec4 __attribute__((ext_vector_type(4)));
+typedef int32_t ivec4u __attribute__((ext_vector_type(4), aligned(4)));
+
+struct ChunkTable {
+  const int32_t* idx;  // the lane's payload: start of the line that holds its first pair of the part
+  const float* val;    // ... the value beside it
+  int32_t pos;         // ... its place in the payload's arrays (may lie up to 31 before them)
+  int head, end;       // its pairs are in slots [head, end) from there
+  uint32_t chunk0;     // its first chunk among the part's
+  uint32_t total;      // chunks of the part
+
+  // `at` and `pairs`: the part's first pair of the lane's payload, and how many there are
+  __device__ __forceinline__ ChunkTable(const int32_t* idx_of, const float* val_of, int32_t at, int32_t pairs, int num_payloads, int lane) {
+    idx = idx_of + at;
+    head = (int)((reinterpret_cast<uintptr_t>(idx) >> 2) & 31u);
+    idx -= head;
+    pos = at - head;
+    val = val_of + at - head;
+    const uint32_t until = (uint32_t)head + (uint32_t)pairs;  // (beyond 2^31 - 1: a foreign region)
+    end = (int)(until < 0x7FFFFFFFu ? until : 0x7FFFFFFFu);
+    const uint32_t own = pairs > 0 ? ((uint32_t)end + (uint32_t)kPartChunk - 1u) / (uint32_t)kPartChunk : 0u;
+    const uint32_t upto = wave_inclusive_sum(own);
+    total = wave_last(upto);
+    chunk0 = lane < num_payloads ? upto - own : 0xFFFFFFFFu;
+  }
+  __device__ __forceinline__ int payload_at(uint32_t chunk) const { return __popcll(__ballot(chunk0 <= chunk)) - 1; }
+};
+
+struct ChunkRound {
+  ivec4 idx;
+  fvec4u x;
+  int w;              // payload of the wavefront's chunk; -1: none
+  int first, last;    // payloads of the whole round
+  int part;           // -1: there is no round
+  bool edge;          // the chunk holds slots that are no pairs of the part:
+  uint32_t wanted;    // ... a bit for each of the lane's four that is one,
+  int back;           // ... and how many places behind its own each was loaded
+
+  // Asks for the next chunk of every one of `waves` wavefronts, of which there is one at least.
+  __device__ __forceinline__ void fetch(const ChunkTable& t, uint32_t& cursor, uint32_t waves, int wave, int lane) {
+    auto of_lane = [&](uint64_t x, int w) {
+      return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, w) |
+             (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), w) << 32;
+    };
+    const uint32_t until = t.total - cursor < waves ? t.total : cursor + waves;
+    first = t.payload_at(cursor);
+    last = t.payload_at(until - 1u);
+    const uint32_t c = cursor + (uint32_t)wave;
+    cursor = until;
+    w = -1;
+    edge = false;
+    if (c >= until) return;  // uniform
+    w = t.payload_at(c);
+    const int slot0 = (int)(c - (uint32_t)__builtin_amdgcn_readlane((int)t.chunk0, w)) * kPartChunk;
+    const int slot = slot0 + 4 * lane;
+    const int head = __builtin_amdgcn_readlane(t.head, w), end = __builtin_amdgcn_readlane(t.end, w);
+    const int32_t* __restrict__ from = reinterpret_cast<const int32_t*>(of_lane(reinterpret_cast<uint64_t>(t.idx), w));
+    const float* __restrict__ values = reinterpret_cast<const float*>(of_lane(reinterpret_cast<uint64_t>(t.val), w));
+    if (slot0 >= head && end - slot0 >= kPartChunk) {
+      idx = __builtin_nontemporal_load(reinterpret_cast<const ivec4*>(from + slot));
+      x = __builtin_nontemporal_load(reinterpret_cast<const fvec4u*>(values + slot));
+    } else {
+      // Slots before the first pair and behind the last hold other parts' pairs, or nothing that matters, or do not
+      // exist.  (What is loaded is sorted out when the round is added: nothing here waits for it.)
+      const EdgeFour four(slot, head, end, __builtin_amdgcn_readlane(t.pos, w) + slot);
+      edge = true;
+      wanted = 0;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) wanted |= EdgeFour::wanted(slot + k, head, end) ? 1u << k : 0u;
+      back = four.whole ? four.back : 0;
+      if (four.whole) {
+        idx = __builtin_nontemporal_load(reinterpret_cast<const ivec4u*>(from + slot - four.back));
+        x = __builtin_nontemporal_load(reinterpret_cast<const fvec4u*>(values + slot - four.back));
+      } else if (four.any) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          if ((wanted >> k) & 1u) {
+            idx[k] = from[slot + k];
+            x[k] = values[slot + k];
+          }
+        }
+      }
+    }
+  }
+};
+
+// Adds a round to a part's accumulator, behind whose elements there is a word per lane for what is no pair of it, and refills
+// it by `fetch`.  `last_w`: payload that was added last (-1: none, the accumulator is being filled).
+template <typename Fetch>
+__device__ __forceinline__ void add_round(ChunkRound& L, float* acc, uint32_t begin, uint32_t length, int32_t scaled, float scale,
+                                          int& last_w, int lane, Fetch& fetch) {
+  uint32_t at[4];
+  float x[4];
+  if (L.edge) {  // uniform
+    if (L.back & 1) {
+      L.idx = ivec4{L.idx[1], L.idx[2], L.idx[3], L.idx[3]};
+      L.x = fvec4u{L.x[1], L.x[2], L.x[3], L.x[3]};
+    }
+    if (L.back & 2) {
+      L.idx = ivec4{L.idx[2], L.idx[3], L.idx[3], L.idx[3]};
+      L.x = fvec4u{L.x[2], L.x[3], L.x[3], L.x[3]};
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (!((L.wanted >> k) & 1u)) L.idx[k] = INT32_MIN;  // outside every range
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const uint32_t r = (uint32_t)L.idx[k] - begin;
+    at[k] = r < length ? r : (uint32_t)(kEmitElements + lane);  // not a pair of the part, or of a foreign region
+    x[k] = scaled ? scale * L.x[k] : L.x[k];
+  }
+  const int first = L.first, last = L.last, own = L.w;
+  fetch(L);
+  for (int w = first; w <= last; ++w) {  // payloads in the order given
+    if (w != last_w) __syncthreads();    // the payload before is added (the first time: the accumulator is filled)
+    last_w = w;
+    if (own == w) {
+      // the indices of one payload are distinct: all reads, then all writes, no barrier between its rounds
+      float sum[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) sum[k] = acc[at[k]] + x[k];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) acc[at[k]] = sum[k];
+    }
+  }
+}
+
+// Four consecutive elements of a range of `len`, from element e (a multiple of four) on.
+__device__ __forceinline__ fvec4u load_quad(const float* src, int32_t len, int e) {
+  fvec4u y = {0.0f, 0.0f, 0.0f, 0.0f};
+  if (e + 4 <= len) {
+    y = __builtin_nontemporal_load(reinterpret_cast<const fvec4u*>(src + e));
+  } else {
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+      if (e + c < len) y[c] = src[e + c];
+  }
+  return y;
+}
+__device__ __forceinline__ void store_quad(float* to, int32_t len, int e, const fvec4u& y) {
+  if (e + 4 <= len) {
+    __builtin_nontemporal_store(y, reinterpret_cast<fvec4u*>(to + e));
+  } else {
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+      if (e + c < len) to[e + c] = y[c];
+  }
+}
+
 // The same sums where every emit workgroup's part of the set has a compute unit to itself: the part's range of `dense`
 // then has a word of LDS for every element, and the pairs need no numbering (no bitmap, no prefix sum over it, no
 // look-up of slots).  Only words of elements that occur are ever touched.  Parts are a quarter as long as the ranges
-// above, so that a set of a few million elements keeps four times as many compute units busy, and a crowded part
-// just takes longer.
-// Bound by latency, as the range kernel: launch included, in a graph, 0.1 % of four workers, replacing: 1 M elements 8.2
-// -> 6.3 us, 7 M in two tensors 8.9 -> 7.3; of sixteen 14.8 -> 8.6 and 16.6 -> 11.3; accumulating 1 % of four workers,
-// 23 tensors of 0.27 M 8.6 -> 6.5, 1 M 12.1 -> 7.1 (part kernels).
+// above, so that a set of a few million elements keeps four times as many compute units busy.  A part that pairs crowd is
+// taken as merge_parts_kernel takes it: all pairs of eight workers of 1 % in a fiftieth of 7 M elements 37.8 us (part kernels
+// 45.9; each pair by itself, three times over, 297), of four of 0.8 % in an eighth of 1 M 9.4 (13.0; 22.2).
+// Bound by latency, as the range kernel: launch included, in a graph, 0.1 % of four workers, replacing: 1 M elements 8.1
+// -> 5.7 us, 7 M in two tensors 9.0 -> 6.9; of sixteen 14.8 -> 7.9 and 18.1 -> 12.8; accumulating 1 % of four workers,
+// 23 tensors of 12 K 5.8 -> 4.5, 1 M 11.4 -> 6.7 (part kernels).
 // REPLACE: the indices of the earlier payloads are elements that start from zero and get no pair: what the new ones
 // share with them gets its sum, the others zero.
 struct DirectShared {
-  float acc[kEmitElements];
+  alignas(16) float acc[kEmitElements + 64];  // behind the part a word per lane for what is no pair of it
   int32_t begin[kMaxPayloads + 1];
   global_ptr<int32_t> idx_at[kMaxPayloads];
   global_ptr<float> val_at[kMaxPayloads];
@@ -674,11 +828,7 @@ __global__ __launch_bounds__(THREADS) void merge_direct_kernel(float* __restrict
                                           reinterpret_cast<const int32_t*>(blocks), tid, THREADS / 64, old_total);
   if (total == 0 && old_total == 0) return;
   const uint32_t nowhere = 0xFFFFFFFFu;  // (an index outside the range: of a region that does not ascend)
-  auto old_at = [&](int q) {
-    const int w = payload_of(was.begin, num_old, q);
-    const uint32_t r = (uint32_t)was.idx_at[w][q - was.begin[w]] - (uint32_t)blk.begin;
-    return r < length ? r : nowhere;
-  };
+
   if (total <= kDirectPairs && old_total <= kDirectPairs) {
     // everything in registers, all loads on their way together
     uint32_t old_rel[kPer], rel[kPer];
@@ -747,42 +897,50 @@ __global__ __launch_bounds__(THREADS) void merge_direct_kernel(float* __restrict
     }
     return;
   }
-  auto pair_at = [&](int q) {
-    const int w = payload_of(sh.begin, num_payloads, q);
-    const uint32_t r = (uint32_t)sh.idx_at[w][q - sh.begin[w]] - (uint32_t)blk.begin;
-    return r < length ? r : nowhere;
+
+  // Pairs that crowd the part: as in merge_parts_kernel the whole of it is read (REPLACE: starts from zero; outside the earlier
+  // payloads' indices it is zero anyway), the pairs are added in chunks, with rounds on their way, and the whole of it is written.
+  constexpr int kWaves = THREADS / 64;
+  constexpr int kRounds = 2 * kPartThreads / THREADS;  // as many pairs on their way as there
+  constexpr int kQuads = kEmitElements / 4 / THREADS;
+  const bool looks_after = lane < num_payloads;
+  const ChunkTable t(looks_after ? p.idx[lane] : nullptr, looks_after ? p.val[lane] : nullptr,
+                     looks_after ? (int32_t)(sh.idx_at[lane] - in_global(p.idx[lane])) : 0,
+                     looks_after ? sh.begin[lane + 1] - sh.begin[lane] : 0, num_payloads, lane);
+  uint32_t cursor = 0;  // next chunk
+  auto fetch = [&](ChunkRound& L) {
+    L.part = -1;
+    if (cursor >= t.total) return;
+    L.part = 0;
+    L.fetch(t, cursor, kWaves, wave, lane);
   };
-  if (REPLACE) {
-    for (int q = tid; q < old_total; q += THREADS) {
-      const uint32_t r = old_at(q);
-      if (r != nowhere) sh.acc[r] = 0.0f;
-    }
+  ChunkRound rounds[kRounds];
+#pragma unroll
+  for (int i = 0; i < kRounds; ++i) fetch(rounds[i]);
+  {
+    fvec4u d[kQuads];
+#pragma unroll
+    for (int i = 0; i < kQuads; ++i) d[i] = load_quad(range, REPLACE ? 0 : (int32_t)length, 4 * (tid + i * THREADS));
+#pragma unroll
+    for (int i = 0; i < kQuads; ++i)
+      *reinterpret_cast<float4*>(&sh.acc[4 * (tid + i * THREADS)]) = make_float4(d[i][0], d[i][1], d[i][2], d[i][3]);
   }
-  for (int q = tid; q < total; q += THREADS) {
-    const uint32_t r = pair_at(q);
-    if (r != nowhere) sh.acc[r] = REPLACE ? 0.0f : range[r];
+  int last_w = -1;
+  for (bool more = true; more;) {
+#pragma unroll
+    for (int i = 0; i < kRounds; ++i) {
+      if (rounds[i].part < 0) {
+        more = false;
+        break;
+      }
+      add_round(rounds[i], sh.acc, (uint32_t)blk.begin, length, scaled, scale, last_w, lane, fetch);
+    }
   }
   __syncthreads();
-  for (int w = 0; w < num_payloads; ++w) {  // payloads in the order given
-    const int len = sh.begin[w + 1] - sh.begin[w];
-    const global_ptr<int32_t> idx = sh.idx_at[w];
-    const global_ptr<float> val = sh.val_at[w];
-    for (int q = tid; q < len; q += THREADS) {
-      const uint32_t r = (uint32_t)idx[q] - (uint32_t)blk.begin;
-      const float x = scaled ? scale * val[q] : val[q];
-      if (r < length) sh.acc[r] = sh.acc[r] + x;
-    }
-    __syncthreads();
-  }
-  for (int q = tid; q < total; q += THREADS) {
-    const uint32_t r = pair_at(q);
-    if (r != nowhere) range[r] = sh.acc[r];
-  }
-  if (REPLACE) {
-    for (int q = tid; q < old_total; q += THREADS) {
-      const uint32_t r = old_at(q);
-      if (r != nowhere) range[r] = sh.acc[r];
-    }
+#pragma unroll
+  for (int i = 0; i < kQuads; ++i) {
+    const float4 y = *reinterpret_cast<const float4*>(&sh.acc[4 * (tid + i * THREADS)]);
+    store_quad(range, (int32_t)length, 4 * (tid + i * THREADS), fvec4u{y.x, y.y, y.z, y.w});
   }
 }
 
@@ -938,38 +1096,12 @@ __global__ __launch_bounds__(kPartThreads) void merge_parts_kernel(float* __rest
                                                                    const MergeBlock* __restrict__ blocks,
                                                                    int32_t num_blocks, int2* __restrict__ found, float scale,
                                                                    int32_t scaled) {
-  typedef float fvec4u __attribute__((ext_vector_type(4), aligned(4)));  // a range starts anywhere
-  typedef int32_t ivec4 __attribute__((ext_vector_type(4)));
-  typedef int32_t ivec4u __attribute__((ext_vector_type(4), aligned(4)));
   constexpr int kQuads = kEmitElements / 4 / kPartThreads;
   constexpr int kWaves = kPartThreads / 64;
   __shared__ alignas(16) float acc[kEmitElements + 64];  // behind the range a word per lane for what is no pair of it
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // four consecutive elements of a range of `len`, from element 4 * (tid + i * kPartThreads) on
-  auto load_quad = [&](const float* src, int32_t len, int i) {
-    const int e = 4 * (tid + i * kPartThreads);
-    fvec4u y = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (e + 4 <= len) {
-      y = __builtin_nontemporal_load(reinterpret_cast<const fvec4u*>(src + e));
-    } else {
-#pragma unroll
-      for (int c = 0; c < 3; ++c)
-        if (e + c < len) y[c] = src[e + c];
-    }
-    return y;
-  };
-  auto store_quad = [&](float* to, int32_t len, int i, const fvec4u& y) {
-    const int e = 4 * (tid + i * kPartThreads);
-    if (e + 4 <= len) {
-      __builtin_nontemporal_store(y, reinterpret_cast<fvec4u*>(to + e));
-    } else {
-#pragma unroll
-      for (int c = 0; c < 3; ++c)
-        if (e + c < len) to[e + c] = y[c];
-    }
-  };
   auto put_quad = [&](int i, const fvec4u& y) {
     *reinterpret_cast<float4*>(&acc[4 * (tid + i * kPartThreads)]) = make_float4(y[0], y[1], y[2], y[3]);
   };
@@ -1012,50 +1144,12 @@ __global__ __launch_bounds__(kPartThreads) void merge_parts_kernel(float* __rest
     if (SEARCH) return part == (int)blockIdx.x && lane < num_payloads ? own_entry[lane] : make_int2(0, 0);
     return part < num_blocks && lane < num_payloads ? found[(int64_t)part * num_payloads + lane] : make_int2(0, 0);
   };
-  struct Table {                // of the part that is being fetched
-    const int32_t* idx;         // the lane's payload: start of the line that holds its first pair of the part
-    const float* val;           // ... the value beside it
-    int32_t pos;                // ... its place in the payload's arrays (may lie up to 31 before them)
-    int head, end;              // its pairs are in slots [head, end) from there
-    uint32_t chunk0;            // its first chunk among the part's
-    uint32_t total;             // chunks of the part
-  };
-  auto make_table = [&](const int2& f) {
-    Table t;
-    t.idx = idx_of + f.x;
-    t.head = (int)((reinterpret_cast<uintptr_t>(t.idx) >> 2) & 31u);
-    t.idx -= t.head;
-    t.pos = f.x - t.head;
-    t.val = val_of + f.x - t.head;
-    const uint32_t until = (uint32_t)t.head + (uint32_t)f.y;  // (beyond 2^31 - 1: a foreign region)
-    t.end = (int)(until < 0x7FFFFFFFu ? until : 0x7FFFFFFFu);
-    const uint32_t own = f.y > 0 ? ((uint32_t)t.end + (uint32_t)kPartChunk - 1u) / (uint32_t)kPartChunk : 0u;
-    const uint32_t upto = wave_inclusive_sum(own);
-    t.total = wave_last(upto);
-    t.chunk0 = lane < num_payloads ? upto - own : 0xFFFFFFFFu;
-    return t;
-  };
-  auto payload_at = [&](const Table& t, uint32_t chunk) { return __popcll(__ballot(t.chunk0 <= chunk)) - 1; };
-  auto of_lane = [&](uint64_t x, int w) {
-    return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, w) |
-           (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), w) << 32;
-  };
-
-  struct Round {
-    ivec4 idx;
-    fvec4u x;
-    int w;              // payload of the wavefront's chunk; -1: none
-    int first, last;    // payloads of the whole round
-    int part;           // -1: there is no round
-    bool edge;          // the chunk holds slots that are no pairs of the part:
-    uint32_t wanted;    // ... a bit for each of the lane's four that is one,
-    int back;           // ... and how many places behind its own each was loaded
-  };
+  auto make_table = [&](const int2& f) { return ChunkTable(idx_of, val_of, f.x, f.y, num_payloads, lane); };
   int fb = b;            // the part that is being fetched
-  Table t = make_table(entry_of(b));
+  ChunkTable t = make_table(entry_of(b));
   int2 next_entry = entry_of(b + step);
   uint32_t cursor = 0;   // next chunk of it
-  auto fetch = [&](Round& L) {
+  auto fetch = [&](ChunkRound& L) {
     while (cursor >= t.total && fb + step < num_blocks) {
       fb += step;
       t = make_table(next_entry);
@@ -1065,49 +1159,10 @@ __global__ __launch_bounds__(kPartThreads) void merge_parts_kernel(float* __rest
     L.part = -1;
     if (cursor >= t.total) return;
     L.part = fb;
-    const uint32_t until = t.total - cursor < (uint32_t)kWaves ? t.total : cursor + (uint32_t)kWaves;
-    L.first = payload_at(t, cursor);
-    L.last = payload_at(t, until - 1u);
-    const uint32_t c = cursor + (uint32_t)wave;
-    cursor = until;
-    L.w = -1;
-    L.edge = false;
-    if (c >= until) return;  // uniform
-    const int w = payload_at(t, c);
-    L.w = w;
-    const int slot0 = (int)(c - (uint32_t)__builtin_amdgcn_readlane((int)t.chunk0, w)) * kPartChunk;
-    const int slot = slot0 + 4 * lane;
-    const int head = __builtin_amdgcn_readlane(t.head, w), end = __builtin_amdgcn_readlane(t.end, w);
-    const int32_t* __restrict__ from = reinterpret_cast<const int32_t*>(of_lane(reinterpret_cast<uint64_t>(t.idx), w));
-    const float* __restrict__ values = reinterpret_cast<const float*>(of_lane(reinterpret_cast<uint64_t>(t.val), w));
-    if (slot0 >= head && end - slot0 >= kPartChunk) {
-      L.idx = __builtin_nontemporal_load(reinterpret_cast<const ivec4*>(from + slot));
-      L.x = __builtin_nontemporal_load(reinterpret_cast<const fvec4u*>(values + slot));
-    } else {
-      // Slots before the first pair and behind the last hold other parts' pairs, or nothing that matters, or do not
-      // exist.  (What is loaded is sorted out when the round is added: nothing here waits for it.)
-      const EdgeFour four(slot, head, end, __builtin_amdgcn_readlane(t.pos, w) + slot);
-      L.edge = true;
-      L.wanted = 0;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) L.wanted |= EdgeFour::wanted(slot + k, head, end) ? 1u << k : 0u;
-      L.back = four.whole ? four.back : 0;
-      if (four.whole) {
-        L.idx = __builtin_nontemporal_load(reinterpret_cast<const ivec4u*>(from + slot - four.back));
-        L.x = __builtin_nontemporal_load(reinterpret_cast<const fvec4u*>(values + slot - four.back));
-      } else if (four.any) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          if ((L.wanted >> k) & 1u) {
-            L.idx[k] = from[slot + k];
-            L.x[k] = values[slot + k];
-          }
-        }
-      }
-    }
+    L.fetch(t, cursor, kWaves, wave, lane);
   };
 
-  Round A, B;
+  ChunkRound A, B;
   bool a_next = true;  // which of the two is added next
   fetch(A);
   fetch(B);
@@ -1115,7 +1170,7 @@ __global__ __launch_bounds__(kPartThreads) void merge_parts_kernel(float* __rest
   {
     fvec4u d[kQuads];
 #pragma unroll
-    for (int i = 0; i < kQuads; ++i) d[i] = load_quad(dense + blk.begin, REPLACE ? 0 : (int32_t)(blk.end - blk.begin), i);
+    for (int i = 0; i < kQuads; ++i) d[i] = load_quad(dense + blk.begin, REPLACE ? 0 : (int32_t)(blk.end - blk.begin), 4 * (tid + i * kPartThreads));
 #pragma unroll
     for (int i = 0; i < kQuads; ++i) put_quad(i, d[i]);
   }
@@ -1126,44 +1181,7 @@ __global__ __launch_bounds__(kPartThreads) void merge_parts_kernel(float* __rest
     const uint32_t length = (uint32_t)(blk.end - blk.begin);  // <= kEmitElements
     bool any = false;
     int last_w = -1;
-    // Adds the round in L and refills L with the next round to fetch.
-    auto add = [&](Round& L) {
-      uint32_t at[4];
-      float x[4];
-      if (L.edge) {  // uniform
-        if (L.back & 1) {
-          L.idx = ivec4{L.idx[1], L.idx[2], L.idx[3], L.idx[3]};
-          L.x = fvec4u{L.x[1], L.x[2], L.x[3], L.x[3]};
-        }
-        if (L.back & 2) {
-          L.idx = ivec4{L.idx[2], L.idx[3], L.idx[3], L.idx[3]};
-          L.x = fvec4u{L.x[2], L.x[3], L.x[3], L.x[3]};
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-          if (!((L.wanted >> k) & 1u)) L.idx[k] = INT32_MIN;  // outside every range
-      }
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const uint32_t r = (uint32_t)L.idx[k] - begin;
-        at[k] = r < length ? r : (uint32_t)(kEmitElements + lane);  // not a pair of the part, or of a foreign region
-        x[k] = scaled ? scale * L.x[k] : L.x[k];
-      }
-      const int first = L.first, last = L.last, own = L.w;
-      fetch(L);
-      for (int w = first; w <= last; ++w) {  // payloads in the order given
-        if (w != last_w) __syncthreads();    // the payload before is added (the first time: the accumulator is filled)
-        last_w = w;
-        if (own == w) {
-          // the indices of one payload are distinct: all reads, then all writes, no barrier between its rounds
-          float sum[4];
-#pragma unroll
-          for (int k = 0; k < 4; ++k) sum[k] = acc[at[k]] + x[k];
-#pragma unroll
-          for (int k = 0; k < 4; ++k) acc[at[k]] = sum[k];
-        }
-      }
-    };
+    auto add = [&](ChunkRound& L) { add_round(L, acc, begin, length, scaled, scale, last_w, lane, fetch); };
     for (;;) {
       if (a_next) {
         if (A.part != b) break;
@@ -1178,13 +1196,13 @@ __global__ __launch_bounds__(kPartThreads) void merge_parts_kernel(float* __rest
     // The range is written, and the accumulator takes the next part's: every thread its own elements.
     fvec4u d[kQuads];
 #pragma unroll
-    for (int i = 0; i < kQuads; ++i) d[i] = load_quad(dense + next.begin, (more && !REPLACE) ? (int32_t)(next.end - next.begin) : 0, i);
+    for (int i = 0; i < kQuads; ++i) d[i] = load_quad(dense + next.begin, (more && !REPLACE) ? (int32_t)(next.end - next.begin) : 0, 4 * (tid + i * kPartThreads));
     __syncthreads();
     float* __restrict__ range = dense + blk.begin;
 #pragma unroll
     for (int k = 0; k < kQuads; ++k) {
       const float4 y = *reinterpret_cast<const float4*>(&acc[4 * (tid + k * kPartThreads)]);
-      if (REPLACE || any) store_quad(range, (int32_t)length, k, fvec4u{y.x, y.y, y.z, y.w});
+      if (REPLACE || any) store_quad(range, (int32_t)length, 4 * (tid + k * kPartThreads), fvec4u{y.x, y.y, y.z, y.w});
     }
     if (!more) break;
 #pragma unroll
