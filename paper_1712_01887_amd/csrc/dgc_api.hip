@@ -1066,9 +1066,8 @@ static dgc_status scatter_regions(dgc_handle* h, float* dense, int32_t num_paylo
       for (int32_t j = 0; j < h->num_tensors; ++j) expected += 8 * h->k[j] + 256;
       const int64_t sized_for = expected < widest ? expected : widest;
       const int64_t longest = (int64_t)std::ceil(1.25 * h->cfg.density * (double)h->longest_tensor);
-      if (!hip_ok(launch_scatter_regions(dense, h->n, p, 0, num_payloads, oo, h->num_tensors, sized_for, longest,
-                                         kScatterClear, 0.0f, nullptr, stream),
-                  "launch scatter kernel"))
+      if (!hip_ok(launch_clear_regions(dense, h->n, p, num_payloads, oo, h->num_tensors, sized_for, longest, stream),
+                  "launch clear kernel"))
         return DGC_ERR_HIP;
     } else if (!hip_ok(launch_clear_parts(dense, p, num_payloads, oo, parts, num_parts, found, stream),
                        "launch clear kernel")) {

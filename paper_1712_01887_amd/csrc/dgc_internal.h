@@ -431,9 +431,8 @@ struct DecodeArgs {
 enum ScatterMode : int32_t {
   kScatterAtomicAdd = 0,
   kScatterPlainAdd = 1,
-  kScatterClear = 2,
-  kScatterAtomicSgd = 3,  // target += scale * value, scale = -learning rate
-  kScatterPlainSgd = 4
+  kScatterAtomicSgd = 2,  // target += scale * value, scale = -learning rate
+  kScatterPlainSgd = 3
 };
 
 // ---- launchers (dgc_compress.hip, dgc_receive.hip, dgc_wire.hip) --------------
@@ -451,10 +450,10 @@ hipError_t launch_emit(const EmitArgs& a, int32_t num_blocks, hipStream_t stream
 hipError_t launch_scatter_pairs(float* dense, int64_t n, const PairPayloads& p, int32_t first,
                                 int32_t num, int64_t max_count, ScatterMode mode, float scale,
                                 uint32_t* diag_flags, hipStream_t stream);
-hipError_t launch_scatter_regions(float* dense, int64_t n, const RegionPayloads& p, int32_t first,
-                                  int32_t num, const int64_t* out_offsets_dev, int32_t num_tensors,
-                                  int64_t total_capacity, int64_t longest, ScatterMode mode, float scale,
-                                  uint32_t* diag_flags, hipStream_t stream);
+// dense[idx] = 0.  `total_capacity`: pairs of a payload that the launch is sized for; `longest`: of its longest tensor
+hipError_t launch_clear_regions(float* dense, int64_t n, const RegionPayloads& p, int32_t num,
+                                const int64_t* out_offsets_dev, int32_t num_tensors, int64_t total_capacity,
+                                int64_t longest, hipStream_t stream);
 
 hipError_t launch_merge_regions(float* dense, const RegionPayloads& p, int32_t num, const RegionPayloads* old,
                                 int32_t num_old, const int64_t* out_offsets_dev, const MergeBlock* blocks,

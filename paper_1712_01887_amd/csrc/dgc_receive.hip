@@ -23,10 +23,8 @@ __device__ __forceinline__ void scatter_one(float* dense, int64_t n, int32_t i, 
   if (mode == kScatterAtomicSgd || mode == kScatterPlainSgd) x = scale * x;
   if (mode == kScatterAtomicAdd || mode == kScatterAtomicSgd) {
     unsafeAtomicAdd(dense + i, x);  // hardware float add at the L2 / memory side
-  } else if (mode == kScatterPlainAdd || mode == kScatterPlainSgd) {
-    dense[i] = dense[i] + x;
   } else {
-    dense[i] = 0.0f;
+    dense[i] = dense[i] + x;
   }
 }
 
@@ -40,12 +38,12 @@ __global__ __launch_bounds__(256) void scatter_pairs_kernel(float* dense, int64_
   const float* __restrict__ val = p.val[w];
   const int64_t stride = (int64_t)gridDim.x * 256;
   for (int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x; q < count; q += stride)
-    scatter_one(dense, n, idx[q], mode == kScatterClear ? 0.0f : val[q], scale, mode, diag_flags);
+    scatter_one(dense, n, idx[q], val[q], scale, mode, diag_flags);
 }
 
 // dense[idx] = 0 for the pairs of region-layout payloads, where a workgroup's number says which tensor it works on:
 // grid = (tensors x per_tensor, payloads).  Bound by latency, the region and its count, then the indices, then the
-// stores; scatter_regions_kernel, which numbers the pairs through all tensors, has a scan and ten dependent LDS reads
+// stores; clear_regions_kernel, which numbers the pairs through all tensors, has a scan and ten dependent LDS reads
 // for every pair's tensor in front of its indices (launches included, in a graph: 23 tensors of 0.27 M elements, 1 % of four
 // workers 7.2 -> 3.0 us, one of 1 M 7.5 -> 3.5, 150 of 3 M 8.7 -> 5.2).
 __global__ __launch_bounds__(kFlatThreads) void clear_tensors_kernel(float* __restrict__ dense, int64_t n, RegionPayloads p,
@@ -73,19 +71,16 @@ __global__ __launch_bounds__(kFlatThreads) void clear_tensors_kernel(float* __re
   }
 }
 
-// Payloads in the per-tensor region layout written by the emit pass.
-// grid = (workgroups per payload, payloads).  The pairs of a payload are numbered
+// The same in sets whose tensors do not get a workgroup each: grid = (workgroups per payload, payloads).  The pairs of a payload are numbered
 // through all its regions (tensor by tensor, only the filled part of each region), and a
 // workgroup takes chunks of kFlatChunk consecutive numbers, grid-strided until the pairs
 // run out, so that every thread that runs has a pair to move however unevenly the
 // tensors are filled and however little of the capacity is used.  The numbering needs the prefix
 // sum of the per-tensor counts: every workgroup forms it in LDS, kFlatTensors tensors at
 // a time, and a thread finds the tensor of its pair by bisection there.
-__global__ __launch_bounds__(kFlatThreads) void scatter_regions_kernel(float* dense, int64_t n,
-                                                                       RegionPayloads p, int32_t first,
-                                                                       const int64_t* __restrict__ out_offsets,
-                                                                       int32_t num_tensors, ScatterMode mode,
-                                                                       float scale, uint32_t* diag_flags) {
+__global__ __launch_bounds__(kFlatThreads) void clear_regions_kernel(float* __restrict__ dense, int64_t n, RegionPayloads p,
+                                                                     const int64_t* __restrict__ out_offsets,
+                                                                     int32_t num_tensors) {
   constexpr int kPerThread = kFlatTensors / kFlatThreads;  // tensors a thread stages per round
   __shared__ int64_t s_off[kFlatTensors];
   __shared__ uint32_t s_pre[kFlatTensors];   // pairs in the staged tensors before each one
@@ -93,10 +88,9 @@ __global__ __launch_bounds__(kFlatThreads) void scatter_regions_kernel(float* de
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
-  const int w = first + blockIdx.y;
+  const int w = blockIdx.y;
   const int32_t* __restrict__ counts = p.counts[w];
   const int32_t* __restrict__ idx = p.idx[w];
-  const float* __restrict__ val = mode == kScatterClear ? nullptr : p.val[w];
   int64_t carry = 0;                                    // pairs in the tensors before the staged ones
   for (int32_t c0 = 0; c0 < num_tensors; c0 += kFlatTensors) {
     uint32_t cnt[kPerThread];
@@ -159,15 +153,11 @@ __global__ __launch_bounds__(kFlatThreads) void scatter_regions_kernel(float* de
         }
       }
       int32_t i[kFlatPer];
-      float x[kFlatPer];
 #pragma unroll
-      for (int k = 0; k < kFlatPer; ++k) {
-        i[k] = slot[k] >= 0 ? idx[slot[k]] : 0;
-        x[k] = (slot[k] >= 0 && mode != kScatterClear) ? val[slot[k]] : 0.0f;
-      }
+      for (int k = 0; k < kFlatPer; ++k) i[k] = slot[k] >= 0 ? idx[slot[k]] : -1;
 #pragma unroll
       for (int k = 0; k < kFlatPer; ++k)
-        if (slot[k] >= 0) scatter_one(dense, n, i[k], x[k], scale, mode, diag_flags);
+        if (i[k] >= 0 && (int64_t)i[k] < n) dense[i[k]] = 0.0f;
     }
     carry += staged;
     __syncthreads();
@@ -1338,12 +1328,11 @@ hipError_t launch_scatter_pairs(float* dense, int64_t n, const PairPayloads& p, 
   return hipGetLastError();
 }
 
-hipError_t launch_scatter_regions(float* dense, int64_t n, const RegionPayloads& p, int32_t first,
-                                  int32_t num, const int64_t* out_offsets_dev, int32_t num_tensors,
-                                  int64_t total_capacity, int64_t longest, ScatterMode mode, float scale,
-                                  uint32_t* diag_flags, hipStream_t stream) {
+hipError_t launch_clear_regions(float* dense, int64_t n, const RegionPayloads& p, int32_t num,
+                                const int64_t* out_offsets_dev, int32_t num_tensors, int64_t total_capacity,
+                                int64_t longest, hipStream_t stream) {
   if (num <= 0 || total_capacity <= 0) return hipSuccess;
-  if (mode == kScatterClear && (int64_t)num_tensors * num <= kClearGroups) {
+  if ((int64_t)num_tensors * num <= kClearGroups) {
     const int64_t most = kClearGroups / 2 / ((int64_t)num_tensors * num), want = ceil_div(longest, kFlatChunk);
     const int64_t per = want < 1 || most < 1 ? 1 : want < most ? want : most;
     if (want <= kClearRounds * per) {
@@ -1356,8 +1345,8 @@ hipError_t launch_scatter_regions(float* dense, int64_t n, const RegionPayloads&
   // pairs, so most workgroups find one chunk; fuller regions make them loop
   int64_t chunks = ceil_div(total_capacity, 4 * kFlatChunk);
   if (chunks > 65536) chunks = 65536;
-  hipLaunchKernelGGL(scatter_regions_kernel, dim3((unsigned)chunks, (unsigned)num), dim3(kFlatThreads), 0, stream,
-                     dense, n, p, first, out_offsets_dev, num_tensors, mode, scale, diag_flags);
+  hipLaunchKernelGGL(clear_regions_kernel, dim3((unsigned)chunks, (unsigned)num), dim3(kFlatThreads), 0, stream,
+                     dense, n, p, out_offsets_dev, num_tensors);
   return hipGetLastError();
 }
 
