@@ -119,8 +119,8 @@ constexpr double kMergeMaxDensity = 0.005;   // receive side: merge by element r
 // is two orders of magnitude slower (30 M elements, 0.8 %, four workers, pairs in a fiftieth of the tensor:
 // 5700 us by ranges, 45 by parts; 1 M elements, pairs in an eighth: 146 and 14).
 constexpr size_t kMergeFewRanges = 256;
-// Sets of up to as many parts have a word of LDS for every element, if the payloads let expect at most this many pairs
-// per element.  Against the part kernels (us): accumulating, two tensors of 3.5 M elements, 0.4 % of sixteen
+// Sets whose parts get a compute unit each (256 here, fewer on a partitioned card) have a word of LDS for every element, which
+// leaves room for one workgroup in a unit, if the payloads let expect at most this many pairs per element.  Against the part kernels (us): accumulating, two tensors of 3.5 M elements, 0.4 % of sixteen
 // workers (0.064) 15.2 and 17.9, 1 % of eight (0.08) 15.2 and 17.3, 30 of 0.1 M 11.1 and 13.9, 1 M 9.2 and 12.5, but 1 % of
 // sixteen (0.16) 17.7 and 13.9.  Replacing, wherever the range kernel would do it:
 // against that, one tensor of 7 M, 0.1 % of sixteen (0.016) 11.1 and 15.6, two of 3.5 M, 0.4 % of eight (0.032) 13.2 and 18.4,
@@ -1055,7 +1055,7 @@ static dgc_status scatter_regions(dgc_handle* h, float* dense, int32_t num_paylo
   void* found = at<char>(workspace, h->lay.part_found);
   // (Replacing, only where the range kernel would do it: elsewhere the previous payloads are not looked at and the whole of
   // `dense` is written, which callers may count on.)
-  const bool direct = h->part_blocks.size() <= kMergeFewRanges && h->cfg.density * (double)num_payloads <= kDirectMaxShare &&
+  const bool direct = num_parts <= compute_units() && h->cfg.density * (double)num_payloads <= kDirectMaxShare &&
                       (few || (!replace && h->searched_parts * num_payloads <= kDirectSearches));
   if (clear) {
     if (few || (h->cfg.density * (double)h->n * (double)num_payloads <= kScatterClearPairs &&

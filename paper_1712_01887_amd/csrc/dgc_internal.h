@@ -447,6 +447,7 @@ hipError_t launch_stream(const StreamArgs& a, hipStream_t stream);
 hipError_t launch_ceiling(const float* a, float* b, float* c, int64_t n, int groups, hipStream_t stream);
 hipError_t launch_refine(const RefineArgs& a, int32_t num_tensors, hipStream_t stream);
 hipError_t launch_emit(const EmitArgs& a, int32_t num_blocks, hipStream_t stream);
+int32_t compute_units();  // of the device that is current at the first call
 hipError_t launch_scatter_pairs(float* dense, int64_t n, const PairPayloads& p, int32_t first,
                                 int32_t num, int64_t max_count, ScatterMode mode, float scale,
                                 uint32_t* diag_flags, hipStream_t stream);

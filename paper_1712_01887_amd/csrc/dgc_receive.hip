@@ -1317,6 +1317,16 @@ __global__ __launch_bounds__(kPartClearThreads) void clear_parts_kernel(float* _
 // ---------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------
+int32_t compute_units() {
+  static const int32_t units = [] {
+    int dev = 0, n = 0;
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
+      n = 256;
+    return (int32_t)n;
+  }();
+  return units;
+}
+
 hipError_t launch_scatter_pairs(float* dense, int64_t n, const PairPayloads& p, int32_t first,
                                 int32_t num, int64_t max_count, ScatterMode mode, float scale,
                                 uint32_t* diag_flags, hipStream_t stream) {
@@ -1405,15 +1415,9 @@ hipError_t launch_merge_parts(float* dense, const RegionPayloads& p, int32_t num
                               const MergeBlock* parts, int32_t num_parts, void* found, bool replace, bool scaled,
                               float scale, hipStream_t stream) {
   if (num <= 0 || num_parts <= 0) return hipSuccess;
-  static int compute_units = 0;  // one workgroup of this kernel fits a compute unit
-  if (compute_units <= 0) {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&compute_units, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || compute_units <= 0)
-      compute_units = 256;
-  }
-  const int grid = num_parts < compute_units ? num_parts : compute_units;
-  const bool search = num_parts <= compute_units && (int64_t)num_parts * num <= kPartSearches;
+  const int units = compute_units();  // one workgroup of this kernel fits each
+  const int grid = num_parts < units ? num_parts : units;
+  const bool search = num_parts <= units && (int64_t)num_parts * num <= kPartSearches;
   if (!search) launch_locate_parts(p, num, out_offsets_dev, parts, num_parts, static_cast<int2*>(found), stream);
   const auto launch = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(kPartThreads), 0, stream, dense, p, num, out_offsets_dev,
