@@ -549,9 +549,8 @@ dgc_status dgc_create(dgc_handle** out, const dgc_config* cfg, int32_t num_tenso
   return DGC_OK;
 }
 
-// Test hook (not part of the interface): workgroups that do themselves whatever of others they do not find at once.
 __attribute__((visibility("default"))) void dgc_test_set_looks(dgc_handle* h, int32_t looks) {
-  if (h && looks >= 0) h->looks = looks;
+  if (h && looks > INT32_MIN) h->looks = looks;
 }
 
 static void profile_release(dgc_handle* h);

@@ -583,7 +583,8 @@ __device__ __forceinline__ float settle_scale(const SelectArgs& a, SelectShared&
     unsigned long long word = ~0ull;
     if (tid < a.num_partials) {
       word = 0;
-      for (int look = 0; look < a.looks; ++look) {
+      const int looks = looks_for(a.looks, tid);
+      for (int look = 0; look < looks; ++look) {
         word = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(a.partials) + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (word != 0) break;
         __builtin_amdgcn_s_sleep(1);

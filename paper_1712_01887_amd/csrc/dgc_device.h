@@ -65,6 +65,10 @@ __device__ __forceinline__ global_ptr<T> in_global(const T* p) {
   return (global_ptr<T>)p;
 }
 
+// How often a workgroup looks for word `c` of those that other workgroups leave.  (Less than zero, which only tests ask for:
+// as often for the even ones, and not at all for the odd ones.)
+__device__ __forceinline__ int looks_for(int looks, int c) { return looks >= 0 ? looks : (c & 1) ? 0 : -looks; }
+
 // Between stores to LDS by some lanes of a wavefront and loads of them by others.  The hardware carries out a
 // wavefront's LDS operations in order; this keeps the compiler from moving them, and costs no instruction.
 __device__ __forceinline__ void wave_lds_fence() {

@@ -276,7 +276,7 @@ struct SelectArgs {
                         // wholly inside one tensor; the others hold a NaN put there once by the host
   double* partials;        // partial sums of the squared norm (clipping on)
   int64_t n;               // elements of g
-  int32_t looks;           // norm and selection in one launch: how often a workgroup looks for a partial sum
+  int32_t looks;           // norm and selection in one launch: how often a workgroup looks for a partial sum (see looks_for)
   double thr_local;        // thr_G / sqrt(N)
   int32_t num_partials;
   float scale_override;    // NaN: unused
@@ -405,7 +405,7 @@ struct EncodeArgs {
   int32_t per_tensor;            // workgroups of every tensor; 0: total_blocks of them, which search
   int32_t self_scan;             // the second pass adds the block sums up itself
   unsigned long long* needs;     // device, total_blocks: one launch; null: two
-  int32_t looks;                 // how often a workgroup looks for what another one leaves
+  int32_t looks;                 // how often a workgroup looks for what another one leaves (see looks_for)
 };
 
 // Segments of the block-sum array handed to the scan kernel: segment s is
@@ -472,4 +472,8 @@ hipError_t launch_encode(EncodeArgs a, hipStream_t stream);
 hipError_t launch_decode(DecodeArgs a, bool in_order, hipStream_t stream);
 
 }  // namespace dgc
+
+// Exported for the tests, and no part of the interface: how often this handle's workgroups look for what others leave
+// before they do it themselves (0: not at all; less than zero: see looks_for).  Every number gives the same results.
+extern "C" void dgc_test_set_looks(dgc_handle* h, int32_t looks);
 #endif  // DGC_INTERNAL_H_

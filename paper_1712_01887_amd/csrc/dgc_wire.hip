@@ -224,7 +224,8 @@ __global__ __launch_bounds__(kWireThreads) void encode_kernel(EncodeArgs a) {
     unsigned long long word = 0;
     const bool mine_to_look = threadIdx.x < slot;
     if (mine_to_look) {
-      for (int look = 0; look < a.looks && (uint32_t)(word >> 32) != (kWireCall | call); ++look) {
+      const int looks = looks_for(a.looks, (int)threadIdx.x);
+      for (int look = 0; look < looks && (uint32_t)(word >> 32) != (kWireCall | call); ++look) {
         if (look > 0) __builtin_amdgcn_s_sleep(1);
         word = __hip_atomic_load(a.needs + threadIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }

@@ -24,9 +24,12 @@ class Encoder:
         self.dgc = B.Dgc(B.make_config(density=0.01, flags=B.DGC_FLAG_SORTED_OUTPUT), self.offsets)
         self.dgc.set_layout(self.layout)
         if alone:
-            hook = B.load().dgc_test_set_looks
-            hook.argtypes, hook.restype = [C.c_void_p, C.c_int32], None
-            hook(self.dgc._h, 0)
+            self.set_looks(0)
+
+    def set_looks(self, looks):
+        hook = B.load().dgc_test_set_looks
+        hook.argtypes, hook.restype = [C.c_void_p, C.c_int32], None
+        hook(self.dgc._h, looks)
 
     def payload(self, counts, rng):
         """Ascending indices of which a third lie in the first hundredth of every tensor: long gaps behind them."""
@@ -123,4 +126,65 @@ def test_encode_once_in_a_graph():
         enc.check(runs, vals, num)
         enc.dgc.dgc_encode(*payload, runs, vals, num)            # an eager call between the replays
         enc.check(runs, vals, num)
+    enc.dgc.close()
+
+
+@pytest.mark.parametrize("looks", [4096, -4096, 0])      # all needs of others found, every second one, none
+@pytest.mark.parametrize("sizes,capacities,counts", [
+    ([24575], [24575], [9000]), ([24576], [24576], [9000]),               # two launches, and one, for want of words for the needs
+    ([700000] + [60] * 300, [150 * CHUNK] + [60, 0, 0] * 100, [100 * CHUNK + 77] + [60, 0, 0] * 100),      # slots searched for
+    ([300] * 320, [300, 0, 300, 300, 0] * 64, [(5 * j) % 7 if j % 5 not in (1, 4) else 0 for j in range(320)]),
+    ([90000] * 60, [4 * CHUNK] * 60, [(2777 * j) % (4 * CHUNK) for j in range(60)]),
+])
+def test_encode_with_needs_found_and_formed_again(sizes, capacities, counts, looks):
+    """... and more tensors than a round of loads tells, some with no region at all."""
+    enc = Encoder(sizes, capacities, False)
+    enc.set_looks(looks)
+    rng = np.random.default_rng(len(sizes))
+    for _ in range(2):
+        payload = enc.payload(counts, rng)
+        out = enc.out()
+        enc.dgc.dgc_encode(*payload, *out)
+        enc.check(*out)
+    enc.dgc.close()
+
+
+@pytest.mark.parametrize("looks", [4096, -4096])
+def test_encode_behind_exact_selection_in_its_scratch(looks):
+    """In a workspace of the size that a set without exact selection needs the band lists of a compress call lie over the
+    needs of the calls of the encoder before and behind it."""
+    import torch
+    sizes = [200001, 70000, 40000, 64]
+    offsets = np.concatenate([[0], np.cumsum(sizes)])
+    n = int(offsets[-1])
+    kw = dict(momentum=0.9, density=0.02, seed=3)
+    sampled = B.Dgc(B.make_config(**kw), offsets)
+    without = sampled.dgc_workspace_bytes()
+    sampled.close()
+    enc = Encoder(sizes, sizes, False)
+    enc.dgc.close()
+    enc.dgc = B.Dgc(B.make_config(flags=B.DGC_FLAG_EXACT_SELECT | B.DGC_FLAG_SORTED_OUTPUT, **kw), offsets)
+    assert enc.dgc.dgc_workspace_bytes() > without
+    enc.dgc.set_layout(enc.layout)
+    enc.set_looks(looks)
+    guard = torch.full((without + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+    enc.dgc.workspace = guard
+    enc.dgc._ws_ptr = (guard.data_ptr() + 255) // 256 * 256
+    enc.dgc._ws_bytes = without
+    u, v = torch.zeros(n, device="cuda"), torch.zeros(n, device="cuda")
+    compressed = enc.dgc.alloc_payload("cuda")
+    rng = np.random.default_rng(6)
+    for it in range(4):
+        payload = enc.payload([1000 * (it + 1), 3000, 0, 5], rng)
+        out = enc.out()
+        enc.dgc.dgc_encode(*payload, *out)
+        enc.check(*out)
+        g = torch.from_numpy((1e-2 * rng.standard_t(3, n)).astype(np.float32)).cuda()
+        enc.dgc.dgc_compress(g, u, v, *compressed, it)
+        idx, val, counts = (t.cpu().numpy() for t in compressed[:3])
+        rows = [slice(enc.layout[j], enc.layout[j] + int(c)) for j, c in enumerate(counts)]
+        enc.expect = O.encode(np.concatenate([idx[r] for r in rows]).astype(np.int64), np.concatenate([val[r] for r in rows]))
+        out = enc.out()
+        enc.dgc.dgc_encode(*compressed[:3], *out)
+        enc.check(*out)
     enc.dgc.close()

@@ -16,10 +16,14 @@ pytestmark = pytest.mark.gpu
 MOST = 4 << 20
 
 
-def never_look(p):
+def set_looks(dgc, looks):
     hook = B.load().dgc_test_set_looks
     hook.argtypes, hook.restype = [C.c_void_p, C.c_int32], None
-    hook(p.dgc._h, 0)
+    hook(dgc._h, looks)
+
+
+def never_look(p):
+    set_looks(p.dgc, 0)
 
 
 @pytest.mark.parametrize("sizes", [[1], [3, 2], [4096 * 4], [4096 * 4 + 1], [50000, 5 * 4096 * 4 - 50000 + 2],
@@ -98,3 +102,32 @@ def test_norm_in_a_graph():
         want = float(np.sqrt((x.astype(np.float64) ** 2).sum()))
         assert abs(d.norm - want) <= 1e-12 * want, it
     dgc.close()
+
+
+@pytest.mark.parametrize("n", [4096 * 4 * 2 + 3, 70 * 4096 * 4, MOST - 1])            # 3 shares, 70 and 128
+def test_norm_of_shares_found_and_formed_again(n):
+    """Every second share is found, and the others are formed again beside it: the same bits as when all are found, and as
+    when none is, in sets of a tensor and of several."""
+    import torch
+    rng = np.random.default_rng(n)
+    grads = [torch.from_numpy((10.0 ** (it - 2) * rng.standard_t(3, n)).astype(np.float32)).cuda() for it in range(3)]
+    for offsets in (np.array([0, n]), np.array([0, n // 3, n // 3 + 5, n])):
+        seen = []
+        for looks in (4096, -4096, 0):
+            dgc = B.Dgc(B.make_config(density=0.004, clip_threshold=0.3, num_workers=4, momentum=0.9, seed=3), offsets)
+            dgc.set_layout(dgc.dgc_recommended_payload_layout(0.004))
+            set_looks(dgc, looks)
+            u, v = torch.zeros(n, device="cuda"), torch.zeros(n, device="cuda")
+            out = dgc.alloc_payload("cuda")
+            norms = []
+            for it, g in enumerate(grads):
+                dgc.dgc_compress(g, u, v, *out, it)
+                d = dgc.dgc_get_diagnostics()
+                want = float(np.sqrt((g.cpu().numpy().astype(np.float64) ** 2).sum()))
+                assert abs(d.norm - want) <= 1e-12 * want, (looks, it)
+                norms.append((d.norm, d.scale))
+            seen.append((norms, u, v, out[2].clone(), out[3].clone()))
+            dgc.close()
+        for other in seen[1:]:
+            assert seen[0][0] == other[0]
+            assert all(torch.equal(a, b) for a, b in zip(seen[0][1:], other[1:]))
