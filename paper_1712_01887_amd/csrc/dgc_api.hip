@@ -1033,7 +1033,8 @@ static dgc_status scatter_regions(dgc_handle* h, float* dense, int32_t num_paylo
   // No atomics at any density, workers in order.  At the densities the method runs at, a
   // workgroup merges the pairs of a range of up to 128 Ki elements in LDS and touches only
   // the elements that occur; at warm-up densities a workgroup keeps one emit part's whole
-  // range of `dense` in LDS.
+  // range of `dense` in LDS.  In small sets, on either side of the line, a workgroup has a part with a word of LDS for every
+  // element and touches those that occur, unless pairs crowd it.
   // Pairs the longest range can expect (kMergeMaxRange elements, or the largest tensor if that is smaller;
   // the sampled threshold lets through up to a quarter more than the density on the inputs seen so far): the
   // range kernel wants them, and the previous payloads' indices when it replaces, in its registers and

@@ -635,8 +635,8 @@ __device__ __forceinline__ float settle_scale(const SelectArgs& a, SelectShared&
   return sh.scale;
 }
 
-// Bound by latency: the gather of the candidates, then the ranking, in one workgroup per tensor.  16.2 us on eleven tensors of
-// 66 M elements, 12.7 on 161 of 25.6 M (13.7 with chains as they were before the next sentence).  Inside the workgroup,
+// Bound by latency: the gather of the candidates, then the ranking, in one workgroup per tensor.  16.9 us on eleven tensors of
+// 66 M elements, 12.8 on 161 of 25.6 M (13.7 with chains as they were before the next sentence).  Inside the workgroup,
 // 1 M elements, from its start:
 // 8.0 -> 6.6 us with the list's length asked for once per wavefront and not per key, four threads to a listed key, no
 // walk over empty slots, and the scale's sum over the lanes inside the vector unit; the step of that set 27.5 ->
