@@ -1077,15 +1077,14 @@ __global__ __launch_bounds__(kFlatThreads) void locate_parts_kernel(RegionPayloa
 // (95 with the first and last loads of a part sorted out, and so waited for, when they are asked for),
 // where 933 parts leave a fourth round of workgroups two thirds full.  Three rounds on their way: 442, 194, 100 against 426, 195, 95.
 //
-// SEARCH: every part has a workgroup of its own, which finds its payloads' pairs itself instead of reading them from the table of a
-// launch before (see kPartSearches).  A wavefront takes up to four payloads, two at a time.
+// SEARCH: every part has a workgroup of its own, which finds its payloads' pairs itself, a payload to a wavefront (two
+// from seventeen on), instead of reading them from the table of a launch before (see kPartSearches).
 template <bool REPLACE, bool SEARCH>
 __global__ __launch_bounds__(kPartThreads) void merge_parts_kernel(float* __restrict__ dense, RegionPayloads p,
                                                                    int32_t num_payloads,
                                                                    const int64_t* __restrict__ out_offsets,
                                                                    const MergeBlock* __restrict__ blocks,
-                                                                   int32_t num_blocks,
-                                                                   const int2* __restrict__ found, float scale,
+                                                                   int32_t num_blocks, int2* __restrict__ found, float scale,
                                                                    int32_t scaled) {
   constexpr int kQuads = kEmitElements / 4 / kPartThreads;
   constexpr int kWaves = kPartThreads / 64;
@@ -1124,9 +1123,9 @@ __global__ __launch_bounds__(kPartThreads) void merge_parts_kernel(float* __rest
       int lo2 = 0, hi2 = !two || count2 < 0 ? 0 : count2 > cap ? (int)cap : count2;
       if (blk.begin != blk.lo || blk.end != blk.hi)  // (a part that is a whole tensor has all its pairs)
         wave_equal_ranges(list, hi, list2, hi2, reinterpret_cast<const int32_t*>(blocks), blk.begin, blk.end, lane, lo, hi, lo2, hi2);
-      if (lane == 0) {
-        own_entry[w] = make_int2((int)region + lo, hi > lo ? hi - lo : 0);
-        if (two) own_entry[w2] = make_int2((int)region + lo2, hi2 > lo2 ? hi2 - lo2 : 0);
+      if (lane == 0) {  // (the table says the same after either way)
+        found[(int64_t)b * num_payloads + w] = own_entry[w] = make_int2((int)region + lo, hi > lo ? hi - lo : 0);
+        if (two) found[(int64_t)b * num_payloads + w2] = own_entry[w2] = make_int2((int)region + lo2, hi2 > lo2 ? hi2 - lo2 : 0);
       }
     }
     __syncthreads();
@@ -1421,7 +1420,7 @@ hipError_t launch_merge_parts(float* dense, const RegionPayloads& p, int32_t num
   if (!search) launch_locate_parts(p, num, out_offsets_dev, parts, num_parts, static_cast<int2*>(found), stream);
   const auto launch = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(kPartThreads), 0, stream, dense, p, num, out_offsets_dev,
-                       parts, num_parts, static_cast<const int2*>(found), scale, scaled ? 1 : 0);
+                       parts, num_parts, static_cast<int2*>(found), scale, scaled ? 1 : 0);
   };
   if (search) launch(replace ? merge_parts_kernel<true, true> : merge_parts_kernel<false, true>);
   else launch(replace ? merge_parts_kernel<true, false> : merge_parts_kernel<false, false>);
