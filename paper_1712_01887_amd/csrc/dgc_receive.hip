@@ -6,6 +6,8 @@
 #include "dgc_internal.h"
 #include "dgc_probe.h"
 
+#include <type_traits>
+
 namespace dgc {
 namespace {
 
@@ -1077,15 +1079,16 @@ __global__ __launch_bounds__(kFlatThreads) void locate_parts_kernel(RegionPayloa
 // (95 with the first and last loads of a part sorted out, and so waited for, when they are asked for),
 // where 933 parts leave a fourth round of workgroups two thirds full.  Three rounds on their way: 442, 194, 100 against 426, 195, 95.
 //
-// SEARCH: every part has a workgroup of its own, which finds its payloads' pairs itself, a payload to a wavefront (two
-// from seventeen on), instead of reading them from the table of a launch before (see kPartSearches).
+// SEARCH: every part has a workgroup of its own, which finds its payloads' pairs itself instead of reading them from the table of a
+// launch before (see kPartSearches).  A wavefront takes up to four payloads, two at a time.
 template <bool REPLACE, bool SEARCH>
 __global__ __launch_bounds__(kPartThreads) void merge_parts_kernel(float* __restrict__ dense, RegionPayloads p,
                                                                    int32_t num_payloads,
                                                                    const int64_t* __restrict__ out_offsets,
                                                                    const MergeBlock* __restrict__ blocks,
-                                                                   int32_t num_blocks, int2* __restrict__ found, float scale,
-                                                                   int32_t scaled) {
+                                                                   int32_t num_blocks,
+                                                                   std::conditional_t<SEARCH, int2, const int2>* __restrict__ found,
+                                                                   float scale, int32_t scaled) {
   constexpr int kQuads = kEmitElements / 4 / kPartThreads;
   constexpr int kWaves = kPartThreads / 64;
   __shared__ alignas(16) float acc[kEmitElements + 64];  // behind the range a word per lane for what is no pair of it
@@ -1106,7 +1109,7 @@ __global__ __launch_bounds__(kPartThreads) void merge_parts_kernel(float* __rest
   const int32_t* const idx_of = lane < num_payloads ? p.idx[lane] : nullptr;
   const float* const val_of = lane < num_payloads ? p.val[lane] : nullptr;
   __shared__ int2 own_entry[SEARCH ? kMaxPayloads : 1];
-  if (SEARCH) {
+  if constexpr (SEARCH) {
     const MergeBlock blk = blocks[b];
     const int64_t region = out_offsets[blk.tensor];
     const int64_t cap = out_offsets[blk.tensor + 1] - region;
@@ -1123,7 +1126,7 @@ __global__ __launch_bounds__(kPartThreads) void merge_parts_kernel(float* __rest
       int lo2 = 0, hi2 = !two || count2 < 0 ? 0 : count2 > cap ? (int)cap : count2;
       if (blk.begin != blk.lo || blk.end != blk.hi)  // (a part that is a whole tensor has all its pairs)
         wave_equal_ranges(list, hi, list2, hi2, reinterpret_cast<const int32_t*>(blocks), blk.begin, blk.end, lane, lo, hi, lo2, hi2);
-      if (lane == 0) {  // (the table says the same after either way)
+      if (lane == 0) {  // (the table says the same after either way: a reader of the workspace can tell what of it is the part kernels')
         found[(int64_t)b * num_payloads + w] = own_entry[w] = make_int2((int)region + lo, hi > lo ? hi - lo : 0);
         if (two) found[(int64_t)b * num_payloads + w2] = own_entry[w2] = make_int2((int)region + lo2, hi2 > lo2 ? hi2 - lo2 : 0);
       }
