@@ -308,7 +308,7 @@ dgc_status dgc_decompress_accumulate(dgc_handle* h, float* dense, int64_t n, int
  * is replaced, in sets of up to 256 ranges that let expect no more than 6144 in the longest
  * tensor, a workgroup touches only the elements that occur in a range of up to 131072 (in sets of no more parts than the
  * device has compute units that let expect at most 0.08 pairs per element, and there above these lines as well unless an aggregate is replaced: the elements that
- * occur in one part, or the whole of a part that more than 2048 pairs fall into); otherwise (the warm-up densities of
+ * occur in one part, or the whole of a part that more than 4096 pairs fall into, 2048 where that is what to expect); otherwise (the warm-up densities of
  * Section 4, or many payloads) it keeps one part's whole range of
  * `dense` on chip, after a launch that finds every payload's pairs of every part (or, in small sets, a search of its own).  A
  * region laid out otherwise gives wrong sums (never an access out of bounds); for

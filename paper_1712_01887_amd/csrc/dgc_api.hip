@@ -1074,7 +1074,8 @@ static dgc_status scatter_regions(dgc_handle* h, float* dense, int32_t num_paylo
       return DGC_ERR_HIP;
     }
   } else if (direct) {
-    if (!hip_ok(launch_merge_direct(dense, p, num_payloads, replace ? &was : nullptr, num_old, oo, parts, num_parts, sgd,
+    const double of_part = h->cfg.density * (double)num_payloads * (double)(h->longest_tensor < kEmitElements ? h->longest_tensor : kEmitElements);
+    if (!hip_ok(launch_merge_direct(dense, p, num_payloads, replace ? &was : nullptr, num_old, oo, parts, num_parts, of_part, sgd,
                                     scale, stream),
                 "launch merge kernel"))
       return DGC_ERR_HIP;

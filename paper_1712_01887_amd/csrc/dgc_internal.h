@@ -96,10 +96,13 @@ constexpr int kMergeCapLarge = 6144;
 static_assert((kMergeMaxRange / 128) % kMergeMaxThreads == 0, "dealt evenly to threads");
 
 // Where the accumulator has a word per element: pairs of a part that a workgroup takes into registers, each with a load and a
-// store of its element.  With more, most sectors of the part are touched, and the whole of it is read and written (7 M
-// elements in two tensors, accumulating 1 % of eight workers, 2621 pairs a part: 15.2 us, 18.1 with 4096 in registers;
-// 1 M, 1 % of four, 1310: 6.7, and 8.2 with 1024).
+// store of its element; with more the whole of the part is read and written.  4096, but 2048 where several payloads spread evenly
+// let expect more than 2048: they touch most sectors of a part then, each of them another one with every pair.  By elements and whole
+// (accumulating, us): 7 M elements, 1 % of eight workers (2621 pairs a part) 18.4 and 14.2, 256 tensors of 32 K, 2 % of four 16.7 and
+// 13.3, but 7.5 % of one 12.9 and 12.7, 64 tensors of 60 K 9.4 and 10.6; and where fewer are expected, pairs that crowd a
+// part lie close together in it: 64 of 60 K, 1 % of four (1200), all in an eighth of each tensor 8.4 and 10.9.
 constexpr int kDirectPairs = 2048;
+constexpr int kDirectPairsMost = 4096;
 
 // Receive side at warm-up densities: a workgroup owns one emit workgroup's part and keeps
 // the whole range of the dense vector in LDS.
@@ -463,7 +466,8 @@ hipError_t launch_merge_regions(float* dense, const RegionPayloads& p, int32_t n
                                 hipStream_t stream);
 hipError_t launch_merge_direct(float* dense, const RegionPayloads& p, int32_t num, const RegionPayloads* old,
                                int32_t num_old, const int64_t* out_offsets_dev, const MergeBlock* parts,
-                               int32_t num_parts, bool scaled, float scale, hipStream_t stream);
+                               int32_t num_parts, double expected_pairs, bool scaled, float scale,
+                               hipStream_t stream);
 hipError_t launch_merge_parts(float* dense, const RegionPayloads& p, int32_t num, const int64_t* out_offsets_dev,
                               const MergeBlock* parts, int32_t num_parts, void* found, bool replace, bool scaled,
                               float scale, hipStream_t stream);

@@ -805,8 +805,7 @@ __global__ __launch_bounds__(THREADS) void merge_direct_kernel(float* __restrict
                                                                int32_t num_old,
                                                                const int64_t* __restrict__ out_offsets,
                                                                const MergeBlock* __restrict__ blocks,
-                                                               float scale, int32_t scaled) {
-  constexpr int kPer = kDirectPairs / THREADS;
+                                                               int32_t most, float scale, int32_t scaled) {
   __shared__ DirectShared sh;
   __shared__ OldLists was;
   const int tid = threadIdx.x;
@@ -821,8 +820,8 @@ __global__ __launch_bounds__(THREADS) void merge_direct_kernel(float* __restrict
   if (total == 0 && old_total == 0) return;
   const uint32_t nowhere = 0xFFFFFFFFu;  // (an index outside the range: of a region that does not ascend)
 
-  if (total <= kDirectPairs && old_total <= kDirectPairs) {
-    // everything in registers, all loads on their way together
+  auto in_registers = [&](auto pairs) {  // up to `pairs` of either set, all loads on their way together
+    constexpr int kPer = decltype(pairs)::value / THREADS;
     uint32_t old_rel[kPer], rel[kPer];
     int pw[kPer];
     float x[kPer];
@@ -887,6 +886,13 @@ __global__ __launch_bounds__(THREADS) void merge_direct_kernel(float* __restrict
       if (k * THREADS < total && rel[k] != nowhere) range[rel[k]] = sh.acc[rel[k]];
       if (REPLACE && k * THREADS < old_total && old_rel[k] != nowhere) range[old_rel[k]] = sh.acc[old_rel[k]];
     }
+  };
+  if (total <= kDirectPairs && old_total <= kDirectPairs) {
+    in_registers(std::integral_constant<int, kDirectPairs>{});
+    return;
+  }
+  if (total <= most && old_total <= most) {
+    in_registers(std::integral_constant<int, kDirectPairsMost>{});
     return;
   }
 
@@ -1391,17 +1397,19 @@ hipError_t launch_merge_regions(float* dense, const RegionPayloads& p, int32_t n
 
 hipError_t launch_merge_direct(float* dense, const RegionPayloads& p, int32_t num, const RegionPayloads* old,
                                int32_t num_old, const int64_t* out_offsets_dev, const MergeBlock* parts,
-                               int32_t num_parts, bool scaled, float scale, hipStream_t stream) {
+                               int32_t num_parts, double expected_pairs, bool scaled, float scale,
+                               hipStream_t stream) {
   if (num <= 0 || num_parts <= 0) return hipSuccess;
   const dim3 grid((unsigned)num_parts);
   const int sc = scaled ? 1 : 0;
+  const int32_t most = num > 1 && expected_pairs > (double)kDirectPairs ? kDirectPairs : kDirectPairsMost;
   const bool few = num <= 8 && num_old <= 8;  // one wavefront per payload in a workgroup of eight
   if (old) {
-    if (few) hipLaunchKernelGGL((merge_direct_kernel<true, 512>), grid, dim3(512), 0, stream, dense, p, num, *old, num_old, out_offsets_dev, parts, scale, sc);
-    else hipLaunchKernelGGL((merge_direct_kernel<true, 1024>), grid, dim3(1024), 0, stream, dense, p, num, *old, num_old, out_offsets_dev, parts, scale, sc);
+    if (few) hipLaunchKernelGGL((merge_direct_kernel<true, 512>), grid, dim3(512), 0, stream, dense, p, num, *old, num_old, out_offsets_dev, parts, most, scale, sc);
+    else hipLaunchKernelGGL((merge_direct_kernel<true, 1024>), grid, dim3(1024), 0, stream, dense, p, num, *old, num_old, out_offsets_dev, parts, most, scale, sc);
   } else {
-    if (few) hipLaunchKernelGGL((merge_direct_kernel<false, 512>), grid, dim3(512), 0, stream, dense, p, num, p, 0, out_offsets_dev, parts, scale, sc);
-    else hipLaunchKernelGGL((merge_direct_kernel<false, 1024>), grid, dim3(1024), 0, stream, dense, p, num, p, 0, out_offsets_dev, parts, scale, sc);
+    if (few) hipLaunchKernelGGL((merge_direct_kernel<false, 512>), grid, dim3(512), 0, stream, dense, p, num, p, 0, out_offsets_dev, parts, most, scale, sc);
+    else hipLaunchKernelGGL((merge_direct_kernel<false, 1024>), grid, dim3(1024), 0, stream, dense, p, num, p, 0, out_offsets_dev, parts, most, scale, sc);
   }
   return hipGetLastError();
 }

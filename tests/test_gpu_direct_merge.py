@@ -130,7 +130,7 @@ def test_replacing_above_half_a_percent_reads_nothing(share, workers, then):
 
 
 @pytest.mark.parametrize("workers", [1, 3, 8, 9, 64])       # at density 0.001: 64 of them 0.064 pairs per element
-@pytest.mark.parametrize("taken", [2048, 2049, 4097, 8193, 16385, 31001])
+@pytest.mark.parametrize("taken", [2048, 2049, 4096, 4097, 8193, 16385, 31001])
 def test_parts_that_pairs_crowd(workers, taken):
     """Parts that start anywhere and end behind any quad, in one of which the payloads together have `taken` pairs and in
     another each of them has as many: on both sides of what a workgroup takes into registers, and of the rounds of chunks."""
