@@ -687,11 +687,12 @@ struct ChunkRound {
     const int slot0 = (int)(c - (uint32_t)__builtin_amdgcn_readlane((int)t.chunk0, w)) * kPartChunk;
     const int slot = slot0 + 4 * lane;
     const int head = __builtin_amdgcn_readlane(t.head, w), end = __builtin_amdgcn_readlane(t.end, w);
-    const int32_t* __restrict__ from = reinterpret_cast<const int32_t*>(of_lane(reinterpret_cast<uint64_t>(t.idx), w));
-    const float* __restrict__ values = reinterpret_cast<const float*>(of_lane(reinterpret_cast<uint64_t>(t.val), w));
+    // (known to be global: the sums' reads of LDS would wait for them, too, otherwise)
+    const global_ptr<int32_t> from = (global_ptr<int32_t>)of_lane(reinterpret_cast<uint64_t>(t.idx), w);
+    const global_ptr<float> values = (global_ptr<float>)of_lane(reinterpret_cast<uint64_t>(t.val), w);
     if (slot0 >= head && end - slot0 >= kPartChunk) {
-      idx = __builtin_nontemporal_load(reinterpret_cast<const ivec4*>(from + slot));
-      x = __builtin_nontemporal_load(reinterpret_cast<const fvec4u*>(values + slot));
+      idx = __builtin_nontemporal_load((global_ptr<ivec4>)(from + slot));
+      x = __builtin_nontemporal_load((global_ptr<fvec4u>)(values + slot));
     } else {
       // Slots before the first pair and behind the last hold other parts' pairs, or nothing that matters, or do not
       // exist.  (What is loaded is sorted out when the round is added: nothing here waits for it.)
@@ -702,8 +703,8 @@ struct ChunkRound {
       for (int k = 0; k < 4; ++k) wanted |= EdgeFour::wanted(slot + k, head, end) ? 1u << k : 0u;
       back = four.whole ? four.back : 0;
       if (four.whole) {
-        idx = __builtin_nontemporal_load(reinterpret_cast<const ivec4u*>(from + slot - four.back));
-        x = __builtin_nontemporal_load(reinterpret_cast<const fvec4u*>(values + slot - four.back));
+        idx = __builtin_nontemporal_load((global_ptr<ivec4u>)(from + slot - four.back));
+        x = __builtin_nontemporal_load((global_ptr<fvec4u>)(values + slot - four.back));
       } else if (four.any) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
