@@ -40,6 +40,7 @@ struct dgc_handle {
   int64_t longest_tensor = 0;
   std::vector<MergeBlock> part_blocks;   // the same with one emit part per range (warm-up densities)
   int64_t searched_parts = 0;            // parts that are not a whole tensor
+  int64_t searched_tensors = 0;          // tensors of more parts than one
   bool layout_may_overflow = true;       // some region of the registered layout is smaller than its tensor
   int32_t looks = kNormLooks;            // how often a workgroup looks for what another one leaves before it does it itself
   int64_t last_replace_expected = 0;     // pairs per range the payloads of the last dgc_decompress_replace_regions call let expect
@@ -535,7 +536,10 @@ dgc_status dgc_create(dgc_handle** out, const dgc_config* cfg, int32_t num_tenso
       if (end > h->offsets[eb.tensor + 1]) end = h->offsets[eb.tensor + 1];
       h->part_blocks.push_back(MergeBlock{(int32_t)begin, (int32_t)end, eb.tensor, (int32_t)h->offsets[eb.tensor],
                                           (int32_t)h->offsets[eb.tensor + 1], 0});
-      if (begin != h->offsets[eb.tensor] || end != h->offsets[eb.tensor + 1]) ++h->searched_parts;
+      if (begin != h->offsets[eb.tensor] || end != h->offsets[eb.tensor + 1]) {
+        ++h->searched_parts;
+        if (begin == h->offsets[eb.tensor]) ++h->searched_tensors;
+      }
     }
     h->ws_out_offsets.resize(num_tensors + 1);
     h->wire_first_block.resize(num_tensors + 1);
@@ -1085,8 +1089,8 @@ static dgc_status scatter_regions(dgc_handle* h, float* dense, int32_t num_paylo
                                      expected_pairs, sgd, scale, stream),
                 "launch merge kernel"))
       return DGC_ERR_HIP;
-  } else if (!hip_ok(launch_merge_parts(dense, p, num_payloads, oo, parts, num_parts, found, replace, sgd, scale,
-                                        stream),
+  } else if (!hip_ok(launch_merge_parts(dense, p, num_payloads, oo, parts, num_parts, h->searched_tensors, found, replace, sgd,
+                                        scale, stream),
                      "launch merge kernel")) {
     return DGC_ERR_HIP;
   }

@@ -111,8 +111,14 @@ constexpr int kPartChunk = 256;  // slots of a payload a wavefront takes at a ti
 // Parts times payloads up to which the workgroups of the part kernel, one to a part, search for themselves.  In one
 // launch and in two, replacing: 1 M elements (32 parts), four workers, 6.25 %: 10.2 and 11.7 us, sixteen 19.8 and 20.6;
 // 7 M (215 parts), four: 13.7 and 15.5, but sixteen 26.4 and 25.4, at 25 % 57.7 and 52.8: without the first guess of the
-// searching launch, every wavefront takes five rounds of probes.
+// searching launch, every wavefront takes five rounds of probes.  And where there is something to search, up to so many lists, none
+// of whose first probes another part's search has in the cache already (tensors of 60 K, 6.25 %: 64 of them and eight workers 15.5 and
+// 16.0, twelve 20.3 and 19.2, sixteen 24.3 and 22.0; 128 and four 15.0 and 15.9, eight 20.9 and 18.8), and payloads, of
+// which a wavefront has two at once from seventeen on and two more one after the other from 33 on (1 M, 24 workers 27.2 and 27.8, 48
+// 50.1 and 45.5, 64 64.2 and 57.2; 16 of 60 K, 24 26.8 and 26.6, 32 34.9 and 32.6).
 constexpr int64_t kPartSearches = 2048;
+constexpr int64_t kPartSearchLists = 512;
+constexpr int kPartSearchPayloads = 24;
 constexpr int kPartClearThreads = 256;
 constexpr int kPartClearLoads = 4;  // loads of four indices a lane has on their way
 static_assert(kEmitElements <= 65536 && kEmitElements % kPartThreads == 0 &&
@@ -469,8 +475,8 @@ hipError_t launch_merge_direct(float* dense, const RegionPayloads& p, int32_t nu
                                int32_t num_parts, double expected_pairs, bool scaled, float scale,
                                hipStream_t stream);
 hipError_t launch_merge_parts(float* dense, const RegionPayloads& p, int32_t num, const int64_t* out_offsets_dev,
-                              const MergeBlock* parts, int32_t num_parts, void* found, bool replace, bool scaled,
-                              float scale, hipStream_t stream);
+                              const MergeBlock* parts, int32_t num_parts, int64_t searched_tensors, void* found, bool replace,
+                              bool scaled, float scale, hipStream_t stream);
 hipError_t launch_clear_parts(float* dense, const RegionPayloads& p, int32_t num, const int64_t* out_offsets_dev,
                               const MergeBlock* parts, int32_t num_parts, void* found, hipStream_t stream);
 hipError_t launch_encode(EncodeArgs a, hipStream_t stream);

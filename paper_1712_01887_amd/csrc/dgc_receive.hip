@@ -1423,12 +1423,13 @@ static void launch_locate_parts(const RegionPayloads& p, int32_t num, const int6
 }
 
 hipError_t launch_merge_parts(float* dense, const RegionPayloads& p, int32_t num, const int64_t* out_offsets_dev,
-                              const MergeBlock* parts, int32_t num_parts, void* found, bool replace, bool scaled,
-                              float scale, hipStream_t stream) {
+                              const MergeBlock* parts, int32_t num_parts, int64_t searched_tensors, void* found, bool replace,
+                              bool scaled, float scale, hipStream_t stream) {
   if (num <= 0 || num_parts <= 0) return hipSuccess;
   const int units = compute_units();  // one workgroup of this kernel fits each
   const int grid = num_parts < units ? num_parts : units;
-  const bool search = num_parts <= units && (int64_t)num_parts * num <= kPartSearches;
+  const bool search = num_parts <= units && (int64_t)num_parts * num <= kPartSearches &&
+                      (searched_tensors == 0 || (searched_tensors * num <= kPartSearchLists && num <= kPartSearchPayloads));
   if (!search) launch_locate_parts(p, num, out_offsets_dev, parts, num_parts, static_cast<int2*>(found), stream);
   const auto launch = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(kPartThreads), 0, stream, dense, p, num, out_offsets_dev,

@@ -250,3 +250,28 @@ def test_part_kernel_that_searches_and_that_looks_up(workers, more):
     dgc.dgc_decompress_replace_regions(dense, *lists)
     assert np.array_equal(dense.cpu().numpy(), fresh)
     dgc.close()
+
+
+@pytest.mark.parametrize("sizes,workers", [([PART + 5] * 21 + [77], 24), ([PART + 5] * 22 + [77], 24), ([PART + 5] * 3, 25),
+                                           ([PART] * 3 + [77], 25), ([PART] * 3 + [77], 64)])
+def test_part_kernel_by_lists_and_payloads(sizes, workers):
+    """Lists that are searched, and payloads, on both sides of where a launch of its own finds the pairs; nothing to search."""
+    import torch
+    rng = np.random.default_rng([len(sizes), workers])
+    offsets = np.concatenate([[0], np.cumsum(sizes)])
+    layout = offsets.tolist()
+    dgc = B.Dgc(B.make_config(density=0.25, num_workers=workers), offsets)
+    dgc.set_layout(layout)
+    new = [payload(0.02 + 0.01 * (w % 5), rng, offsets, layout, 0) for w in range(workers)]
+    lists = tuple([d[i] for _, d in new] for i in range(3))
+    start = rng.standard_normal(layout[-1]).astype(np.float32)
+    expect, fresh = start.copy(), np.zeros_like(start)
+    for (e, x), _ in new:
+        expect[e] = (expect[e] + x).astype(np.float32)
+        fresh[e] = (fresh[e] + x).astype(np.float32)
+    dense = torch.from_numpy(start).cuda()
+    dgc.dgc_decompress_accumulate_regions(dense, *lists)
+    assert np.array_equal(dense.cpu().numpy(), expect)
+    dgc.dgc_decompress_replace_regions(dense, *lists)
+    assert np.array_equal(dense.cpu().numpy(), fresh)
+    dgc.close()
