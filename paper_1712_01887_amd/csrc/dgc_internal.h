@@ -136,10 +136,11 @@ constexpr int kWireRounds = kWireChunk / kWireThreads;   // rounds of 64 pairs a
 // against 16.
 constexpr int kWireSelfScan = 16384;
 // Up to as many workgroup slots the encoder is one launch; their needs lie at the end of the block sums, a word of 64 bits
-// each with the call's number above (and a bit that no block sum has).  (Calls in two launches and in one, in a graph, us: one
-// slot 7.1 and 5.3, 60 8.8 and 7.4, 174 11.1 and 9.1, 216 10.8 and 10.2, 243 10.3 and 10.4: every workgroup
-// looks for all the needs before its own.)  The block sums have room for them in sets of 24576 elements and more, or of some 500
-// tensors; in smaller ones the encoder is two launches.
+// each with the call's number above (and a bit that no block sum has).  Calls in two launches and in one, us: in a graph one
+// slot 7.1 and 5.3, 64 of 30 pairs 7.3 and 7.0, of 300 10.0 and 8.9, 128 7.4 and 7.5, 10.1 and 9.4, 192 7.4 and 8.4, 10.1 and 10.4, 256 7.4
+// and 9.0, 10.1 and 11.2 (every workgroup looks for all the needs before its own); from a stream, where the host enqueues them,
+// 128 10.5 and 6.8, 10.8 and 8.6, 256 10.4 and 8.2, 10.6 and 10.3: the line is where calls of that kind stop gaining.  The block
+// sums have room for the needs in sets of 24576 elements and more, or of some 500 tensors; in smaller ones the encoder is two launches.
 constexpr int kWireOnce = 256;
 constexpr uint32_t kWireCall = 0x80000000u;
 static_assert(kWireOnce <= kWireThreads, "a thread looks for each slot before its own");
