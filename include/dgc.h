@@ -307,8 +307,9 @@ dgc_status dgc_decompress_accumulate(dgc_handle* h, float* dense, int64_t n, int
  * in the longest range (density x payloads x its elements x 1.25), and above it, unless an aggregate
  * is replaced, in sets of up to 256 ranges that let expect no more than 6144 in the longest
  * tensor, a workgroup touches only the elements that occur in a range of up to 131072 (in sets of no more parts than the
- * device has compute units that let expect at most 0.08 pairs per element, and there above these lines as well unless an aggregate is replaced: the elements that
- * occur in one part, or the whole of a part that more than 4096 pairs fall into, 2048 where that is what to expect); otherwise (the warm-up densities of
+ * device has compute units that let expect at most 0.08 pairs per element, in one part; so it does there above these
+ * lines, unless an aggregate is replaced, but may then store the whole of a part that more than 2048 pairs fall into, and so may
+ * a call below them that replaces an aggregate); otherwise (the warm-up densities of
  * Section 4, or many payloads) it keeps one part's whole range of
  * `dense` on chip, after a launch that finds every payload's pairs of every part (or, in small sets, a search of its own).  A
  * region laid out otherwise gives wrong sums (never an access out of bounds); for

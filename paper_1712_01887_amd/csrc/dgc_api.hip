@@ -1038,7 +1038,8 @@ static dgc_status scatter_regions(dgc_handle* h, float* dense, int32_t num_paylo
   // workgroup merges the pairs of a range of up to 128 Ki elements in LDS and touches only
   // the elements that occur; at warm-up densities a workgroup keeps one emit part's whole
   // range of `dense` in LDS.  In small sets, on either side of the line, a workgroup has a part with a word of LDS for every
-  // element and touches those that occur, unless pairs crowd it.
+  // element and touches those that occur.  (Where the part kernels are the other way, and replacing, one that pairs crowd is
+  // written whole.)
   // Pairs the longest range can expect (kMergeMaxRange elements, or the largest tensor if that is smaller;
   // the sampled threshold lets through up to a quarter more than the density on the inputs seen so far): the
   // range kernel wants them, and the previous payloads' indices when it replaces, in its registers and
@@ -1079,8 +1080,8 @@ static dgc_status scatter_regions(dgc_handle* h, float* dense, int32_t num_paylo
     }
   } else if (direct) {
     const double of_part = h->cfg.density * (double)num_payloads * (double)(h->longest_tensor < kEmitElements ? h->longest_tensor : kEmitElements);
-    if (!hip_ok(launch_merge_direct(dense, p, num_payloads, replace ? &was : nullptr, num_old, oo, parts, num_parts, of_part, sgd,
-                                    scale, stream),
+    if (!hip_ok(launch_merge_direct(dense, p, num_payloads, replace ? &was : nullptr, num_old, oo, parts, num_parts, of_part, few,
+                                    sgd, scale, stream),
                 "launch merge kernel"))
       return DGC_ERR_HIP;
   } else if (few) {

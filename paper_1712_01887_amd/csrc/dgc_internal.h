@@ -471,10 +471,11 @@ hipError_t launch_merge_regions(float* dense, const RegionPayloads& p, int32_t n
                                 int32_t num_old, const int64_t* out_offsets_dev, const MergeBlock* blocks,
                                 int32_t num_blocks, int64_t expected_pairs, bool scaled, float scale,
                                 hipStream_t stream);
+// named_only: accumulating, elements that no pair names are not stored
 hipError_t launch_merge_direct(float* dense, const RegionPayloads& p, int32_t num, const RegionPayloads* old,
                                int32_t num_old, const int64_t* out_offsets_dev, const MergeBlock* parts,
-                               int32_t num_parts, double expected_pairs, bool scaled, float scale,
-                               hipStream_t stream);
+                               int32_t num_parts, double expected_pairs, bool named_only, bool scaled,
+                               float scale, hipStream_t stream);
 hipError_t launch_merge_parts(float* dense, const RegionPayloads& p, int32_t num, const int64_t* out_offsets_dev,
                               const MergeBlock* parts, int32_t num_parts, int64_t searched_tensors, void* found, bool replace,
                               bool scaled, float scale, hipStream_t stream);

@@ -719,10 +719,14 @@ struct ChunkRound {
 };
 
 // Adds a round to a part's accumulator, behind whose elements there is a word per lane for what is no pair of it, and refills
-// it by `fetch`.  `last_w`: payload that was added last (-1: none, the accumulator is being filled).
-template <typename Fetch>
+// it by `fetch`.  `last_w`: payload that was added last (-1: none, the accumulator is being filled).  NAMED: `seen` gets
+// a bit for every element that is added to, bit r / kSeenWords of word r % kSeenWords: neighbours are in words, and so
+// in banks, of their own (1 M elements, 0.4 % of four workers in an eighth:
+// 8.4 us without the bits, 10.5; 11.8 with 32 neighbours to a word).
+constexpr int kSeenWords = kEmitElements / 32;
+template <bool NAMED, typename Fetch>
 __device__ __forceinline__ void add_round(ChunkRound& L, float* acc, uint32_t begin, uint32_t length, int32_t scaled, float scale,
-                                          int& last_w, int lane, Fetch& fetch) {
+                                          int& last_w, int lane, Fetch& fetch, uint32_t* seen) {
   uint32_t at[4];
   float x[4];
   if (L.edge) {  // uniform
@@ -756,6 +760,11 @@ __device__ __forceinline__ void add_round(ChunkRound& L, float* acc, uint32_t be
       for (int k = 0; k < 4; ++k) sum[k] = acc[at[k]] + x[k];
 #pragma unroll
       for (int k = 0; k < 4; ++k) acc[at[k]] = sum[k];
+      if constexpr (NAMED) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          if (at[k] < length) atomicOr(&seen[at[k] % kSeenWords], 1u << (at[k] / kSeenWords));
+      }
     }
   }
 }
@@ -793,6 +802,8 @@ __device__ __forceinline__ void store_quad(float* to, int32_t len, int e, const 
 // 23 tensors of 12 K 5.8 -> 4.5, 1 M 11.4 -> 6.7 (part kernels).
 // REPLACE: the indices of the earlier payloads are elements that start from zero and get no pair: what the new ones
 // share with them gets its sum, the others zero.
+// NAMED: elements that no pair names are not stored, also where pairs crowd a part (they may be another stream's to update), which takes a
+// crowded part longer: 0.4 % of eight workers in a fiftieth of 7 M elements 27.7 us, 20.2 written whole, 122 each pair by itself.
 struct DirectShared {
   alignas(16) float acc[kEmitElements + 64];  // behind the part a word per lane for what is no pair of it
   int32_t begin[kMaxPayloads + 1];
@@ -800,7 +811,7 @@ struct DirectShared {
   global_ptr<float> val_at[kMaxPayloads];
 };
 
-template <bool REPLACE, int THREADS>
+template <bool REPLACE, bool NAMED, int THREADS>
 __global__ __launch_bounds__(THREADS) void merge_direct_kernel(float* __restrict__ dense, RegionPayloads p,
                                                                int32_t num_payloads, RegionPayloads old,
                                                                int32_t num_old,
@@ -808,6 +819,7 @@ __global__ __launch_bounds__(THREADS) void merge_direct_kernel(float* __restrict
                                                                const MergeBlock* __restrict__ blocks,
                                                                int32_t most, float scale, int32_t scaled) {
   __shared__ DirectShared sh;
+  __shared__ alignas(16) uint32_t seen[NAMED ? kSeenWords : 4];
   __shared__ OldLists was;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -924,6 +936,9 @@ __global__ __launch_bounds__(THREADS) void merge_direct_kernel(float* __restrict
     for (int i = 0; i < kQuads; ++i)
       *reinterpret_cast<float4*>(&sh.acc[4 * (tid + i * THREADS)]) = make_float4(d[i][0], d[i][1], d[i][2], d[i][3]);
   }
+  if constexpr (NAMED) {
+    for (int i = tid; i < kSeenWords; i += THREADS) seen[i] = 0;
+  }
   int last_w = -1;
   for (bool more = true; more;) {
 #pragma unroll
@@ -932,14 +947,29 @@ __global__ __launch_bounds__(THREADS) void merge_direct_kernel(float* __restrict
         more = false;
         break;
       }
-      add_round(rounds[i], sh.acc, (uint32_t)blk.begin, length, scaled, scale, last_w, lane, fetch);
+      add_round<NAMED>(rounds[i], sh.acc, (uint32_t)blk.begin, length, scaled, scale, last_w, lane, fetch, seen);
     }
   }
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < kQuads; ++i) {
-    const float4 y = *reinterpret_cast<const float4*>(&sh.acc[4 * (tid + i * THREADS)]);
-    store_quad(range, (int32_t)length, 4 * (tid + i * THREADS), fvec4u{y.x, y.y, y.z, y.w});
+    const int e = 4 * (tid + i * THREADS);
+    const float4 y = *reinterpret_cast<const float4*>(&sh.acc[e]);
+    const fvec4u four = {y.x, y.y, y.z, y.w};
+    if constexpr (NAMED) {
+      const uint4 q = *reinterpret_cast<const uint4*>(&seen[e % kSeenWords]);
+      const uint32_t bit = 1u << (e / kSeenWords);
+      if (q.x & q.y & q.z & q.w & bit) {
+        store_quad(range, (int32_t)length, e, four);
+      } else {
+        if (q.x & bit) range[e] = four[0];
+        if (q.y & bit) range[e + 1] = four[1];
+        if (q.z & bit) range[e + 2] = four[2];
+        if (q.w & bit) range[e + 3] = four[3];
+      }
+    } else {
+      store_quad(range, (int32_t)length, e, four);
+    }
   }
 }
 
@@ -1181,7 +1211,7 @@ __global__ __launch_bounds__(kPartThreads) void merge_parts_kernel(float* __rest
     const uint32_t length = (uint32_t)(blk.end - blk.begin);  // <= kEmitElements
     bool any = false;
     int last_w = -1;
-    auto add = [&](ChunkRound& L) { add_round(L, acc, begin, length, scaled, scale, last_w, lane, fetch); };
+    auto add = [&](ChunkRound& L) { add_round<false>(L, acc, begin, length, scaled, scale, last_w, lane, fetch, nullptr); };
     for (;;) {
       if (a_next) {
         if (A.part != b) break;
@@ -1398,19 +1428,22 @@ hipError_t launch_merge_regions(float* dense, const RegionPayloads& p, int32_t n
 
 hipError_t launch_merge_direct(float* dense, const RegionPayloads& p, int32_t num, const RegionPayloads* old,
                                int32_t num_old, const int64_t* out_offsets_dev, const MergeBlock* parts,
-                               int32_t num_parts, double expected_pairs, bool scaled, float scale,
-                               hipStream_t stream) {
+                               int32_t num_parts, double expected_pairs, bool named_only, bool scaled,
+                               float scale, hipStream_t stream) {
   if (num <= 0 || num_parts <= 0) return hipSuccess;
   const dim3 grid((unsigned)num_parts);
   const int sc = scaled ? 1 : 0;
   const int32_t most = num > 1 && expected_pairs > (double)kDirectPairs ? kDirectPairs : kDirectPairsMost;
-  const bool few = num <= 8 && num_old <= 8;  // one wavefront per payload in a workgroup of eight
-  if (old) {
-    if (few) hipLaunchKernelGGL((merge_direct_kernel<true, 512>), grid, dim3(512), 0, stream, dense, p, num, *old, num_old, out_offsets_dev, parts, most, scale, sc);
-    else hipLaunchKernelGGL((merge_direct_kernel<true, 1024>), grid, dim3(1024), 0, stream, dense, p, num, *old, num_old, out_offsets_dev, parts, most, scale, sc);
+  const auto launch = [&](auto kernel, int threads) {
+    hipLaunchKernelGGL(kernel, grid, dim3((unsigned)threads), 0, stream, dense, p, num, old ? *old : p, old ? num_old : 0,
+                       out_offsets_dev, parts, most, scale, sc);
+  };
+  if (num <= 8 && (!old || num_old <= 8)) {  // one wavefront per payload in a workgroup of eight
+    old ? launch(merge_direct_kernel<true, false, 512>, 512)
+        : named_only ? launch(merge_direct_kernel<false, true, 512>, 512) : launch(merge_direct_kernel<false, false, 512>, 512);
   } else {
-    if (few) hipLaunchKernelGGL((merge_direct_kernel<false, 512>), grid, dim3(512), 0, stream, dense, p, num, p, 0, out_offsets_dev, parts, most, scale, sc);
-    else hipLaunchKernelGGL((merge_direct_kernel<false, 1024>), grid, dim3(1024), 0, stream, dense, p, num, p, 0, out_offsets_dev, parts, most, scale, sc);
+    old ? launch(merge_direct_kernel<true, false, 1024>, 1024)
+        : named_only ? launch(merge_direct_kernel<false, true, 1024>, 1024) : launch(merge_direct_kernel<false, false, 1024>, 1024);
   }
   return hipGetLastError();
 }

@@ -180,6 +180,45 @@ def test_parts_that_pairs_crowd(workers, taken):
     dgc.close()
 
 
+@pytest.mark.parametrize("workers", [2, 9])                   # 512 threads, 1024
+@pytest.mark.parametrize("scale", [None, 0.5])
+def test_elements_that_no_pair_names_are_another_streams(workers, scale):
+    """Two streams add to one vector, one to elements of even and one to elements of odd numbers of parts that pairs crowd."""
+    import torch
+    rng = np.random.default_rng(workers)
+    n, taken, calls = 3 * PART + 513, 9001, 40
+    expect = rng.standard_normal(n).astype(np.float32)
+    dense = torch.from_numpy(expect).cuda()
+    sides = []
+    for odd in (0, 1):
+        dgc = B.Dgc(B.make_config(density=0.001, num_workers=workers), [0, n])
+        dgc.set_layout([0, taken])
+        lists = [[], [], []]
+        pairs = []
+        for _ in range(workers):
+            e = 2 * np.sort(rng.choice(3 * PART // 4, taken, replace=False)).astype(np.int32) + odd
+            x = rng.standard_normal(taken).astype(np.float32)
+            pairs.append((e, x if scale is None else np.float32(-scale) * x))
+            for to, t in zip(lists, (e, x, np.array([taken], np.int32))):
+                to.append(torch.from_numpy(t).cuda())
+        for _ in range(calls):
+            for e, x in pairs:
+                expect[e] = (expect[e] + x).astype(np.float32)
+        sides.append((dgc, lists, torch.cuda.Stream()))
+    torch.cuda.synchronize()
+    for _ in range(calls):
+        for dgc, lists, stream in sides:
+            with torch.cuda.stream(stream):
+                if scale is None:
+                    dgc.dgc_decompress_accumulate_regions(dense, *lists)
+                else:
+                    dgc.dgc_sparse_sgd_apply_regions(dense, scale, *lists)
+    torch.cuda.synchronize()
+    assert np.array_equal(dense.cpu().numpy(), expect)
+    for dgc, _, _ in sides:
+        dgc.close()
+
+
 def best_of(call, turns=8, calls=20):
     """Time of a call in us, of the fastest of several rows of them in a captured graph."""
     import time
